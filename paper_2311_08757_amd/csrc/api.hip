@@ -45,6 +45,14 @@ T* dalloc(ddeig_problem* P, size_t count) {
   return static_cast<T*>(p);
 }
 
+// Storage of a chain factor (zero: the row solves' layout has unused entries).
+template <typename T>
+T* dalloc_factor(ddeig_problem* P, size_t count) {
+  T* p = dalloc<T>(P, count);
+  check_hip(hipMemsetAsync(p, 0, sizeof(T) * count, P->stream), "clear factor");
+  return p;
+}
+
 void dfree(ddeig_problem* P, void* p) {
   if (!p) return;
   auto it = std::find(P->allocs.begin(), P->allocs.end(), p);
@@ -191,6 +199,26 @@ double cell_vmin(const ddeig_problem* P) {
   return vmin;
 }
 
+size_t class_factor_entries(const ddeig_problem* P, const SubType& t) {
+  int b = 0, nch = 0;
+  for (const auto& c : P->types) {
+    b = std::max(b, c.box.b);
+    nch = std::max(nch, c.box.nch);
+  }
+  return ddeig::factor_entries(P->g.D, t.box, b, nch);
+}
+
+// FP64 chain factors of every class
+void factor_classes(ddeig_problem* P) {
+  std::vector<Box> boxes;
+  std::vector<double*> Ws;
+  for (const auto& t : P->types) {
+    boxes.push_back(t.box);
+    Ws.push_back(t.W);
+  }
+  chain_factor(P, boxes, Ws, P->tabAs, P->stream);
+}
+
 void factor_types(ddeig_problem* P) {
   if (P->opt.local_prec >= 2) {
     // dense local solves: FP64 block-chain factors of the unclipped box, its
@@ -198,11 +226,10 @@ void factor_types(ddeig_problem* P) {
     // lo) split, then for every clipped class (B~_TT)^{-1} from the rounded
     // inverse (FP64 Gauss-Jordan, symmetrised) and G = B~_ST (B~_TT)^{-1}
     ddeig::DenseHost& H = P->dh;
-    chain_factor(P, H.box, P->tabAs, H.W, P->stream);
+    chain_factor(P, {H.box}, {H.W}, P->tabAs, P->stream);
     check_launch("local factorisation");
     double* Ainv = dalloc<double>(P, (size_t)H.m * H.m);
-    launch_identity(Ainv, H.m, P->stream);
-    launch_chain_solve_box(P, H.box, P->tabAs, H.W, Ainv, H.m, P->stream);
+    launch_chain_inverse(P, H.box, P->tabAs, H.W, Ainv, P->stream);
     launch_split_inverse(Ainv, H.m, H.ld, H.Ah, H.Al, P->stream);
     check_launch("dense inverse");
     sync(P);
@@ -219,14 +246,14 @@ void factor_types(ddeig_problem* P) {
     }
     return;
   }
+  factor_classes(P);
   for (auto& t : P->types) {
-    chain_factor(P, t.box, P->tabAs, t.W, P->stream);
     if (P->opt.local_prec == 1) {
       if (P->chain_mfma)
         launch_pad_float(t.W, t.W32, (long)t.box.nch * t.box.b, t.box.b, (t.box.b + 3) / 4 * 4,
                          P->stream);
       else
-        launch_to_float(t.W, t.W32, (long)t.box.nch * t.box.b * t.box.b, P->stream);
+        launch_to_float(t.W, t.W32, (long)class_factor_entries(P, t), P->stream);
     }
   }
   check_launch("local factorisation");
@@ -321,8 +348,8 @@ bool fallback_fp32(ddeig_problem* P) {
   for (size_t t = 0; t < P->types.size(); ++t) {
     auto& T = P->types[t];
     const long mm = (long)T.box.nch * T.box.b;
-    T.W = dalloc<double>(P, (size_t)T.box.nch * T.box.b * T.box.b);
-    T.W32 = dalloc<float>(P, (size_t)T.box.nch * T.box.b * T.box.b);
+    T.W = dalloc_factor<double>(P, class_factor_entries(P, T));
+    T.W32 = dalloc_factor<float>(P, class_factor_entries(P, T));
     dfree(P, T.batch);
     T.batch = dalloc<double>(P, (size_t)T.nmem * mm);
     TypeDev& d = tdev[t];
@@ -351,9 +378,9 @@ bool fallback_fp32(ddeig_problem* P) {
   P->opt.local_prec = 1;
   clear_graphs(P);
   clear_flag(P);
+  factor_classes(P);
   for (auto& T : P->types) {
-    chain_factor(P, T.box, P->tabAs, T.W, s);
-    launch_to_float(T.W, T.W32, (long)T.box.nch * T.box.b * T.box.b, s);
+    launch_to_float(T.W, T.W32, (long)class_factor_entries(P, T), s);
   }
   check_launch("fallback factorisation");
   if (read_flag(P)) throw Failure{DDEIG_ENOTSPD, "a local matrix A_sigma,i is not positive definite"};
@@ -1089,7 +1116,7 @@ ddeig_status ddeig_assemble(const ddeig_geometry* geom, double h, const ddeig_po
       H.m = hb.b * hb.nch;
       H.ld = (H.m + 127) / 128 * 128;
       H.mp = nsub > ddeig::kGemvMax ? (nsub + 127) / 128 * 128 : ddeig::kGemvMax;
-      H.W = dalloc<double>(P, (size_t)hb.nch * hb.b * hb.b);
+      H.W = dalloc_factor<double>(P, ddeig::factor_entries(g.D, hb, hb.b, hb.nch));
       const size_t aa = (size_t)H.ld * H.ld, rr = (size_t)H.mp * H.ld;
       // K columns per GEMM stage (the kernel's pipeline depth): 64 with a
       // single bf16 inverse, 32 with the hi/lo pair; K split so that the GEMM
@@ -1263,8 +1290,10 @@ ddeig_status ddeig_assemble(const ddeig_geometry* geom, double h, const ddeig_po
         tdev[t].Z = H.Z;
         tdev[t].zsplit = (long)H.mp * H.ld;
       } else {
-        T.W = dalloc<double>(P, (size_t)T.box.nch * T.box.b * T.box.b);
-        if (o.local_prec == 1) T.W32 = dalloc<float>(P, (size_t)T.box.nch * T.box.b * ldw);
+        T.W = dalloc_factor<double>(P, class_factor_entries(P, T));
+        if (o.local_prec == 1)
+          T.W32 = dalloc_factor<float>(P, chain_mfma ? (size_t)T.box.nch * T.box.b * ldw
+                                                     : class_factor_entries(P, T));
         T.batch = dalloc<double>(P, (size_t)T.nmem * mm);
         for (int a = 0; a < 3; ++a) {
           tdev[t].hm[a] = T.box.m[a];
@@ -1387,8 +1416,9 @@ ddeig_status ddeig_assemble(const ddeig_geometry* geom, double h, const ddeig_po
       check_hip(hipEventCreateWithFlags(&P->ev_state[e], hipEventDisableTiming), "create event");
     check_hip(hipHostMalloc(reinterpret_cast<void**>(&P->hst), 2 * sizeof(ddeig::PcgState)),
               "pinned state");
-    P->gjbuf = dalloc<double>(P, 4 * (size_t)gjmax);
+    P->gj_jobs = dense ? 1 : (int)P->types.size();
     P->gj_stride = gjmax;
+    P->gjbuf = dalloc<double>(P, (size_t)ddeig::gj_buffer_doubles(gjmax, P->gj_jobs));
     P->psi = dalloc<double>(P, g.tsize);
     P->crhs = dalloc<double>(P, nsub);
     // per-axis covering tables of the expanding directions
@@ -1948,13 +1978,13 @@ ddeig_status ddeig_cell_shift(ddeig_problem* P, double* sigma_out, double* psi_c
     if (!g.isx[a]) s0 += mu_min(g.nel[a], g.h);
   P->sigma = s0;
   launch_shift_table(P, s);
-  double* Wc = dalloc<double>(P, (size_t)cb.nch * cb.b * cb.b);
+  double* Wc = dalloc_factor<double>(P, ddeig::factor_entries(g.D, cb, cb.b, cb.nch));
   double* v0 = dalloc<double>(P, nc);  // psi_k
   double* v1 = dalloc<double>(P, nc);  // M psi_k
   double* v2 = dalloc<double>(P, nc);  // solve
   double* v3 = dalloc<double>(P, nc);  // M solve
   clear_flag(P);
-  chain_factor(P, cb, P->tabAs, Wc, s);
+  chain_factor(P, {cb}, {Wc}, P->tabAs, s);
   check_launch("cell factorisation");
   if (read_flag(P)) {
     dfree(P, Wc); dfree(P, v0); dfree(P, v1); dfree(P, v2); dfree(P, v3);
@@ -1966,7 +1996,7 @@ ddeig_status ddeig_cell_shift(ddeig_problem* P, double* sigma_out, double* psi_c
   for (; it < 2000; ++it) {
     launch_box_stencil(P, cb, P->tabM, v0, v1, nullptr, nullptr, s);
     launch_copy(v2, v1, nc, s);
-    launch_chain_solve_box(P, cb, P->tabAs, Wc, v2, 1, s);
+    launch_chain_solve(P, cb, P->tabAs, Wc, v2, v3, s);
     Red s4 = slot(P, 4), s5 = slot(P, 5), s6 = slot(P, 6);
     launch_box_stencil(P, cb, P->tabM, v2, v3, &s4, &s5, s);
     launch_ipm_normalise(nc, v2, v3, v0, v1, s4, s5, s6, s);

@@ -433,8 +433,8 @@ struct ddeig_problem {
   long gm_ldv = 0;
   int gm_cap = 0;
   int* flag = nullptr;      // factorisation error flag
-  double* gjbuf = nullptr;  // Gauss-Jordan row/column buffers (4 x gj_stride)
-  int gj_stride = 0;
+  double* gjbuf = nullptr;  // blocked Gauss-Jordan panels of gj_jobs matrices of <= gj_stride rows
+  int gj_stride = 0, gj_jobs = 1;
   double* cellS = nullptr;  // scratch for Schur builds (maxb^2)
   std::vector<void*> allocs;
 };
@@ -463,12 +463,17 @@ void launch_stencil_dir(const ddeig_problem* P, const double* z, const double* p
 void launch_box_stencil(const ddeig_problem* P, const Box& bx, const double* tab, const double* x,
                         double* y, Red* dot, Red* sum, hipStream_t s);
 
-// chain factorisation of a box: W[i] = S_i^{-1}; flag set on a non-positive pivot
-void chain_factor(ddeig_problem* P, const Box& bx, const double* tab, double* W, hipStream_t s);
+// chain factorisation of boxes: W[i] = S_i^{-1}; flag set on a non-positive pivot
+void chain_factor(ddeig_problem* P, const std::vector<Box>& boxes, const std::vector<double*>& Ws,
+                  const double* tab, hipStream_t s);
+long gj_buffer_doubles(int bmax, int njobs);
+size_t factor_entries(int D, const Box& bx, int bmax, int nchmax);
 void launch_gj_invert(ddeig_problem* P, double* A, int b, hipStream_t s);
-// chain solve in place on nrhs right-hand sides stored contiguously (nch*b each)
-void launch_chain_solve_box(const ddeig_problem* P, const Box& bx, const double* tab,
-                            const double* W, double* v, int nrhs, hipStream_t s);
+// chain solve in place of one right-hand side (tmp: as many values), and the inverse
+void launch_chain_solve(const ddeig_problem* P, const Box& bx, const double* tab, const double* W,
+                        double* v, double* tmp, hipStream_t s);
+void launch_chain_inverse(const ddeig_problem* P, const Box& bx, const double* tab, const double* W,
+                          double* x, hipStream_t s);
 
 // preconditioner pieces
 // PCG iteration k, update fused into the restriction: alpha = rho_{k-1} / gamma
@@ -512,7 +517,6 @@ void launch_coarse_extend(const ddeig_problem* P, const double* r, double* z, Re
                           const PcgState* st, hipStream_t s);
 void launch_symmetrise(double* A, int N, hipStream_t s);
 void launch_split_inverse(const double* Ainv, int m, int ld, void* Ah, void* Al, hipStream_t s);
-void launch_identity(double* v, int m, hipStream_t s);
 void launch_dense_gemm(const ddeig_problem* P, const PcgState* st, hipStream_t s,
                        const double* coarse_r = nullptr);
 void launch_dense_gemv(const ddeig_problem* P, const PcgState* st, hipStream_t s);

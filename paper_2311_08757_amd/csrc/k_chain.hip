@@ -44,115 +44,540 @@ __device__ inline long box_tnode(const Geo& g, const Box& bx, const int* u) {
   return table_node(g, bx.o[0] + u[0], bx.o[1] + u[1], bx.o[2] + u[2]);
 }
 
-// S = D_i - E_i Wprev E_i^T for slice i (Wprev = nullptr for i = 0), row-major b x b.
-__global__ void k_schur_build(Geo g, Box bx, int i, const double* __restrict__ T,
-                              const double* __restrict__ Wprev, double* __restrict__ S) {
-  const int b = bx.b, D = g.D, last = D - 1;
-  const long bb = (long)b * b;
-  for (long idx = blockIdx.x * (long)blockDim.x + threadIdx.x; idx < bb;
-       idx += (long)gridDim.x * blockDim.x) {
-    const int r = (int)(idx / b), s = (int)(idx % b);
-    int ur[3], us[3];
-    slice_coords(bx, D, r, ur);
-    slice_coords(bx, D, s, us);
-    ur[last] = i;
-    us[last] = i;
-    const long tr = box_tnode(g, bx, ur);
-    double v = 0.0;
-    for (int t = 0; t < g.ntaps; ++t) {
-      int d[3];
-      tap_offsets(t, g.ntaps, d[0], d[1], d[2]);
-      if (d[last] != 0) continue;
-      int rn;
-      if (slice_nbr(bx, D, ur, d, rn) && rn == s) v += T[t * g.tsize + tr];
+// ---- factorisation
+//
+// S_i = D_i - E_i W_{i-1} E_i^T and W_i = S_i^{-1} by Gauss-Jordan elimination
+// without pivoting (the leading minors are positive; a non-positive pivot sets
+// the flag).  Slices depend on each other, so the work is nch dependent
+// inversions; everything below serves the length of that chain.
+//  * 2-D slices of at most kFacMaxB unknowns (k_chain_factor2d): one workgroup
+//    per class runs the whole chain, with the matrix in registers (16 x 16
+//    threads, NA x NA entries each) and one barrier per kFacP pivots.  Four
+//    waves, one per SIMD: the instructions around the update (broadcast reads,
+//    reciprocals, selects) are per wave, and they, not the update, set the pace
+//    (16 waves of fewer entries each took 1.2 us a pivot, one pivot per barrier
+//    0.62, four 0.49 with the Schur complement: 2.2 ms for 63 slices of 71).
+//  * larger slices: the Schur complement by one workgroup per row
+//    (k_schur_row), the inversion in pivot blocks of kGjNb (two launches per
+//    block: the inverse of the diagonal block times its row panel, then the
+//    rank-kGjNb update of the rest), for all classes at once.
+// One launch per pivot took 2.9 us a pivot (6.1 us at b = 1085): 13.7 ms for
+// a 63-slice chain of b = 71 and 217 ms for a 31-slice one of b = 1085.
+constexpr int kFacMaxB = 128;
+constexpr int kRowsMaxB = 128;
+constexpr int kFacG = 16;  // thread grid: kFacG x kFacG = kBlock
+static_assert(kFacG * kFacG == kBlock, "square thread grid");
+
+struct FactorJobs {
+  Box bx[kMaxTypes];
+  double* W[kMaxTypes];
+};
+
+// Layout of the factors that the row solves read (chain_rows): the columns in 8
+// parts of chunk = ceil(b / 8), 8 row pairs per wave: lane 8 part + q of a wave
+// holds the pair (2 rp, 2 rp + 1), rp = 8 wave + q, of the columns s =
+// part chunk + k; a load of a wave is 1 KB of consecutive memory: pair
+// ((i nw + wave) chunk + k) 64 + lane of slice i.  Entries of no row or column
+// stay zero.
+struct RowsLayout {
+  int nw, chunk;  // waves, columns per part
+  __host__ __device__ explicit RowsLayout(int b) : nw((b + 15) / 16), chunk((b + 7) / 8) {}
+  __host__ __device__ int slice() const { return nw * chunk * 64; }  // pairs per slice
+  __host__ __device__ int at(int s, int r) const {                   // entry of column s, row r
+    const int rp = r >> 1, part = s / chunk, k = s - part * chunk;
+    return (((rp >> 3) * chunk + k) * 64 + part * 8 + (rp & 7)) * 2 + (r & 1);
+  }
+};
+
+// 1 / x for a positive, normal x, to about an ulp: the hardware estimate and
+// three Newton steps (a full division is a third longer in the pivot chain).
+__device__ __forceinline__ double fast_rcp(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+#pragma unroll
+  for (int q = 0; q < 3; ++q) y = y + y * (1.0 - x * y);
+  return y;
+}
+
+// Gauss-Jordan inversion of a b x b matrix spread over a workgroup, kFacP
+// pivots at a time: thread (ti, tj) holds entries (ti + 16 x, tj + 16 y).
+// rowb (kFacP x 16 NA) and colb (16 NA x kFacP), in two copies, hold the rows
+// and columns of the pivot block before its step.  Rows and columns handed to
+// LDS are zeroed in the registers; with X the inverse of the diagonal block
+// (formed by every thread), rs = X r, rs_j = X_j for the block's columns and
+// c_i = -(unit vector) for its rows, one update a -= c rs forms all of the new
+// matrix.  Rows past b act as unit pivots.  Returns false (for the whole
+// workgroup) at a non-positive pivot.
+constexpr int kFacP = 4;
+template <int NA>
+__device__ __forceinline__ bool gj_registers(double (&a)[NA][NA], int b, int ti, int tj,
+                                             double* __restrict__ rowb, double* __restrict__ colb) {
+  constexpr int LD = kFacG * NA;
+  // rows and columns 16 kb + kl .. + 3 of the current matrix into copy `c`
+  auto publish = [&](int kb, int kl, int c) {
+    double* rn = rowb + c * kFacP * LD;
+    double* cn = colb + c * kFacP * LD;
+    const unsigned pi = (unsigned)(ti - kl), pj = (unsigned)(tj - kl);
+    if (pj < (unsigned)kFacP) {
+#pragma unroll
+      for (int x = 0; x < NA; ++x) cn[(ti + kFacG * x) * kFacP + pj] = a[x][kb];
     }
-    if (Wprev != nullptr) {
-      const long ts = box_tnode(g, bx, us);
-      double corr = 0.0;
-      for (int t1 = 0; t1 < g.ntaps; ++t1) {
-        int d1[3];
-        tap_offsets(t1, g.ntaps, d1[0], d1[1], d1[2]);
-        if (d1[last] != -1) continue;
-        int n1;
-        if (!slice_nbr(bx, D, ur, d1, n1)) continue;
-        const double e1 = T[t1 * g.tsize + tr];
-        double inner = 0.0;
-        for (int t2 = 0; t2 < g.ntaps; ++t2) {
-          int d2[3];
-          tap_offsets(t2, g.ntaps, d2[0], d2[1], d2[2]);
-          if (d2[last] != -1) continue;
-          int n2;
-          if (!slice_nbr(bx, D, us, d2, n2)) continue;
-          inner += T[t2 * g.tsize + ts] * Wprev[(long)n1 * b + n2];
+    if (pi < (unsigned)kFacP) {
+#pragma unroll
+      for (int y = 0; y < NA; ++y) rn[pi * LD + tj + kFacG * y] = a[kb][y];
+    }
+#pragma unroll
+    for (int x = 0; x < NA; ++x) a[x][kb] = pj < (unsigned)kFacP ? 0.0 : a[x][kb];
+#pragma unroll
+    for (int y = 0; y < NA; ++y) a[kb][y] = pi < (unsigned)kFacP ? 0.0 : a[kb][y];
+  };
+  publish(0, 0, 0);
+  __syncthreads();
+#pragma unroll
+  for (int kb = 0; kb < NA; ++kb) {
+    for (int kl = 0; kl < kFacG; kl += kFacP) {
+      const int k = kFacG * kb + kl, cp = (kl / kFacP) & 1;
+      if (k >= b) return true;
+      const double* rk = rowb + cp * kFacP * LD;
+      const double* ck = colb + cp * kFacP * LD;
+      double X[kFacP][kFacP], r[kFacP][NA], c[NA][kFacP];
+#pragma unroll
+      for (int p = 0; p < kFacP; ++p)
+#pragma unroll
+        for (int q = 0; q < kFacP; ++q) X[p][q] = rk[p * LD + k + q];
+#pragma unroll
+      for (int x = 0; x < NA; ++x)
+#pragma unroll
+        for (int p = 0; p < kFacP; ++p) {
+          r[p][x] = rk[p * LD + tj + kFacG * x];
+          c[x][p] = ck[(ti + kFacG * x) * kFacP + p];
         }
-        corr += e1 * inner;
+      bool ok = true;
+#pragma unroll
+      for (int p = 0; p < kFacP; ++p) {
+        const double piv = k + p < b ? X[p][p] : 1.0;
+        ok = ok && piv > 0.0;
+        const double ip = fast_rcp(piv);
+        X[p][p] = 1.0;
+#pragma unroll
+        for (int q = 0; q < kFacP; ++q) X[p][q] *= ip;
+#pragma unroll
+        for (int i = 0; i < kFacP; ++i) {
+          if (i == p) continue;
+          const double f = X[i][p];
+          X[i][p] = 0.0;
+#pragma unroll
+          for (int q = 0; q < kFacP; ++q) X[i][q] -= f * X[p][q];
+        }
       }
-      v -= corr;
+      if (!ok) return false;
+      const int pi = ti - kl, pj = tj - kl;
+#pragma unroll
+      for (int y = 0; y < NA; ++y) {
+        double t[kFacP];
+#pragma unroll
+        for (int p = 0; p < kFacP; ++p) {
+          t[p] = X[p][0] * r[0][y];
+#pragma unroll
+          for (int q = 1; q < kFacP; ++q) t[p] += X[p][q] * r[q][y];
+        }
+#pragma unroll
+        for (int p = 0; p < kFacP; ++p) r[p][y] = t[p];
+      }
+#pragma unroll
+      for (int p = 0; p < kFacP; ++p)
+#pragma unroll
+        for (int q = 0; q < kFacP; ++q) {
+          if (pj == q) r[p][kb] = X[p][q];
+          if (pi == q) c[kb][p] = p == q ? -1.0 : 0.0;
+        }
+#pragma unroll
+      for (int x = 0; x < NA; ++x)
+#pragma unroll
+        for (int y = 0; y < NA; ++y)
+#pragma unroll
+          for (int p = 0; p < kFacP; ++p) a[x][y] -= c[x][p] * r[p][y];
+      if (kl + kFacP < kFacG) publish(kb, kl + kFacP, cp ^ 1);
+      else if (kb + 1 < NA) publish(kb + 1 < NA ? kb + 1 : kb, 0, cp ^ 1);
+      __syncthreads();
     }
-    S[idx] = v;
+  }
+  return true;
+}
+
+// The whole chain of one 2-D class (chain along y, slices along x, couplings
+// d0 = -1..1) in one workgroup; W_{i-1} stays in LDS for the next slice, and
+// the next slice's 6 b coefficients are loaded while the current one is
+// inverted.
+template <int NA>
+__global__ void __launch_bounds__(kBlock) k_chain_factor2d(Geo g, const double* __restrict__ T,
+                                                           FactorJobs jobs, int rows,
+                                                           int* __restrict__ flag) {
+  constexpr int LD = kFacG * NA;
+  constexpr int NC = (6 * LD + kBlock - 1) / kBlock;  // coefficients per thread
+  extern __shared__ double wp[];  // b x b
+  // cf: taps 0..2 (E_i), then 3..5 (D_i) of every node of the slice
+  __shared__ __align__(16) double row[2 * kFacP * LD], col[2 * kFacP * LD];
+  __shared__ double cf[NC * kBlock];
+  const Box bx = jobs.bx[blockIdx.x];
+  double* __restrict__ W = jobs.W[blockIdx.x];
+  const int b = bx.b, per = bx.per[0];
+  const int ti = threadIdx.x / kFacG, tj = threadIdx.x % kFacG;
+  // neighbour u + d - 1 in the slice; one that does not exist points at the
+  // node itself and has coefficient zero
+  auto nbr = [&](int u, int d) {
+    const int v = u + d - 1;
+    return v < 0 ? (per ? b - 1 : u) : v >= b ? (per ? 0 : u) : v;
+  };
+  const double* Tc[NC];
+  bool cload[NC];
+  double cnext[NC];
+#pragma unroll
+  for (int q = 0; q < NC; ++q) {
+    const int idx = threadIdx.x + q * kBlock, ct = idx / LD, cu = idx % LD, v = cu + ct % 3 - 1;
+    cload[q] = ct < 6 && cu < b && (per || (v >= 0 && v < b));
+    Tc[q] = T + (cload[q] ? ct * g.tsize + (bx.o[0] + cu + 1 + g.ne) % g.ne : 0);
+    cnext[q] = cload[q] ? Tc[q][(long)g.P[0] * bx.o[1]] : 0.0;
+  }
+  for (int i = 0; i < bx.nch; ++i) {
+#pragma unroll
+    for (int q = 0; q < NC; ++q) cf[threadIdx.x + q * kBlock] = cnext[q];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NC; ++q)
+      if (cload[q] && i + 1 < bx.nch) cnext[q] = Tc[q][(long)g.P[0] * (bx.o[1] + i + 1)];
+    // (opaque copies: the entries' addresses hoisted out of the slice loop would spill)
+    int vi = ti, vj = tj;
+    asm volatile("" : "+v"(vi), "+v"(vj));
+    double a[NA][NA];
+#pragma unroll
+    for (int x = 0; x < NA; ++x)
+#pragma unroll
+      for (int y = 0; y < NA; ++y) {
+        const int r = vi + kFacG * x, c = vj + kFacG * y;
+        double v = 0.0;
+        if (r < b && c < b) {
+#pragma unroll
+          for (int d = 0; d < 3; ++d)
+            if (nbr(r, d) == c) v += cf[(3 + d) * LD + r];
+          if (i > 0) {
+            double corr = 0.0;
+#pragma unroll
+            for (int d1 = 0; d1 < 3; ++d1) {
+              const double* wr = wp + nbr(r, d1) * b;
+              double inner = 0.0;
+#pragma unroll
+              for (int d2 = 0; d2 < 3; ++d2) inner += cf[d2 * LD + c] * wr[nbr(c, d2)];
+              corr += cf[d1 * LD + r] * inner;
+            }
+            v -= corr;
+          }
+        }
+        a[x][y] = v;
+      }
+    if (!gj_registers<NA>(a, b, ti, tj, row, col)) {
+      if (threadIdx.x == 0) atomicOr(flag, 1);
+      return;
+    }
+    // (every read of the previous slice's wp and cf lies before the elimination's barriers)
+    const RowsLayout l(b);
+    double* Wi = W + (long)i * (rows ? 2 * l.slice() : b * b);
+#pragma unroll
+    for (int x = 0; x < NA; ++x)
+#pragma unroll
+      for (int y = 0; y < NA; ++y) {
+        const int r = ti + kFacG * x, c = tj + kFacG * y;
+        if (r < b && c < b) {
+          Wi[rows ? l.at(r, c) : r * b + c] = a[x][y];  // (symmetric)
+          wp[r * b + c] = a[x][y];
+        }
+      }
   }
 }
 
-// Gauss-Jordan inversion in place, one launch per pivot.  rowk/colk hold row
-// and column k of the matrix before step k; the launch also records row and
-// column k+1 after step k into rown/coln for the next pivot.
-__global__ void k_gj_step(double* __restrict__ A, int b, int k, const double* __restrict__ rowk,
-                          const double* __restrict__ colk, double* __restrict__ rown,
-                          double* __restrict__ coln, int* __restrict__ flag) {
-  const double piv = rowk[k];
-  if (!(piv > 0.0)) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(flag, 1);
+// A single inversion of at most kFacMaxB unknowns in one workgroup.
+template <int NA>
+__global__ void __launch_bounds__(kBlock) k_gj_small(double* __restrict__ A, int b,
+                                                    int* __restrict__ flag) {
+  __shared__ __align__(16) double row[2 * kFacP * kFacG * NA], col[2 * kFacP * kFacG * NA];
+  const int ti = threadIdx.x / kFacG, tj = threadIdx.x % kFacG;
+  double a[NA][NA];
+#pragma unroll
+  for (int x = 0; x < NA; ++x)
+#pragma unroll
+    for (int y = 0; y < NA; ++y) {
+      const int i = ti + kFacG * x, j = tj + kFacG * y;
+      a[x][y] = i < b && j < b ? A[(long)i * b + j] : 0.0;
+    }
+  if (!gj_registers<NA>(a, b, ti, tj, row, col)) {
+    if (threadIdx.x == 0) atomicOr(flag, 1);
     return;
   }
-  const double ipiv = 1.0 / piv;
-  const long bb = (long)b * b;
-  for (long idx = blockIdx.x * (long)blockDim.x + threadIdx.x; idx < bb;
-       idx += (long)gridDim.x * blockDim.x) {
-    const int i = (int)(idx / b), j = (int)(idx % b);
-    double v;
-    if (i == k) {
-      v = (j == k) ? ipiv : rowk[j] * ipiv;
-    } else {
-      const double f = colk[i];
-      v = (j == k) ? -f * ipiv : A[idx] - f * (rowk[j] * ipiv);
+#pragma unroll
+  for (int x = 0; x < NA; ++x)
+#pragma unroll
+    for (int y = 0; y < NA; ++y) {
+      const int i = ti + kFacG * x, j = tj + kFacG * y;
+      if (i < b && j < b) A[(long)i * b + j] = a[x][y];
     }
-    A[idx] = v;
-    if (i == k + 1) rown[j] = v;
-    if (j == k + 1) coln[i] = v;
+}
+
+// S_i of every job, one workgroup per (row, job): row r of E_i W_{i-1} is
+// formed once in LDS from 3^(D-1) coalesced rows of W_{i-1}, then every entry
+// of the row takes its 3^(D-1) couplings from LDS (the product entry by entry
+// would read W_{i-1} 9^(D-1) times: 420 us a slice at b = 1085).
+constexpr int kSchurTaps = 9;
+__global__ void __launch_bounds__(kBlock) k_schur_row(Geo g, FactorJobs jobs, int i,
+                                                      const double* __restrict__ T) {
+  extern __shared__ double u[];  // b
+  const Box bx = jobs.bx[blockIdx.y];
+  const int b = bx.b, D = g.D, last = D - 1, r = blockIdx.x;
+  if (r >= b || i >= bx.nch) return;
+  const int ntap = D == 2 ? 3 : 9;  // taps of one slice offset, in tap order
+  const long bb = (long)b * b;
+  double* __restrict__ S = jobs.W[blockIdx.y] + (long)i * bb + (long)r * b;
+  int ur[3];
+  slice_coords(bx, D, r, ur);
+  ur[last] = i;
+  const long tr = box_tnode(g, bx, ur);
+  auto offs = [&](int t, int* d) {
+    d[0] = t % 3 - 1;
+    d[1] = D == 3 ? t / 3 - 1 : 0;
+    d[2] = 0;
+  };
+  if (i > 0) {
+    const double* Wp = jobs.W[blockIdx.y] + (long)(i - 1) * bb;
+    double e[kSchurTaps];
+    long at[kSchurTaps];
+#pragma unroll
+    for (int t = 0; t < kSchurTaps; ++t) {
+      e[t] = 0.0;
+      at[t] = (long)r * b;
+      int d[3], n1;
+      offs(t, d);
+      if (t < ntap && slice_nbr(bx, D, ur, d, n1)) {
+        e[t] = T[t * g.tsize + tr];
+        at[t] = (long)n1 * b;
+      }
+    }
+    for (int s = threadIdx.x; s < b; s += kBlock) {
+      double v = 0.0;
+#pragma unroll
+      for (int t = 0; t < kSchurTaps; ++t) v += e[t] * Wp[at[t] + s];
+      u[s] = v;
+    }
+    __syncthreads();
+  }
+  for (int s = threadIdx.x; s < b; s += kBlock) {
+    int us[3];
+    slice_coords(bx, D, s, us);
+    us[last] = i;
+    const long ts = box_tnode(g, bx, us);
+    double v = 0.0, corr = 0.0;
+    for (int t = 0; t < ntap; ++t) {
+      int d[3], n;
+      offs(t, d);
+      if (slice_nbr(bx, D, ur, d, n) && n == s) v += T[(ntap + t) * g.tsize + tr];
+      if (i > 0 && slice_nbr(bx, D, us, d, n)) corr += T[t * g.tsize + ts] * u[n];
+    }
+    S[s] = v - corr;
   }
 }
 
-__global__ void k_gj_init(const double* __restrict__ A, int b, double* __restrict__ row0,
-                          double* __restrict__ col0) {
-  for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < b; j += gridDim.x * blockDim.x) {
-    row0[j] = A[j];
-    col0[j] = A[(long)j * b];
+// Blocked Gauss-Jordan, pivot block [k0, k0 + nb) of every job (grid y).  The
+// panel kernel inverts the diagonal block (every workgroup for itself, in
+// registers) and writes, for its kGjTile rows and columns, the row panel
+// R = D^{-1} A_kj (with R_kk = D^{-1}) and a copy of the column panel C = A_ik;
+// the update kernel then applies A_ij -= C_i R_j, A_ik = -C_i D^{-1},
+// A_kj = R_j.  Buffers per job: R (kGjNb x b), then C (b x kGjNb).
+constexpr int kGjNb = 32, kGjTile = 64;
+
+__global__ void __launch_bounds__(kBlock) k_gj_panel(FactorJobs jobs, int i, int k0,
+                                                     double* __restrict__ buf, long bstride,
+                                                     int* __restrict__ flag) {
+  constexpr int NA = kGjNb / kFacG;
+  __shared__ __align__(16) double row[2 * kFacP * kGjNb], col[2 * kFacP * kGjNb];
+  __shared__ double D[kGjNb][kGjNb + 1], P[kGjNb][kGjTile + 1];
+  const Box bx = jobs.bx[blockIdx.y];
+  const int b = bx.b;
+  const int c0 = blockIdx.x * kGjTile;
+  if (k0 >= b || c0 >= b || i >= bx.nch) return;
+  const int nb = min(kGjNb, b - k0);
+  const double* __restrict__ A = jobs.W[blockIdx.y] + (long)i * b * b;
+  double* __restrict__ R = buf + blockIdx.y * bstride;
+  double* __restrict__ C = R + (long)kGjNb * b;
+  const int ti = threadIdx.x / kFacG, tj = threadIdx.x % kFacG;
+  double a[NA][NA];
+#pragma unroll
+  for (int x = 0; x < NA; ++x)
+#pragma unroll
+    for (int y = 0; y < NA; ++y) {
+      const int r = ti + kFacG * x, c = tj + kFacG * y;
+      a[x][y] = r < nb && c < nb ? A[(long)(k0 + r) * b + k0 + c] : 0.0;
+    }
+  // this workgroup's columns of the row panel, and rows of the column panel
+#pragma unroll
+  for (int q = threadIdx.x; q < kGjNb * kGjTile; q += kBlock) {
+    const int k = q / kGjTile, j = q % kGjTile;
+    P[k][j] = k < nb && c0 + j < b ? A[(long)(k0 + k) * b + c0 + j] : 0.0;
+    const int kk = q % kGjNb, r = c0 + q / kGjNb;
+    if (r < b) C[(long)r * kGjNb + kk] = kk < nb ? A[(long)r * b + k0 + kk] : 0.0;
+  }
+  if (!gj_registers<NA>(a, nb, ti, tj, row, col)) {
+    if (threadIdx.x == 0) atomicOr(flag, 1);
+    return;
+  }
+#pragma unroll
+  for (int x = 0; x < NA; ++x)
+#pragma unroll
+    for (int y = 0; y < NA; ++y) {
+      const int r = ti + kFacG * x, c = tj + kFacG * y;
+      D[r][c] = r < nb && c < nb ? a[x][y] : 0.0;
+    }
+  __syncthreads();
+#pragma unroll
+  for (int q = threadIdx.x; q < kGjNb * kGjTile; q += kBlock) {
+    const int r = q / kGjTile, jl = q % kGjTile, j = c0 + jl;
+    double v = 0.0;
+    if (j >= k0 && j < k0 + nb) {
+      v = D[r][j - k0];
+    } else {
+#pragma unroll 8
+      for (int k = 0; k < kGjNb; ++k) v += D[r][k] * P[k][jl];
+    }
+    if (j < b) R[(long)r * b + j] = v;
   }
 }
+
+__global__ void __launch_bounds__(kBlock) k_gj_update(FactorJobs jobs, int i, int k0,
+                                                      const double* __restrict__ buf, long bstride) {
+  __shared__ double Cs[kGjNb][kGjTile + 2], Rs[kGjNb][kGjTile + 2];
+  const Box bx = jobs.bx[blockIdx.z];
+  const int b = bx.b;
+  const int i0 = blockIdx.y * kGjTile, j0 = blockIdx.x * kGjTile;
+  if (k0 >= b || i0 >= b || j0 >= b || i >= bx.nch) return;
+  const int nb = min(kGjNb, b - k0);
+  double* __restrict__ A = jobs.W[blockIdx.z] + (long)i * b * b;
+  const double* __restrict__ R = buf + blockIdx.z * bstride;
+  const double* __restrict__ C = R + (long)kGjNb * b;
+  for (int q = threadIdx.x; q < kGjNb * kGjTile; q += kBlock) {
+    const int k = q / kGjTile, j = q % kGjTile;
+    Rs[k][j] = j0 + j < b ? R[(long)k * b + j0 + j] : 0.0;
+    const int kk = q % kGjNb, r = q / kGjNb;
+    Cs[kk][r] = i0 + r < b ? C[(long)(i0 + r) * kGjNb + kk] : 0.0;
+  }
+  // thread: rows 4 ty .. + 3, columns tx + 16 y
+  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+  double acc[4][4];
+#pragma unroll
+  for (int x = 0; x < 4; ++x)
+#pragma unroll
+    for (int y = 0; y < 4; ++y) {
+      const int r = i0 + 4 * ty + x, j = j0 + tx + 16 * y;
+      const bool kj = j >= k0 && j < k0 + nb;
+      acc[x][y] = r < b && j < b && !kj ? A[(long)r * b + j] : 0.0;
+    }
+  __syncthreads();
+#pragma unroll 8
+  for (int k = 0; k < kGjNb; ++k) {
+    double c[4], r[4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      c[x] = Cs[k][4 * ty + x];
+      r[x] = Rs[k][tx + 16 * x];
+    }
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+      for (int y = 0; y < 4; ++y) acc[x][y] -= c[x] * r[y];
+  }
+#pragma unroll
+  for (int x = 0; x < 4; ++x)
+#pragma unroll
+    for (int y = 0; y < 4; ++y) {
+      const int r = i0 + 4 * ty + x, j = j0 + tx + 16 * y;
+      if (r >= b || j >= b) continue;
+      const bool ki = r >= k0 && r < k0 + nb;
+      A[(long)r * b + j] = ki ? Rs[r - k0][tx + 16 * y] : acc[x][y];
+    }
+}
+
+// Inverts slice i of every job in pivot blocks.
+static void gj_blocked(ddeig_problem* P, const FactorJobs& jobs, int njobs, int bmax, int i,
+                       hipStream_t s) {
+  const long stride = 2L * kGjNb * P->gj_stride;
+  const int nt = (bmax + kGjTile - 1) / kGjTile;
+  for (int k0 = 0; k0 < bmax; k0 += kGjNb) {
+    hipLaunchKernelGGL(k_gj_panel, dim3(nt, njobs), dim3(kBlock), 0, s, jobs, i, k0, P->gjbuf, stride,
+                       P->flag);
+    hipLaunchKernelGGL(k_gj_update, dim3(nt, nt, njobs), dim3(kBlock), 0, s, jobs, i, k0, P->gjbuf,
+                       stride);
+  }
+}
+
+long gj_buffer_doubles(int bmax, int njobs) { return 2L * kGjNb * bmax * njobs; }
 
 void launch_gj_invert(ddeig_problem* P, double* A, int b, hipStream_t s) {
-  const long st = P->gj_stride;
-  double* bufs[2][2] = {{P->gjbuf, P->gjbuf + st}, {P->gjbuf + 2 * st, P->gjbuf + 3 * st}};
-  hipLaunchKernelGGL(k_gj_init, dim3((b + kBlock - 1) / kBlock), dim3(kBlock), 0, s, A, b,
-                     bufs[0][0], bufs[0][1]);
-  const long bb = (long)b * b;
-  const int blocks = (int)std::min<long>((bb + kBlock - 1) / kBlock, 4096);
-  for (int k = 0; k < b; ++k) {
-    double** cur = bufs[k & 1];
-    double** nxt = bufs[(k + 1) & 1];
-    hipLaunchKernelGGL(k_gj_step, dim3(blocks), dim3(kBlock), 0, s, A, b, k, cur[0], cur[1],
-                       nxt[0], nxt[1], P->flag);
+  if (b <= kFacMaxB) {
+    auto kern = b <= 32 ? k_gj_small<2> : b <= 64 ? k_gj_small<4> : b <= 80 ? k_gj_small<5> : k_gj_small<8>;
+    hipLaunchKernelGGL(kern, dim3(1), dim3(kBlock), 0, s, A, b, P->flag);
+    return;
   }
+  FactorJobs jobs{};
+  jobs.bx[0].b = b;
+  jobs.bx[0].nch = 1;
+  jobs.W[0] = A;
+  gj_blocked(P, jobs, 1, b, 0, s);
 }
 
-void chain_factor(ddeig_problem* P, const Box& bx, const double* tab, double* W, hipStream_t s) {
-  const long bb = (long)bx.b * bx.b;
-  const int blocks = (int)std::min<long>((bb + kBlock - 1) / kBlock, 4096);
-  for (int i = 0; i < bx.nch; ++i) {
-    double* Wi = W + (long)i * bb;
-    const double* Wp = i > 0 ? W + (long)(i - 1) * bb : nullptr;
-    hipLaunchKernelGGL(k_schur_build, dim3(blocks), dim3(kBlock), 0, s, P->g, bx, i, tab, Wp, Wi);
-    launch_gj_invert(P, Wi, bx.b, s);
+// Row solves (chain_rows) of slices of b, nch of them: the LDS copy of the
+// right-hand side has to fit, and one wave holds a slice.
+constexpr size_t kRowsLds = 128 * 1024;
+static size_t rows_lds(int b, int nch) { return ((size_t)b * nch + 2 * 64 + 2) * sizeof(double); }
+static bool rows_ok(int b, int nch) { return b <= kRowsMaxB && rows_lds(b, nch) <= kRowsLds; }
+
+// Entries of a 2-D or 3-D box's factor, in either layout; bmax, nchmax: over the
+// problem's classes (one kernel serves them all).
+size_t factor_entries(int D, const Box& bx, int bmax, int nchmax) {
+  if (D == 2 && rows_ok(bmax, nchmax)) return (size_t)bx.nch * 2 * RowsLayout(bx.b).slice();
+  return (size_t)bx.nch * bx.b * bx.b;
+}
+
+// The chains of all boxes (their W pointers alongside); as many at once as the
+// pivot buffers hold.
+void chain_factor(ddeig_problem* P, const std::vector<Box>& boxes, const std::vector<double*>& Ws,
+                  const double* tab, hipStream_t s) {
+  int bmax = 0, nch = 0;
+  for (const Box& bx : boxes) {
+    bmax = std::max(bmax, bx.b);
+    nch = std::max(nch, bx.nch);
+  }
+  const bool small = P->g.D == 2 && bmax <= kFacMaxB;
+  const int rows = P->g.D == 2 && rows_ok(bmax, nch);
+  const int at_once = small ? kMaxTypes : std::min(kMaxTypes, P->gj_jobs);
+  for (size_t j0 = 0; j0 < boxes.size(); j0 += at_once) {
+    const int nj = (int)std::min<size_t>(at_once, boxes.size() - j0);
+    FactorJobs jobs{};
+    for (int j = 0; j < nj; ++j) {
+      jobs.bx[j] = boxes[j0 + j];
+      jobs.W[j] = Ws[j0 + j];
+    }
+    if (small) {
+      auto kern = bmax <= 32 ? k_chain_factor2d<2>
+                             : bmax <= 48 ? k_chain_factor2d<3>
+                             : bmax <= 64 ? k_chain_factor2d<4>
+                             : bmax <= 80 ? k_chain_factor2d<5> : k_chain_factor2d<8>;
+      const size_t lds = (size_t)bmax * bmax * sizeof(double);
+      check_hip(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds),
+                "factorisation LDS");
+      hipLaunchKernelGGL(kern, dim3(nj), dim3(kBlock), lds, s, P->g, tab, jobs, rows, P->flag);
+      continue;
+    }
+    for (int i = 0; i < nch; ++i) {
+      hipLaunchKernelGGL(k_schur_row, dim3(bmax, nj), dim3(kBlock), (size_t)bmax * sizeof(double), s,
+                         P->g, jobs, i, tab);
+      gj_blocked(P, jobs, nj, bmax, i, s);
+    }
   }
 }
 
@@ -224,18 +649,153 @@ __device__ void chain_solve_block(const Geo& g, const Box& bx, const double* __r
   }
 }
 
-__global__ void __launch_bounds__(kBlock) k_chain_solve_box(Geo g, Box bx,
-                                                            const double* __restrict__ T,
-                                                            const double* __restrict__ W,
-                                                            double* __restrict__ v) {
-  extern __shared__ double sh[];
-  chain_solve_block<double>(g, bx, T, W, v + (long)blockIdx.x * bx.nch * bx.b, sh);
+// ---- chain solves of one box with wide slices (3-D boxes, 2-D ones of more than
+// kRowsMaxB unknowns), one launch per sweep step over all CUs (one workgroup
+// for the whole solve took 1 ms a step at b = 992).
+//
+// The couplings of slice i with slice i - 1 (d = -1) or i + 1 (d = +1): the
+// right-hand side of row k without b_i.
+__device__ __forceinline__ double slice_coupling(const Geo& g, const Box& bx,
+                                                 const double* __restrict__ T, int i, int k, int d,
+                                                 const double* __restrict__ nb) {
+  const int D = g.D, ntap = D == 2 ? 3 : 9;
+  int u[3];
+  slice_coords(bx, D, k, u);
+  u[D - 1] = i;
+  const long tn = box_tnode(g, bx, u) + (d < 0 ? 0 : 2 * ntap) * g.tsize;
+  double v = 0.0;
+#pragma unroll
+  for (int t = 0; t < 9; ++t) {
+    if (t >= ntap) break;
+    const int dd[3] = {t % 3 - 1, D == 3 ? t / 3 - 1 : 0, 0};
+    int n;
+    if (slice_nbr(bx, D, u, dd, n)) v += T[t * g.tsize + tn] * nb[n];
+  }
+  return v;
 }
 
-void launch_chain_solve_box(const ddeig_problem* P, const Box& bx, const double* tab,
-                            const double* W, double* v, int nrhs, hipStream_t s) {
-  const size_t lds = 2 * (size_t)bx.b * sizeof(double);
-  hipLaunchKernelGGL(k_chain_solve_box, dim3(nrhs), dim3(kBlock), lds, s, P->g, bx, tab, W, v);
+// One right-hand side: workgroup = 8 rows of W_i.  Every workgroup forms the
+// slice's g for itself in LDS (the slice before it is the last launch's
+// output); forward t_i = W_i (b_i - E_i t_{i-1}) into out, backward
+// x_i = t_i - W_i E_{i+1}^T x_{i+1}.  bi: b_i (forward); ti: t_i (backward).
+constexpr int kWideRows = 8;
+template <bool FWD>
+__global__ void __launch_bounds__(kBlock) k_wide_row(Geo g, Box bx, const double* __restrict__ T,
+                                                     const double* __restrict__ W, int i,
+                                                     const double* __restrict__ bi,
+                                                     const double* __restrict__ nb,
+                                                     const double* __restrict__ ti,
+                                                     double* __restrict__ out) {
+  extern __shared__ double gs[];  // b
+  const int b = bx.b;
+  for (int k = threadIdx.x; k < b; k += kBlock) {
+    const double c = FWD && i == 0 ? 0.0 : slice_coupling(g, bx, T, i, k, FWD ? -1 : 1, nb);
+    gs[k] = FWD ? bi[k] - c : c;
+  }
+  __syncthreads();
+  const int lane = threadIdx.x & 63;
+  const double* Wi = W + (long)i * b * b;
+#pragma unroll
+  for (int q = 0; q < kWideRows / 4; ++q) {
+    const int r = blockIdx.x * kWideRows + (threadIdx.x >> 6) * (kWideRows / 4) + q;
+    if (r >= b) break;
+    double acc = 0.0;
+#pragma unroll 8
+    for (int k = lane; k < b; k += 64) acc += Wi[(long)r * b + k] * gs[k];
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
+    if (lane == 0) out[r] = FWD ? acc : ti[r] - acc;
+  }
+}
+
+// The columns of the identity, x[col] (nch b values each): 64 x 64 tiles of
+// (rows of the slice, columns), 4 x 4 entries per thread, g formed while it is
+// staged (the unit entry needs no memory).  A forward tile whose columns all
+// start in a later slice is zero.
+constexpr int kWideT = 64, kWideK = 32;
+template <bool FWD>
+__global__ void __launch_bounds__(kBlock) k_wide_tile(Geo g, Box bx, const double* __restrict__ T,
+                                                      const double* __restrict__ W, int i, int ncol,
+                                                      double* __restrict__ x) {
+  __shared__ double Ws[kWideK][kWideT], Gs[kWideK][kWideT + 1];
+  const int b = bx.b, r0 = blockIdx.x * kWideT, c0 = blockIdx.y * kWideT;
+  const long m = (long)bx.nch * b;
+  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;  // rows r0 + tx + 16 y, columns c0 + ty + 16 z
+  double acc[4][4] = {};
+  if (!FWD || c0 < (i + 1) * b) {
+    const double* Wi = W + (long)i * b * b;
+    for (int k0 = 0; k0 < b; k0 += kWideK) {
+#pragma unroll
+      for (int q = 0; q < kWideK * kWideT / kBlock; ++q) {
+        const int idx = threadIdx.x + q * kBlock;
+        const int k = k0 + idx / kWideT, r = r0 + idx % kWideT;
+        Ws[idx / kWideT][idx % kWideT] = k < b && r < b ? Wi[(long)k * b + r] : 0.0;
+        const int kk = k0 + idx % kWideK, c = c0 + idx / kWideK;
+        double v = 0.0;
+        if (kk < b && c < ncol) {
+          if (!FWD || i > 0)
+            v = slice_coupling(g, bx, T, i, kk, FWD ? -1 : 1, x + c * m + (long)(FWD ? i - 1 : i + 1) * b);
+          if (FWD) v = (c == i * b + kk ? 1.0 : 0.0) - v;
+        }
+        Gs[idx % kWideK][idx / kWideK] = v;
+      }
+      __syncthreads();
+#pragma unroll 8
+      for (int k = 0; k < kWideK; ++k) {
+        double w[4], v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          w[q] = Ws[k][tx + 16 * q];
+          v[q] = Gs[k][ty + 16 * q];
+        }
+#pragma unroll
+        for (int z = 0; z < 4; ++z)
+#pragma unroll
+          for (int y = 0; y < 4; ++y) acc[z][y] += w[y] * v[z];
+      }
+      __syncthreads();
+    }
+  }
+#pragma unroll
+  for (int z = 0; z < 4; ++z)
+#pragma unroll
+    for (int y = 0; y < 4; ++y) {
+      const int r = r0 + tx + 16 * y, c = c0 + ty + 16 * z;
+      if (r >= b || c >= ncol) continue;
+      double* o = x + c * m + (long)i * b + r;
+      *o = FWD ? acc[z][y] : *o - acc[z][y];
+    }
+}
+
+bool launch_rows_box(const ddeig_problem* P, const Box& bx, const double* tab, const double* W,
+                     double* v, int nrhs, int identity, hipStream_t s);
+
+// v <- A^{-1} v for one right-hand side; tmp: nch b values
+void launch_chain_solve(const ddeig_problem* P, const Box& bx, const double* tab, const double* W,
+                        double* v, double* tmp, hipStream_t s) {
+  if (launch_rows_box(P, bx, tab, W, v, 1, 0, s)) return;
+  const int b = bx.b, n = bx.nch;
+  const size_t lds = (size_t)b * sizeof(double);
+  const dim3 grid((b + kWideRows - 1) / kWideRows);
+  for (int i = 0; i < n; ++i)
+    hipLaunchKernelGGL(k_wide_row<true>, grid, dim3(kBlock), lds, s, P->g, bx, tab, W, i,
+                       v + (long)i * b, i > 0 ? tmp + (long)(i - 1) * b : nullptr, nullptr,
+                       tmp + (long)i * b);
+  launch_copy(v + (long)(n - 1) * b, tmp + (long)(n - 1) * b, b, s);
+  for (int i = n - 2; i >= 0; --i)
+    hipLaunchKernelGGL(k_wide_row<false>, grid, dim3(kBlock), lds, s, P->g, bx, tab, W, i, nullptr,
+                       v + (long)(i + 1) * b, tmp + (long)i * b, v + (long)i * b);
+}
+
+// x <- A^{-1} (all nch b columns)
+void launch_chain_inverse(const ddeig_problem* P, const Box& bx, const double* tab, const double* W,
+                          double* x, hipStream_t s) {
+  const int m = bx.nch * bx.b;
+  if (launch_rows_box(P, bx, tab, W, x, m, 1, s)) return;
+  const dim3 grid((bx.b + kWideT - 1) / kWideT, (m + kWideT - 1) / kWideT);
+  for (int i = 0; i < bx.nch; ++i)
+    hipLaunchKernelGGL(k_wide_tile<true>, grid, dim3(kBlock), 0, s, P->g, bx, tab, W, i, m, x);
+  for (int i = bx.nch - 2; i >= 0; --i)
+    hipLaunchKernelGGL(k_wide_tile<false>, grid, dim3(kBlock), 0, s, P->g, bx, tab, W, i, m, x);
 }
 
 // All local subdomain solves of the level-1 preconditioner in one launch:
@@ -502,169 +1062,301 @@ void launch_local_solves(const ddeig_problem* P, const PcgState* st, hipStream_t
 
 namespace ddeig {
 
-// Local solves of the 2-D decompositions (slices along x of at most kFastB
-// unknowns, chain along y).  W_i is staged in LDS with double buffering;
-// while step i computes from LDS, every thread already holds its share of
-// W_{i+1} (W_{i-1} in the backward sweep), the next slice of the right-hand
-// side and the next coupling coefficients in registers.  Each row's dot
-// product is split over np = floor(256 / b) thread groups and the parts are
-// added in a fixed order.  In 2-D the couplings to the neighbouring slice are
-// the taps (d0, d1) = (-1..1, -1) (forward) and (-1..1, +1) (backward), i.e.
-// table taps 0..2 and 6..8, with in-slice neighbours r-1, r, r+1.
-constexpr int kFastB = 72;
-constexpr int kFastRegs = (kFastB * kFastB + kBlock - 1) / kBlock;
+// ---- chain solves of 2-D boxes: slices along x of at most kRowsMaxB unknowns,
+// chain along y, one workgroup per right-hand side.
+//
+// A sweep is 2 nch - 1 dependent steps t = W_i g, g = b_i - E_i t_{i-1} (or
+// E_{i+1}^T x_{i+1}), so a step's latency is the time of the solve.  It is a
+// chain of instructions (a wave issues one every 4 to 5 cycles) and LDS round
+// trips, so it is split to keep what the chain waits for short:
+//  - wave 0 forms g, two rows per lane, from the last slice in LDS; couplings
+//    and b_i are in its registers by then;
+//  - a lane of the other waves multiplies its part's columns of g by its pair of
+//    rows of W_i (RowsLayout), the 8 parts of a row are added across the wave,
+//    and the lane that ends up with a row writes it to the slice in LDS.  They
+//    load W of the slice after next while wave 0 forms g.
+// The right-hand side and the sweep's vectors stay in LDS throughout: no global
+// store, and no load whose latency a step waits for.  At b = 71: W_i staged
+// through LDS with three barriers a step 2.2 us; partial sums passed through LDS
+// 0.96; every wave forming g for itself (one barrier) 0.60, at b = 35 0.46; this
+// 0.60 and 0.36 (there the loads of W, 45 KB a step through a 64-byte port, are
+// the larger part; 256 subdomains of 63 lines: 285 -> 84 us).
+// In 2-D the couplings are the taps (-1..1, -1), i.e. table taps 0..2
+// (forward), and (-1..1, +1), taps 6..8 (backward).
 template <typename WT>
-__device__ inline double dot_part(const WT* __restrict__ wc, const double* __restrict__ gv, int b,
-                                  int r, int s0, int s1) {
-  double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-  int s = s0;
-  for (; s + 3 < s1; s += 4) {
-    a0 += (double)wc[s * b + r] * gv[s];
-    a1 += (double)wc[(s + 1) * b + r] * gv[s + 1];
-    a2 += (double)wc[(s + 2) * b + r] * gv[s + 2];
-    a3 += (double)wc[(s + 3) * b + r] * gv[s + 3];
-  }
-  for (; s < s1; ++s) a0 += (double)wc[s * b + r] * gv[s];
-  return (a0 + a1) + (a2 + a3);
+struct Pair;
+template <>
+struct Pair<double> {
+  typedef double __attribute__((ext_vector_type(2))) type;
+};
+template <>
+struct Pair<float> {
+  typedef float __attribute__((ext_vector_type(2))) type;
+};
+
+// The values of a and b of all 8 parts added: lanes 0..31 receive the sums of
+// a, lanes 32..63 those of b.
+__device__ __forceinline__ double part_sum2(double a, double b) {
+  typedef unsigned __attribute__((ext_vector_type(2))) u2;
+  auto join = [](unsigned lo, unsigned hi) { return __builtin_bit_cast(double, u2{lo, hi}); };
+  const u2 ua = __builtin_bit_cast(u2, a), ub = __builtin_bit_cast(u2, b);
+  // lanes 0..31: a of both halves, lanes 32..63: b of both halves
+  auto l = __builtin_amdgcn_permlane32_swap(ua.x, ub.x, false, false);
+  auto h = __builtin_amdgcn_permlane32_swap(ua.y, ub.y, false, false);
+  double v = join(l[0], h[0]) + join(l[1], h[1]);
+  u2 u = __builtin_bit_cast(u2, v);
+  l = __builtin_amdgcn_permlane16_swap(u.x, u.x, false, false);
+  h = __builtin_amdgcn_permlane16_swap(u.y, u.y, false, false);
+  v = join(l[0], h[0]) + join(l[1], h[1]);
+  u = __builtin_bit_cast(u2, v);
+  // row_ror:8
+  return v + join(__builtin_amdgcn_update_dpp(0, u.x, 0x128, 0xf, 0xf, false),
+                  __builtin_amdgcn_update_dpp(0, u.y, 0x128, 0xf, 0xf, false));
 }
-template <typename WT>
-__global__ void __launch_bounds__(kBlock) k_local_solves_2d(Geo g, const double* __restrict__ T,
-                                                            const TypeDev* __restrict__ types,
-                                                            const SubDev* __restrict__ subs,
-                                                            const PcgState* __restrict__ st) {
-  __shared__ WT wbuf[2][kFastB * kFastB];
-  __shared__ double gb[kFastB];
-  __shared__ double tb[kFastB];
-  __shared__ double red[kBlock];
+
+// o0, o1: origin of the box; per: periodic in x.  col >= 0: the right-hand side
+// is column col of the identity (v is not read, and the sweep starts in its
+// slice i0).  tbuf: rows_lds(b, nch) bytes of LDS.
+template <typename WT, int KM>
+__device__ __forceinline__ void chain_rows(const Geo& g, const double* __restrict__ T,
+                                           const WT* __restrict__ W, double* __restrict__ v, int b,
+                                           int nch, int o0, int o1, bool per, int col,
+                                           double* __restrict__ tbuf) {
+  typedef typename Pair<WT>::type wpair;
+  constexpr int GS = KM | 1;  // stride of a part's columns of g (odd: distinct banks)
+  __shared__ double gsh[8 * GS + 1];  // g, and a slot for rows that do not exist
+  const int tid = threadIdx.x, lane = tid & 63, nth = blockDim.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const RowsLayout l(b);
+  const int i0 = col < 0 ? 0 : col / b;
+  const int nf = nch - i0, nst = nf + nch - 1;  // forward steps, all steps
+  // the slice after slice i of step st (past the last step: any slice)
+  auto next = [&](int i, int st) {
+    return __builtin_amdgcn_readfirstlane(max(i + (st + 1 < nf ? 1 : -1), 0));
+  };
+  // one row in front of the slices and 64 rows behind them are read, not used
+  double* tb = tbuf + 1;
+  const int dump = nch * b;
+  for (int q = tid; q < nch * b; q += nth) tb[q] = col < 0 ? v[q] : (q == col ? 1.0 : 0.0);
+  for (int q = tid; q < 2 * 64; q += nth) tb[dump + q] = 0.0;
+  if (tid == 0) tbuf[0] = 0.0;
+  for (int q = tid; q < 8 * GS + 1; q += nth) gsh[q] = 0.0;
+  __syncthreads();
+  // (the step past the last that an odd count needs changes nothing: a break
+  // inside the loops would spoil the compiler's load counters)
+  if (wave == 0) {
+    // rows r0, r0 + 1 of this lane, the columns that hold their neighbours, and
+    // their places in g
+    const int r0 = 2 * lane, r1 = r0 + 1;
+    const int nl = per && r0 == 0 ? b - 1 : r0 - 1;  // left of r0
+    const int nm = per && r0 == b - 1 ? 0 : r1;      // right of r0, and r1 itself
+    const int nr = per && r1 == b - 1 ? 0 : r0 + 2;  // right of r1
+    auto place = [&](int r) { return r < b ? r / l.chunk * GS + r % l.chunk : 8 * GS; };
+    double* g0p = gsh + place(r0);
+    double* g1p = gsh + place(r1);
+    // couplings of a step: three taps of each row (zero without a neighbour)
+    const auto rt = __builtin_amdgcn_make_buffer_rsrc((void*)T, (short)0, (int)(9 * g.tsize * 8),
+                                                      0x00020000);
+    int coff[6];
+#pragma unroll
+    for (int t = 0; t < 6; ++t) {
+      const int u = t < 3 ? r0 : r1, d = t % 3, n = u + d - 1;
+      const bool in = u < b && (per || (n >= 0 && n < b));
+      // (an offset past the table reads as zero)
+      coff[t] = (int)(in ? d * g.tsize + (o0 + u + 1 + g.ne) % g.ne : 9 * g.tsize) * 8;
+    }
+    const int cline = g.P[0] * 8, cback = (int)(6 * g.tsize * 8);
+    struct Coup {
+      double e[6];
+    };
+    auto loadc = [&](int i, int st) {
+      Coup c;
+#pragma unroll
+      for (int t = 0; t < 6; ++t)
+        c.e[t] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(
+                                                rt, coff[t], (o1 + i) * cline + (st < nf ? 0 : cback), 0));
+      return c;
+    };
+    int sp = i0, s1 = next(i0, 0), s2 = next(s1, 1), s3 = next(s2, 2);
+    Coup ca{}, cb = loadc(s1, 1), cc = loadc(s2, 2);  // (step 0 has no couplings)
+    double v0 = tb[i0 * b + r0], v1 = tb[i0 * b + r1];
+    int s0 = i0;
+    // step st: couplings in c, replaced by those of step st + 3
+    auto step = [&](int st, Coup& c) {
+      const double* tp = tb + sp * b;
+      const double tl = tp[nl], t0 = tp[r0], t1 = tp[nm], tr = tp[nr];
+      const double sg = st < nf ? -1.0 : 1.0;  // g = b_i - E t, or E^T x
+      double h0 = c.e[0] * tl, h1 = c.e[3] * t0;
+      h0 += c.e[1] * t0;
+      h1 += c.e[4] * t1;
+      h0 += c.e[2] * t1;
+      h1 += c.e[5] * tr;
+      *g0p = v0 + sg * h0;
+      *g1p = v1 + sg * h1;
+      __syncthreads();
+      c = loadc(s3, st + 3);
+      v0 = tb[s1 * b + r0];
+      v1 = tb[s1 * b + r1];
+      if (st + 1 >= nf) v0 = v1 = 0.0;
+      sp = s0;
+      s0 = s1;
+      s1 = s2;
+      s2 = s3;
+      s3 = next(s3, st + 3);
+      __syncthreads();
+    };
+    for (int st = 0; st < nst; st += 3) {
+      step(st, ca);
+      step(st + 1, cb);
+      step(st + 2, cc);
+    }
+  } else {
+    const int w0 = wave - 1, q = lane & 7;
+    // this lane's pairs of W.  Loads past a part's columns read the next wave's
+    // or slice's entries, or zero past the end: those terms meet a zero of g;
+    // lanes without rows read nothing.
+    constexpr int WB = (int)sizeof(wpair);
+    const int sbytes = l.slice() * WB;
+    const auto rw = __builtin_amdgcn_make_buffer_rsrc((void*)W, (short)0, nch * sbytes, 0x00020000);
+    const int wlane = w0 < l.nw && 16 * w0 + 2 * q < b ? (w0 * l.chunk * 64 + lane) * WB : nch * sbytes;
+    auto loadw = [&](wpair (&w)[KM], int i) {
+      const int base = i * sbytes;
+#pragma unroll
+      for (int k = 0; k < KM; ++k) {
+        constexpr int reach = 4096 / (64 * WB);  // loads an immediate offset reaches
+        const int imm = k % reach * 64 * WB, off = base + k / reach * 4096;
+        if constexpr (sizeof(WT) == 8)
+          w[k] = __builtin_bit_cast(wpair, __builtin_amdgcn_raw_buffer_load_b128(rw, wlane + imm, off, 0));
+        else
+          w[k] = __builtin_bit_cast(wpair, __builtin_amdgcn_raw_buffer_load_b64(rw, wlane + imm, off, 0));
+      }
+    };
+    const double* gl = gsh + (lane >> 3) * GS;
+    // the row that part_sum2 leaves in this lane
+    const int own = 16 * w0 + 2 * q + (lane >> 5);
+    const bool owner = (lane & 24) == 0 && own < b;
+    int s0 = i0, s1 = next(i0, 0), s2 = next(s1, 1);
+    wpair wa[KM], wb[KM], wc[KM];
+    loadw(wa, s0);
+    loadw(wb, s1);
+    // step st: W in w; loads W of step st + 2 into wn
+    auto step = [&](int st, const wpair (&w)[KM], wpair (&wn)[KM]) {
+      loadw(wn, s2);
+      const double told = tb[s0 * b + own];
+      double* out = tb + (owner && st < nst ? s0 * b + own : dump);
+      s0 = s1;
+      s1 = s2;
+      s2 = next(s2, st + 2);
+      __syncthreads();
+      double a0 = 0.0, a1 = 0.0;
+#pragma unroll
+      for (int k = 0; k < KM; ++k) {
+        a0 += (double)w[k].x * gl[k];
+        a1 += (double)w[k].y * gl[k];
+      }
+      const double t = part_sum2(a0, a1);
+      *out = st < nf ? t : told - t;
+      __syncthreads();
+    };
+    for (int st = 0; st < nst; st += 3) {
+      step(st, wa, wc);
+      step(st + 1, wb, wa);
+      step(st + 2, wc, wb);
+    }
+  }
+  for (int q = tid; q < nch * b; q += nth) v[q] = tb[q];
+}
+
+// The level-1 preconditioner's local solves: workgroup = subdomain, with its
+// class's factor.
+template <typename WT, int NT, int KM>
+__global__ void __launch_bounds__(NT) k_rows_local(Geo g, const double* __restrict__ T,
+                                                   const TypeDev* __restrict__ types,
+                                                   const SubDev* __restrict__ subs,
+                                                   const PcgState* __restrict__ st) {
+  extern __shared__ double tb[];
   if (st != nullptr && st->done) return;
   const SubDev sd = subs[blockIdx.x];
-  const TypeDev td = types[sd.type];
-  const int b = td.b, nch = td.nch;
-  const int bb = b * b;
-  const int tid = threadIdx.x;
-  const int np = kBlock / b;  // thread groups per row
-  const int chunk = (b + np - 1) / np;
-  const int part = tid / b, rr = tid - part * b;
-  const bool dot_thread = part < np;
-  const int s0 = min(b, part * chunk), s1 = min(b, s0 + chunk);
-  const WT* __restrict__ W;
+  const TypeDev& td = types[sd.type];
+  const WT* W;
   if constexpr (sizeof(WT) == 4) W = reinterpret_cast<const WT*>(td.W32);
   else W = reinterpret_cast<const WT*>(td.W);
-  double* __restrict__ v = td.batch + (long)sd.slot * nch * b;
-  const bool row = tid < b;
-  const int jx = row ? (sd.o[0] + tid + 1) % g.ne : 0;
-  const bool has_l = tid > 0, has_r = tid + 1 < b;
-  WT pre[kFastRegs];
-  for (int j = tid; j < bb; j += kBlock) wbuf[0][j] = W[j];
-  double vnext = row ? v[tid] : 0.0;
-  double cn0 = 0.0, cn1 = 0.0, cn2 = 0.0;
-  __syncthreads();
-  // forward sweep: t_i = W_i (b_i - E_i t_{i-1})
-  for (int i = 0; i < nch; ++i) {
-    const double vi = vnext, c0 = cn0, c1 = cn1, c2 = cn2;
-    if (i + 1 < nch) {
-      const WT* Wn = W + (long)(i + 1) * bb;
-#pragma unroll
-      for (int j = 0; j < kFastRegs; ++j) {
-        const int idx = tid + j * kBlock;
-        if (idx < bb) pre[j] = Wn[idx];
-      }
-      if (row) {
-        vnext = v[(long)(i + 1) * b + tid];
-        const long tn = jx + (long)g.P[0] * (sd.o[1] + i + 1);
-        cn0 = T[0 * g.tsize + tn];
-        cn1 = T[1 * g.tsize + tn];
-        cn2 = T[2 * g.tsize + tn];
-      }
-    }
-    if (row) {
-      double val = vi;
-      if (i > 0) {
-        if (has_l) val -= c0 * tb[tid - 1];
-        val -= c1 * tb[tid];
-        if (has_r) val -= c2 * tb[tid + 1];
-      }
-      gb[tid] = val;
-    }
-    __syncthreads();
-    if (dot_thread) red[tid] = dot_part(wbuf[i & 1], gb, b, rr, s0, s1);
-    __syncthreads();
-    if (row) {
-      double acc = red[tid];
-      for (int pp = 1; pp < np; ++pp) acc += red[pp * b + tid];
-      v[(long)i * b + tid] = acc;
-      tb[tid] = acc;
-    }
-    if (i + 1 < nch) {
-#pragma unroll
-      for (int j = 0; j < kFastRegs; ++j) {
-        const int idx = tid + j * kBlock;
-        if (idx < bb) wbuf[(i + 1) & 1][idx] = pre[j];
-      }
-    }
-    __syncthreads();
-  }
-  // backward sweep: x_i = t_i - W_i E_{i+1}^T x_{i+1}; W_{nch-2} is still in wbuf[nch & 1]
-  if (nch >= 2 && row) {
-    const long tn = jx + (long)g.P[0] * (sd.o[1] + nch - 2);
-    cn0 = T[6 * g.tsize + tn];
-    cn1 = T[7 * g.tsize + tn];
-    cn2 = T[8 * g.tsize + tn];
-    vnext = v[(long)(nch - 2) * b + tid];
-  }
-  for (int i = nch - 2; i >= 0; --i) {
-    const double vi = vnext, c0 = cn0, c1 = cn1, c2 = cn2;
-    if (i >= 1) {
-      const WT* Wn = W + (long)(i - 1) * bb;
-#pragma unroll
-      for (int j = 0; j < kFastRegs; ++j) {
-        const int idx = tid + j * kBlock;
-        if (idx < bb) pre[j] = Wn[idx];
-      }
-      if (row) {
-        vnext = v[(long)(i - 1) * b + tid];
-        const long tn = jx + (long)g.P[0] * (sd.o[1] + i - 1);
-        cn0 = T[6 * g.tsize + tn];
-        cn1 = T[7 * g.tsize + tn];
-        cn2 = T[8 * g.tsize + tn];
-      }
-    }
-    if (row) {
-      double val = c1 * tb[tid];
-      if (has_l) val += c0 * tb[tid - 1];
-      if (has_r) val += c2 * tb[tid + 1];
-      gb[tid] = val;
-    }
-    __syncthreads();
-    if (dot_thread) red[tid] = dot_part(wbuf[i & 1], gb, b, rr, s0, s1);
-    __syncthreads();
-    if (row) {
-      double acc = red[tid];
-      for (int pp = 1; pp < np; ++pp) acc += red[pp * b + tid];
-      const double x = vi - acc;
-      v[(long)i * b + tid] = x;
-      tb[tid] = x;
-    }
-    if (i >= 1) {
-#pragma unroll
-      for (int j = 0; j < kFastRegs; ++j) {
-        const int idx = tid + j * kBlock;
-        if (idx < bb) wbuf[(i - 1) & 1][idx] = pre[j];
-      }
-    }
-    __syncthreads();
+  chain_rows<WT, KM>(g, T, W, td.batch + (long)sd.slot * td.nch * td.b, td.b, td.nch, sd.o[0],
+                         sd.o[1], false, -1, tb);
+}
+
+// Right-hand sides of one box (FP64 factors): workgroup = right-hand side;
+// columns of the identity start in their own slice.
+template <int NT, int KM>
+__global__ void __launch_bounds__(NT) k_rows_box(Geo g, Box bx, const double* __restrict__ T,
+                                                 const double* __restrict__ W,
+                                                 double* __restrict__ v, int identity) {
+  extern __shared__ double tb[];
+  const long m = (long)bx.nch * bx.b;
+  const int col = identity ? (int)blockIdx.x : -1;
+  chain_rows<double, KM>(g, T, W, v + blockIdx.x * m, bx.b, bx.nch, bx.o[0], bx.o[1],
+                             bx.per[0] != 0, col, tb);
+}
+
+// The kernel for slices of at most b: columns per part (b / 8 rounded up), and
+// threads (wave 0 and a wave per 16 rows).
+#define ROWS_PICK(KERN, b, ...)                                                         \
+  ((b) <= 24   ? KERN<__VA_ARGS__ 192, 3>                                               \
+   : (b) <= 40 ? KERN<__VA_ARGS__ 256, 5>                                               \
+   : (b) <= 56 ? KERN<__VA_ARGS__ 320, 7>                                               \
+   : (b) <= 64 ? KERN<__VA_ARGS__ 320, 8>                                               \
+   : (b) <= 72 ? KERN<__VA_ARGS__ 384, 9>                                               \
+   : (b) <= 80 ? KERN<__VA_ARGS__ 384, 10>                                              \
+   : (b) <= 96 ? KERN<__VA_ARGS__ 448, 12> : KERN<__VA_ARGS__ 576, 16>)
+#define ROWS_COMMA ,
+
+template <typename K>
+static void rows_launch(K kern, int b, int nch, size_t& lds, int& nt) {
+  lds = rows_lds(b, nch);
+  nt = 64 * (RowsLayout(b).nw + 1);
+  check_hip(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds),
+            "chain solve LDS");
+}
+
+bool launch_rows_box(const ddeig_problem* P, const Box& bx, const double* tab, const double* W,
+                     double* v, int nrhs, int identity, hipStream_t s) {
+  if (P->g.D != 2 || !rows_ok(bx.b, bx.nch)) return false;
+  auto kern = ROWS_PICK(k_rows_box, bx.b);
+  size_t lds;
+  int nt;
+  rows_launch(kern, bx.b, bx.nch, lds, nt);
+  hipLaunchKernelGGL(kern, dim3(nrhs), dim3(nt), lds, s, P->g, bx, tab, W, v, identity);
+  return true;
+}
+
+static void class_extents(const ddeig_problem* P, int& b, int& nch) {
+  b = nch = 0;
+  for (const auto& t : P->types) {
+    b = std::max(b, t.box.b);
+    nch = std::max(nch, t.box.nch);
   }
 }
 
-bool local_solves_fast_ok(const ddeig_problem* P) { return P->maxb <= kFastB && P->g.D == 2; }
+bool local_solves_fast_ok(const ddeig_problem* P) {
+  int b, nch;
+  class_extents(P, b, nch);
+  return P->g.D == 2 && rows_ok(b, nch);
+}
+
+template <typename WT>
+static void launch_rows_local(const ddeig_problem* P, const PcgState* st, hipStream_t s) {
+  int b, nch, nt;
+  size_t lds;
+  class_extents(P, b, nch);
+  auto kern = ROWS_PICK(k_rows_local, b, WT ROWS_COMMA);
+  rows_launch(kern, b, nch, lds, nt);
+  hipLaunchKernelGGL(kern, dim3(P->nsub), dim3(nt), lds, s, P->g, P->tabAs, P->dTypes, P->dSubs, st);
+}
 
 void launch_local_solves_fast(const ddeig_problem* P, const PcgState* st, hipStream_t s) {
-  if (P->opt.local_prec == 1)
-    hipLaunchKernelGGL(k_local_solves_2d<float>, dim3(P->nsub), dim3(kBlock), 0, s, P->g,
-                       P->tabAs, P->dTypes, P->dSubs, st);
-  else
-    hipLaunchKernelGGL(k_local_solves_2d<double>, dim3(P->nsub), dim3(kBlock), 0, s, P->g,
-                       P->tabAs, P->dTypes, P->dSubs, st);
+  if (P->opt.local_prec == 1) launch_rows_local<float>(P, st, s);
+  else launch_rows_local<double>(P, st, s);
 }
 
 }  // namespace ddeig

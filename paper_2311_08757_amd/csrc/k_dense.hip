@@ -65,19 +65,6 @@ void launch_split_inverse(const double* Ainv, int m, int ld, void* Ah, void* Al,
                      (__bf16*)Ah, (__bf16*)Al);
 }
 
-__global__ void k_identity(double* __restrict__ v, int m) {
-  const long tot = (long)m * m;
-  for (long idx = blockIdx.x * (long)blockDim.x + threadIdx.x; idx < tot;
-       idx += (long)gridDim.x * blockDim.x)
-    v[idx] = (idx / m == idx % m) ? 1.0 : 0.0;
-}
-
-void launch_identity(double* v, int m, hipStream_t s) {
-  const long tot = (long)m * m;
-  const int blocks = (int)std::min<long>((tot + kBlock - 1) / kBlock, 8192);
-  hipLaunchKernelGGL(k_identity, dim3(blocks), dim3(kBlock), 0, s, v, m);
-}
-
 // One 128 x 128 tile of Z (rows: subdomains of one class, columns: local
 // unknowns) over the K range [k0, k1) of one split.  4 waves as 2 x 2, each
 // owning 2 x 2 MFMA tiles of 32 x 32.  Operands go global -> registers -> LDS
