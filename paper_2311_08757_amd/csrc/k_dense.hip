@@ -42,26 +42,33 @@ __device__ inline void split_bf16(double x, __bf16& hi, __bf16& lo) {
 }
 
 // Ainv (m x m FP64, row-major, from the chain solves of the identity) ->
-// symmetrised bf16 hi/lo pairs in an ld x ld zero-padded array.
-__global__ void k_split_inverse(const double* __restrict__ Ainv, int m, int ld,
-                                __bf16* __restrict__ Ah, __bf16* __restrict__ Al) {
-  const long tot = (long)ld * ld;
-  for (long idx = blockIdx.x * (long)blockDim.x + threadIdx.x; idx < tot;
-       idx += (long)gridDim.x * blockDim.x) {
-    const int i = (int)(idx / ld), j = (int)(idx % ld);
+// symmetrised bf16 hi/lo pairs in an ld x ld zero-padded array.  One workgroup
+// per 32 x 32 tile; the transposed tile goes through LDS (read straight from
+// memory, a column per line, the kernel took 297 us at m = 4473).
+constexpr int kSpT = 32;
+__global__ void __launch_bounds__(kBlock) k_split_inverse(const double* __restrict__ Ainv, int m,
+                                                          int ld, __bf16* __restrict__ Ah,
+                                                          __bf16* __restrict__ Al) {
+  __shared__ double tr[kSpT][kSpT + 1];  // tr[j][i] = Ainv[j0 + j][i0 + i]
+  const int i0 = blockIdx.y * kSpT, j0 = blockIdx.x * kSpT;
+  const int c = threadIdx.x % kSpT;
+  for (int r = threadIdx.x / kSpT; r < kSpT; r += kBlock / kSpT)
+    tr[r][c] = j0 + r < m && i0 + c < m ? Ainv[(long)(j0 + r) * m + i0 + c] : 0.0;
+  __syncthreads();
+  for (int r = threadIdx.x / kSpT; r < kSpT; r += kBlock / kSpT) {
+    const int i = i0 + r, j = j0 + c;
     double v = 0.0;
-    if (i < m && j < m) v = 0.5 * (Ainv[(long)i * m + j] + Ainv[(long)j * m + i]);
+    if (i < m && j < m) v = 0.5 * (Ainv[(long)i * m + j] + tr[c][r]);
     __bf16 hi, lo;
     split_bf16(v, hi, lo);
-    Ah[idx] = hi;
-    if (Al != nullptr) Al[idx] = lo;
+    Ah[(long)i * ld + j] = hi;
+    if (Al != nullptr) Al[(long)i * ld + j] = lo;
   }
 }
 
 void launch_split_inverse(const double* Ainv, int m, int ld, void* Ah, void* Al, hipStream_t s) {
-  const long tot = (long)ld * ld;
-  const int blocks = (int)std::min<long>((tot + kBlock - 1) / kBlock, 8192);
-  hipLaunchKernelGGL(k_split_inverse, dim3(blocks), dim3(kBlock), 0, s, Ainv, m, ld,
+  // (ld is a multiple of 128)
+  hipLaunchKernelGGL(k_split_inverse, dim3(ld / kSpT, ld / kSpT), dim3(kBlock), 0, s, Ainv, m, ld,
                      (__bf16*)Ah, (__bf16*)Al);
 }
 
@@ -364,7 +371,11 @@ void launch_embed_gather(const ddeig_problem* P, const EmbedDev& E, double* C, h
 }
 
 // Set-up: G = B~_ST (B~_TT)^{-1}, t-major over the unclipped box, zero for
-// the nodes in T; one thread per entry, FP64 sums in index order.
+// the nodes in T; FP64 sums in index order.  A product of mH x nT x nT (2.3
+// GFLOP at mH = 4473, nT = 504): 64 x 64 tiles, 4 x 4 entries per thread, both
+// operands through LDS in steps of 32 terms.  B~ is symmetric, so its row of a
+// T node serves as the column, which coalesces.  One thread per entry reading
+// columns of B~ took 2.4 ms.
 __device__ inline bool embed_in_box(const EmbedDev& E, int e, int hm0, int hm1) {
   const int u0 = e % hm0, rest = e / hm0;
   const int u1 = rest % hm1, u2 = rest / hm1;
@@ -372,33 +383,63 @@ __device__ inline bool embed_in_box(const EmbedDev& E, int e, int hm0, int hm1) 
          u2 >= E.off[2] && u2 < E.off[2] + E.m[2];
 }
 
-__global__ void k_embed_gmat(EmbedDev E, const __bf16* __restrict__ Ah, const __bf16* __restrict__ Al,
-                             int ld, int hm0, int hm1, int mH, const double* __restrict__ C,
-                             float* __restrict__ G) {
-  const long tot = (long)E.nT * mH;
-  for (long idx = blockIdx.x * (long)blockDim.x + threadIdx.x; idx < tot;
-       idx += (long)gridDim.x * blockDim.x) {
-    const int t = (int)(idx / mH), e = (int)(idx % mH);
-    double v = 0.0;
-    if (embed_in_box(E, e, hm0, hm1)) {
-      for (int j = 0; j < E.nT; ++j) {
-        const long a = (long)e * ld + E.Tidx[j];
-        double b = (double)(float)Ah[a];
-        if (Al != nullptr) b += (double)(float)Al[a];
-        v += b * C[(long)j * E.nT + t];
+constexpr int kGmT = 64, kGmK = 32;
+__global__ void __launch_bounds__(kBlock) k_embed_gmat(EmbedDev E, const __bf16* __restrict__ Ah,
+                                                       const __bf16* __restrict__ Al, int ld,
+                                                       int hm0, int hm1, int mH,
+                                                       const double* __restrict__ C,
+                                                       float* __restrict__ G) {
+  __shared__ double Bs[kGmK][kGmT], Cs[kGmK][kGmT];
+  const int e0 = blockIdx.x * kGmT, t0 = blockIdx.y * kGmT;
+  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;  // entries e0 + tx + 16 y, t0 + ty + 16 x
+  double acc[4][4] = {};
+  for (int j0 = 0; j0 < E.nT; j0 += kGmK) {
+#pragma unroll
+    for (int q = 0; q < kGmK * kGmT / kBlock; ++q) {
+      const int idx = threadIdx.x + q * kBlock, j = j0 + idx / kGmT, c = idx % kGmT;
+      double bv = 0.0, cv = 0.0;
+      if (j < E.nT) {
+        if (e0 + c < mH) {
+          const long a = (long)E.Tidx[j] * ld + e0 + c;
+          bv = (double)(float)Ah[a];
+          if (Al != nullptr) bv += (double)(float)Al[a];
+        }
+        if (t0 + c < E.nT) cv = C[(long)j * E.nT + t0 + c];
       }
+      Bs[idx / kGmT][c] = bv;
+      Cs[idx / kGmT][c] = cv;
     }
-    G[idx] = (float)v;
+    __syncthreads();
+#pragma unroll 8
+    for (int k = 0; k < kGmK; ++k) {
+      double bv[4], cv[4];
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        bv[x] = Bs[k][tx + 16 * x];
+        cv[x] = Cs[k][ty + 16 * x];
+      }
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+#pragma unroll
+        for (int y = 0; y < 4; ++y) acc[x][y] += bv[y] * cv[x];
+    }
+    __syncthreads();
   }
+#pragma unroll
+  for (int x = 0; x < 4; ++x)
+#pragma unroll
+    for (int y = 0; y < 4; ++y) {
+      const int t = t0 + ty + 16 * x, e = e0 + tx + 16 * y;
+      if (t < E.nT && e < mH)
+        G[(long)t * mH + e] = embed_in_box(E, e, hm0, hm1) ? (float)acc[x][y] : 0.0f;
+    }
 }
 
 void launch_embed_gmat(const ddeig_problem* P, const EmbedDev& E, const double* C, float* G,
                        hipStream_t s) {
   const DenseHost& H = P->dh;
-  const long tot = (long)E.nT * H.m;
-  const int blocks = (int)std::min<long>((tot + kBlock - 1) / kBlock, 16384);
-  hipLaunchKernelGGL(k_embed_gmat, dim3(blocks), dim3(kBlock), 0, s, E, H.Ah, H.Al, H.ld,
-                     H.box.m[0], H.box.m[1], H.m, C, G);
+  hipLaunchKernelGGL(k_embed_gmat, dim3((H.m + kGmT - 1) / kGmT, (E.nT + kGmT - 1) / kGmT),
+                     dim3(kBlock), 0, s, E, H.Ah, H.Al, H.ld, H.box.m[0], H.box.m[1], H.m, C, G);
 }
 
 // Per application: y_S = u_S - G u_T for the members of one job of a class
