@@ -216,7 +216,7 @@ void factor_classes(ddeig_problem* P) {
     boxes.push_back(t.box);
     Ws.push_back(t.W);
   }
-  chain_factor(P, boxes, Ws, P->tabAs, P->stream);
+  chain_factor(P, boxes, Ws, P->tabAs, P->stream, P->chain_mfma != 0);
 }
 
 void factor_types(ddeig_problem* P) {
@@ -1265,7 +1265,7 @@ ddeig_status ddeig_assemble(const ddeig_geometry* geom, double h, const ddeig_po
       if (batched_chain) {
         const int mg = chain_mfma ? ddeig::chain_mfma_members() : ddeig::chain_group_members();
         for (int m0 = 0; m0 < T.nmem; m0 += mg)
-          chainjobs.push_back(ddeig::ChainJob{(int)t, m0, std::min(mg, T.nmem - m0), mtot + m0});
+          chainjobs.push_back(ddeig::ChainJob{(int)t, m0, std::min(mg, T.nmem - m0), mtot + m0, 0});
         mtot += T.nmem;
       }
       for (int a = 0; a < 3; ++a) tdev[t].m[a] = T.box.m[a];
@@ -1314,6 +1314,17 @@ ddeig_status ddeig_assemble(const ddeig_geometry* geom, double h, const ddeig_po
       tdev[t].fm0 = ddeig::make_fastdiv((unsigned)T.box.m[0]);
     }
     if (P->types.size() > (size_t)ddeig::kMaxTypes) throw Failure{DDEIG_EINTERNAL, "too many classes"};
+    if (chain_mfma) {
+      // the lower chains' jobs, in the second half of the partial buffer
+      const size_t nu = chainjobs.size();
+      for (size_t j = 0; j < nu; ++j) {
+        ddeig::ChainJob jb = chainjobs[j];
+        jb.mg0 += mtot;
+        jb.dir = 1;
+        chainjobs.push_back(jb);
+      }
+      mtot *= 2;
+    }
     if (batched_chain) {
       P->chain_bmax = maxb_types;
       P->chain_mtot = mtot;
@@ -1416,7 +1427,7 @@ ddeig_status ddeig_assemble(const ddeig_geometry* geom, double h, const ddeig_po
       check_hip(hipEventCreateWithFlags(&P->ev_state[e], hipEventDisableTiming), "create event");
     check_hip(hipHostMalloc(reinterpret_cast<void**>(&P->hst), 2 * sizeof(ddeig::PcgState)),
               "pinned state");
-    P->gj_jobs = dense ? 1 : (int)P->types.size();
+    P->gj_jobs = (dense ? 1 : (int)P->types.size()) * (chain_mfma ? 2 : 1);
     P->gj_stride = gjmax;
     P->gjbuf = dalloc<double>(P, (size_t)ddeig::gj_buffer_doubles(gjmax, P->gj_jobs));
     P->psi = dalloc<double>(P, g.tsize);

@@ -239,9 +239,10 @@ struct CoarseSolveArgs {
 
 // A group of at most 64 members of one class in the batched chain solves:
 // class, first member within the class, count, and the group's first member
-// in the partial-product buffer (members of all classes numbered in order).
+// in the partial-product buffer (members of all classes numbered in order); dir:
+// the upper (0) or lower (1) chain of the two-ended elimination.
 struct ChainJob {
-  int type, m0, nm, mg0;
+  int type, m0, nm, mg0, dir;
 };
 
 struct GemmTile {
@@ -464,8 +465,9 @@ void launch_box_stencil(const ddeig_problem* P, const Box& bx, const double* tab
                         double* y, Red* dot, Red* sum, hipStream_t s);
 
 // chain factorisation of boxes: W[i] = S_i^{-1}; flag set on a non-positive pivot
+// (both_ends: eliminated from both ends towards slice nch / 2; wide slices only)
 void chain_factor(ddeig_problem* P, const std::vector<Box>& boxes, const std::vector<double*>& Ws,
-                  const double* tab, hipStream_t s);
+                  const double* tab, hipStream_t s, bool both_ends = false);
 long gj_buffer_doubles(int bmax, int njobs);
 size_t factor_entries(int D, const Box& bx, int bmax, int nchmax);
 void launch_gj_invert(ddeig_problem* P, double* A, int b, hipStream_t s);

@@ -68,9 +68,24 @@ constexpr int kRowsMaxB = 128;
 constexpr int kFacG = 16;  // thread grid: kFacG x kFacG = kBlock
 static_assert(kFacG * kFacG == kBlock, "square thread grid");
 
+// Matrices factored together; one chain from slice 0 (dir 0), or two: the upper
+// half 0..h-1 (dir 0), the lower one nch-1..h+1 (dir 1), h = nch / 2, and the
+// middle (step kFacMid of the dir 0 jobs).
+constexpr int kFacMid = -1;
+constexpr int kFacJobs = 2 * kMaxTypes;
 struct FactorJobs {
-  Box bx[kMaxTypes];
-  double* W[kMaxTypes];
+  Box bx[kFacJobs];
+  double* W[kFacJobs];
+  int dir[kFacJobs];
+  int both;
+  // slice of job j in a step, or -1
+  __host__ __device__ int slice(int j, int step) const {
+    const int n = bx[j].nch, h = n / 2;
+    if (!both) return step < n ? step : -1;
+    if (step == kFacMid) return dir[j] ? -1 : h;
+    const int i = dir[j] ? n - 1 - step : step;
+    return (dir[j] ? i > h : i < h) ? i : -1;
+  }
 };
 
 // Layout of the factors that the row solves read (chain_rows): the columns in 8
@@ -326,12 +341,13 @@ __global__ void __launch_bounds__(kBlock) k_gj_small(double* __restrict__ A, int
 // of the row takes its 3^(D-1) couplings from LDS (the product entry by entry
 // would read W_{i-1} 9^(D-1) times: 420 us a slice at b = 1085).
 constexpr int kSchurTaps = 9;
-__global__ void __launch_bounds__(kBlock) k_schur_row(Geo g, FactorJobs jobs, int i,
+__global__ void __launch_bounds__(kBlock) k_schur_row(Geo g, FactorJobs jobs, int step,
                                                       const double* __restrict__ T) {
   extern __shared__ double u[];  // b
   const Box bx = jobs.bx[blockIdx.y];
   const int b = bx.b, D = g.D, last = D - 1, r = blockIdx.x;
-  if (r >= b || i >= bx.nch) return;
+  const int i = jobs.slice(blockIdx.y, step);
+  if (r >= b || i < 0) return;
   const int ntap = D == 2 ? 3 : 9;  // taps of one slice offset, in tap order
   const long bb = (long)b * b;
   double* __restrict__ S = jobs.W[blockIdx.y] + (long)i * bb + (long)r * b;
@@ -344,8 +360,24 @@ __global__ void __launch_bounds__(kBlock) k_schur_row(Geo g, FactorJobs jobs, in
     d[1] = D == 3 ? t / 3 - 1 : 0;
     d[2] = 0;
   };
-  if (i > 0) {
-    const double* Wp = jobs.W[blockIdx.y] + (long)(i - 1) * bb;
+  for (int s = threadIdx.x; s < b; s += kBlock) {
+    double v = 0.0;
+    for (int t = 0; t < ntap; ++t) {
+      int d[3], n;
+      offs(t, d);
+      if (slice_nbr(bx, D, ur, d, n) && n == s) v += T[(ntap + t) * g.tsize + tr];
+    }
+    S[s] = v;
+  }
+  // the eliminated neighbours: slice i - 1 of an upper chain, i + 1 of a lower
+  // one, both of the middle
+  const bool mid = step == kFacMid, low = jobs.dir[blockIdx.y] != 0;
+  for (int side = 0; side < 2; ++side) {
+    if (!mid && side != (low ? 1 : 0)) continue;
+    const int j = side ? i + 1 : i - 1;
+    if (j < 0 || j >= bx.nch) continue;
+    const long tap0 = side ? 2 * ntap : 0;  // the taps towards slice j
+    const double* Wp = jobs.W[blockIdx.y] + (long)j * bb;
     double e[kSchurTaps];
     long at[kSchurTaps];
 #pragma unroll
@@ -355,10 +387,11 @@ __global__ void __launch_bounds__(kBlock) k_schur_row(Geo g, FactorJobs jobs, in
       int d[3], n1;
       offs(t, d);
       if (t < ntap && slice_nbr(bx, D, ur, d, n1)) {
-        e[t] = T[t * g.tsize + tr];
+        e[t] = T[(tap0 + t) * g.tsize + tr];
         at[t] = (long)n1 * b;
       }
     }
+    __syncthreads();  // (u of the other side has been read)
     for (int s = threadIdx.x; s < b; s += kBlock) {
       double v = 0.0;
 #pragma unroll
@@ -366,20 +399,19 @@ __global__ void __launch_bounds__(kBlock) k_schur_row(Geo g, FactorJobs jobs, in
       u[s] = v;
     }
     __syncthreads();
-  }
-  for (int s = threadIdx.x; s < b; s += kBlock) {
-    int us[3];
-    slice_coords(bx, D, s, us);
-    us[last] = i;
-    const long ts = box_tnode(g, bx, us);
-    double v = 0.0, corr = 0.0;
-    for (int t = 0; t < ntap; ++t) {
-      int d[3], n;
-      offs(t, d);
-      if (slice_nbr(bx, D, ur, d, n) && n == s) v += T[(ntap + t) * g.tsize + tr];
-      if (i > 0 && slice_nbr(bx, D, us, d, n)) corr += T[t * g.tsize + ts] * u[n];
+    for (int s = threadIdx.x; s < b; s += kBlock) {
+      int us[3];
+      slice_coords(bx, D, s, us);
+      us[last] = i;
+      const long ts = box_tnode(g, bx, us);
+      double corr = 0.0;
+      for (int t = 0; t < ntap; ++t) {
+        int d[3], n;
+        offs(t, d);
+        if (slice_nbr(bx, D, us, d, n)) corr += T[(tap0 + t) * g.tsize + ts] * u[n];
+      }
+      S[s] -= corr;
     }
-    S[s] = v - corr;
   }
 }
 
@@ -391,7 +423,7 @@ __global__ void __launch_bounds__(kBlock) k_schur_row(Geo g, FactorJobs jobs, in
 // A_kj = R_j.  Buffers per job: R (kGjNb x b), then C (b x kGjNb).
 constexpr int kGjNb = 32, kGjTile = 64;
 
-__global__ void __launch_bounds__(kBlock) k_gj_panel(FactorJobs jobs, int i, int k0,
+__global__ void __launch_bounds__(kBlock) k_gj_panel(FactorJobs jobs, int step, int k0,
                                                      double* __restrict__ buf, long bstride,
                                                      int* __restrict__ flag) {
   constexpr int NA = kGjNb / kFacG;
@@ -400,7 +432,8 @@ __global__ void __launch_bounds__(kBlock) k_gj_panel(FactorJobs jobs, int i, int
   const Box bx = jobs.bx[blockIdx.y];
   const int b = bx.b;
   const int c0 = blockIdx.x * kGjTile;
-  if (k0 >= b || c0 >= b || i >= bx.nch) return;
+  const int i = jobs.slice(blockIdx.y, step);
+  if (k0 >= b || c0 >= b || i < 0) return;
   const int nb = min(kGjNb, b - k0);
   const double* __restrict__ A = jobs.W[blockIdx.y] + (long)i * b * b;
   double* __restrict__ R = buf + blockIdx.y * bstride;
@@ -448,13 +481,14 @@ __global__ void __launch_bounds__(kBlock) k_gj_panel(FactorJobs jobs, int i, int
   }
 }
 
-__global__ void __launch_bounds__(kBlock) k_gj_update(FactorJobs jobs, int i, int k0,
+__global__ void __launch_bounds__(kBlock) k_gj_update(FactorJobs jobs, int step, int k0,
                                                       const double* __restrict__ buf, long bstride) {
   __shared__ double Cs[kGjNb][kGjTile + 2], Rs[kGjNb][kGjTile + 2];
   const Box bx = jobs.bx[blockIdx.z];
   const int b = bx.b;
   const int i0 = blockIdx.y * kGjTile, j0 = blockIdx.x * kGjTile;
-  if (k0 >= b || i0 >= b || j0 >= b || i >= bx.nch) return;
+  const int i = jobs.slice(blockIdx.z, step);
+  if (k0 >= b || i0 >= b || j0 >= b || i < 0) return;
   const int nb = min(kGjNb, b - k0);
   double* __restrict__ A = jobs.W[blockIdx.z] + (long)i * b * b;
   const double* __restrict__ R = buf + blockIdx.z * bstride;
@@ -501,16 +535,16 @@ __global__ void __launch_bounds__(kBlock) k_gj_update(FactorJobs jobs, int i, in
     }
 }
 
-// Inverts slice i of every job in pivot blocks.
-static void gj_blocked(ddeig_problem* P, const FactorJobs& jobs, int njobs, int bmax, int i,
+// Inverts every job's slice of a step in pivot blocks.
+static void gj_blocked(ddeig_problem* P, const FactorJobs& jobs, int njobs, int bmax, int step,
                        hipStream_t s) {
   const long stride = 2L * kGjNb * P->gj_stride;
   const int nt = (bmax + kGjTile - 1) / kGjTile;
   for (int k0 = 0; k0 < bmax; k0 += kGjNb) {
-    hipLaunchKernelGGL(k_gj_panel, dim3(nt, njobs), dim3(kBlock), 0, s, jobs, i, k0, P->gjbuf, stride,
-                       P->flag);
-    hipLaunchKernelGGL(k_gj_update, dim3(nt, nt, njobs), dim3(kBlock), 0, s, jobs, i, k0, P->gjbuf,
-                       stride);
+    hipLaunchKernelGGL(k_gj_panel, dim3(nt, njobs), dim3(kBlock), 0, s, jobs, step, k0, P->gjbuf,
+                       stride, P->flag);
+    hipLaunchKernelGGL(k_gj_update, dim3(nt, nt, njobs), dim3(kBlock), 0, s, jobs, step, k0,
+                       P->gjbuf, stride);
   }
 }
 
@@ -545,7 +579,7 @@ size_t factor_entries(int D, const Box& bx, int bmax, int nchmax) {
 // The chains of all boxes (their W pointers alongside); as many at once as the
 // pivot buffers hold.
 void chain_factor(ddeig_problem* P, const std::vector<Box>& boxes, const std::vector<double*>& Ws,
-                  const double* tab, hipStream_t s) {
+                  const double* tab, hipStream_t s, bool both_ends) {
   int bmax = 0, nch = 0;
   for (const Box& bx : boxes) {
     bmax = std::max(bmax, bx.b);
@@ -553,13 +587,16 @@ void chain_factor(ddeig_problem* P, const std::vector<Box>& boxes, const std::ve
   }
   const bool small = P->g.D == 2 && bmax <= kFacMaxB;
   const int rows = P->g.D == 2 && rows_ok(bmax, nch);
-  const int at_once = small ? kMaxTypes : std::min(kMaxTypes, P->gj_jobs);
+  const int nd = both_ends ? 2 : 1;
+  const size_t at_once = small ? (size_t)kFacJobs : std::max<size_t>(1, std::min(kFacJobs, P->gj_jobs) / nd);
   for (size_t j0 = 0; j0 < boxes.size(); j0 += at_once) {
-    const int nj = (int)std::min<size_t>(at_once, boxes.size() - j0);
+    const int nb = (int)std::min(at_once, boxes.size() - j0), nj = nb * nd;
     FactorJobs jobs{};
+    jobs.both = both_ends ? 1 : 0;
     for (int j = 0; j < nj; ++j) {
-      jobs.bx[j] = boxes[j0 + j];
-      jobs.W[j] = Ws[j0 + j];
+      jobs.bx[j] = boxes[j0 + j % nb];
+      jobs.W[j] = Ws[j0 + j % nb];
+      jobs.dir[j] = j / nb;
     }
     if (small) {
       auto kern = bmax <= 32 ? k_chain_factor2d<2>
@@ -573,11 +610,13 @@ void chain_factor(ddeig_problem* P, const std::vector<Box>& boxes, const std::ve
       hipLaunchKernelGGL(kern, dim3(nj), dim3(kBlock), lds, s, P->g, tab, jobs, rows, P->flag);
       continue;
     }
-    for (int i = 0; i < nch; ++i) {
-      hipLaunchKernelGGL(k_schur_row, dim3(bmax, nj), dim3(kBlock), (size_t)bmax * sizeof(double), s,
+    auto step = [&](int i, int n) {
+      hipLaunchKernelGGL(k_schur_row, dim3(bmax, n), dim3(kBlock), (size_t)bmax * sizeof(double), s,
                          P->g, jobs, i, tab);
-      gj_blocked(P, jobs, nj, bmax, i, s);
-    }
+      gj_blocked(P, jobs, n, bmax, i, s);
+    };
+    for (int i = 0; i < (both_ends ? nch / 2 : nch); ++i) step(i, nj);
+    if (both_ends) step(kFacMid, nb);
   }
 }
 

@@ -1,20 +1,26 @@
 // Batched block-chain local solves of 3-D boxes with FP32 factors on MFMA.
 //
 // The local matrices A_sigma,i of §3 (eq:twoLevelASMPreconditioner) are block
-// tridiagonal along the last (fixed) direction; their block elimination gives
-// W_i = S_i^{-1} per slice (k_chain.hip), and a solve is
-//   forward   t_i = W_i (b_i - E_i t_{i-1}),
-//   backward  x_{n-1} = t_{n-1},  x_i = t_i - W_i E_{i+1}^T x_{i+1}.
-// All members of a class share W_i, so each sweep step is one product of W_i
+// tridiagonal along the last (fixed) direction.  They are eliminated from both
+// ends towards slice h = n / 2 (k_chain.hip): for the upper chain (i < h)
+// W_i = S_i^{-1} with S_i = D_i - E_i W_{i-1} E_i^T, for the lower one (i > h)
+// the same with slice i + 1, and slice h takes both.  A solve is
+//   inwards   t_i = W_i (b_i - coupling of i with the slice before it),
+//   middle    x_h = W_h (b_h - both couplings),
+//   outwards  x_i = t_i - W_i (coupling of i with the slice nearer to h).
+// The two chains run in the same launches, so a solve is n dependent steps
+// instead of 2 n - 1 (a step is bound by its latency: with one chain, 61 steps
+// of 31 slices took 16 us each at 16 subdomains, 31 steps of two 22 us).
+// All members of a class share W_i, so each step is one product of W_i
 // (b x b, FP32) with the right-hand sides of all members of the class.  A step
 // is two launches:
-//   k_cm_rhs: finishes the previous step (t_{i-1} in the forward sweep,
-//     x_{i+1} in the backward one, as the fixed-order sum of the previous
-//     product's K-chunk partials, less t_{i+1} in the backward sweep), stores
-//     it for the workgroup's own rows, and forms this step's right-hand sides
-//     g from it with the coupling taps of the period-cell table.  The previous
-//     step's values are gathered into LDS for the workgroup's rows and a halo
-//     of one slice line on each side, which covers every coupling tap.
+//   k_cm_rhs: finishes the previous step (t or x of the neighbouring slice, as
+//     the fixed-order sum of the previous product's K-chunk partials, less t
+//     outwards), stores it for the workgroup's own rows, and forms this step's
+//     right-hand sides g from it with the coupling taps of the period-cell
+//     table.  The previous step's values are gathered into LDS for the
+//     workgroup's rows and a halo of one slice line on each side, which covers
+//     every coupling tap.
 //   k_cm_mm: the product W_i g on v_mfma_f32_32x32x2f32: workgroup = 128 rows
 //     x 64 members x one K chunk of 72, four waves of 32 rows x 64 members (two
 //     32 x 32 tiles sharing the W_i fragment; the second is skipped when the
@@ -22,8 +28,8 @@
 //     of the chunk and g are staged through LDS with coalesced loads (W_i is
 //     symmetric, so its rows are the columns of the A operand), the partial
 //     tile goes out through LDS so that every wave writes whole rows.
-// One more launch after the backward sweep finishes x_0.  The right-hand sides
-// are formed and the partials summed in FP64; W_i, g and the products are FP32
+// One more launch finishes the outermost slices.  The right-hand sides are
+// formed and the partials summed in FP64; W_i, g and the products are FP32
 // (FP32 accumulation on the matrix cores).
 #include "k_common.h"
 
@@ -84,78 +90,109 @@ __device__ inline double cm_prev(const float* __restrict__ part, int nkc, int mt
   return sub != nullptr ? *sub - acc : acc;
 }
 
-// Right-hand sides of sweep step i.  Grid: (row blocks, jobs, members of a job).
-// FWD: t_{i-1} from the partials (i > 0) into tbatch, g = b_i - E_i t_{i-1}.
-// BWD: x_{i+1} = (i + 1 == nch - 1 ? 0 : t_{i+1}) - ... : the partials of the
-// product of step i + 1 are W_{i+1} E_{i+2}^T x_{i+2}, or t_{n-1} itself after
-// the last forward step; x_{i+1} into batch, g = E_{i+1}^T x_{i+1}.
-template <bool FWD, int MAXK>
+// The parts of a solve: inwards step k, the middle, outwards step k.
+enum { kCmIn = 0, kCmMid = 1, kCmOut = 2 };
+
+// Slice of a job in step k of a part, or -1 when its chain has none.
+__device__ __forceinline__ int cm_slice(int mode, int k, int n, int dir) {
+  const int h = n / 2;
+  if (mode == kCmMid) return dir ? -1 : h;
+  if (mode == kCmIn) {
+    const int i = dir ? n - 1 - k : k;
+    return (dir ? i > h : i < h) ? i : -1;
+  }
+  const int i = dir ? h + 1 + k : h - 1 - k;
+  return i >= 0 && i < n ? i : -1;
+}
+
+// The coupling of row (u0, u1) of slice i with the slice d2 = -1 / +1 next to
+// it, from its values prev (row r0 + idx of the slice at prev[idx]).
+__device__ __forceinline__ double cm_couple(const Geo& g, const double* __restrict__ T,
+                                            const TypeDev& td, int u0, int u1, int i, int d2,
+                                            const double* prev, int r0) {
+  const int m0 = td.m[0], m1 = td.m[1];
+  const long tn = table_node(g, td.o[0] + u0, td.o[1] + u1, td.o[2] + i);
+  double acc = 0.0;
+#pragma unroll
+  for (int t9 = 0; t9 < 9; ++t9) {
+    const int w0 = u0 + t9 % 3 - 1, w1 = u1 + t9 / 3 - 1;
+    if (w0 < 0 || w0 >= m0 || w1 < 0 || w1 >= m1) continue;
+    acc += T[(t9 + 9 * (d2 + 1)) * g.tsize + tn] * prev[w0 + m0 * w1 - r0];
+  }
+  return acc;
+}
+
+// Right-hand sides of a step.  Grid: (row blocks, jobs, members of a job).  The
+// values of the neighbouring slice j are t_j inwards (into tbatch), and
+// x_j = t_j - partials outwards (into batch; x_h, the middle's product, is the
+// neighbour of both chains' first outward step and stored by the upper one).
+template <int MODE, int MAXK>
 __global__ void __launch_bounds__(kBlock) k_cm_rhs(Geo g, const double* __restrict__ T,
                                                    const TypeDev* __restrict__ types,
-                                                   const ChainJob* __restrict__ jobs, int i,
+                                                   const ChainJob* __restrict__ jobs, int k,
                                                    int mtot, int bmax,
                                                    const float* __restrict__ part,
                                                    float* __restrict__ G,
                                                    const PcgState* __restrict__ st) {
-  __shared__ double prev[kCmRb + 2 * kCmHalo];
+  constexpr int NP = kCmRb + 2 * kCmHalo;
+  __shared__ double prev[MODE == kCmMid ? 2 : 1][NP];
   if (st != nullptr && st->done) return;
   const ChainJob jb = jobs[blockIdx.y];
   const int m = blockIdx.z;
   if (m >= jb.nm) return;
   const TypeDev td = types[jb.type];
   const int b = td.b, nch = td.nch;
-  const int nkc = (b + kCmKc - 1) / kCmKc;
+  const int i = cm_slice(MODE, k, nch, jb.dir);
   const int R0 = blockIdx.x * kCmRb;
-  if (R0 >= b) return;
-  const int m0 = td.m[0], m1 = td.m[1];
+  if (i < 0 || R0 >= b) return;
+  const int nkc = (b + kCmKc - 1) / kCmKc;
+  const int m0 = td.m[0];
   const int H = m0 + 1;
-  const int slot = jb.mg0 + m;
+  const int slot = jb.mg0 + m, half = mtot / 2;  // (slots of the lower chains: + half)
   const long base = (long)(jb.m0 + m) * nch * b;
-  const bool couple = FWD ? i > 0 : true;
-  if (couple) {
-    // the previous step's values on rows [R0 - H, R0 + kCmRb + H) of the slice
-    const int j = FWD ? i - 1 : i + 1;
-    const int lo = max(R0 - H, 0), hi = min(R0 + kCmRb + H, b);
+  // sides: up to two neighbours (the middle's), d2 of each, whether there is one
+  constexpr int NS = MODE == kCmMid ? 2 : 1;
+  const int d2s[2] = {MODE == kCmMid ? -1 : ((MODE == kCmIn) == (jb.dir == 0) ? -1 : 1), 1};
+  const bool on[2] = {MODE == kCmMid ? i > 0 : (MODE == kCmOut || k > 0), i + 1 < nch};
+  const int lo = max(R0 - H, 0), hi = min(R0 + kCmRb + H, b);
+#pragma unroll
+  for (int sd = 0; sd < NS; ++sd) {
+    if (!on[sd]) continue;
+    const int j = i + d2s[sd];
+    const bool mid = MODE == kCmOut && k == 0;  // the neighbour is slice h
+    const int ps = MODE == kCmMid ? slot + sd * half : (mid && jb.dir ? slot - half : slot);
     for (int r = lo + threadIdx.x; r < hi; r += kBlock) {
       double v;
-      if (FWD || j == nch - 1) {
-        v = cm_prev<MAXK>(part, nkc, mtot, bmax, slot, r, nullptr);
+      if (MODE != kCmOut || mid) {
+        v = cm_prev<MAXK>(part, nkc, mtot, bmax, ps, r, nullptr);
       } else {
         const double t = td.tbatch[base + (long)j * b + r];
-        v = cm_prev<MAXK>(part, nkc, mtot, bmax, slot, r, &t);
+        v = cm_prev<MAXK>(part, nkc, mtot, bmax, ps, r, &t);
       }
-      prev[r - (R0 - H)] = v;
-      if (r >= R0 && r < R0 + kCmRb) {
-        if (FWD) td.tbatch[base + (long)j * b + r] = v;
-        else td.batch[base + (long)j * b + r] = v;
-      }
+      prev[sd][r - (R0 - H)] = v;
+      if (r >= R0 && r < R0 + kCmRb && !(mid && jb.dir))
+        (MODE == kCmOut ? td.batch : td.tbatch)[base + (long)j * b + r] = v;
     }
-    __syncthreads();
   }
+  __syncthreads();
   const int r = R0 + threadIdx.x;
   if (r >= b) return;
   const int u1 = r / m0, u0 = r - u1 * m0;
-  const int d2 = FWD ? -1 : 1;
-  double acc = FWD ? td.batch[base + (long)i * b + r] : 0.0;
-  if (couple) {
-    const long tn = table_node(g, td.o[0] + u0, td.o[1] + u1, td.o[2] + i);
+  double acc = MODE == kCmOut ? 0.0 : td.batch[base + (long)i * b + r];
 #pragma unroll
-    for (int t9 = 0; t9 < 9; ++t9) {
-      const int w0 = u0 + t9 % 3 - 1, w1 = u1 + t9 / 3 - 1;
-      if (w0 < 0 || w0 >= m0 || w1 < 0 || w1 >= m1) continue;
-      const double c = T[(t9 + 9 * (d2 + 1)) * g.tsize + tn];
-      const double v = prev[w0 + m0 * w1 - (R0 - H)];
-      acc += FWD ? -c * v : c * v;
-    }
+  for (int sd = 0; sd < NS; ++sd) {
+    if (!on[sd]) continue;
+    const double c = cm_couple(g, T, td, u0, u1, i, d2s[sd], prev[sd], R0 - H);
+    acc += MODE == kCmOut ? c : -c;
   }
   G[(long)slot * bmax + r] = (float)acc;
 }
 
-// Partial product of sweep step i: rows [R0, R0 + 128) x the job's members x
+// Partial product of a step: rows [R0, R0 + 128) x the job's members x
 // K chunk [K0, K0 + kCmKc) of W_i g, into part[kc][slot][row].
 __global__ void __launch_bounds__(kBlock) k_cm_mm(const TypeDev* __restrict__ types,
-                                                  const ChainJob* __restrict__ jobs, int i,
-                                                  int mtot, int bmax,
+                                                  const ChainJob* __restrict__ jobs, int mode,
+                                                  int k, int mtot, int bmax,
                                                   const float* __restrict__ G,
                                                   float* __restrict__ part,
                                                   const PcgState* __restrict__ st) {
@@ -168,7 +205,8 @@ __global__ void __launch_bounds__(kBlock) k_cm_mm(const TypeDev* __restrict__ ty
   const TypeDev td = types[jb.type];
   const int b = td.b, ldw = td.ldw;
   const int R0 = blockIdx.x * kCmRows, K0 = blockIdx.y * kCmKc;
-  if (R0 >= b || K0 >= b) return;
+  const int i = cm_slice(mode, k, td.nch, jb.dir);
+  if (i < 0 || R0 >= b || K0 >= b) return;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   // W_i through an address-space-1 pointer: its loads are global loads (a flat
   // load would also hold up the LDS wait counter)
@@ -249,7 +287,7 @@ __global__ void __launch_bounds__(kBlock) k_cm_mm(const TypeDev* __restrict__ ty
   }
 }
 
-// x_0 = t_0 - (partials) after the backward sweep, or x_0 = t_0 = (partials)
+// The outermost slice of every chain: x = t - (partials), or x_0 = (partials)
 // for a chain of one slice.  Grid: (row blocks, jobs, members).
 template <int MAXK>
 __global__ void __launch_bounds__(kBlock) k_cm_fin(const TypeDev* __restrict__ types,
@@ -261,11 +299,12 @@ __global__ void __launch_bounds__(kBlock) k_cm_fin(const TypeDev* __restrict__ t
   const int m = blockIdx.z;
   if (m >= jb.nm) return;
   const TypeDev td = types[jb.type];
-  const int b = td.b;
+  const int b = td.b, h = td.nch / 2;
+  if (jb.dir && h + 1 >= td.nch) return;  // no lower chain
   const int nkc = (b + kCmKc - 1) / kCmKc;
   const int r = blockIdx.x * kBlock + threadIdx.x;
   if (r >= b) return;
-  const long at = (long)(jb.m0 + m) * td.nch * b + r;
+  const long at = ((long)(jb.m0 + m) * td.nch + (jb.dir ? td.nch - 1 : 0)) * b + r;
   const int slot = jb.mg0 + m;
   if (td.nch == 1) {
     td.batch[at] = cm_prev<MAXK>(part, nkc, mtot, bmax, slot, r, nullptr);
@@ -280,9 +319,9 @@ size_t chain_mfma_part_bytes(int bmax, int mtot) {
   return (size_t)(nkc + 1) * mtot * bmax * sizeof(float);
 }
 
-// The two sweeps over the chain of every class (all classes share nch).
+// The solves of every class (all classes share nch).
 void launch_chain_mfma(const ddeig_problem* P, const PcgState* st, hipStream_t s) {
-  const int nch = P->types[0].box.nch;
+  const int nch = P->types[0].box.nch, h = nch / 2;
   const int bmax = P->chain_bmax, mtot = P->chain_mtot;
   const int nkc = (bmax + kCmKc - 1) / kCmKc;
   float* part = reinterpret_cast<float*>(P->chain_part);
@@ -290,23 +329,20 @@ void launch_chain_mfma(const ddeig_problem* P, const PcgState* st, hipStream_t s
   const dim3 grhs((bmax + kCmRb - 1) / kCmRb, P->nchainjobs, kCmMembers);
   const dim3 gmm((bmax + kCmRows - 1) / kCmRows, nkc, P->nchainjobs);
   const bool k16 = nkc <= 16;
-  auto rhs_f = k16 ? k_cm_rhs<true, 16> : k_cm_rhs<true, kCmMaxKc>;
-  auto rhs_b = k16 ? k_cm_rhs<false, 16> : k_cm_rhs<false, kCmMaxKc>;
-  auto fin = k16 ? k_cm_fin<16> : k_cm_fin<kCmMaxKc>;
-  for (int i = 0; i < nch; ++i) {
-    hipLaunchKernelGGL(rhs_f, grhs, dim3(kBlock), 0, s, P->g, P->tabAs, P->dTypes,
-                       P->dChainJobs, i, mtot, bmax, part, G, st);
-    hipLaunchKernelGGL(k_cm_mm, gmm, dim3(kBlock), 0, s, P->dTypes, P->dChainJobs, i, mtot, bmax,
-                       G, part, st);
-  }
-  for (int i = nch - 2; i >= 0; --i) {
-    hipLaunchKernelGGL(rhs_b, grhs, dim3(kBlock), 0, s, P->g, P->tabAs, P->dTypes,
-                       P->dChainJobs, i, mtot, bmax, part, G, st);
-    hipLaunchKernelGGL(k_cm_mm, gmm, dim3(kBlock), 0, s, P->dTypes, P->dChainJobs, i, mtot, bmax,
-                       G, part, st);
-  }
+  auto step = [&](int mode, int k, auto rhs) {
+    hipLaunchKernelGGL(rhs, grhs, dim3(kBlock), 0, s, P->g, P->tabAs, P->dTypes, P->dChainJobs, k,
+                       mtot, bmax, part, G, st);
+    hipLaunchKernelGGL(k_cm_mm, gmm, dim3(kBlock), 0, s, P->dTypes, P->dChainJobs, mode, k, mtot,
+                       bmax, G, part, st);
+  };
+  for (int k = 0; k < h; ++k)
+    step(kCmIn, k, k16 ? k_cm_rhs<kCmIn, 16> : k_cm_rhs<kCmIn, kCmMaxKc>);
+  step(kCmMid, 0, k16 ? k_cm_rhs<kCmMid, 16> : k_cm_rhs<kCmMid, kCmMaxKc>);
+  for (int k = 0; k < h; ++k)
+    step(kCmOut, k, k16 ? k_cm_rhs<kCmOut, 16> : k_cm_rhs<kCmOut, kCmMaxKc>);
   const dim3 gfin((bmax + kBlock - 1) / kBlock, P->nchainjobs, kCmMembers);
-  hipLaunchKernelGGL(fin, gfin, dim3(kBlock), 0, s, P->dTypes, P->dChainJobs, mtot, bmax, part, st);
+  hipLaunchKernelGGL(k16 ? k_cm_fin<16> : k_cm_fin<kCmMaxKc>, gfin, dim3(kBlock), 0, s, P->dTypes,
+                     P->dChainJobs, mtot, bmax, part, st);
 }
 
 }  // namespace ddeig
