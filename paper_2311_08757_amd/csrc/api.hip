@@ -1328,9 +1328,13 @@ ddeig_status ddeig_assemble(const ddeig_geometry* geom, double h, const ddeig_po
     if (batched_chain) {
       P->chain_bmax = maxb_types;
       P->chain_mtot = mtot;
-      P->chain_part = dalloc<unsigned char>(
-          P, chain_mfma ? ddeig::chain_mfma_part_bytes(maxb_types, mtot)
-                        : ddeig::chain_part_bytes(maxb_types, mtot, o.local_prec == 1));
+      size_t joff, poff;
+      const size_t bytes =
+          chain_mfma ? ddeig::chain_mfma_bytes(maxb_types, mtot, (int)chainjobs.size(), &joff, &poff)
+                     : ddeig::chain_part_bytes(maxb_types, mtot, o.local_prec == 1);
+      P->chain_part = dalloc<unsigned char>(P, bytes);
+      check_hip(hipMemsetAsync(P->chain_part, 0, bytes, s), "clear chain buffer");
+      if (chain_mfma) ddeig::chain_mfma_setup(P, tdev, chainjobs, s);
       P->nchainjobs = (int)chainjobs.size();
       P->dChainJobs = dalloc<ddeig::ChainJob>(P, chainjobs.size());
       check_hip(hipMemcpyAsync(P->dChainJobs, chainjobs.data(),

@@ -392,6 +392,7 @@ struct ddeig_problem {
   int chain_bmax = 0, chain_mtot = 0;  // largest slice, all members of all classes
   void* chain_part = nullptr;          // K-chunk partial products of a sweep step
   int chain_mfma = 0;                  // FP32 chain solves on MFMA (k_chain_mfma.hip)
+  int chain_nm = 0;                    // most members of a job of those
   ddeig::GemmTile* dTiles = nullptr;
   ddeig::GemvRows* dGemv = nullptr;
   ddeig::GemmType* dGtypes = nullptr;
@@ -505,7 +506,9 @@ size_t chain_part_bytes(int bmax, int mtot, int fp32);
 // FP32 batched chain solves on MFMA (k_chain_mfma.hip)
 int chain_mfma_members();
 bool chain_mfma_ok(int b, int m0);
-size_t chain_mfma_part_bytes(int bmax, int mtot);
+size_t chain_mfma_bytes(int bmax, int mtot, int njobs, size_t* job_off, size_t* part_off);
+void chain_mfma_setup(ddeig_problem* P, const std::vector<TypeDev>& types,
+                      const std::vector<ChainJob>& jobs, hipStream_t s);
 void launch_chain_mfma(const ddeig_problem* P, const PcgState* st, hipStream_t s);
 void launch_pad_float(const double* src, float* dst, long rows, int b, int ldw, hipStream_t s);
 void launch_coarse_solve(const ddeig_problem* P, const PcgState* st, hipStream_t s);

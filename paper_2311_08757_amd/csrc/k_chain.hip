@@ -693,31 +693,41 @@ __device__ void chain_solve_block(const Geo& g, const Box& bx, const double* __r
 // for the whole solve took 1 ms a step at b = 992).
 //
 // The couplings of slice i with slice i - 1 (d = -1) or i + 1 (d = +1): the
-// right-hand side of row k without b_i.
+// right-hand side of row k without b_i.  All loads are issued before any is
+// used (a neighbour that does not exist is row k itself, masked): loaded one by
+// one behind their tests they made a step 36 us at b = 992.
 __device__ __forceinline__ double slice_coupling(const Geo& g, const Box& bx,
                                                  const double* __restrict__ T, int i, int k, int d,
                                                  const double* __restrict__ nb) {
-  const int D = g.D, ntap = D == 2 ? 3 : 9;
-  int u[3];
-  slice_coords(bx, D, k, u);
+  const int D = g.D, m0 = bx.m[0], m1 = D == 3 ? bx.m[1] : 1;
+  const int u1 = k / m0, u0 = k - u1 * m0;
+  int u[3] = {u0, u1, 0};
   u[D - 1] = i;
-  const long tn = box_tnode(g, bx, u) + (d < 0 ? 0 : 2 * ntap) * g.tsize;
-  double v = 0.0;
+  const int ntap = D == 2 ? 3 : 9;
+  const double* Tk = T + box_tnode(g, bx, u) + (d < 0 ? 0 : 2 * ntap) * g.tsize;
+  double c[9], v[9];
 #pragma unroll
   for (int t = 0; t < 9; ++t) {
-    if (t >= ntap) break;
-    const int dd[3] = {t % 3 - 1, D == 3 ? t / 3 - 1 : 0, 0};
-    int n;
-    if (slice_nbr(bx, D, u, dd, n)) v += T[t * g.tsize + tn] * nb[n];
+    int w0 = u0 + t % 3 - 1, w1 = D == 3 ? u1 + t / 3 - 1 : 0;
+    if (bx.per[0]) w0 = w0 < 0 ? w0 + m0 : w0 >= m0 ? w0 - m0 : w0;
+    if (D == 3 && bx.per[1]) w1 = w1 < 0 ? w1 + m1 : w1 >= m1 ? w1 - m1 : w1;
+    const bool in = t < ntap && w0 >= 0 && w0 < m0 && w1 >= 0 && w1 < m1;
+    const double ct = Tk[min(t, ntap - 1) * g.tsize], vt = nb[in ? w0 + m0 * w1 : k];
+    c[t] = in ? ct : 0.0;
+    v[t] = vt;
   }
-  return v;
+  double s = 0.0;
+#pragma unroll
+  for (int t = 0; t < 9; ++t) s += c[t] * v[t];
+  return s;
 }
 
-// One right-hand side: workgroup = 8 rows of W_i.  Every workgroup forms the
-// slice's g for itself in LDS (the slice before it is the last launch's
-// output); forward t_i = W_i (b_i - E_i t_{i-1}) into out, backward
+// One right-hand side: workgroup = 4 rows of W_i, one per wave, whose entries
+// (up to kWideKeep per lane) are loaded before anything is waited for.  Every
+// workgroup forms the slice's g for itself in LDS (the slice before it is the
+// last launch's output); forward t_i = W_i (b_i - E_i t_{i-1}) into out, backward
 // x_i = t_i - W_i E_{i+1}^T x_{i+1}.  bi: b_i (forward); ti: t_i (backward).
-constexpr int kWideRows = 8;
+constexpr int kWideRows = kBlock / 64, kWideKeep = 18;
 template <bool FWD>
 __global__ void __launch_bounds__(kBlock) k_wide_row(Geo g, Box bx, const double* __restrict__ T,
                                                      const double* __restrict__ W, int i,
@@ -726,24 +736,28 @@ __global__ void __launch_bounds__(kBlock) k_wide_row(Geo g, Box bx, const double
                                                      const double* __restrict__ ti,
                                                      double* __restrict__ out) {
   extern __shared__ double gs[];  // b
-  const int b = bx.b;
+  const int b = bx.b, lane = threadIdx.x & 63;
+  const int r = min((int)blockIdx.x * kWideRows + ((int)threadIdx.x >> 6), b - 1);
+  const double* Wr = W + ((long)i * b + r) * b;
+  double w[kWideKeep];
+#pragma unroll
+  for (int q = 0; q < kWideKeep; ++q) w[q] = Wr[min(lane + 64 * q, b - 1)];
+  const double t = FWD ? 0.0 : ti[r];
   for (int k = threadIdx.x; k < b; k += kBlock) {
     const double c = FWD && i == 0 ? 0.0 : slice_coupling(g, bx, T, i, k, FWD ? -1 : 1, nb);
     gs[k] = FWD ? bi[k] - c : c;
   }
   __syncthreads();
-  const int lane = threadIdx.x & 63;
-  const double* Wi = W + (long)i * b * b;
+  double acc = 0.0;
 #pragma unroll
-  for (int q = 0; q < kWideRows / 4; ++q) {
-    const int r = blockIdx.x * kWideRows + (threadIdx.x >> 6) * (kWideRows / 4) + q;
-    if (r >= b) break;
-    double acc = 0.0;
-#pragma unroll 8
-    for (int k = lane; k < b; k += 64) acc += Wi[(long)r * b + k] * gs[k];
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
-    if (lane == 0) out[r] = FWD ? acc : ti[r] - acc;
+  for (int q = 0; q < kWideKeep; ++q) {
+    const int k = lane + 64 * q;
+    acc += k < b ? w[q] * gs[k] : 0.0;
   }
+  for (int k = lane + 64 * kWideKeep; k < b; k += 64) acc += Wr[k] * gs[k];
+  for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
+  // (the waves past the last row repeat it: same value)
+  if (lane == 0) out[r] = FWD ? acc : t - acc;
 }
 
 // The columns of the identity, x[col] (nch b values each): 64 x 64 tiles of

@@ -22,15 +22,20 @@
 //     workgroup's rows and a halo of one slice line on each side, which covers
 //     every coupling tap.
 //   k_cm_mm: the product W_i g on v_mfma_f32_32x32x2f32: workgroup = 128 rows
-//     x 64 members x one K chunk of 72, four waves of 32 rows x 64 members (two
-//     32 x 32 tiles sharing the W_i fragment; the second is skipped when the
-//     job has at most 32 members), so W_i is read once per class; W_i rows
-//     of the chunk and g are staged through LDS with coalesced loads (W_i is
-//     symmetric, so its rows are the columns of the A operand), the partial
-//     tile goes out through LDS so that every wave writes whole rows.
+//     x 64 members x one K chunk of 8 NK rows of W_i.  W_i comes straight from
+//     memory into the A operand: a lane loads 4 consecutive entries of its row
+//     k of W_i (W_i is symmetric, so its rows are the columns of the operand)
+//     and they feed four 32-row tiles, whose rows interleave; each wave takes a
+//     quarter of the chunk, with all of its loads in flight at once, and the
+//     four sums are added through LDS.  NK (9, 18 or 34) is the largest that
+//     leaves about a workgroup per CU: the launch is a stream of W_i (26 MB a
+//     step for three classes of b = 1085, two chains).
 // One more launch finishes the outermost slices.  The right-hand sides are
 // formed and the partials summed in FP64; W_i, g and the products are FP32
-// (FP32 accumulation on the matrix cores).
+// (FP32 accumulation on the matrix cores).  W_i staged through LDS in chunks of
+// 72 rows took 14.8 us a step (1.8 TB/s); this takes 10.2 us, and 8.2 (3.2 TB/s)
+// on 16-wide tiles, which 14 members fill; the right-hand sides 6.9 -> 4.2 us
+// with a quarter of the partials and one descriptor load.
 #include "k_common.h"
 
 namespace ddeig {
@@ -39,12 +44,23 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
 constexpr int kCmRows = 128;    // output rows per product workgroup
-constexpr int kCmKc = 72;       // K chunk per product workgroup (a slice of 35 x 31 in 16 chunks)
 constexpr int kCmMembers = 64;  // members per job: two 32-wide MFMA tiles per wave
 constexpr int kCmRb = 256;      // rows per right-hand-side workgroup
 constexpr int kCmHalo = 256;    // largest halo (one slice line + 1) of the rhs kernel
-constexpr int kCmMaxKc = 32;    // largest number of K chunks (slices of at most 2304 nodes)
-constexpr int kCmLdw = kCmRows + 4;  // LDS row of the staged W_i chunk (bank offset per row)
+constexpr int kCmMaxB = 2304;   // largest slice
+constexpr int kCmMaxKc = 32;    // largest number of K chunks (2304 / 72)
+constexpr int kCmPad = 272;     // the longest K chunk: G rows end in as many zeros
+constexpr int kCmLdr = kCmRows + 4;  // LDS row of a member's partial sums
+
+// What the step kernels read of a job and of one of its members, in one load.
+struct CmJob {
+  const float* W;  // factors of the class, rows of ldw values
+  int b, ldw, nch, dir, nm, slot0;
+};
+struct CmMember {
+  double *batch, *tbatch;  // this member's nch b values
+  int b, nch, m0, m1, o[3], dir;
+};
 
 // FP64 factors (rows of b values) -> FP32 rows of ldw values, zero padded.
 __global__ void k_pad_float(const double* __restrict__ src, float* __restrict__ dst, long rows,
@@ -68,14 +84,14 @@ void launch_pad_float(const double* src, float* dst, long rows, int b, int ldw, 
 int chain_mfma_members() { return kCmMembers; }
 
 bool chain_mfma_ok(int b, int m0) {
-  return m0 + 1 <= kCmHalo && b >= 1 && b <= kCmMaxKc * kCmKc;
+  return m0 + 1 <= kCmHalo && b >= 1 && b <= kCmMaxB;
 }
 
-// Previous step's value of row r of member (slot) m: the sum of the nkc K-chunk
-// partials of its class (b / kCmKc rounded up, at most MAXK) in chunk order,
-// subtracted from t (backward, sub != nullptr).  Every load is issued before
-// the first add (clamped addresses, masked values), so their latencies overlap;
-// MAXK (16 or 32, the batch's largest chunk count rounded up) bounds the loads.
+// Previous step's value of row r of a member (slot): the sum of the nkc K-chunk
+// partials of its class (at most MAXK) in chunk order, subtracted from t (sub !=
+// nullptr).  Every load is issued before the first add (clamped addresses,
+// masked values), so their latencies overlap; MAXK (the batch's largest chunk
+// count rounded up) bounds the loads.
 template <int MAXK>
 __device__ inline double cm_prev(const float* __restrict__ part, int nkc, int mtot, int bmax,
                                  int slot, int r, const double* sub) {
@@ -105,244 +121,331 @@ __device__ __forceinline__ int cm_slice(int mode, int k, int n, int dir) {
   return i >= 0 && i < n ? i : -1;
 }
 
-// The coupling of row (u0, u1) of slice i with the slice d2 = -1 / +1 next to
-// it, from its values prev (row r0 + idx of the slice at prev[idx]).
-__device__ __forceinline__ double cm_couple(const Geo& g, const double* __restrict__ T,
-                                            const TypeDev& td, int u0, int u1, int i, int d2,
-                                            const double* prev, int r0) {
-  const int m0 = td.m[0], m1 = td.m[1];
-  const long tn = table_node(g, td.o[0] + u0, td.o[1] + u1, td.o[2] + i);
-  double acc = 0.0;
-#pragma unroll
-  for (int t9 = 0; t9 < 9; ++t9) {
-    const int w0 = u0 + t9 % 3 - 1, w1 = u1 + t9 / 3 - 1;
-    if (w0 < 0 || w0 >= m0 || w1 < 0 || w1 >= m1) continue;
-    acc += T[(t9 + 9 * (d2 + 1)) * g.tsize + tn] * prev[w0 + m0 * w1 - r0];
-  }
-  return acc;
-}
-
-// Right-hand sides of a step.  Grid: (row blocks, jobs, members of a job).  The
-// values of the neighbouring slice j are t_j inwards (into tbatch), and
-// x_j = t_j - partials outwards (into batch; x_h, the middle's product, is the
-// neighbour of both chains' first outward step and stored by the upper one).
+// Right-hand sides of a step.  Grid: (row blocks, slots).  The values of the
+// neighbouring slice j are t_j inwards (into tbatch), and x_j = t_j - partials
+// outwards (into batch; x_h, the middle's product, is the neighbour of both
+// chains' first outward step and stored by the upper one).
 template <int MODE, int MAXK>
 __global__ void __launch_bounds__(kBlock) k_cm_rhs(Geo g, const double* __restrict__ T,
-                                                   const TypeDev* __restrict__ types,
-                                                   const ChainJob* __restrict__ jobs, int k,
-                                                   int mtot, int bmax,
+                                                   const CmMember* __restrict__ mem, int k, int kc,
+                                                   int pstr, int gstr,
                                                    const float* __restrict__ part,
                                                    float* __restrict__ G,
                                                    const PcgState* __restrict__ st) {
   constexpr int NP = kCmRb + 2 * kCmHalo;
-  __shared__ double prev[MODE == kCmMid ? 2 : 1][NP];
+  constexpr int NS = MODE == kCmMid ? 2 : 1;  // neighbours
+  __shared__ double prev[NS][NP];
+  const int mtot = gridDim.y, slot = blockIdx.y, half = mtot / 2;  // (lower chains: + half)
+  const CmMember md = mem[slot];
   if (st != nullptr && st->done) return;
-  const ChainJob jb = jobs[blockIdx.y];
-  const int m = blockIdx.z;
-  if (m >= jb.nm) return;
-  const TypeDev td = types[jb.type];
-  const int b = td.b, nch = td.nch;
-  const int i = cm_slice(MODE, k, nch, jb.dir);
+  const int b = md.b, nch = md.nch;
+  const int i = cm_slice(MODE, k, nch, md.dir);
   const int R0 = blockIdx.x * kCmRb;
   if (i < 0 || R0 >= b) return;
-  const int nkc = (b + kCmKc - 1) / kCmKc;
-  const int m0 = td.m[0];
+  const int nkc = (b + kc - 1) / kc;
+  const int m0 = md.m0, m1 = md.m1;
   const int H = m0 + 1;
-  const int slot = jb.mg0 + m, half = mtot / 2;  // (slots of the lower chains: + half)
-  const long base = (long)(jb.m0 + m) * nch * b;
-  // sides: up to two neighbours (the middle's), d2 of each, whether there is one
-  constexpr int NS = MODE == kCmMid ? 2 : 1;
-  const int d2s[2] = {MODE == kCmMid ? -1 : ((MODE == kCmIn) == (jb.dir == 0) ? -1 : 1), 1};
+  // d2 of each neighbour and whether there is one
+  const int d2s[2] = {MODE == kCmMid ? -1 : ((MODE == kCmIn) == (md.dir == 0) ? -1 : 1), 1};
   const bool on[2] = {MODE == kCmMid ? i > 0 : (MODE == kCmOut || k > 0), i + 1 < nch};
+  // this thread's couplings and b_i, loaded before the neighbour is gathered
+  const int r = R0 + threadIdx.x;
+  const int rc = min(r, b - 1), u1 = rc / m0, u0 = rc - u1 * m0;
+  const long tn = table_node(g, md.o[0] + u0, md.o[1] + u1, md.o[2] + i);
+  double c[NS][9];
+#pragma unroll
+  for (int sd = 0; sd < NS; ++sd)
+#pragma unroll
+    for (int t = 0; t < 9; ++t) c[sd][t] = T[(t + 9 * (d2s[sd] + 1)) * g.tsize + tn];
+  double acc = MODE == kCmOut ? 0.0 : md.batch[(long)i * b + rc];
   const int lo = max(R0 - H, 0), hi = min(R0 + kCmRb + H, b);
 #pragma unroll
   for (int sd = 0; sd < NS; ++sd) {
     if (!on[sd]) continue;
     const int j = i + d2s[sd];
     const bool mid = MODE == kCmOut && k == 0;  // the neighbour is slice h
-    const int ps = MODE == kCmMid ? slot + sd * half : (mid && jb.dir ? slot - half : slot);
-    for (int r = lo + threadIdx.x; r < hi; r += kBlock) {
+    const int ps = MODE == kCmMid ? slot + sd * half : (mid && md.dir ? slot - half : slot);
+    for (int q = lo + threadIdx.x; q < hi; q += kBlock) {
       double v;
       if (MODE != kCmOut || mid) {
-        v = cm_prev<MAXK>(part, nkc, mtot, bmax, ps, r, nullptr);
+        v = cm_prev<MAXK>(part, nkc, mtot, pstr, ps, q, nullptr);
       } else {
-        const double t = td.tbatch[base + (long)j * b + r];
-        v = cm_prev<MAXK>(part, nkc, mtot, bmax, ps, r, &t);
+        const double t = md.tbatch[(long)j * b + q];
+        v = cm_prev<MAXK>(part, nkc, mtot, pstr, ps, q, &t);
       }
-      prev[sd][r - (R0 - H)] = v;
-      if (r >= R0 && r < R0 + kCmRb && !(mid && jb.dir))
-        (MODE == kCmOut ? td.batch : td.tbatch)[base + (long)j * b + r] = v;
+      prev[sd][q - (R0 - H)] = v;
+      if (q >= R0 && q < R0 + kCmRb && !(mid && md.dir))
+        (MODE == kCmOut ? md.batch : md.tbatch)[(long)j * b + q] = v;
     }
   }
   __syncthreads();
-  const int r = R0 + threadIdx.x;
   if (r >= b) return;
-  const int u1 = r / m0, u0 = r - u1 * m0;
-  double acc = MODE == kCmOut ? 0.0 : td.batch[base + (long)i * b + r];
 #pragma unroll
   for (int sd = 0; sd < NS; ++sd) {
     if (!on[sd]) continue;
-    const double c = cm_couple(g, T, td, u0, u1, i, d2s[sd], prev[sd], R0 - H);
-    acc += MODE == kCmOut ? c : -c;
+    double s = 0.0;
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+      const int w0 = u0 + t % 3 - 1, w1 = u1 + t / 3 - 1;
+      if (w0 < 0 || w0 >= m0 || w1 < 0 || w1 >= m1) continue;
+      s += c[sd][t] * prev[sd][w0 + m0 * w1 - (R0 - H)];
+    }
+    acc += MODE == kCmOut ? s : -s;
   }
-  G[(long)slot * bmax + r] = (float)acc;
+  G[(long)slot * gstr + r] = (float)acc;
 }
 
-// Partial product of a step: rows [R0, R0 + 128) x the job's members x
-// K chunk [K0, K0 + kCmKc) of W_i g, into part[kc][slot][row].
-__global__ void __launch_bounds__(kBlock) k_cm_mm(const TypeDev* __restrict__ types,
-                                                  const ChainJob* __restrict__ jobs, int mode,
-                                                  int k, int mtot, int bmax,
+// Partial product of a step: rows [R0, R0 + 128) x the job's members x K chunk
+// [K0, K0 + 8 NK) of W_i g, into part[chunk][slot][row].  The half-wave kh of
+// wave w takes k = K0 + (2 w + kh) NK + q, q < NK.
+template <int NK>
+__global__ void __launch_bounds__(kBlock) k_cm_mm(const CmJob* __restrict__ jobs, int mode, int k,
+                                                  int mtot, int pstr, int gstr,
                                                   const float* __restrict__ G,
                                                   float* __restrict__ part,
                                                   const PcgState* __restrict__ st) {
-  // W_i rows of the chunk [k][row] (row stride kCmLdw); reused for the output
-  // tile [row][member] (row stride kCmMembers + 1)
-  __shared__ __attribute__((aligned(16))) float ws[kCmKc * kCmLdw];
-  __shared__ float gs[kCmKc][kCmMembers + 1];
+  __shared__ __attribute__((aligned(16))) float red[4][32 * kCmLdr];
+  const CmJob jb = jobs[blockIdx.z];
   if (st != nullptr && st->done) return;
-  const ChainJob jb = jobs[blockIdx.z];
-  const TypeDev td = types[jb.type];
-  const int b = td.b, ldw = td.ldw;
-  const int R0 = blockIdx.x * kCmRows, K0 = blockIdx.y * kCmKc;
-  const int i = cm_slice(mode, k, td.nch, jb.dir);
+  const int b = jb.b, ldw = jb.ldw;
+  const int R0 = blockIdx.x * kCmRows, K0 = blockIdx.y * (8 * NK);
+  const int i = cm_slice(mode, k, jb.nch, jb.dir);
   if (i < 0 || R0 >= b || K0 >= b) return;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  // W_i through an address-space-1 pointer: its loads are global loads (a flat
-  // load would also hold up the LDS wait counter)
-  typedef __attribute__((address_space(1))) const f32x4* gvec4;
-  const float* Wi = td.W32 + (long)i * b * ldw;
-  // W_i rows K0.. of the chunk, columns R0..R0+127 (16-byte loads: ldw and R0
-  // are multiples of 4; columns b..ldw-1 of the padded rows are zero), and g
-  // of the job's members on the chunk.  All loads are issued before any is
-  // used: out-of-range ones read a valid address and are masked afterwards.
-  constexpr int NW = (kCmKc * kCmRows / 4) / kBlock, NG = (kCmKc * kCmMembers) / kBlock;
-  f32x4 wv[NW];
-  float gv[NG];
-#pragma unroll
-  for (int q = 0; q < NW; ++q) {
-    const int idx = tid + q * kBlock;
-    const int k = idx / (kCmRows / 4), col = R0 + 4 * (idx % (kCmRows / 4));
-    const bool ok = K0 + k < b && col < ldw;
-    wv[q] = *(gvec4)(Wi + (ok ? (long)(K0 + k) * ldw + col : 0));
-  }
-#pragma unroll
-  for (int q = 0; q < NG; ++q) {
-    const int idx = tid + q * kBlock;
-    const int j = idx / kCmKc, k = idx % kCmKc;
-    const bool ok = j < jb.nm && K0 + k < b;
-    gv[q] = G[ok ? (long)(jb.mg0 + j) * bmax + K0 + k : 0];
-  }
-#pragma unroll
-  for (int q = 0; q < NW; ++q) {
-    const int idx = tid + q * kBlock;
-    const int k = idx / (kCmRows / 4), c4 = idx % (kCmRows / 4);
-    const bool ok = K0 + k < b && R0 + 4 * c4 < ldw;
-    const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-    *reinterpret_cast<f32x4*>(&ws[k * kCmLdw + 4 * c4]) = ok ? wv[q] : zero;
-  }
-#pragma unroll
-  for (int q = 0; q < NG; ++q) {
-    const int idx = tid + q * kBlock;
-    const int j = idx / kCmKc, k = idx % kCmKc;
-    gs[k][j] = (j < jb.nm && K0 + k < b) ? gv[q] : 0.0f;
-  }
-  __syncthreads();
-  f32x16 acc[2];
-#pragma unroll
-  for (int t = 0; t < 2; ++t)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc[t][e] = 0.0f;
   const int kh = lane >> 5, l32 = lane & 31;
-  if (jb.nm > 32) {
-#pragma unroll 8
-    for (int kk = 0; kk < kCmKc; kk += 2) {
-      const float a = ws[(kk + kh) * kCmLdw + w * 32 + l32];
-      acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, gs[kk + kh][l32], acc[0], 0, 0, 0);
-      acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, gs[kk + kh][32 + l32], acc[1], 0, 0, 0);
-    }
-  } else {
-#pragma unroll 8
-    for (int kk = 0; kk < kCmKc; kk += 2) {
-      const float a = ws[(kk + kh) * kCmLdw + w * 32 + l32];
-      acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, gs[kk + kh][l32], acc[0], 0, 0, 0);
-    }
-  }
-  __syncthreads();
-  // accumulator layout: lane l, element e holds row 8 (e / 4) + 4 (l / 32) + e % 4
-  // of the wave's 32 rows and member l % 32 of the tile
-  constexpr int LO = kCmMembers + 1;
+  const int kb = K0 + (2 * w + kh) * NK;
+  // rows of W_i past b read as zero (the resource ends with the slice); columns
+  // past ldw are other rows' entries and end in output rows that are not stored
+  const auto rw = __builtin_amdgcn_make_buffer_rsrc((void*)(jb.W + (long)i * b * ldw), (short)0,
+                                                    b * ldw * 4, 0x00020000);
+  f32x4 wv[NK];
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
+  for (int q = 0; q < NK; ++q)
+    wv[q] = __builtin_bit_cast(
+        f32x4, __builtin_amdgcn_raw_buffer_load_b128(rw, ((kb + q) * ldw + R0 + 4 * l32) * 4, 0, 0));
+  for (int mt = 0; mt < jb.nm; mt += 32) {
+    // g of member mt + l32 (a lane without one repeats the last; its column of
+    // the product is not stored); rows past b hold zeros
+    const float* gp = G + (long)(jb.slot0 + min(mt + l32, jb.nm - 1)) * gstr + kb;
+    typedef __attribute__((address_space(1))) const float* gptr;
+    float gv[NK];
+#pragma unroll
+    for (int q = 0; q < NK; ++q) gv[q] = ((gptr)gp)[q];
+    f32x16 acc[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[t][e] = 0.0f;
+#pragma unroll
+    for (int q = 0; q < NK; ++q)
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[q][t], gv[q], acc[t], 0, 0, 0);
+    // accumulator layout: lane l, element e holds A row 8 (e / 4) + 4 (l / 32) +
+    // e % 4, which is row 4 of that + t of the workgroup, and member l % 32
+    if (mt > 0) __syncthreads();
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      const int row = w * 32 + 8 * (e >> 2) + 4 * kh + (e & 3);
-      ws[row * LO + 32 * t + l32] = acc[t][e];
+      const int row = 8 * (e >> 2) + 4 * kh + (e & 3);
+      *reinterpret_cast<f32x4*>(&red[w][l32 * kCmLdr + 4 * row]) =
+          f32x4{acc[0][e], acc[1][e], acc[2][e], acc[3][e]};
     }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 32 * kCmRows / 4 / kBlock; ++q) {
+      const int idx = tid + q * kBlock, j = idx / (kCmRows / 4), c4 = 4 * (idx % (kCmRows / 4));
+      if (mt + j >= jb.nm || R0 + c4 >= pstr) continue;
+      f32x4 v = *reinterpret_cast<const f32x4*>(&red[0][j * kCmLdr + c4]);
+#pragma unroll
+      for (int p = 1; p < 4; ++p) v += *reinterpret_cast<const f32x4*>(&red[p][j * kCmLdr + c4]);
+      *reinterpret_cast<f32x4*>(
+          &part[((long)blockIdx.y * mtot + jb.slot0 + mt + j) * pstr + R0 + c4]) = v;
+    }
+  }
+}
+
+// The same product for jobs of at most 16 members, on v_mfma_f32_16x16x4f32
+// (half the matrix instructions' time: a wave's share at NK = 34 is 3.6 us on
+// 32-wide tiles).  Quarter-wave kq of wave w takes k = K0 + (4 w + kq) NQ + q,
+// q < NQ = NK / 2; a lane's two loads of a row feed 16-row tiles (h, t) whose
+// row m is row 64 h + 4 m + t of the workgroup.
+template <int NK>
+__global__ void __launch_bounds__(kBlock) k_cm_mm16(const CmJob* __restrict__ jobs, int mode, int k,
+                                                    int mtot, int pstr, int gstr,
+                                                    const float* __restrict__ G,
+                                                    float* __restrict__ part,
+                                                    const PcgState* __restrict__ st) {
+  static_assert(NK % 2 == 0, "whole quarter-wave shares");
+  constexpr int NQ = NK / 2;
+  __shared__ __attribute__((aligned(16))) float red[4][16 * kCmLdr];
+  const CmJob jb = jobs[blockIdx.z];
+  if (st != nullptr && st->done) return;
+  const int b = jb.b, ldw = jb.ldw;
+  const int R0 = blockIdx.x * kCmRows, K0 = blockIdx.y * (8 * NK);
+  const int i = cm_slice(mode, k, jb.nch, jb.dir);
+  if (i < 0 || R0 >= b || K0 >= b) return;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int kq = lane >> 4, l16 = lane & 15;
+  const int kb = K0 + (4 * w + kq) * NQ;
+  const auto rw = __builtin_amdgcn_make_buffer_rsrc((void*)(jb.W + (long)i * b * ldw), (short)0,
+                                                    b * ldw * 4, 0x00020000);
+  f32x4 wv[NQ][2];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q)
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      wv[q][h] = __builtin_bit_cast(
+          f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                     rw, ((kb + q) * ldw + R0 + 64 * h + 4 * l16) * 4, 0, 0));
+  typedef __attribute__((address_space(1))) const float* gptr;
+  const float* gp = G + (long)(jb.slot0 + min(l16, jb.nm - 1)) * gstr + kb;
+  float gv[NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) gv[q] = ((gptr)gp)[q];
+  __builtin_amdgcn_sched_barrier(0);  // every load issued before the first product
+  f32x4 acc[2][4];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) acc[h][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int q = 0; q < NQ; ++q)
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        acc[h][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[q][h][t], gv[q], acc[h][t], 0, 0, 0);
+  // accumulator layout: lane l, element e holds tile row 4 (l / 16) + e, member l % 16
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      *reinterpret_cast<f32x4*>(&red[w][l16 * kCmLdr + 64 * h + 4 * (4 * kq + e)]) =
+          f32x4{acc[h][0][e], acc[h][1][e], acc[h][2][e], acc[h][3][e]};
   __syncthreads();
-  for (int idx = tid; idx < kCmMembers * kCmRows; idx += kBlock) {
-    const int j = idx / kCmRows, rr = idx % kCmRows;
-    if (j < jb.nm && R0 + rr < b)
-      part[((long)blockIdx.y * mtot + jb.mg0 + j) * bmax + R0 + rr] = ws[rr * LO + j];
+#pragma unroll
+  for (int q = 0; q < 16 * kCmRows / 4 / kBlock; ++q) {
+    const int idx = tid + q * kBlock, j = idx / (kCmRows / 4), c4 = 4 * (idx % (kCmRows / 4));
+    if (j >= jb.nm || R0 + c4 >= pstr) continue;
+    f32x4 v = *reinterpret_cast<const f32x4*>(&red[0][j * kCmLdr + c4]);
+#pragma unroll
+    for (int p = 1; p < 4; ++p) v += *reinterpret_cast<const f32x4*>(&red[p][j * kCmLdr + c4]);
+    *reinterpret_cast<f32x4*>(&part[((long)blockIdx.y * mtot + jb.slot0 + j) * pstr + R0 + c4]) = v;
   }
 }
 
 // The outermost slice of every chain: x = t - (partials), or x_0 = (partials)
-// for a chain of one slice.  Grid: (row blocks, jobs, members).
+// for a chain of one slice.  Grid: (row blocks, slots).
 template <int MAXK>
-__global__ void __launch_bounds__(kBlock) k_cm_fin(const TypeDev* __restrict__ types,
-                                                   const ChainJob* __restrict__ jobs, int mtot,
-                                                   int bmax, const float* __restrict__ part,
+__global__ void __launch_bounds__(kBlock) k_cm_fin(const CmMember* __restrict__ mem, int kc,
+                                                   int pstr, const float* __restrict__ part,
                                                    const PcgState* __restrict__ st) {
+  const int mtot = gridDim.y, slot = blockIdx.y;
+  const CmMember md = mem[slot];
   if (st != nullptr && st->done) return;
-  const ChainJob jb = jobs[blockIdx.y];
-  const int m = blockIdx.z;
-  if (m >= jb.nm) return;
-  const TypeDev td = types[jb.type];
-  const int b = td.b, h = td.nch / 2;
-  if (jb.dir && h + 1 >= td.nch) return;  // no lower chain
-  const int nkc = (b + kCmKc - 1) / kCmKc;
+  const int b = md.b, h = md.nch / 2;
+  if (md.dir && h + 1 >= md.nch) return;  // no lower chain
+  const int nkc = (b + kc - 1) / kc;
   const int r = blockIdx.x * kBlock + threadIdx.x;
   if (r >= b) return;
-  const long at = ((long)(jb.m0 + m) * td.nch + (jb.dir ? td.nch - 1 : 0)) * b + r;
-  const int slot = jb.mg0 + m;
-  if (td.nch == 1) {
-    td.batch[at] = cm_prev<MAXK>(part, nkc, mtot, bmax, slot, r, nullptr);
+  const long at = (long)(md.dir ? md.nch - 1 : 0) * b + r;
+  if (md.nch == 1) {
+    md.batch[at] = cm_prev<MAXK>(part, nkc, mtot, pstr, slot, r, nullptr);
   } else {
-    const double t = td.tbatch[at];
-    td.batch[at] = cm_prev<MAXK>(part, nkc, mtot, bmax, slot, r, &t);
+    const double t = md.tbatch[at];
+    md.batch[at] = cm_prev<MAXK>(part, nkc, mtot, pstr, slot, r, &t);
   }
 }
 
-size_t chain_mfma_part_bytes(int bmax, int mtot) {
-  const int nkc = (bmax + kCmKc - 1) / kCmKc;
-  return (size_t)(nkc + 1) * mtot * bmax * sizeof(float);
+// Strides and sizes: partial rows of whole float4s, G rows of b values and the
+// zeros that a last K chunk reads.
+static int cm_pstr(int bmax) { return (bmax + 3) / 4 * 4; }
+static int cm_gstr(int bmax) { return bmax + kCmPad; }
+
+// Rows of W_i per half-wave: the largest K chunk (8 NK rows) that leaves about
+// three quarters of the CUs a workgroup, so that the partials are few.
+static int cm_nk(int bmax, int njobs) {
+  const int tiles = (bmax + kCmRows - 1) / kCmRows * njobs;
+  for (int nk : {34, 18})
+    if (tiles * ((bmax + 8 * nk - 1) / (8 * nk)) >= 192) return nk;
+  return 9;
+}
+
+// The members' and jobs' descriptors, the partial buffer and G (zeros behind
+// every row of G).
+size_t chain_mfma_bytes(int bmax, int mtot, int njobs, size_t* job_off, size_t* part_off) {
+  size_t off = (size_t)mtot * sizeof(CmMember);
+  *job_off = off;
+  off += (size_t)njobs * sizeof(CmJob);
+  off = (off + 255) / 256 * 256;
+  *part_off = off;
+  const int nk = cm_nk(bmax, njobs), nkc = (bmax + 8 * nk - 1) / (8 * nk);
+  return off + ((size_t)nkc * mtot * cm_pstr(bmax) + (size_t)mtot * cm_gstr(bmax)) * sizeof(float);
+}
+
+// Fills the descriptors at the head of the (cleared) chain buffer.
+void chain_mfma_setup(ddeig_problem* P, const std::vector<TypeDev>& types,
+                      const std::vector<ChainJob>& jobs, hipStream_t s) {
+  std::vector<CmJob> cj;
+  std::vector<CmMember> cm(P->chain_mtot);
+  P->chain_nm = 0;
+  for (const ChainJob& j : jobs) {
+    const TypeDev& t = types[j.type];
+    P->chain_nm = std::max(P->chain_nm, j.nm);
+    cj.push_back(CmJob{t.W32, t.b, t.ldw, t.nch, j.dir, j.nm, j.mg0});
+    for (int m = 0; m < j.nm; ++m) {
+      const long at = (long)(j.m0 + m) * t.nch * t.b;
+      cm[j.mg0 + m] = CmMember{t.batch + at, t.tbatch + at, t.b, t.nch, t.m[0], t.m[1],
+                               {t.o[0], t.o[1], t.o[2]}, j.dir};
+    }
+  }
+  size_t joff, poff;
+  chain_mfma_bytes(P->chain_bmax, P->chain_mtot, (int)jobs.size(), &joff, &poff);
+  unsigned char* base = static_cast<unsigned char*>(P->chain_part);
+  check_hip(hipMemcpyAsync(base, cm.data(), sizeof(CmMember) * cm.size(), hipMemcpyHostToDevice, s),
+            "copy chain members");
+  check_hip(hipMemcpyAsync(base + joff, cj.data(), sizeof(CmJob) * cj.size(), hipMemcpyHostToDevice,
+                           s), "copy chain jobs");
+  check_hip(hipStreamSynchronize(s), "chain descriptors");
+}
+
+template <int NK, int MAXK>
+static void cm_solve(const ddeig_problem* P, const PcgState* st, hipStream_t s) {
+  const int nch = P->types[0].box.nch, h = nch / 2;
+  const int bmax = P->chain_bmax, mtot = P->chain_mtot, njobs = P->nchainjobs;
+  constexpr int kc = 8 * NK;
+  const int nkc = (bmax + kc - 1) / kc, pstr = cm_pstr(bmax), gstr = cm_gstr(bmax);
+  size_t joff, poff;
+  chain_mfma_bytes(bmax, mtot, njobs, &joff, &poff);
+  unsigned char* base = static_cast<unsigned char*>(P->chain_part);
+  const CmMember* mem = reinterpret_cast<const CmMember*>(base);
+  const CmJob* jobs = reinterpret_cast<const CmJob*>(base + joff);
+  float* part = reinterpret_cast<float*>(base + poff);
+  float* G = part + (long)nkc * mtot * pstr;
+  const dim3 grow((bmax + kCmRb - 1) / kCmRb, mtot);
+  const dim3 gmm((bmax + kCmRows - 1) / kCmRows, nkc, njobs);
+  auto mm = k_cm_mm<NK>;
+  if constexpr (NK % 2 == 0)
+    if (P->chain_nm <= 16) mm = k_cm_mm16<NK>;
+  auto step = [&](int mode, int k, auto rhs) {
+    hipLaunchKernelGGL(rhs, grow, dim3(kBlock), 0, s, P->g, P->tabAs, mem, k, kc, pstr, gstr, part,
+                       G, st);
+    hipLaunchKernelGGL(mm, gmm, dim3(kBlock), 0, s, jobs, mode, k, mtot, pstr, gstr, G, part, st);
+  };
+  for (int k = 0; k < h; ++k) step(kCmIn, k, k_cm_rhs<kCmIn, MAXK>);
+  step(kCmMid, 0, k_cm_rhs<kCmMid, MAXK>);
+  for (int k = 0; k < h; ++k) step(kCmOut, k, k_cm_rhs<kCmOut, MAXK>);
+  hipLaunchKernelGGL(k_cm_fin<MAXK>, grow, dim3(kBlock), 0, s, mem, kc, pstr, part, st);
 }
 
 // The solves of every class (all classes share nch).
 void launch_chain_mfma(const ddeig_problem* P, const PcgState* st, hipStream_t s) {
-  const int nch = P->types[0].box.nch, h = nch / 2;
-  const int bmax = P->chain_bmax, mtot = P->chain_mtot;
-  const int nkc = (bmax + kCmKc - 1) / kCmKc;
-  float* part = reinterpret_cast<float*>(P->chain_part);
-  float* G = part + (long)nkc * mtot * bmax;
-  const dim3 grhs((bmax + kCmRb - 1) / kCmRb, P->nchainjobs, kCmMembers);
-  const dim3 gmm((bmax + kCmRows - 1) / kCmRows, nkc, P->nchainjobs);
-  const bool k16 = nkc <= 16;
-  auto step = [&](int mode, int k, auto rhs) {
-    hipLaunchKernelGGL(rhs, grhs, dim3(kBlock), 0, s, P->g, P->tabAs, P->dTypes, P->dChainJobs, k,
-                       mtot, bmax, part, G, st);
-    hipLaunchKernelGGL(k_cm_mm, gmm, dim3(kBlock), 0, s, P->dTypes, P->dChainJobs, mode, k, mtot,
-                       bmax, G, part, st);
-  };
-  for (int k = 0; k < h; ++k)
-    step(kCmIn, k, k16 ? k_cm_rhs<kCmIn, 16> : k_cm_rhs<kCmIn, kCmMaxKc>);
-  step(kCmMid, 0, k16 ? k_cm_rhs<kCmMid, 16> : k_cm_rhs<kCmMid, kCmMaxKc>);
-  for (int k = 0; k < h; ++k)
-    step(kCmOut, k, k16 ? k_cm_rhs<kCmOut, 16> : k_cm_rhs<kCmOut, kCmMaxKc>);
-  const dim3 gfin((bmax + kBlock - 1) / kBlock, P->nchainjobs, kCmMembers);
-  hipLaunchKernelGGL(k16 ? k_cm_fin<16> : k_cm_fin<kCmMaxKc>, gfin, dim3(kBlock), 0, s, P->dTypes,
-                     P->dChainJobs, mtot, bmax, part, st);
+  const int nk = cm_nk(P->chain_bmax, P->nchainjobs);
+  const int nkc = (P->chain_bmax + 8 * nk - 1) / (8 * nk);
+  if (nk == 34) nkc <= 4 ? cm_solve<34, 4>(P, st, s) : cm_solve<34, 9>(P, st, s);
+  else if (nk == 18) nkc <= 8 ? cm_solve<18, 8>(P, st, s) : cm_solve<18, 16>(P, st, s);
+  else nkc <= 8 ? cm_solve<9, 8>(P, st, s) : nkc <= 16 ? cm_solve<9, 16>(P, st, s)
+                                                       : cm_solve<9, kCmMaxKc>(P, st, s);
 }
 
 }  // namespace ddeig
