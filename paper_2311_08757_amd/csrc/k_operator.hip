@@ -407,27 +407,38 @@ __global__ void __launch_bounds__(kBlock) k_stencil3d(Geo g, const double* __res
   if (use_sum) write_partial(accs, sum.part);
 }
 
-// The 2-D sweep when n_e divides 64 (every lane keeps one cell-local x
-// position across its 64-node strides): one 256 x 8 tile per workgroup, the
-// 2 x 9 table coefficients of the thread's rows loaded before the staging so
-// that both latency rounds overlap, and 32-bit tile-local index arithmetic
-// (fewer registers, more resident waves).  Same arithmetic and tap order as
-// k_stencil<2, MODE>.
+// The 2-D sweep for n_e <= 64: a lane's nodes are a stride of whole cells apart
+// (W = 64 when n_e divides 64, else the largest multiple of n_e below; the
+// lanes past W idle), so it keeps one cell-local x position.  One 4 W x 8 tile
+// per workgroup, the 2 x 9 table coefficients of the thread's rows loaded
+// before the staging so that both latency rounds overlap, and 32-bit
+// tile-local index arithmetic (fewer registers, more resident waves).  Same
+// arithmetic and tap order as k_stencil<2, MODE>, which reloads the
+// coefficients for every node and stages entry by entry (h = 1/30, 890,851
+// unknowns: 11.2 us an apply, here 5.2).
 // The body takes the block's tile index `bid` (blockIdx.x of a single
 // problem, or the block's index within its instance in a grouped launch).
 // YFAST numbers the tiles y fastest: with bid = xcd_slab(blockIdx.x) an XCD
 // then holds a run of whole tile columns, so the halo rows a tile shares with
 // its y neighbours come from that XCD's L2 instead of HBM (the grids of these
 // problems are a few tiles tall and very wide).
-template <int MODE, int TY = 8, bool YFAST = false>
+struct Tile2 {
+  int w, hx;    // lanes in use (the stride of a lane's nodes), 4 w + 2
+  FastDiv fhx;
+};
+
+template <int MODE, int TY = 8, bool YFAST = false, bool W64 = true>
 __device__ __forceinline__ void stencil2d_body(const Geo& g, const double* __restrict__ T,
                                                const double* __restrict__ x,
                                                const double* __restrict__ pold,
                                                double* __restrict__ pnew, double* __restrict__ y,
                                                const DirArgs& dir, int use_dot, const Red& dot,
-                                               int use_sum, const Red& sum, int bid) {
-  constexpr int TX = 256, HX = TX + 2, HY = TY + 2, RX = TX / 64, RY = TY / 4;
-  __shared__ double sv[HX * HY];
+                                               int use_sum, const Red& sum, int bid,
+                                               const Tile2& tl = Tile2{}) {
+  constexpr int RX = 4, HY = TY + 2, RY = TY / 4, HXM = 64 * RX + 2;
+  const int LW = W64 ? 64 : tl.w, TX = RX * LW, HX = W64 ? HXM : tl.hx;
+  auto row_of = [&](int e) { return W64 ? e / HXM : (int)fdiv((unsigned)e, tl.fhx); };
+  __shared__ double sv[HXM * HY];
   double beta = 0.0;
   if constexpr (MODE == 1) {
     const double rho = sum_partials(dir.rz.part, dir.rz.np);
@@ -460,7 +471,8 @@ __device__ __forceinline__ void stencil2d_body(const Geo& g, const double* __res
   }
   // the halo staging, unrolled in rounds of SB entries per thread so that all
   // loads of a round are in flight together
-  constexpr int NH = HX * HY, NS = (NH + kBlock - 1) / kBlock, SB = 8;
+  constexpr int NS = (HXM * HY + kBlock - 1) / kBlock, SB = 8;
+  const int NH = HX * HY;
   const long base = (long)N0 * y0 + x0;
 #pragma unroll
   for (int s0 = 0; s0 < NS; s0 += SB) {
@@ -470,7 +482,7 @@ __device__ __forceinline__ void stencil2d_body(const Geo& g, const double* __res
 #pragma unroll
     for (int u = 0; u < SB; ++u) {
       const int e = threadIdx.x + kBlock * (s0 + u);
-      const int ex = e % HX, ey = e / HX;
+      const int ey = row_of(e), ex = e - ey * HX;
       const int gx = x0 - 1 + ex, gy = y0 - 1 + ey;
       in[u] = e < NH && gx >= 0 && gx < N0 && gy >= 0 && gy < N1;
       off[u] = (long)N0 * (ey - 1) + (ex - 1);
@@ -485,7 +497,7 @@ __device__ __forceinline__ void stencil2d_body(const Geo& g, const double* __res
       if constexpr (MODE == 1) {
         if (in[u]) {
           if (dir.k > 1) val += beta * vo[u];
-          const int ex = e % HX, ey = e / HX;
+          const int ey = row_of(e), ex = e - ey * HX;
           if (ex >= 1 && ex <= TX && ey >= 1 && ey <= TY) pnew[base + off[u]] = val;
         }
       }
@@ -500,9 +512,9 @@ __device__ __forceinline__ void stencil2d_body(const Geo& g, const double* __res
     if (gy >= N1) continue;
 #pragma unroll
     for (int s = 0; s < RX; ++s) {
-      const int gx = x0 + lane + 64 * s;
-      if (gx >= N0) continue;
-      const int cx = lane + 64 * s + 1;
+      const int gx = x0 + lane + LW * s;
+      if (gx >= N0 || (!W64 && lane >= LW)) continue;
+      const int cx = lane + LW * s + 1;
       double a = 0.0;
 #pragma unroll
       for (int t = 0; t < 9; ++t) a += c[j][t] * sv[(cx + t % 3 - 1) + HX * (ty + t / 3)];
@@ -518,15 +530,16 @@ __device__ __forceinline__ void stencil2d_body(const Geo& g, const double* __res
   if (use_sum) write_partial_at(accs, sum.part, bid);
 }
 
-template <int MODE, int TY>
+template <int MODE, int TY, bool W64>
 __global__ void __launch_bounds__(kBlock) k_stencil2d(Geo g, const double* __restrict__ T,
                                                       const double* __restrict__ x,
                                                       const double* __restrict__ pold,
                                                       double* __restrict__ pnew,
                                                       double* __restrict__ y, DirArgs dir,
-                                                      int use_dot, Red dot, int use_sum, Red sum) {
-  stencil2d_body<MODE, TY, true>(g, T, x, pold, pnew, y, dir, use_dot, dot, use_sum, sum,
-                                 xcd_slab(blockIdx.x, gridDim.x));
+                                                      int use_dot, Red dot, int use_sum, Red sum,
+                                                      Tile2 tl) {
+  stencil2d_body<MODE, TY, true, W64>(g, T, x, pold, pnew, y, dir, use_dot, dot, use_sum, sum,
+                                      xcd_slab(blockIdx.x, gridDim.x), tl);
 }
 
 // The 2-D sweep of wide grids (n_e dividing 64): one wave per workgroup owns
@@ -948,23 +961,27 @@ void launch_b_stencil_plain(const InstDev* I, const BlockMap& bm, const int* act
                      which);
 }
 
-// Rows of the 2-D sweep's tiles (n_e dividing 64): 4 while 4-row tiles number
+// Columns of the 2-D sweep's tiles: four strides of whole cells, 64 columns at most.
+static int stencil2d_w(const Geo& g) { return g.ne * (64 / g.ne); }
+
+// Rows of the 2-D sweep's tiles (n_e <= 64): 4 while 4-row tiles number
 // at most 1024 (one partial each), else 8.  Small grids, whose vectors sit in
 // the Infinity Cache and whose sweep is latency-bound, get twice the
 // workgroups (config 2: 1024 tiles, 7.2 -> 5.9 us per sweep).
 int stencil2d_ty(const Geo& g) {
-  const long t4 = (long)((g.N[0] + 255) / 256) * ((g.N[1] + 3) / 4);
+  const int tx = 4 * stencil2d_w(g);
+  const long t4 = (long)((g.N[0] + tx - 1) / tx) * ((g.N[1] + 3) / 4);
   return t4 <= kMaxRed ? 4 : 8;
 }
 
-static bool stencil2d_fast(const Geo& g) { return g.D == 2 && 64 % g.ne == 0; }
+static bool stencil2d_fast(const Geo& g) { return g.D == 2 && g.ne <= 64; }
 
 // The row march serves 2-D grids with n_e dividing 64 whose width gives at
 // least 1024 of its 512-column workgroups (ddeig_options.sweep 0), or on
 // request (sweep 2); sweep 1 keeps the tiles (in 3-D as well).
 static bool stencil2d_march(const ddeig_problem* P) {
   const Geo& g = P->g;
-  if (!stencil2d_fast(g) || P->opt.sweep == 1) return false;
+  if (g.D != 2 || 64 % g.ne != 0 || P->opt.sweep == 1) return false;
   return P->opt.sweep == 2 || (g.N[0] + kMarchX - 1) / kMarchX >= 1024;
 }
 
@@ -991,8 +1008,8 @@ long stencil_blocks(const ddeig_problem* P) {
 
 long stencil_tiles(const Geo& g) {
   if (stencil2d_fast(g)) {
-    const int ty = stencil2d_ty(g);
-    return (long)((g.N[0] + 255) / 256) * ((g.N[1] + ty - 1) / ty);
+    const int ty = stencil2d_ty(g), tx = 4 * stencil2d_w(g);
+    return (long)((g.N[0] + tx - 1) / tx) * ((g.N[1] + ty - 1) / ty);
   }
   if (g.D == 2)
     return (long)((g.N[0] + TileShape<2>::TX - 1) / TileShape<2>::TX) *
@@ -1037,6 +1054,17 @@ static void finish_tile_red(const ddeig_problem* P, const TileRed& t, hipStream_
                        (long)t.use.np, t.final.part);
 }
 
+template <int MODE>
+static auto stencil2d_kernel(const Geo& g) {
+  if (64 % g.ne == 0) return stencil2d_ty(g) == 4 ? k_stencil2d<MODE, 4, true> : k_stencil2d<MODE, 8, true>;
+  return stencil2d_ty(g) == 4 ? k_stencil2d<MODE, 4, false> : k_stencil2d<MODE, 8, false>;
+}
+
+static Tile2 stencil2d_tile(const Geo& g) {
+  const int w = stencil2d_w(g);
+  return Tile2{w, 4 * w + 2, make_fastdiv(4 * w + 2)};
+}
+
 void launch_stencil(const ddeig_problem* P, const double* tab, const double* x, double* y,
                     Red* dot, Red* sum, hipStream_t s) {
   const long tiles = stencil_blocks(P);
@@ -1054,9 +1082,9 @@ void launch_stencil(const ddeig_problem* P, const double* tab, const double* x, 
                        nullptr, nullptr, y, nodir, dot ? 1 : 0, td.use, sum ? 1 : 0, ts.use);
   }
   else if (stencil2d_fast(P->g)) {
-    auto kern = stencil2d_ty(P->g) == 4 ? k_stencil2d<0, 4> : k_stencil2d<0, 8>;
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(kBlock), 0, s, P->g, tab, x, nullptr, nullptr, y,
-                       nodir, dot ? 1 : 0, td.use, sum ? 1 : 0, ts.use);
+    hipLaunchKernelGGL(stencil2d_kernel<0>(P->g), dim3(blocks), dim3(kBlock), 0, s, P->g, tab, x,
+                       nullptr, nullptr, y, nodir, dot ? 1 : 0, td.use, sum ? 1 : 0, ts.use,
+                       stencil2d_tile(P->g));
   }
   else if (P->g.D == 2)
     hipLaunchKernelGGL((k_stencil<2, 0>), dim3(blocks), dim3(kBlock), 0, s, P->g, tab, x,
@@ -1089,9 +1117,8 @@ void launch_stencil_dir(const ddeig_problem* P, const double* z, const double* p
                        pold, pnew, q, dir, 1, tg.use, 0, none);
   }
   else if (stencil2d_fast(P->g)) {
-    auto kern = stencil2d_ty(P->g) == 4 ? k_stencil2d<1, 4> : k_stencil2d<1, 8>;
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(kBlock), 0, s, P->g, P->tabAs, z, pold, pnew, q,
-                       dir, 1, tg.use, 0, none);
+    hipLaunchKernelGGL(stencil2d_kernel<1>(P->g), dim3(blocks), dim3(kBlock), 0, s, P->g, P->tabAs,
+                       z, pold, pnew, q, dir, 1, tg.use, 0, none, stencil2d_tile(P->g));
   }
   else if (P->g.D == 2)
     hipLaunchKernelGGL((k_stencil<2, 1>), dim3(blocks), dim3(kBlock), 0, s, P->g, P->tabAs, z,
