@@ -2329,6 +2329,8 @@ struct ddeig_batch {
   hipEvent_t ev_st[2] = {nullptr, nullptr};   // recorded after each block's state copy
   std::vector<void*> allocs;
   int tile_rows = 128;      // GEMM tile rows (128, or 64 to skip padding rows)
+  bool fold = false;        // the GEMM's tiles fold the K splits (one set of Z)
+  int zsets = 1;            // sets of Z that the correction and the extension add
   double tune_us[12] = {};  // [tile rows 128, 64][split 1..3][order 0..1]
   // hipGraph replay of the grouped iterations: one executable graph per
   // (first iteration of a block of 8, maxit), captured on first use
@@ -2373,7 +2375,8 @@ ddeig::BlockMap make_map(ddeig_batch* B, const std::vector<int>& counts) {
 // of one (instance, column tile, split), which read the same rows of that
 // instance's inverse.  order 1 interleaves eight groups of equal size so that
 // a group's tiles get workgroup ids 8 apart (one XCD, one L2 copy of the rows).
-std::vector<ddeig::GemmTile> batch_tiles(const ddeig_batch* B, int ks, int order, int tm) {
+std::vector<ddeig::GemmTile> batch_tiles(const ddeig_batch* B, int ks, int order, int tm,
+                                         bool fold = false) {
   const int bk = B->local_prec == 2 ? 32 : 64;
   const int npair = B->ld / bk / 2;
   std::vector<std::vector<ddeig::GemmTile>> groups;
@@ -2381,13 +2384,14 @@ std::vector<ddeig::GemmTile> batch_tiles(const ddeig_batch* B, int ks, int order
     // row tiles of tm rows covering the instance's subdomains (the rows past
     // them, up to its padded row count, are skipped when tm = 64)
     const int nrt = (B->P[j]->nsub + tm - 1) / tm;
-    for (int sp = 0; sp < ks; ++sp) {
+    // (fold: one tile takes all splits)
+    for (int sp = 0; sp < (fold ? 1 : ks); ++sp) {
       const int kb0 = 2 * (int)((long)npair * sp / ks);
-      const int kb1 = 2 * (int)((long)npair * (sp + 1) / ks);
+      const int kb1 = fold ? 2 * npair : 2 * (int)((long)npair * (sp + 1) / ks);
       for (int nt = 0; nt < B->ld / 128; ++nt) {
         std::vector<ddeig::GemmTile> grp;
         for (int mt = 0; mt < nrt; ++mt)
-          grp.push_back(ddeig::GemmTile{j, mt * tm, nt * 128, kb0 * bk, kb1 * bk, sp});
+          grp.push_back(ddeig::GemmTile{j, mt * tm, nt * 128, kb0 * bk, kb1 * bk, fold ? ks : sp});
         groups.push_back(grp);
       }
     }
@@ -2426,14 +2430,14 @@ void batch_iteration(ddeig_batch* B, int k, int maxit, hipStream_t s) {
   launch_b_restrict(B->dInst, B->bm_node, k, s);
   check_hip(hipEventRecord(B->ev_fork, s), "record fork");
   check_hip(hipStreamWaitEvent(B->aux, B->ev_fork, 0), "wait fork");
-  launch_gemm_tiles(B->dTiles, B->ntiles, B->dGt, B->local_prec, s, B->tile_rows);
-  launch_embed_jobs(B->dEmbJobs, B->nembjobs, B->dEmb, B->ksplit, B->ld, B->hm0, B->hm1, B->mH, s);
+  launch_gemm_tiles(B->dTiles, B->ntiles, B->dGt, B->local_prec, s, B->tile_rows, B->fold);
+  launch_embed_jobs(B->dEmbJobs, B->nembjobs, B->dEmb, B->zsets, B->ld, B->hm0, B->hm1, B->mH, s);
   launch_b_coarse_rhs(B->dInst, B->bm_crhs, B->aux);
   launch_b_coarse_solve(B->dInst, B->bm_csol, B->aux);
   launch_b_coarse_field(B->dInst, B->bm_cf, B->aux);
   check_hip(hipEventRecord(B->ev_join, B->aux), "record join");
   check_hip(hipStreamWaitEvent(s, B->ev_join, 0), "wait join");
-  launch_b_extend(B->dInst, B->bm_node, k, maxit, B->ksplit, s);
+  launch_b_extend(B->dInst, B->bm_node, k, maxit, B->zsets, s);
 }
 
 // PCG on A_sigma,j x_j = b_j for the instances with active[j] != 0 (the
@@ -2452,15 +2456,15 @@ void batch_pcg(ddeig_batch* B, const std::vector<int>& active, const std::vector
     launch_b_pcg_init(B->dInst, B->n, act, rtol, s);
     check_hip(hipEventRecord(B->ev_fork, s), "record fork");
     check_hip(hipStreamWaitEvent(B->aux, B->ev_fork, 0), "wait fork");
-    launch_gemm_tiles(B->dTiles, B->ntiles, B->dGt, B->local_prec, s, B->tile_rows);
-    launch_embed_jobs(B->dEmbJobs, B->nembjobs, B->dEmb, B->ksplit, B->ld, B->hm0, B->hm1, B->mH,
+    launch_gemm_tiles(B->dTiles, B->ntiles, B->dGt, B->local_prec, s, B->tile_rows, B->fold);
+    launch_embed_jobs(B->dEmbJobs, B->nembjobs, B->dEmb, B->zsets, B->ld, B->hm0, B->hm1, B->mH,
                       s);
     launch_b_coarse_rhs(B->dInst, B->bm_crhs, B->aux);
     launch_b_coarse_solve(B->dInst, B->bm_csol, B->aux);
     launch_b_coarse_field(B->dInst, B->bm_cf, B->aux);
     check_hip(hipEventRecord(B->ev_join, B->aux), "record join");
     check_hip(hipStreamWaitEvent(s, B->ev_join, 0), "wait join");
-    launch_b_extend(B->dInst, B->bm_node, 0, maxit, B->ksplit, s, 0);
+    launch_b_extend(B->dInst, B->bm_node, 0, maxit, B->zsets, s, 0);
   } else {
     for (int j = 0; j < B->n; ++j) {
       if (!active[j]) continue;
@@ -2656,6 +2660,19 @@ ddeig_status ddeig_batch_create(ddeig_problem* const* probs, int n, int flags, d
       B->order = choice[1];
       B->tile_rows = choice[2];
       best_tiles = batch_tiles(B, B->ksplit, B->order, B->tile_rows);
+      if ((flags & DDEIG_BATCH_REPRODUCIBLE) && B->ksplit > 1) {
+        // The splits folded into one tile (same bits) once there is a tile for
+        // each of the 256 CUs without them: 32 instances of 16..256 subdomains
+        // (n_e = 32, 450 folded tiles) solve in 243.8 ms against 266.7 ms split
+        // in three (64-row tiles: 252.6 against 274.7).  Below that the split
+        // is what fills the chip.
+        std::vector<ddeig::GemmTile> folded =
+            batch_tiles(B, B->ksplit, B->order, B->tile_rows, true);
+        if (folded.size() >= 256) {
+          B->fold = true;
+          best_tiles.swap(folded);
+        }
+      }
     } else {
       // every tile shape (128 or 64 rows), K split and order; the tile rows do
       // not change the arithmetic (each output sums the same K stages in the
@@ -2682,6 +2699,7 @@ ddeig_status ddeig_batch_create(ddeig_problem* const* probs, int n, int flags, d
       std::lock_guard<std::mutex> lk(g_tune_mu);
       g_tune.emplace(shape, std::array<int, 3>{B->ksplit, B->order, B->tile_rows});
     }
+    B->zsets = B->fold ? 1 : B->ksplit;
     B->dTiles = bupload(B, best_tiles);
     B->ntiles = (int)best_tiles.size();
     // clipped classes of every instance, each checked against its instance's state
@@ -2734,7 +2752,7 @@ ddeig_status ddeig_batch_create(ddeig_problem* const* probs, int n, int flags, d
       d.rr.np = d.nb_node;
       d.rz = slot(P, 2);
       d.rz.np = d.nb_node;
-      d.da = ddeig::DenseArgs{H.Rh, H.Rl, H.Z, (long)H.mp * H.ld, H.ld, B->ksplit, H.box.m[0],
+      d.da = ddeig::DenseArgs{H.Rh, H.Rl, H.Z, (long)H.mp * H.ld, H.ld, B->zsets, H.box.m[0],
                               H.box.m[1]};
       d.psi = P->psi;
       d.cf = P->cfield;

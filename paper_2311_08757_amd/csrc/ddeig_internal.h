@@ -246,7 +246,8 @@ struct ChainJob {
 };
 
 struct GemmTile {
-  int type, m0, n0, k0, k1, split;
+  int type, m0, n0, k0, k1;
+  int split;  // the K split this tile is of; the number of splits it folds (k_dense_gemm FOLD)
 };
 
 // Rows [r0, r1) of one small dense class for the streaming kernel.
@@ -545,7 +546,7 @@ void launch_b_coarse_rhs(const InstDev* I, const BlockMap& bm, hipStream_t s);
 void launch_b_coarse_solve(const InstDev* I, const BlockMap& bm, hipStream_t s);
 void launch_b_coarse_field(const InstDev* I, const BlockMap& bm, hipStream_t s);
 void launch_gemm_tiles(const GemmTile* tiles, int ntiles, const GemmType* gt, int local_prec,
-                       hipStream_t s, int tile_rows = 128);
+                       hipStream_t s, int tile_rows = 128, bool fold = false);
 void launch_embed_jobs(const EmbedJob* jobs, int njobs, const EmbedDev* cls, int ksplit, int ld,
                        int hm0, int hm1, int mH, hipStream_t s);
 void launch_b_states(const InstDev* I, int n, PcgState* out, int mark_done, hipStream_t s);

@@ -104,11 +104,18 @@ typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
 // Workgroups beyond the ntiles tiles form the coarse right-hand side R_0 r
 // (ca.n of them, one per subdomain) on the CUs the tiles leave free; they
 // share nothing with the tiles, so no workgroup waits for another.
-template <bool RLO, bool ALO, int MI = 2, bool BND = false>
-__global__ void __launch_bounds__(kBlock) k_dense_gemm(const GemmTile* __restrict__ tiles,
-                                                       const GemmType* __restrict__ gtypes,
-                                                       const PcgState* __restrict__ st,
-                                                       int ntiles, CoarseRhsArgs ca) {
+// FOLD: the tile takes every K split in turn (t.split of them, bounds as the
+// host's) and adds each one's sum to the others' in split order, so that Z
+// holds one set of values with the bits that the extension's sum of the splits'
+// sets would have: for batches with enough tiles to fill the chip without the
+// splits, whose separate sets cost their writes, their reads and a launch's
+// fixed time per tile.  Its bound of two workgroups per CU keeps it at 236
+// registers (317 without: one workgroup per CU, 32 instances of 16..256
+// subdomains 258 ms against 244).
+template <bool RLO, bool ALO, int MI = 2, bool BND = false, bool FOLD = false>
+__global__ void __launch_bounds__(kBlock, FOLD ? 2 : 1)
+    k_dense_gemm(const GemmTile* __restrict__ tiles, const GemmType* __restrict__ gtypes,
+                 const PcgState* __restrict__ st, int ntiles, CoarseRhsArgs ca) {
   using C = GemmCfg<RLO, ALO, MI>;
   constexpr int BK = C::BK, LDK = C::LDK, NR = C::NR, NOP = C::NOP, NV = C::NV, NVT = C::NVT;
   constexpr int NVR = C::NVR, NS = C::NS, WPS = C::WPS;
@@ -259,13 +266,37 @@ __global__ void __launch_bounds__(kBlock) k_dense_gemm(const GemmTile* __restric
     }
     __syncthreads();
   };
+  floatx16 tot[FOLD ? MI : 1][2];
+  int sp = 1;  // FOLD: the next split's first stage is 2 (nk / 2 sp / splits)
+  if constexpr (FOLD) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) tot[i][j][e] = 0.0f;
+  }
   for (int kb = 0; kb < nk; kb += 2) {
     half(ra, rb, 0, kb);
     half(rb, ra, 1, kb + 1);
+    if constexpr (FOLD) {
+      if (kb + 2 == 2 * (nk / 2 * sp / t.split)) {
+        ++sp;
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+              tot[i][j][e] += acc[i][j][e];
+              acc[i][j][e] = 0.0f;
+            }
+      }
+    }
   }
   // accumulator layout of the 32 x 32 MFMA tile: lane l, element e holds
   // row 8 (e / 4) + 4 (l / 32) + e % 4, column l % 32
-  float* Zp = gt.Z + (long)t.split * gt.zsplit + (long)t.m0 * ld + t.n0;
+  float* Zp = gt.Z + (FOLD ? 0L : (long)t.split * gt.zsplit) + (long)t.m0 * ld + t.n0;
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -274,7 +305,8 @@ __global__ void __launch_bounds__(kBlock) k_dense_gemm(const GemmTile* __restric
       for (int e = 0; e < 16; ++e) {
         const int r = (wm * MI + i) * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
         const int c = (wn * 2 + j) * 32 + (lane & 31);
-        if (!BND || t.m0 + r < gt.rows) Zp[(long)r * ld + c] = acc[i][j][e];
+        const float v = FOLD ? tot[i][j][e] : acc[i][j][e];
+        if (!BND || t.m0 + r < gt.rows) Zp[(long)r * ld + c] = v;
       }
 }
 
@@ -658,15 +690,21 @@ bool fused_coarse(const ddeig_problem* P) {
 // Grouped launches over the instances of a batch: the tiles / correction jobs
 // carry the instance in their type / class index, and each instance's CG
 // state is checked through GemmType::st / EmbedDev::st.
+template <bool FOLD>
+static auto batch_gemm_kernel(int local_prec, int tile_rows) {
+  return local_prec == 2 ? (tile_rows == 64 ? k_dense_gemm<true, true, 1, true, FOLD>
+                                            : k_dense_gemm<true, true, 2, true, FOLD>)
+                         : (tile_rows == 64 ? k_dense_gemm<false, false, 1, true, FOLD>
+                                            : k_dense_gemm<false, false, 2, true, FOLD>);
+}
+
 void launch_gemm_tiles(const GemmTile* tiles, int ntiles, const GemmType* gt, int local_prec,
-                       hipStream_t s, int tile_rows) {
+                       hipStream_t s, int tile_rows, bool fold) {
   if (ntiles <= 0) return;
   CoarseRhsArgs none{};
   none.n = 0;
-  auto kern = local_prec == 2 ? (tile_rows == 64 ? k_dense_gemm<true, true, 1, true>
-                                                 : k_dense_gemm<true, true, 2, true>)
-                              : (tile_rows == 64 ? k_dense_gemm<false, false, 1, true>
-                                                 : k_dense_gemm<false, false, 2, true>);
+  auto kern = fold ? batch_gemm_kernel<true>(local_prec, tile_rows)
+                   : batch_gemm_kernel<false>(local_prec, tile_rows);
   hipLaunchKernelGGL(kern, dim3(ntiles), dim3(kBlock), 0, s, tiles, gt, nullptr, ntiles, none);
 }
 
