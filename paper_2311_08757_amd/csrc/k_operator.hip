@@ -722,20 +722,37 @@ __global__ void __launch_bounds__(64) k_stencil2d_march(Geo g, const double* __r
 // k + 1: each output receives its taps in the order t = 0..26 of the tile
 // sweep, from the same values, and equals the tile sweep's result bit for
 // bit.  Plane k - 1 is then complete and stored.  Each plane of the block is
-// read once and the next plane is loaded one step ahead; the loads are buffer
-// loads whose per-lane offsets stay in one register each (the tap and plane
-// offsets ride in scalar registers), from clamped in-range offsets, the masks
-// applied when a plane is staged.  MODE 1 stages p_k = z + beta p_{k-1} as
-// the tile sweep does, writes the owned entries of p_k and forms the partials
-// of p_k.q.  One partial per workgroup; needs 8 N < 2^31 (stencil3d_march).
+// read once and the next plane is loaded one step ahead.  All global accesses
+// are buffer operations whose per-lane offsets stay in one register each (tap
+// and plane offsets ride in scalar registers); an offset past the end reads 0
+// and is not stored, so that a step has no branch.  MODE 1 stages
+// p_k = z + beta p_{k-1} as the tile sweep does, writes the owned entries of
+// p_k and forms the partials of p_k.q; DOT: x.y (p.q) and the sum of y are
+// wanted (the centre values come from a third LDS plane, the one before the
+// plane in work).  One partial per workgroup; needs 8 N < 2^31
+// (stencil3d_march).
+//
+// Loads complete in issue order, so what a step waits for must be issued before
+// what it leaves in flight: the coefficients of plane k + 1 go out after the
+// last use of plane k's and before the stores, the input plane k + 2 after the
+// staging of plane k + 1.  With the coefficients behind the input plane's loads
+// every step waited for memory.  Blocks are numbered x fastest, so that an XCD
+// works on few rows of the table and keeps them in its L2 (with y fastest the
+// reads were 719 MB instead of 655).  62,979,135 unknowns, 1.008 GB: 319 us
+// before both, 286 us now (3.5 TB/s); 186 (DOT) / 180 registers, two waves per
+// SIMD.  A block of 16 rows reads less (610 MB) but runs one workgroup per CU,
+// 301 us; 128 columns take twice the table reads and 579 us; a second set of
+// coefficient registers, loaded a whole step ahead, 291 us.
 constexpr int kPlaneTX = 256, kPlaneTY = 8;
+
+typedef __attribute__((__vector_size__(2 * sizeof(unsigned)))) unsigned u32x2;
 
 __device__ __forceinline__ double buf_load(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
   return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
 }
 
-template <int MODE>
-__global__ void __launch_bounds__(kBlock) k_stencil3d_march(Geo g, const double* __restrict__ T,
+template <int MODE, bool DOT>
+__global__ void __launch_bounds__(kBlock, 2) k_stencil3d_march(Geo g, const double* __restrict__ T,
                                                             const double* __restrict__ x,
                                                             const double* __restrict__ pold,
                                                             double* __restrict__ pnew,
@@ -744,7 +761,7 @@ __global__ void __launch_bounds__(kBlock) k_stencil3d_march(Geo g, const double*
   constexpr int TX = kPlaneTX, TY = kPlaneTY, HX = TX + 2, HY = TY + 2, NH = HX * HY, RX = 8;
   constexpr int NS = (NH + kBlock - 1) / kBlock;
   static_assert(TY == 2 * (kBlock / 64) && TX == 32 * RX, "two rows per wave, 32 lanes per row");
-  __shared__ double pl[2][NH];
+  __shared__ double pl[3][NS * kBlock];  // (the last slots pad the last pass)
   double beta = 0.0;
   if constexpr (MODE == 1) {
     const double rho = sum_partials(dir.rz.part, dir.rz.np);
@@ -762,9 +779,9 @@ __global__ void __launch_bounds__(kBlock) k_stencil3d_march(Geo g, const double*
   const bool upd = MODE == 1 && dir.k > 1;
   const int N0 = g.N[0], N1 = g.N[1], N2 = g.N[2];
   const long N01 = (long)N0 * N1;
-  const int nby = (N1 + TY - 1) / TY;
+  const int nbx = (N0 + TX - 1) / TX;
   const int bid = xcd_slab(blockIdx.x, gridDim.x);
-  const int x0 = (bid / nby) * TX, y0 = (bid % nby) * TY;
+  const int x0 = (bid % nbx) * TX, y0 = (bid / nbx) * TY;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int xl = lane & 31, ty = 2 * w + (lane >> 5);
   const unsigned tsz8 = (unsigned)(g.tsize * 8);
@@ -772,7 +789,9 @@ __global__ void __launch_bounds__(kBlock) k_stencil3d_march(Geo g, const double*
   const unsigned pl8 = (unsigned)(N01 * 8);
   const int nbytes = (int)(N01 * N2 * 8);
   const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)x, (short)0, nbytes, 0x00020000);
-  const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc((void*)pold, (short)0, nbytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc((void*)pold, (short)0, upd ? nbytes : 0, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rn = __builtin_amdgcn_make_buffer_rsrc((void*)pnew, (short)0, nbytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc((void*)y, (short)0, nbytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t rt = __builtin_amdgcn_make_buffer_rsrc((void*)T, (short)0,
                                                                       (int)(27 * g.tsize * 8), 0x00020000);
   const int j0 = (int)((unsigned)(x0 + xl + 1) - g.ne * fdiv((unsigned)(x0 + xl + 1), g.fne));
@@ -781,130 +800,121 @@ __global__ void __launch_bounds__(kBlock) k_stencil3d_march(Geo g, const double*
   const int gyc = min(gy, N1 - 1);
   const int j1 = g.isx[1] ? (int)((unsigned)(gyc + 1) - g.ne * fdiv((unsigned)(gyc + 1), g.fne)) : gyc;
   const unsigned coff = (unsigned)(j0 + g.P[0] * j1) * 8u;
-  // staging slots of this thread: in-plane offsets (0 when outside the grid),
-  // in-grid and owned masks
+  // staging slots of this thread: in-plane offsets, past every buffer's end
+  // when outside the grid (loads give 0) or not owned (stores of p_k dropped)
+  constexpr unsigned kOut = 0x80000000u;
   unsigned voff[NS];
-  unsigned inm = 0, own = 0;
+  unsigned own = 0;
 #pragma unroll
   for (int u = 0; u < NS; ++u) {
     const int e = threadIdx.x + kBlock * u;
     const int ex = e % HX, ey = e / HX;
     const int gx = x0 - 1 + ex, gyy = y0 - 1 + ey;
     const bool in = e < NH && gx >= 0 && gx < N0 && gyy >= 0 && gyy < N1;
-    voff[u] = in ? (unsigned)(gx + N0 * gyy) * 8u : 0u;
-    inm |= in ? (1u << u) : 0u;
+    voff[u] = in ? (unsigned)(gx + N0 * gyy) * 8u : kOut;
     own |= (in && ex >= 1 && ex <= TX && ey >= 1 && ey <= TY) ? (1u << u) : 0u;
   }
-  double nx[NS], np[NS];
+  unsigned yoff[RX];
 #pragma unroll
-  for (int u = 0; u < NS; ++u) {
-    nx[u] = buf_load(rx, voff[u], 0);
-    if (upd) np[u] = buf_load(rp, voff[u], 0);
-  }
-  double am[RX], a0[RX], ap[RX], vc[RX], vp[RX];
+  for (int s = 0; s < RX; ++s)
+    yoff[s] = rowin && x0 + xl + 32 * s < N0 ? (unsigned)(x0 + xl + 32 * s + N0 * gy) * 8u : kOut;
+  double nx[NS], np[MODE == 1 ? NS : 1], c[27];
+  auto load_plane = [&](int k) {
+#pragma unroll
+    for (int u = 0; u < NS; ++u) {
+      nx[u] = buf_load(rx, voff[u], pl8 * (unsigned)k);
+      if constexpr (MODE == 1) np[u] = buf_load(rp, voff[u], pl8 * (unsigned)k);
+    }
+  };
+  // coefficients of the taps plane k gives to planes k - 1, k, k + 1 (plane
+  // indices clamped: the sums of planes -1 and N2 are never used)
+  auto load_coef = [&](int k) {
+    const unsigned om = pp8 * (unsigned)max(k - 1, 0), o0 = pp8 * (unsigned)k,
+                   op = pp8 * (unsigned)min(k + 1, N2 - 1);
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+      c[t] = buf_load(rt, coff, (18 + t) * tsz8 + om);
+      c[9 + t] = buf_load(rt, coff, (9 + t) * tsz8 + o0);
+      c[18 + t] = buf_load(rt, coff, t * tsz8 + op);
+    }
+  };
+  double am[RX], a0[RX], ap[RX];
 #pragma unroll
   for (int s = 0; s < RX; ++s) {
     am[s] = 0.0;
     a0[s] = 0.0;
     ap[s] = 0.0;
-    vp[s] = 0.0;
   }
   double acc = 0.0, accs = 0.0;
+  // plane k complete: stored, and added to the partials (dead kOut: no plane)
+  auto store = [&](const double* Q, int k, unsigned dead) {
+#pragma unroll
+    for (int s = 0; s < RX; ++s) {
+      const unsigned vo = yoff[s] | dead;
+      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, am[s]), ry, vo,
+                                            pl8 * (unsigned)k, MODE == 0 ? 2 : 0);
+    }
+    if constexpr (DOT) {
+#pragma unroll
+      for (int s = 0; s < RX; ++s) {
+        const double a = (yoff[s] | dead) < kOut ? am[s] : 0.0;
+        const double v = Q[xl + 32 * s + 1 + HX * (ty + 1)];
+        acc += (dead ? 0.0 : v) * a;
+        accs += a;
+      }
+    }
+  };
+  load_plane(0);
+  __builtin_amdgcn_sched_barrier(0);
+  load_coef(0);
+  __builtin_amdgcn_sched_barrier(0);
+  int buf = 0;
+#pragma unroll 1
   for (int k = 0; k < N2; ++k) {
-    double* P = pl[k & 1];
+    double* P = pl[buf];
+    const double* Q = pl[buf == 0 ? 2 : buf - 1];
+    buf = buf == 2 ? 0 : buf + 1;
 #pragma unroll
     for (int u = 0; u < NS; ++u) {
       const int e = threadIdx.x + kBlock * u;
-      if (e >= NH) continue;
       double v = nx[u];
-      if (upd) v += beta * np[u];
-      v = (inm >> u) & 1 ? v : 0.0;
+      if constexpr (MODE == 1) v = upd ? v + beta * np[u] : v;
       P[e] = v;
-      if constexpr (MODE == 1) {
-        if ((own >> u) & 1) pnew[voff[u] / 8 + N01 * k] = v;
-      }
+      if constexpr (MODE == 1)
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rn,
+                                              (own >> u) & 1 ? voff[u] : kOut, pl8 * (unsigned)k, 0);
     }
-    if (k + 1 < N2) {
-#pragma unroll
-      for (int u = 0; u < NS; ++u) {
-        nx[u] = buf_load(rx, voff[u], pl8 * (k + 1));
-        if (upd) np[u] = buf_load(rp, voff[u], pl8 * (k + 1));
-      }
-    }
-    // coefficients of the taps plane k gives to planes k - 1, k, k + 1 (plane
-    // indices clamped: the sums of planes -1 and N2 are never used)
-    double c[27];
-    {
-      const unsigned om = pp8 * (unsigned)max(k - 1, 0), o0 = pp8 * (unsigned)k,
-                     op = pp8 * (unsigned)min(k + 1, N2 - 1);
-#pragma unroll
-      for (int t = 0; t < 9; ++t) {
-        c[t] = buf_load(rt, coff, (18 + t) * tsz8 + om);
-        c[9 + t] = buf_load(rt, coff, (9 + t) * tsz8 + o0);
-        c[18 + t] = buf_load(rt, coff, t * tsz8 + op);
-      }
-    }
+    __builtin_amdgcn_sched_barrier(0);
+    load_plane(min(k + 1, N2 - 1));
+    __builtin_amdgcn_sched_barrier(0);
     __syncthreads();
-    // MODE 0 takes the columns in two halves with a barrier between them
-    // (outside the divergent row test): left to itself the compiler issues
-    // all 72 LDS reads of a plane before the first FMA and the kernel needs
-    // ~270 VGPRs (one wave per SIMD); by halves it needs ~200 and two waves
-    // fit (62,979,135 unknowns: 411 -> 350 us).  MODE 1 holds the previous
-    // direction's plane as well and stays near 270 VGPRs either way; the
-    // barrier only costs it time, so it keeps one group.
-    constexpr int NG = MODE == 0 ? 2 : 1;
 #pragma unroll
-    for (int h = 0; h < NG; ++h) {
-      if (h > 0) __syncthreads();
-      if (rowin) {
+    for (int h = 0; h < RX / 2; ++h) {
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int s = h * (RX / NG); s < (h + 1) * (RX / NG); ++s) {
-          const int cx = xl + 32 * s + 1;
+      for (int s = 2 * h; s < 2 * h + 2; ++s) {
+        const int cx = xl + 32 * s + 1;
 #pragma unroll
-          for (int t = 0; t < 9; ++t) {
-            const double v = P[(cx + t % 3 - 1) + HX * (ty + t / 3)];
-            if (t == 4) vc[s] = v;
-            am[s] += c[t] * v;
-            a0[s] += c[9 + t] * v;
-            ap[s] += c[18 + t] * v;
-          }
+        for (int t = 0; t < 9; ++t) {
+          const double v = P[(cx + t % 3 - 1) + HX * (ty + t / 3)];
+          am[s] += c[t] * v;
+          a0[s] += c[9 + t] * v;
+          ap[s] += c[18 + t] * v;
         }
       }
     }
-    if (rowin) {
-      if (k > 0) {
-#pragma unroll
-        for (int s = 0; s < RX; ++s) {
-          const int gx = x0 + xl + 32 * s;
-          if (gx >= N0) continue;
-          double* yp = &y[gx + (long)N0 * gy + N01 * (k - 1)];
-          if constexpr (MODE == 0) __builtin_nontemporal_store(am[s], yp);
-          else *yp = am[s];
-          acc += vp[s] * am[s];
-          accs += am[s];
-        }
-      }
-#pragma unroll
-      for (int s = 0; s < RX; ++s) {
-        am[s] = a0[s];
-        a0[s] = ap[s];
-        ap[s] = 0.0;
-        vp[s] = vc[s];
-      }
-    }
-  }
-  if (rowin) {
+    __builtin_amdgcn_sched_barrier(0);
+    load_coef(min(k + 1, N2 - 1));
+    __builtin_amdgcn_sched_barrier(0);
+    store(Q, max(k - 1, 0), k > 0 ? 0u : kOut);
 #pragma unroll
     for (int s = 0; s < RX; ++s) {
-      const int gx = x0 + xl + 32 * s;
-      if (gx >= N0) continue;
-      double* yp = &y[gx + (long)N0 * gy + N01 * (N2 - 1)];
-      if constexpr (MODE == 0) __builtin_nontemporal_store(am[s], yp);
-      else *yp = am[s];
-      acc += vp[s] * am[s];
-      accs += am[s];
+      am[s] = a0[s];
+      a0[s] = ap[s];
+      ap[s] = 0.0;
     }
   }
+  store(pl[(N2 - 1) % 3], N2 - 1, 0u);
   if (use_dot) write_partial(acc, dot.part);
   if (use_sum) write_partial(accs, sum.part);
 }
@@ -1078,7 +1088,8 @@ void launch_stencil(const ddeig_problem* P, const double* tab, const double* x, 
                        nullptr, y, nodir, dot ? 1 : 0, td.use, sum ? 1 : 0, ts.use);
   }
   else if (stencil3d_march(P)) {
-    hipLaunchKernelGGL(k_stencil3d_march<0>, dim3(blocks), dim3(kBlock), 0, s, P->g, tab, x,
+    auto kern = dot || sum ? k_stencil3d_march<0, true> : k_stencil3d_march<0, false>;
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(kBlock), 0, s, P->g, tab, x,
                        nullptr, nullptr, y, nodir, dot ? 1 : 0, td.use, sum ? 1 : 0, ts.use);
   }
   else if (stencil2d_fast(P->g)) {
@@ -1113,7 +1124,7 @@ void launch_stencil_dir(const ddeig_problem* P, const double* z, const double* p
                        pold, pnew, q, dir, 1, tg.use, 0, none);
   }
   else if (stencil3d_march(P)) {
-    hipLaunchKernelGGL(k_stencil3d_march<1>, dim3(blocks), dim3(kBlock), 0, s, P->g, P->tabAs, z,
+    hipLaunchKernelGGL((k_stencil3d_march<1, true>), dim3(blocks), dim3(kBlock), 0, s, P->g, P->tabAs, z,
                        pold, pnew, q, dir, 1, tg.use, 0, none);
   }
   else if (stencil2d_fast(P->g)) {
