@@ -1213,13 +1213,21 @@ ddeig_status ddeig_assemble(const ddeig_geometry* geom, double h, const ddeig_po
       if (nsub > ddeig::kGemvMax) {
         std::vector<std::vector<ddeig::GemmTile>> groups;
         const int npair = H.ld / bk / 2;
+        // 64-row tiles (the same sums) while they fit one to a CU: they leave
+        // fewer CUs idle and each has half the rows to stage and multiply
+        // (256 subdomains of 35 x 31 unknowns in bf16x3, 54 tiles of 128 rows:
+        // 14.1 us, 10.4 us as 108 of 64).  More than one to a CU would read the inverse twice
+        // through the caches for nothing (71 x 63 unknowns in bf16, 210 tiles:
+        // 17.7 us, 21.0 us as 420).
+        P->tile_rows = (nsub + 63) / 64 * (H.ld / 128) * P->ksplit <= 256 ? 64 : 128;
         for (int sp = 0; sp < P->ksplit; ++sp) {
           const int kb0 = 2 * (int)((long)npair * sp / P->ksplit);
           const int kb1 = 2 * (int)((long)npair * (sp + 1) / P->ksplit);
           for (int nt = 0; nt < H.ld / 128; ++nt) {
             std::vector<ddeig::GemmTile> grp;
-            for (int mt = 0; mt < H.mp / 128; ++mt)
-              grp.push_back(ddeig::GemmTile{0, mt * 128, nt * 128, kb0 * bk, kb1 * bk, sp});
+            for (int mt = 0; mt * P->tile_rows < nsub; ++mt)
+              grp.push_back(
+                  ddeig::GemmTile{0, mt * P->tile_rows, nt * 128, kb0 * bk, kb1 * bk, sp});
             groups.push_back(grp);
           }
         }

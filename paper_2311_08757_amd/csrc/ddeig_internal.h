@@ -387,6 +387,7 @@ struct ddeig_problem {
   ddeig::EmbedJob* dEmbJobs = nullptr;
   int nembjobs = 0, maxT = 0;
   int ntiles = 0, ngemv = 0, ksplit = 1;
+  int tile_rows = 128;  // rows of a dense GEMM tile (128, or 64)
   // batched chain solves (3-D FP64 / FP32 local solves)
   ddeig::ChainJob* dChainJobs = nullptr;
   int nchainjobs = 0;

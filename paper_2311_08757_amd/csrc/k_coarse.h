@@ -11,12 +11,12 @@ namespace ddeig {
 // one workgroup per subdomain.  Thread t takes the box elements t + kBlock q
 // (natural order; the grid line from a multiply-high division), 8 at a time
 // with all 16 loads issued before the products; the products are added in q
-// order, then the threads in a fixed order.
+// order, then the threads in a fixed order.  sh: kBlock / 64 + 1 doubles of LDS.
 __device__ __forceinline__ void coarse_rhs_body(const Geo& g, const PcgState* __restrict__ st,
                                                 const double* __restrict__ r,
                                                 const TypeDev* __restrict__ types,
                                                 const SubDev* __restrict__ subs,
-                                                double* __restrict__ crhs, int bid) {
+                                                double* __restrict__ crhs, int bid, double* sh) {
   if (st != nullptr && st->done) return;
   const SubDev sd = subs[bid];
   const TypeDev td = types[sd.type];
@@ -41,7 +41,7 @@ __device__ __forceinline__ void coarse_rhs_body(const Geo& g, const PcgState* __
 #pragma unroll
     for (int q = 0; q < U; ++q) acc += ph[q] * rv[q];
   }
-  const double sum = block_sum(acc);
+  const double sum = block_sum_in<kBlock>(acc, sh);
   if (threadIdx.x == 0) crhs[bid] = sum;
 }
 

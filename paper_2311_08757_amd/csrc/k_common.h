@@ -12,22 +12,28 @@ __device__ inline __bf16 to_bf16(double x) { return (__bf16)x; }
 
 // Sum over a workgroup of NT threads; every thread receives the total.  The
 // order of additions is fixed (shuffle tree inside each wave64, then the
-// waves in order), so repeated runs give identical bits.
+// waves in order), so repeated runs give identical bits.  sh: NT / 64 + 1
+// doubles of LDS.
 template <int NT>
-__device__ inline double block_sum_n(double v) {
-  __shared__ double sh_red[NT / 64 + 1];
+__device__ inline double block_sum_in(double v, double* sh) {
   for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   __syncthreads();
-  if (lane == 0) sh_red[w] = v;
+  if (lane == 0) sh[w] = v;
   __syncthreads();
   if (threadIdx.x == 0) {
     double t = 0.0;
-    for (int i = 0; i < NT / 64; ++i) t += sh_red[i];
-    sh_red[NT / 64] = t;
+    for (int i = 0; i < NT / 64; ++i) t += sh[i];
+    sh[NT / 64] = t;
   }
   __syncthreads();
-  return sh_red[NT / 64];
+  return sh[NT / 64];
+}
+
+template <int NT>
+__device__ inline double block_sum_n(double v) {
+  __shared__ double sh_red[NT / 64 + 1];
+  return block_sum_in<NT>(v, sh_red);
 }
 
 __device__ inline double block_sum(double v) { return block_sum_n<kBlock>(v); }

@@ -121,10 +121,13 @@ __global__ void __launch_bounds__(kBlock, FOLD ? 2 : 1)
   constexpr int NVR = C::NVR, NS = C::NS, WPS = C::WPS;
   static_assert(MI == 1 || MI == 2, "64- or 128-row tiles");
   // [buffer][operand][row * LDK + k]; operands: R parts first, then A parts
-  __shared__ __bf16 sm[2][NOP][kTM * LDK];
+  __shared__ __align__(16) __bf16 sm[2][NOP][kTM * LDK];
   if (st != nullptr && st->done) return;
   if ((int)blockIdx.x >= ntiles) {
-    coarse_rhs_body(ca.g, nullptr, ca.r, ca.types, ca.subs, ca.crhs, blockIdx.x - ntiles);
+    // (its few doubles of LDS are the staging buffer's: with LDS of their own
+    // the bf16x3 kernel would need 40 bytes more than half a CU's)
+    coarse_rhs_body(ca.g, nullptr, ca.r, ca.types, ca.subs, ca.crhs, blockIdx.x - ntiles,
+                    reinterpret_cast<double*>(&sm[0][0][0]));
     return;
   }
   const GemmTile t = tiles[blockIdx.x];
@@ -672,12 +675,11 @@ void launch_dense_gemm(const ddeig_problem* P, const PcgState* st, hipStream_t s
     if (coarse_r != nullptr)
       ca = CoarseRhsArgs{P->nsub, P->g, coarse_r, P->dTypes, P->dSubs, P->crhs};
     const dim3 grid(P->ntiles + ca.n);
-    if (P->opt.local_prec == 2)
-      hipLaunchKernelGGL((k_dense_gemm<true, true>), grid, dim3(kBlock), 0, s, P->dTiles,
-                         P->dGtypes, st, P->ntiles, ca);
-    else
-      hipLaunchKernelGGL((k_dense_gemm<false, false>), grid, dim3(kBlock), 0, s, P->dTiles,
-                         P->dGtypes, st, P->ntiles, ca);
+    const bool low = P->tile_rows == 64;
+    auto kern = P->opt.local_prec == 2
+                    ? (low ? k_dense_gemm<true, true, 1> : k_dense_gemm<true, true>)
+                    : (low ? k_dense_gemm<false, false, 1> : k_dense_gemm<false, false>);
+    hipLaunchKernelGGL(kern, grid, dim3(kBlock), 0, s, P->dTiles, P->dGtypes, st, P->ntiles, ca);
   }
 }
 

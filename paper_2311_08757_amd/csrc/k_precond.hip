@@ -510,7 +510,8 @@ __global__ void __launch_bounds__(kBlock) k_coarse_rhs(Geo g, const PcgState* __
                                                        const TypeDev* __restrict__ types,
                                                        const SubDev* __restrict__ subs,
                                                        double* __restrict__ crhs) {
-  coarse_rhs_body(g, st, r, types, subs, crhs, blockIdx.x);
+  __shared__ double sh[kBlock / 64 + 1];
+  coarse_rhs_body(g, st, r, types, subs, crhs, blockIdx.x, sh);
 }
 
 void launch_coarse_rhs(const ddeig_problem* P, const double* r, const PcgState* st,
