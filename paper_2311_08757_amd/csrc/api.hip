@@ -1012,6 +1012,7 @@ ddeig_status ddeig_assemble(const ddeig_geometry* geom, double h, const ddeig_po
   g.fN0 = ddeig::make_fastdiv((unsigned)g.N[0]);
   g.fN1 = ddeig::make_fastdiv((unsigned)g.N[1]);
   g.fne = ddeig::make_fastdiv((unsigned)ne);
+  g.fseg = ddeig::make_fastdiv((unsigned)((g.N[0] + kBlock - 1) / kBlock));
 
   ddeig_problem* P = new (std::nothrow) ddeig_problem();
   if (!P) return set_error(DDEIG_ENOMEM, "host allocation failed");

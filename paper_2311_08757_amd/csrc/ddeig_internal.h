@@ -60,6 +60,7 @@ struct Geo {
   long tsize;     // P0 P1 P2 (table nodes == cell unknowns)
   double h, ell;
   FastDiv fN0, fN1, fne;
+  FastDiv fseg;   // 256-node segments of a grid line along dim 0
 };
 
 // Subdomains covering one grid line along an expanding axis: at most two

@@ -11,6 +11,8 @@
 #include "k_common.h"
 #include "k_coarse.h"
 
+#include <type_traits>
+
 namespace ddeig {
 
 // 1-based cells covering node index gi (1-based) along one expanding axis.
@@ -21,6 +23,12 @@ __device__ inline void covering(int gi, int ne, int L, int delta, int& clo, int&
   chi = (gi + delta - 1) / ne + 1;
   if (clo < 1) clo = 1;
   if (chi > L) chi = L;
+}
+
+// The same with the multiply-high division by n_e (num + n_e < 2^31).
+__device__ inline void covering(int gi, const Geo& g, int delta, int& clo, int& chi) {
+  clo = max(1, (int)fdiv((unsigned)max(gi - delta + g.ne, 0), g.fne));
+  chi = min(g.L, (int)fdiv((unsigned)(gi + delta - 1), g.fne) + 1);
 }
 
 // Distance from node coordinate (index gi, in units of h) to the faces of
@@ -175,13 +183,6 @@ __global__ void __launch_bounds__(kBig) k_restrict(Geo g, int ntypes, PcgState* 
 // below therefore issue all of a node's loads at once (no table look-ups in
 // between); the covering cells come from covering() and the partition-of-unity
 // weights from the same per-axis tables as in the generic kernels.
-__device__ inline long dense_index(const Geo& g, int delta, const DenseArgs& da, const int* i,
-                                   int c0, int c1) {
-  const int u0 = i[0] + delta - (c0 - 1) * g.ne;
-  const int u1 = g.p == 2 ? i[1] + delta - (c1 - 1) * g.ne : i[1];
-  return u0 + (long)da.hm0 * (u1 + (long)da.hm1 * i[2]);
-}
-
 // Covering cells of a node: slot q = q0 + 2 q1 (q1 = 0 for one expanding
 // axis) is cell (clo0 + q0, clo1 + q1) when that exists.  Out-of-range slots
 // are clamped to an existing cell so that their loads stay valid and can be
@@ -192,13 +193,66 @@ struct Cover {
   int clo0, chi0, clo1, chi1;
   __device__ Cover(const Geo& g, int delta, const int* i) {
     clo1 = chi1 = 1;
-    covering(i[0] + 1, g.ne, g.L, delta, clo0, chi0);
-    if (PX == 2) covering(i[1] + 1, g.ne, g.L, delta, clo1, chi1);
+    covering(i[0] + 1, g, delta, clo0, chi0);
+    if (PX == 2) covering(i[1] + 1, g, delta, clo1, chi1);
   }
   __device__ bool val(int q) const { return clo0 + (q & 1) <= chi0 && clo1 + (q >> 1) <= chi1; }
   __device__ int c0(int q) const { return min(clo0 + (q & 1), chi0); }
   __device__ int c1(int q) const { return min(clo1 + (q >> 1), chi1); }
 };
+
+// One item of the node-parallel dense kernels: 256 consecutive nodes of one grid
+// line, a thread each.  The item is the same for the four waves that share it,
+// so its part of every address is scalar and a lane adds a 32-bit byte offset.
+// The kernels move 52 MB (restriction with the CG update) and 30 MB (extension)
+// at 1,032,129 unknowns, 10.5 and 6 us at the card's copy rate; with divisions
+// and 64-bit addresses per thread, eight waves a SIMD spent as long on issuing
+// instructions as on memory, and the extension spilled at its 64 registers:
+// 12.4 -> 11.9 us and 11.0 -> 9.3 us (32 instances of 16..256 subdomains,
+// n_e = 32: 45.0 -> 43.4 and 33.6 -> 29.3 us).
+struct LineItem {
+  bool live;     // false: past the last item (the last one stands in for its loads)
+  int s0, i1, i2;
+  long line;
+  __device__ LineItem(const Geo& g, unsigned it, unsigned items) {
+    live = it < items;
+    it = min(it, items - 1);
+    line = fdiv(it, g.fseg);
+    s0 = (int)(it - (unsigned)line * g.fseg.d) * kBlock;
+    i2 = g.D == 3 ? (int)fdiv((unsigned)line, g.fN1) : 0;
+    i1 = (int)line - i2 * g.N[1];
+  }
+};
+
+// Batch positions of a lane's node: position(q) = base(q1) + lane(q0) for the
+// covering cells q = q0 + 2 q1.  Along an axis the position moves by ld - n_e
+// (axis 0) from a cell to the next; the first lane's first cell gives the base.
+template <int PX>
+struct DensePos {
+  long base[PX];
+  unsigned lane[2];
+  int cw;
+  __device__ DensePos(const Geo& g, int delta, const DenseArgs& da, const LineItem& t, int tl,
+                      const Cover<PX>& cv) {
+    cw = __builtin_amdgcn_readfirstlane(cv.clo0);
+    const int step = da.ld - g.ne;
+#pragma unroll
+    for (int q1 = 0; q1 < PX; ++q1) {
+      const int c1 = cv.c1(2 * q1);
+      const int u1 = PX == 2 ? t.i1 + delta - (c1 - 1) * g.ne : t.i1;
+      base[q1] = (long)(cw - 1) * step + t.s0 + delta + (PX == 2 ? (long)g.L * (c1 - 1) * da.ld : 0L) +
+                 (long)da.hm0 * (u1 + (long)da.hm1 * t.i2);
+    }
+#pragma unroll
+    for (int q0 = 0; q0 < 2; ++q0) lane[q0] = (unsigned)((cv.c0(q0) - cw) * step + tl);
+  }
+};
+
+template <class T>
+__device__ __forceinline__ T& at_bytes(T* p, unsigned off) {
+  typedef std::conditional_t<std::is_const_v<T>, const char, char> byte_t;
+  return *reinterpret_cast<T*>(reinterpret_cast<byte_t*>(p) + off);
+}
 
 // Bodies of the node-parallel kernels take the block index `bid` and the
 // block count `nblk` of their problem (blockIdx.x / gridDim.x of a single
@@ -222,65 +276,57 @@ __device__ __forceinline__ void restrict_dense_body(const Geo& g, int delta,
     }
     alpha = st->rho[(xr.k - 1) & 1] / gamma;
   }
-  const int N0 = g.N[0], N1 = g.N[1];
-  const int segs = (N0 + kBlock - 1) / kBlock;
-  const long items = (long)segs * N1 * g.N[2];
-  const int sub = threadIdx.x / kBlock, tx = threadIdx.x % kBlock;
+  const int N0 = g.N[0];
+  const unsigned items = g.fseg.d * (unsigned)(g.N[1] * g.N[2]);
+  const int sub = __builtin_amdgcn_readfirstlane(threadIdx.x / kBlock), tx = threadIdx.x % kBlock;
   double acc = 0.0;
   // two nodes per thread and pass (items it and it + IPB), all their loads
   // issued before either is updated: the grid (node_grid_dense) fits on the
   // chip in one round
-  constexpr int IPB = kBig / kBlock;
-  for (long grp = bid; grp * 2 * IPB < items; grp += nblk) {
-    bool ok[2];
-    long kk[2];
-    int ii[2][3];
+  constexpr unsigned IPB = kBig / kBlock;
+  for (unsigned grp = bid; grp * 2 * IPB < items; grp += nblk) {
+    const LineItem t[2] = {LineItem(g, grp * 2 * IPB + sub, items),
+                           LineItem(g, grp * 2 * IPB + IPB + sub, items)};
+    int tl[2];
     double rv[2], qv[2], pv[2], xv[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      const long it = grp * 2 * IPB + u * IPB + sub;
-      const int line = (int)(it / segs);
-      const int i0 = (int)(it - (long)line * segs) * kBlock + tx;
-      ok[u] = it < items && i0 < N0;
-      const int i2 = g.D == 3 ? (int)fdiv((unsigned)line, g.fN1) : 0;
-      ii[u][0] = i0; ii[u][1] = line - i2 * N1; ii[u][2] = i2;
-      kk[u] = i0 + (long)N0 * line;
-      rv[u] = qv[u] = pv[u] = xv[u] = 0.0;
-      if (ok[u]) {
-        rv[u] = xr.on == 2 ? xr.q[kk[u]] : r[kk[u]];
-        if (xr.on == 1) {
-          qv[u] = xr.q[kk[u]];
-          pv[u] = xr.p[kk[u]];
-          xv[u] = xr.x[kk[u]];
-        }
+      const long k0 = t[u].s0 + N0 * t[u].line;
+      tl[u] = min(tx, N0 - 1 - t[u].s0);  // (lanes past the line: its last node)
+      const unsigned o = 8u * tl[u];
+      rv[u] = at_bytes((xr.on == 2 ? xr.q : r) + k0, o);
+      if (xr.on == 1) {
+        qv[u] = at_bytes(xr.q + k0, o);
+        pv[u] = at_bytes(xr.p + k0, o);
+        xv[u] = at_bytes(xr.x + k0, o);
       }
     }
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      if (!ok[u]) continue;
-      const long k = kk[u];
-      const int* i = ii[u];
+      if (!t[u].live || tl[u] < tx) continue;
+      const long k0 = t[u].s0 + N0 * t[u].line;
+      const unsigned o = 8u * tl[u];
       double rvv = rv[u];
       if (xr.on == 1) {
         rvv -= alpha * qv[u];
-        xr.x[k] = xv[u] + alpha * pv[u];
-        r[k] = rvv;
+        at_bytes(xr.x + k0, o) = xv[u] + alpha * pv[u];
+        at_bytes(r + k0, o) = rvv;
         acc += rvv * rvv;
       } else if (xr.on == 2) {
-        xr.x[k] = 0.0;
-        r[k] = rvv;
+        at_bytes(xr.x + k0, o) = 0.0;
+        at_bytes(r + k0, o) = rvv;
         acc += rvv * rvv;
       }
       const __bf16 hi = to_bf16(rvv);
       const __bf16 lo = to_bf16(rvv - (double)hi);
+      const int i[3] = {t[u].s0 + tl[u], t[u].i1, t[u].i2};
       const Cover<PX> cv(g, delta, i);
+      const DensePos<PX> pos(g, delta, da, t[u], tl[u], cv);
 #pragma unroll
       for (int q = 0; q < Cover<PX>::NC; ++q) {
         if (!cv.val(q)) continue;
-        const int c0 = cv.c0(q), c1 = cv.c1(q);
-        const long at = (long)((c0 - 1) + g.L * (c1 - 1)) * da.ld + dense_index(g, delta, da, i, c0, c1);
-        da.Rh[at] = hi;
-        if (da.Rl != nullptr) da.Rl[at] = lo;
+        at_bytes(da.Rh + pos.base[q >> 1], 2u * pos.lane[q & 1]) = hi;
+        if (da.Rl != nullptr) at_bytes(da.Rl + pos.base[q >> 1], 2u * pos.lane[q & 1]) = lo;
       }
     }
   }
@@ -327,75 +373,67 @@ __device__ __forceinline__ void extend_dense_body(const Geo& g, int delta, int c
     if (conv || last) return;
   }
   double acc = 0.0;
-  const int N0 = g.N[0], N1 = g.N[1];
-  const int segs = (N0 + kBlock - 1) / kBlock;
-  const long items = (long)segs * N1 * g.N[2];
-  const int sub = threadIdx.x / kBlock, tx = threadIdx.x % kBlock;
+  const int N0 = g.N[0];
+  const unsigned items = g.fseg.d * (unsigned)(g.N[1] * g.N[2]);
+  const int sub = __builtin_amdgcn_readfirstlane(threadIdx.x / kBlock), tx = threadIdx.x % kBlock;
   // NPT nodes per thread and pass (items it + u IPB): every load of them
   // first, then their sums
-  constexpr int IPB = kBig / kBlock;
-  for (long grp = bid; grp * NPT * IPB < items; grp += nblk) {
-    bool okn[NPT];
-    long kn[NPT];
-    int in_[NPT][3];
-    XCover xan[NPT];
-    double yan[NPT][2], rkn[NPT];
+  constexpr unsigned IPB = kBig / kBlock;
+  constexpr bool XI = INL && PX == 1;  // the inline field's two weights and y0 values
+  for (unsigned grp = bid; grp * NPT * IPB < items; grp += nblk) {
+    bool okn[NPT], two[NPT];
+    unsigned on[NPT];
+    double wan[NPT][2], yan[NPT][2], rkn[NPT], psn[NPT];
     float zsn[NPT][NC][KS];
 #pragma unroll
     for (int u = 0; u < NPT; ++u) {
-      const long it = grp * NPT * IPB + u * IPB + sub;
-      const int line = (int)(it / segs);
-      const int i0 = (int)(it - (long)line * segs) * kBlock + tx;
-      okn[u] = it < items && i0 < N0;
-      const int i2 = g.D == 3 ? (int)fdiv((unsigned)line, g.fN1) : 0;
-      in_[u][0] = i0;
-      in_[u][1] = line - i2 * N1;
-      in_[u][2] = i2;
-      kn[u] = i0 + (long)N0 * line;
-      yan[u][0] = yan[u][1] = 0.0;
-      if (!okn[u]) continue;
-      const Cover<PX> cv(g, delta, in_[u]);
-      // (the inline coarse field with one expanding axis: the covering-table
-      // entry and the two y0 values)
-      if constexpr (INL && PX == 1) {
-        if (coarse) {
-          xan[u] = xc0[i0];
-          yan[u][0] = cf[cv.c0(0) - 1];
-          yan[u][1] = cf[cv.c0(1) - 1];
+      const LineItem t(g, grp * NPT * IPB + u * IPB + sub, items);
+      const int tl = min(tx, N0 - 1 - t.s0);  // (lanes past the line: its last node)
+      okn[u] = t.live && tl == tx;
+      on[u] = 8u * tl;
+      const int i[3] = {t.s0 + tl, t.i1, t.i2};
+      const Cover<PX> cv(g, delta, i);
+      const DensePos<PX> pos(g, delta, da, t, tl, cv);
+      two[u] = cv.val(1);
+      psn[u] = 0.0;
+      if (coarse) {
+        // cell-local table node: x dims (i + 1) mod n_e
+        const int j0 = i[0] + 1 - g.ne * (int)fdiv((unsigned)(i[0] + 1), g.fne);
+        const int j1 = PX == 2 ? t.i1 + 1 - g.ne * (int)fdiv((unsigned)(t.i1 + 1), g.fne) : t.i1;
+        psn[u] = at_bytes(psi + (long)g.P[0] * (j1 + (long)g.P[1] * t.i2), 8u * j0);
+        if constexpr (XI) {
+          const double* w = &xc0[t.s0].w[0];
+          wan[u][0] = at_bytes(w, (unsigned)sizeof(XCover) * tl);
+          wan[u][1] = at_bytes(w + 1, (unsigned)sizeof(XCover) * tl);
+          yan[u][0] = at_bytes(cf + (pos.cw - 1), 8u * (cv.c0(0) - pos.cw));
+          yan[u][1] = at_bytes(cf + (pos.cw - 1), 8u * (cv.c0(1) - pos.cw));
+        } else if constexpr (!INL) {
+          yan[u][0] = at_bytes(cf + (PX == 1 ? (long)t.s0 : t.s0 + (long)N0 * t.i1), on[u]);
         }
       }
 #pragma unroll
-      for (int q = 0; q < NC; ++q) {
-        const int c0 = cv.c0(q), c1 = cv.c1(q);
-        const int sid = (c0 - 1) + g.L * (c1 - 1);
-        const long at = (long)sid * da.ld + dense_index(g, delta, da, in_[u], c0, c1);
+      for (int q = 0; q < NC; ++q)
 #pragma unroll
-        for (int sp = 0; sp < KS; ++sp) zsn[u][q][sp] = da.Z[sp * da.zsplit + at];
-      }
-      rkn[u] = r[kn[u]];
+        for (int sp = 0; sp < KS; ++sp)
+          zsn[u][q][sp] = at_bytes(da.Z + (sp * da.zsplit + pos.base[q >> 1]), 4u * pos.lane[q & 1]);
+      rkn[u] = at_bytes(r + (t.s0 + N0 * t.line), on[u]);
     }
 #pragma unroll
     for (int u = 0; u < NPT; ++u) {
     if (!okn[u]) continue;
-    const int* i = in_[u];
-    const int i0 = i[0], i2 = i[2];
-    const long k = kn[u];
+    const LineItem t(g, grp * NPT * IPB + u * IPB + sub, items);
+    const int i[3] = {t.s0 + tx, t.i1, t.i2};
+    // (one expanding axis: both cells exist, or the second stands in for none)
     const Cover<PX> cv(g, delta, i);
-    const XCover& xa = xan[u];
-    const double* ya = yan[u];
+    auto val = [&](int q) { return PX == 1 ? q == 0 || two[u] : cv.val(q); };
     float (&zs)[NC][KS] = zsn[u];
     const double rk = rkn[u];
-    double ps = 0.0, zc = 0.0;
+    double ps = psn[u], zc = 0.0;
     if (coarse) {
-      // cell-local table node: x dims (i + 1) mod n_e
-      const int j0 = (int)((unsigned)(i0 + 1) - g.ne * fdiv((unsigned)(i0 + 1), g.fne));
-      const int j1 = PX == 2 ? (int)((unsigned)(i[1] + 1) - g.ne * fdiv((unsigned)(i[1] + 1), g.fne))
-                             : i[1];
-      ps = psi[j0 + (long)g.P[0] * (j1 + (long)g.P[1] * i2)];
-      if constexpr (INL && PX == 1) {
+      if constexpr (XI) {
         // the weights of the one expanding axis (cover_weight for p = 1)
-        zc = xa.w[0] * ya[0];
-        if (cv.val(1)) zc = fma(xa.w[1], ya[1], zc);
+        zc = wan[u][0] * yan[u][0];
+        if (two[u]) zc = fma(wan[u][1], yan[u][1], zc);
       } else if constexpr (INL) {
         const XCover* xc[2] = {xc0, xc1};
 #pragma unroll
@@ -406,14 +444,14 @@ __device__ __forceinline__ void extend_dense_body(const Geo& g, int delta, int c
           zc += cover_weight(g, delta, pu, xc, c, i, which) * cf[(c[0] - 1) + g.L * (cv.c1(q) - 1)];
         }
       } else {
-        zc = cf[PX == 1 ? (long)i0 : i0 + (long)N0 * i[1]];
+        zc = yan[u][0];
       }
     }
     // ... then the sums, cells in slot order and splits in split order
     double zl = 0.0;
 #pragma unroll
     for (int q = 0; q < NC; ++q) {
-      if (!cv.val(q)) continue;
+      if (!val(q)) continue;
       float zq = 0.0f;
 #pragma unroll
       for (int sp = 0; sp < KS; ++sp) zq += zs[q][sp];
@@ -428,7 +466,7 @@ __device__ __forceinline__ void extend_dense_body(const Geo& g, int delta, int c
     }
     // one rounding for the coarse term, whatever the compiler knows of `coarse`
     const double zv = coarse ? fma(ps, zc, zl) : zl;
-    z[k] = zv;
+    at_bytes(z + (t.s0 + N0 * t.line), on[u]) = zv;
     acc += rk * zv;
     }
   }
