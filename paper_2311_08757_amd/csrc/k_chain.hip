@@ -57,6 +57,9 @@ __device__ inline long box_tnode(const Geo& g, const Box& bx, const int* u) {
 //    reciprocals, selects) are per wave, and they, not the update, set the pace
 //    (16 waves of fewer entries each took 1.2 us a pivot, one pivot per barrier
 //    0.62, four 0.49 with the Schur complement: 2.2 ms for 63 slices of 71).
+//    Chains whose row solves go from both ends (rows_both) are factored from
+//    both, a workgroup each, the middle slices in a second launch: 2.19 -> 0.99
+//    ms there.
 //  * larger slices: the Schur complement by one workgroup per row
 //    (k_schur_row), the inversion in pivot blocks of kGjNb (two launches per
 //    block: the inverse of the diagonal block times its row panel, then the
@@ -219,47 +222,64 @@ __device__ __forceinline__ bool gj_registers(double (&a)[NA][NA], int b, int ti,
   return true;
 }
 
-// The whole chain of one 2-D class (chain along y, slices along x, couplings
-// d0 = -1..1) in one workgroup; W_{i-1} stays in LDS for the next slice, and
-// the next slice's 6 b coefficients are loaded while the current one is
-// inverted.
-template <int NA>
+// The chain of a 2-D class (along y, slices along x, couplings d0 = -1..1), or
+// one half of it (FactorJobs), in one workgroup; the last inverse stays in LDS
+// for the next slice, and the next slice's 6 b coefficients are loaded while the
+// current one is inverted.  MID: the middle slices of the two-ended jobs, from
+// the inverses on either side.
+template <int NA, bool MID>
 __global__ void __launch_bounds__(kBlock) k_chain_factor2d(Geo g, const double* __restrict__ T,
                                                            FactorJobs jobs, int rows,
                                                            int* __restrict__ flag) {
   constexpr int LD = kFacG * NA;
-  constexpr int NC = (6 * LD + kBlock - 1) / kBlock;  // coefficients per thread
-  extern __shared__ double wp[];  // b x b
-  // cf: taps 0..2 (E_i), then 3..5 (D_i) of every node of the slice
+  constexpr int NT = MID ? 9 : 6;                        // taps per node
+  constexpr int NC = (NT * LD + kBlock - 1) / kBlock;    // coefficients per thread
+  extern __shared__ double wp[];  // b x b, two of them with MID
+  // cf: the taps to the last slice of every node of the slice, its own (D_i),
+  // and with MID those to the slice after
   __shared__ __align__(16) double row[2 * kFacP * LD], col[2 * kFacP * LD];
   __shared__ double cf[NC * kBlock];
-  const Box bx = jobs.bx[blockIdx.x];
-  double* __restrict__ W = jobs.W[blockIdx.x];
+  const int job = blockIdx.x, dir = jobs.dir[job];
+  const Box bx = jobs.bx[job];
+  double* __restrict__ W = jobs.W[job];
   const int b = bx.b, per = bx.per[0];
   const int ti = threadIdx.x / kFacG, tj = threadIdx.x % kFacG;
+  const RowsLayout l(b);
+  const long wslice = rows ? 2 * l.slice() : b * b;
   // neighbour u + d - 1 in the slice; one that does not exist points at the
   // node itself and has coefficient zero
   auto nbr = [&](int u, int d) {
     const int v = u + d - 1;
     return v < 0 ? (per ? b - 1 : u) : v >= b ? (per ? 0 : u) : v;
   };
+  const int mid = MID ? jobs.slice(job, kFacMid) : 0;
+  if (MID) {
+    for (int q = threadIdx.x; q < 2 * b * b; q += kBlock) {
+      const int i = q < b * b ? mid - 1 : mid + 1, rc = q < b * b ? q : q - b * b;
+      wp[q] = i >= 0 && i < bx.nch ? W[i * wslice + (rows ? l.at(rc / b, rc % b) : rc)] : 0.0;
+    }
+  }
   const double* Tc[NC];
   bool cload[NC];
   double cnext[NC];
+  int i = MID ? mid : jobs.slice(job, 0);
+  if (i < 0) return;
 #pragma unroll
   for (int q = 0; q < NC; ++q) {
     const int idx = threadIdx.x + q * kBlock, ct = idx / LD, cu = idx % LD, v = cu + ct % 3 - 1;
-    cload[q] = ct < 6 && cu < b && (per || (v >= 0 && v < b));
-    Tc[q] = T + (cload[q] ? ct * g.tsize + (bx.o[0] + cu + 1 + g.ne) % g.ne : 0);
-    cnext[q] = cload[q] ? Tc[q][(long)g.P[0] * bx.o[1]] : 0.0;
+    const int tap = !MID && dir && ct < 3 ? ct + 6 : ct;
+    cload[q] = ct < NT && cu < b && (per || (v >= 0 && v < b));
+    Tc[q] = T + (cload[q] ? tap * g.tsize + (bx.o[0] + cu + 1 + g.ne) % g.ne : 0);
+    cnext[q] = cload[q] ? Tc[q][(long)g.P[0] * (bx.o[1] + i)] : 0.0;
   }
-  for (int i = 0; i < bx.nch; ++i) {
+  for (int step = 0; i >= 0; ++step) {
 #pragma unroll
     for (int q = 0; q < NC; ++q) cf[threadIdx.x + q * kBlock] = cnext[q];
     __syncthreads();
+    const int inext = MID ? -1 : jobs.slice(job, step + 1);
 #pragma unroll
     for (int q = 0; q < NC; ++q)
-      if (cload[q] && i + 1 < bx.nch) cnext[q] = Tc[q][(long)g.P[0] * (bx.o[1] + i + 1)];
+      if (cload[q] && inext >= 0) cnext[q] = Tc[q][(long)g.P[0] * (bx.o[1] + inext)];
     // (opaque copies: the entries' addresses hoisted out of the slice loop would spill)
     int vi = ti, vj = tj;
     asm volatile("" : "+v"(vi), "+v"(vj));
@@ -269,23 +289,26 @@ __global__ void __launch_bounds__(kBlock) k_chain_factor2d(Geo g, const double* 
 #pragma unroll
       for (int y = 0; y < NA; ++y) {
         const int r = vi + kFacG * x, c = vj + kFacG * y;
+        // (E W E^T)_rc of a neighbouring slice's inverse
+        auto schur = [&](const double* wn, const double* e) {
+          double corr = 0.0;
+#pragma unroll
+          for (int d1 = 0; d1 < 3; ++d1) {
+            const double* wr = wn + nbr(r, d1) * b;
+            double inner = 0.0;
+#pragma unroll
+            for (int d2 = 0; d2 < 3; ++d2) inner += e[d2 * LD + c] * wr[nbr(c, d2)];
+            corr += e[d1 * LD + r] * inner;
+          }
+          return corr;
+        };
         double v = 0.0;
         if (r < b && c < b) {
 #pragma unroll
           for (int d = 0; d < 3; ++d)
             if (nbr(r, d) == c) v += cf[(3 + d) * LD + r];
-          if (i > 0) {
-            double corr = 0.0;
-#pragma unroll
-            for (int d1 = 0; d1 < 3; ++d1) {
-              const double* wr = wp + nbr(r, d1) * b;
-              double inner = 0.0;
-#pragma unroll
-              for (int d2 = 0; d2 < 3; ++d2) inner += cf[d2 * LD + c] * wr[nbr(c, d2)];
-              corr += cf[d1 * LD + r] * inner;
-            }
-            v -= corr;
-          }
+          if (MID) v -= schur(wp, cf) + schur(wp + b * b, cf + 6 * LD);
+          else if (step > 0) v -= schur(wp, cf);
         }
         a[x][y] = v;
       }
@@ -294,8 +317,7 @@ __global__ void __launch_bounds__(kBlock) k_chain_factor2d(Geo g, const double* 
       return;
     }
     // (every read of the previous slice's wp and cf lies before the elimination's barriers)
-    const RowsLayout l(b);
-    double* Wi = W + (long)i * (rows ? 2 * l.slice() : b * b);
+    double* Wi = W + i * wslice;
 #pragma unroll
     for (int x = 0; x < NA; ++x)
 #pragma unroll
@@ -303,9 +325,10 @@ __global__ void __launch_bounds__(kBlock) k_chain_factor2d(Geo g, const double* 
         const int r = ti + kFacG * x, c = tj + kFacG * y;
         if (r < b && c < b) {
           Wi[rows ? l.at(r, c) : r * b + c] = a[x][y];  // (symmetric)
-          wp[r * b + c] = a[x][y];
+          if (!MID) wp[r * b + c] = a[x][y];
         }
       }
+    i = inext;
   }
 }
 
@@ -566,8 +589,21 @@ void launch_gj_invert(ddeig_problem* P, double* A, int b, hipStream_t s) {
 // Row solves (chain_rows) of slices of b, nch of them: the LDS copy of the
 // right-hand side has to fit, and one wave holds a slice.
 constexpr size_t kRowsLds = 128 * 1024;
-static size_t rows_lds(int b, int nch) { return ((size_t)b * nch + 2 * 64 + 2) * sizeof(double); }
-static bool rows_ok(int b, int nch) { return b <= kRowsMaxB && rows_lds(b, nch) <= kRowsLds; }
+static size_t rows_lds(int b, int nch) {
+  return ((size_t)b * (nch | 1) + 2 * 64 + 2) * sizeof(double);
+}
+static bool rows_ok(int b, int nch) {
+  return b <= kRowsMaxB && ((size_t)b * nch + 2 * 64 + 2) * sizeof(double) <= kRowsLds;
+}
+
+// Whether the row solves and their factor eliminate from both ends: half the
+// dependent steps, twice the waves, of which a CU holds those of 80 rows.
+// FP32 factors are eliminated from one end: the rounded factors of the two
+// differ in their last bit, and so would the results.
+constexpr int kRowsBothB = 80;  // (k_chain_factor2d<5, true> at most)
+static bool rows_both(const ddeig_problem* P, int b, int nch) {
+  return P->g.D == 2 && rows_ok(b, nch) && b <= kRowsBothB && P->opt.local_prec != 1;
+}
 
 // Entries of a 2-D or 3-D box's factor, in either layout; bmax, nchmax: over the
 // problem's classes (one kernel serves them all).
@@ -587,8 +623,9 @@ void chain_factor(ddeig_problem* P, const std::vector<Box>& boxes, const std::ve
   }
   const bool small = P->g.D == 2 && bmax <= kFacMaxB;
   const int rows = P->g.D == 2 && rows_ok(bmax, nch);
+  if (rows_both(P, bmax, nch)) both_ends = true;
   const int nd = both_ends ? 2 : 1;
-  const size_t at_once = small ? (size_t)kFacJobs : std::max<size_t>(1, std::min(kFacJobs, P->gj_jobs) / nd);
+  const size_t at_once = small ? (size_t)(kFacJobs / nd) : std::max<size_t>(1, std::min(kFacJobs, P->gj_jobs) / nd);
   for (size_t j0 = 0; j0 < boxes.size(); j0 += at_once) {
     const int nb = (int)std::min(at_once, boxes.size() - j0), nj = nb * nd;
     FactorJobs jobs{};
@@ -599,15 +636,20 @@ void chain_factor(ddeig_problem* P, const std::vector<Box>& boxes, const std::ve
       jobs.dir[j] = j / nb;
     }
     if (small) {
-      auto kern = bmax <= 32 ? k_chain_factor2d<2>
-                             : bmax <= 48 ? k_chain_factor2d<3>
-                             : bmax <= 64 ? k_chain_factor2d<4>
-                             : bmax <= 80 ? k_chain_factor2d<5> : k_chain_factor2d<8>;
-      const size_t lds = (size_t)bmax * bmax * sizeof(double);
-      check_hip(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds),
-                "factorisation LDS");
-      hipLaunchKernelGGL(kern, dim3(nj), dim3(kBlock), lds, s, P->g, tab, jobs, rows, P->flag);
+#define FACTOR_PICK(MID)                                                            \
+  (bmax <= 32   ? k_chain_factor2d<2, MID>                                          \
+   : bmax <= 48 ? k_chain_factor2d<3, MID>                                          \
+   : bmax <= 64 ? k_chain_factor2d<4, MID> : k_chain_factor2d<5, MID>)
+      for (int m = 0; m < nd; ++m) {  // the chains, then the slices between two halves
+        auto kern = m ? FACTOR_PICK(true) : bmax <= 80 ? FACTOR_PICK(false) : k_chain_factor2d<8, false>;
+        const size_t lds = (size_t)(m + 1) * bmax * bmax * sizeof(double);
+        check_hip(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds),
+                  "factorisation LDS");
+        hipLaunchKernelGGL(kern, dim3(m ? nb : nj), dim3(kBlock), lds, s, P->g, tab, jobs, rows,
+                           P->flag);
+      }
+#undef FACTOR_PICK
       continue;
     }
     auto step = [&](int i, int n) {
@@ -1118,7 +1160,7 @@ namespace ddeig {
 // ---- chain solves of 2-D boxes: slices along x of at most kRowsMaxB unknowns,
 // chain along y, one workgroup per right-hand side.
 //
-// A sweep is 2 nch - 1 dependent steps t = W_i g, g = b_i - E_i t_{i-1} (or
+// A sweep from one end is 2 nch - 1 dependent steps t = W_i g, g = b_i - E_i t_{i-1} (or
 // E_{i+1}^T x_{i+1}), so a step's latency is the time of the solve.  It is a
 // chain of instructions (a wave issues one every 4 to 5 cycles) and LDS round
 // trips, so it is split to keep what the chain waits for short:
@@ -1132,8 +1174,10 @@ namespace ddeig {
 // store, and no load whose latency a step waits for.  At b = 71: W_i staged
 // through LDS with three barriers a step 2.2 us; partial sums passed through LDS
 // 0.96; every wave forming g for itself (one barrier) 0.60, at b = 35 0.46; this
-// 0.60 and 0.36 (there the loads of W, 45 KB a step through a 64-byte port, are
-// the larger part; 256 subdomains of 63 lines: 285 -> 84 us).
+// 0.60 and 0.36.  From both ends (BOTH) a step takes two slices: 1.09 us and
+// 0.26 us, half as many; at b = 71 the 90 KB of W it reads, 21 TB/s over the 256
+// workgroups, are what it waits for (256 subdomains of 63 lines: 285 -> 84 -> 76
+// us; 32 of 31 lines of 35: 20.9 -> 16.6 us).
 // In 2-D the couplings are the taps (-1..1, -1), i.e. table taps 0..2
 // (forward), and (-1..1, +1), taps 6..8 (backward).
 template <typename WT>
@@ -1168,36 +1212,44 @@ __device__ __forceinline__ double part_sum2(double a, double b) {
 }
 
 // o0, o1: origin of the box; per: periodic in x.  col >= 0: the right-hand side
-// is column col of the identity (v is not read, and the sweep starts in its
-// slice i0).  tbuf: rows_lds(b, nch) bytes of LDS.
-template <typename WT, int KM>
+// is column col of the identity (v is not read, and the sweep starts at its
+// slice's step).  tbuf: rows_lds(b, nch) bytes of LDS.
+// Step st = 0 .. 2 h works on slice min(st, 2 h - st); BOTH: h = nch / 2 and the
+// mirrored slice 2 h minus that one is worked on at the same time by waves of
+// its own (an even nch has no slice 2 h; its W reads as zero).  Otherwise h = nch - 1.
+template <typename WT, int KM, bool BOTH>
 __device__ __forceinline__ void chain_rows(const Geo& g, const double* __restrict__ T,
                                            const WT* __restrict__ W, double* __restrict__ v, int b,
                                            int nch, int o0, int o1, bool per, int col,
                                            double* __restrict__ tbuf) {
   typedef typename Pair<WT>::type wpair;
   constexpr int GS = KM | 1;  // stride of a part's columns of g (odd: distinct banks)
-  __shared__ double gsh[8 * GS + 1];  // g, and a slot for rows that do not exist
+  constexpr int NS = BOTH ? 2 : 1;
+  __shared__ double gsh[NS][8 * GS + 1];  // g, and a slot for rows that do not exist
   const int tid = threadIdx.x, lane = tid & 63, nth = blockDim.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const RowsLayout l(b);
+  const int h = BOTH ? nch / 2 : nch - 1;
   const int i0 = col < 0 ? 0 : col / b;
-  const int nf = nch - i0, nst = nf + nch - 1;  // forward steps, all steps
-  // the slice after slice i of step st (past the last step: any slice)
-  auto next = [&](int i, int st) {
-    return __builtin_amdgcn_readfirstlane(max(i + (st + 1 < nf ? 1 : -1), 0));
+  const int st0 = min(i0, 2 * h - i0), end = 2 * h + 1;  // the steps are [st0, end)
+  // waves 0 .. NS - 1 form g, the rest multiply, those of the mirrored side last
+  const int side = !BOTH ? 0 : wave < NS ? wave : (wave - NS >= l.nw ? 1 : 0);
+  // the slice of step st (past the last step: any slice)
+  auto slice = [&](int st) {
+    const int u = max(min(st, 2 * h - st), 0);
+    return __builtin_amdgcn_readfirstlane(side ? 2 * h - u : u);
   };
   // one row in front of the slices and 64 rows behind them are read, not used
   double* tb = tbuf + 1;
-  const int dump = nch * b;
+  const int dump = (BOTH ? nch | 1 : nch) * b;
   for (int q = tid; q < nch * b; q += nth) tb[q] = col < 0 ? v[q] : (q == col ? 1.0 : 0.0);
-  for (int q = tid; q < 2 * 64; q += nth) tb[dump + q] = 0.0;
+  for (int q = nch * b + tid; q < dump + 2 * 64; q += nth) tb[q] = 0.0;
   if (tid == 0) tbuf[0] = 0.0;
-  for (int q = tid; q < 8 * GS + 1; q += nth) gsh[q] = 0.0;
+  for (int q = tid; q < NS * (8 * GS + 1); q += nth) gsh[0][q] = 0.0;
   __syncthreads();
-  // (the step past the last that an odd count needs changes nothing: a break
-  // inside the loops would spoil the compiler's load counters)
-  if (wave == 0) {
+  // (the steps past the last that the unrolling by three needs change nothing: a
+  // break inside the loops would spoil the compiler's load counters)
+  if (wave < NS) {
     // rows r0, r0 + 1 of this lane, the columns that hold their neighbours, and
     // their places in g
     const int r0 = 2 * lane, r1 = r0 + 1;
@@ -1205,8 +1257,8 @@ __device__ __forceinline__ void chain_rows(const Geo& g, const double* __restric
     const int nm = per && r0 == b - 1 ? 0 : r1;      // right of r0, and r1 itself
     const int nr = per && r1 == b - 1 ? 0 : r0 + 2;  // right of r1
     auto place = [&](int r) { return r < b ? r / l.chunk * GS + r % l.chunk : 8 * GS; };
-    double* g0p = gsh + place(r0);
-    double* g1p = gsh + place(r1);
+    double* g0p = gsh[side] + place(r0);
+    double* g1p = gsh[side] + place(r1);
     // couplings of a step: three taps of each row (zero without a neighbour)
     const auto rt = __builtin_amdgcn_make_buffer_rsrc((void*)T, (short)0, (int)(9 * g.tsize * 8),
                                                       0x00020000);
@@ -1222,49 +1274,66 @@ __device__ __forceinline__ void chain_rows(const Geo& g, const double* __restric
     struct Coup {
       double e[6];
     };
-    auto loadc = [&](int i, int st) {
+    // couplings of slice i to the slice before it, or after it
+    auto loadc = [&](int i, bool after) {
       Coup c;
 #pragma unroll
       for (int t = 0; t < 6; ++t)
         c.e[t] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(
-                                                rt, coff[t], (o1 + i) * cline + (st < nf ? 0 : cback), 0));
+                                                rt, coff[t], (o1 + i) * cline + (after ? cback : 0), 0));
       return c;
     };
-    int sp = i0, s1 = next(i0, 0), s2 = next(s1, 1), s3 = next(s2, 2);
-    Coup ca{}, cb = loadc(s1, 1), cc = loadc(s2, 2);  // (step 0 has no couplings)
-    double v0 = tb[i0 * b + r0], v1 = tb[i0 * b + r1];
-    int s0 = i0;
-    // step st: couplings in c, replaced by those of step st + 3
-    auto step = [&](int st, Coup& c) {
-      const double* tp = tb + sp * b;
+    // (a side meets the slice it has solved last)
+    auto after = [&](int st) { return (st > h) != (side != 0); };
+    int sp = slice(st0), s0 = sp, s1 = slice(st0 + 1), s2 = slice(st0 + 2), s3 = slice(st0 + 3);
+    // (the first step has no couplings)
+    Coup ca{}, cb = loadc(s1, after(st0 + 1)), cc = loadc(s2, after(st0 + 2));
+    const Coup cm = BOTH ? loadc(h, true) : Coup{};
+    double v0 = tb[s0 * b + r0], v1 = tb[s0 * b + r1];
+    // h of the lane's rows from the slice at tp
+    auto couple = [&](const double* tp, const Coup& c, double& h0, double& h1) {
       const double tl = tp[nl], t0 = tp[r0], t1 = tp[nm], tr = tp[nr];
-      const double sg = st < nf ? -1.0 : 1.0;  // g = b_i - E t, or E^T x
-      double h0 = c.e[0] * tl, h1 = c.e[3] * t0;
+      h0 = c.e[0] * tl;
+      h1 = c.e[3] * t0;
       h0 += c.e[1] * t0;
       h1 += c.e[4] * t1;
       h0 += c.e[2] * t1;
       h1 += c.e[5] * tr;
+    };
+    // step st: couplings in c, replaced by those of step st + 3
+    auto step = [&](int st, Coup& c) {
+      const double sg = st <= h ? -1.0 : 1.0;  // g = b_i - E t, or E^T x
+      double h0, h1;
+      couple(tb + sp * b, c, h0, h1);
+      if (BOTH && st == h) {  // the middle slice takes both neighbours
+        double m0, m1;
+        couple(tb + min(h + 1, nch) * b, cm, m0, m1);
+        if (h + 1 < nch) {
+          h0 += m0;
+          h1 += m1;
+        }
+      }
       *g0p = v0 + sg * h0;
       *g1p = v1 + sg * h1;
       __syncthreads();
-      c = loadc(s3, st + 3);
+      c = loadc(s3, after(st + 3));
       v0 = tb[s1 * b + r0];
       v1 = tb[s1 * b + r1];
-      if (st + 1 >= nf) v0 = v1 = 0.0;
+      if (st + 1 > h) v0 = v1 = 0.0;
       sp = s0;
       s0 = s1;
       s1 = s2;
       s2 = s3;
-      s3 = next(s3, st + 3);
+      s3 = slice(st + 4);
       __syncthreads();
     };
-    for (int st = 0; st < nst; st += 3) {
+    for (int st = st0; st < end; st += 3) {
       step(st, ca);
       step(st + 1, cb);
       step(st + 2, cc);
     }
   } else {
-    const int w0 = wave - 1, q = lane & 7;
+    const int w0 = wave - NS - (side ? l.nw : 0), q = lane & 7;
     // this lane's pairs of W.  Loads past a part's columns read the next wave's
     // or slice's entries, or zero past the end: those terms meet a zero of g;
     // lanes without rows read nothing.
@@ -1277,29 +1346,31 @@ __device__ __forceinline__ void chain_rows(const Geo& g, const double* __restric
 #pragma unroll
       for (int k = 0; k < KM; ++k) {
         constexpr int reach = 4096 / (64 * WB);  // loads an immediate offset reaches
-        const int imm = k % reach * 64 * WB, off = base + k / reach * 4096;
+        // (a scalar offset past the buffer's end would wrap in its bounds check)
+        const int imm = k % reach * 64 * WB, off = min(base + k / reach * 4096, nch * sbytes);
         if constexpr (sizeof(WT) == 8)
           w[k] = __builtin_bit_cast(wpair, __builtin_amdgcn_raw_buffer_load_b128(rw, wlane + imm, off, 0));
         else
           w[k] = __builtin_bit_cast(wpair, __builtin_amdgcn_raw_buffer_load_b64(rw, wlane + imm, off, 0));
       }
     };
-    const double* gl = gsh + (lane >> 3) * GS;
+    const double* gl = gsh[side] + (lane >> 3) * GS;
     // the row that part_sum2 leaves in this lane
     const int own = 16 * w0 + 2 * q + (lane >> 5);
     const bool owner = (lane & 24) == 0 && own < b;
-    int s0 = i0, s1 = next(i0, 0), s2 = next(s1, 1);
+    int s0 = slice(st0), s1 = slice(st0 + 1), s2 = slice(st0 + 2);
     wpair wa[KM], wb[KM], wc[KM];
     loadw(wa, s0);
     loadw(wb, s1);
-    // step st: W in w; loads W of step st + 2 into wn
+    // step st: W in w; loads W of step st + 2 into wn.  (In the middle step the
+    // mirrored side has no slice of its own.)
     auto step = [&](int st, const wpair (&w)[KM], wpair (&wn)[KM]) {
       loadw(wn, s2);
       const double told = tb[s0 * b + own];
-      double* out = tb + (owner && st < nst ? s0 * b + own : dump);
+      double* out = tb + (owner && st < end && !(side && st == h) ? s0 * b + own : dump);
       s0 = s1;
       s1 = s2;
-      s2 = next(s2, st + 2);
+      s2 = slice(st + 3);
       __syncthreads();
       double a0 = 0.0, a1 = 0.0;
 #pragma unroll
@@ -1308,10 +1379,10 @@ __device__ __forceinline__ void chain_rows(const Geo& g, const double* __restric
         a1 += (double)w[k].y * gl[k];
       }
       const double t = part_sum2(a0, a1);
-      *out = st < nf ? t : told - t;
+      *out = st <= h ? t : told - t;
       __syncthreads();
     };
-    for (int st = 0; st < nst; st += 3) {
+    for (int st = st0; st < end; st += 3) {
       step(st, wa, wc);
       step(st + 1, wb, wa);
       step(st + 2, wc, wb);
@@ -1322,7 +1393,7 @@ __device__ __forceinline__ void chain_rows(const Geo& g, const double* __restric
 
 // The level-1 preconditioner's local solves: workgroup = subdomain, with its
 // class's factor.
-template <typename WT, int NT, int KM>
+template <typename WT, int NT, int KM, bool BOTH>
 __global__ void __launch_bounds__(NT) k_rows_local(Geo g, const double* __restrict__ T,
                                                    const TypeDev* __restrict__ types,
                                                    const SubDev* __restrict__ subs,
@@ -1334,39 +1405,45 @@ __global__ void __launch_bounds__(NT) k_rows_local(Geo g, const double* __restri
   const WT* W;
   if constexpr (sizeof(WT) == 4) W = reinterpret_cast<const WT*>(td.W32);
   else W = reinterpret_cast<const WT*>(td.W);
-  chain_rows<WT, KM>(g, T, W, td.batch + (long)sd.slot * td.nch * td.b, td.b, td.nch, sd.o[0],
-                         sd.o[1], false, -1, tb);
+  chain_rows<WT, KM, BOTH>(g, T, W, td.batch + (long)sd.slot * td.nch * td.b, td.b, td.nch,
+                           sd.o[0], sd.o[1], false, -1, tb);
 }
 
 // Right-hand sides of one box (FP64 factors): workgroup = right-hand side;
 // columns of the identity start in their own slice.
-template <int NT, int KM>
+template <int NT, int KM, bool BOTH>
 __global__ void __launch_bounds__(NT) k_rows_box(Geo g, Box bx, const double* __restrict__ T,
                                                  const double* __restrict__ W,
                                                  double* __restrict__ v, int identity) {
   extern __shared__ double tb[];
   const long m = (long)bx.nch * bx.b;
   const int col = identity ? (int)blockIdx.x : -1;
-  chain_rows<double, KM>(g, T, W, v + blockIdx.x * m, bx.b, bx.nch, bx.o[0], bx.o[1],
-                             bx.per[0] != 0, col, tb);
+  chain_rows<double, KM, BOTH>(g, T, W, v + blockIdx.x * m, bx.b, bx.nch, bx.o[0], bx.o[1],
+                               bx.per[0] != 0, col, tb);
 }
 
 // The kernel for slices of at most b: columns per part (b / 8 rounded up), and
-// threads (wave 0 and a wave per 16 rows).
+// threads (per side a wave that forms g and a wave per 16 rows).
 #define ROWS_PICK(KERN, b, ...)                                                         \
-  ((b) <= 24   ? KERN<__VA_ARGS__ 192, 3>                                               \
-   : (b) <= 40 ? KERN<__VA_ARGS__ 256, 5>                                               \
-   : (b) <= 56 ? KERN<__VA_ARGS__ 320, 7>                                               \
-   : (b) <= 64 ? KERN<__VA_ARGS__ 320, 8>                                               \
-   : (b) <= 72 ? KERN<__VA_ARGS__ 384, 9>                                               \
-   : (b) <= 80 ? KERN<__VA_ARGS__ 384, 10>                                              \
-   : (b) <= 96 ? KERN<__VA_ARGS__ 448, 12> : KERN<__VA_ARGS__ 576, 16>)
+  ((b) <= 24   ? KERN<__VA_ARGS__ 192, 3, false>                                        \
+   : (b) <= 40 ? KERN<__VA_ARGS__ 256, 5, false>                                        \
+   : (b) <= 56 ? KERN<__VA_ARGS__ 320, 7, false>                                        \
+   : (b) <= 64 ? KERN<__VA_ARGS__ 320, 8, false>                                        \
+   : (b) <= 72 ? KERN<__VA_ARGS__ 384, 9, false>                                        \
+   : (b) <= 80 ? KERN<__VA_ARGS__ 384, 10, false>                                       \
+   : (b) <= 96 ? KERN<__VA_ARGS__ 448, 12, false> : KERN<__VA_ARGS__ 576, 16, false>)
+#define ROWS_PICK_BOTH(KERN, b, ...)                                                    \
+  ((b) <= 24   ? KERN<__VA_ARGS__ 384, 3, true>                                         \
+   : (b) <= 40 ? KERN<__VA_ARGS__ 512, 5, true>                                         \
+   : (b) <= 56 ? KERN<__VA_ARGS__ 640, 7, true>                                         \
+   : (b) <= 64 ? KERN<__VA_ARGS__ 640, 8, true>                                         \
+   : (b) <= 72 ? KERN<__VA_ARGS__ 768, 9, true> : KERN<__VA_ARGS__ 768, 10, true>)
 #define ROWS_COMMA ,
 
 template <typename K>
-static void rows_launch(K kern, int b, int nch, size_t& lds, int& nt) {
+static void rows_launch(K kern, bool both, int b, int nch, size_t& lds, int& nt) {
   lds = rows_lds(b, nch);
-  nt = 64 * (RowsLayout(b).nw + 1);
+  nt = 64 * (RowsLayout(b).nw + 1) * (both ? 2 : 1);
   check_hip(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds),
             "chain solve LDS");
@@ -1375,10 +1452,11 @@ static void rows_launch(K kern, int b, int nch, size_t& lds, int& nt) {
 bool launch_rows_box(const ddeig_problem* P, const Box& bx, const double* tab, const double* W,
                      double* v, int nrhs, int identity, hipStream_t s) {
   if (P->g.D != 2 || !rows_ok(bx.b, bx.nch)) return false;
-  auto kern = ROWS_PICK(k_rows_box, bx.b);
+  const bool both = rows_both(P, bx.b, bx.nch);
+  auto kern = both ? ROWS_PICK_BOTH(k_rows_box, bx.b) : ROWS_PICK(k_rows_box, bx.b);
   size_t lds;
   int nt;
-  rows_launch(kern, bx.b, bx.nch, lds, nt);
+  rows_launch(kern, both, bx.b, bx.nch, lds, nt);
   hipLaunchKernelGGL(kern, dim3(nrhs), dim3(nt), lds, s, P->g, bx, tab, W, v, identity);
   return true;
 }
@@ -1402,8 +1480,11 @@ static void launch_rows_local(const ddeig_problem* P, const PcgState* st, hipStr
   int b, nch, nt;
   size_t lds;
   class_extents(P, b, nch);
+  const bool both = rows_both(P, b, nch);
   auto kern = ROWS_PICK(k_rows_local, b, WT ROWS_COMMA);
-  rows_launch(kern, b, nch, lds, nt);
+  if constexpr (sizeof(WT) == 8)
+    if (both) kern = ROWS_PICK_BOTH(k_rows_local, b, WT ROWS_COMMA);
+  rows_launch(kern, both, b, nch, lds, nt);
   hipLaunchKernelGGL(kern, dim3(P->nsub), dim3(nt), lds, s, P->g, P->tabAs, P->dTypes, P->dSubs, st);
 }
 
