@@ -216,7 +216,7 @@ void factor_classes(ddeig_problem* P) {
     boxes.push_back(t.box);
     Ws.push_back(t.W);
   }
-  chain_factor(P, boxes, Ws, P->tabAs, P->stream, P->chain_mfma != 0);
+  chain_factor(P, boxes, Ws, P->tabAs, P->stream, P->chain_mfma != 0 || classes_both(P));
 }
 
 void factor_types(ddeig_problem* P) {
@@ -226,7 +226,7 @@ void factor_types(ddeig_problem* P) {
     // lo) split, then for every clipped class (B~_TT)^{-1} from the rounded
     // inverse (FP64 Gauss-Jordan, symmetrised) and G = B~_ST (B~_TT)^{-1}
     ddeig::DenseHost& H = P->dh;
-    chain_factor(P, {H.box}, {H.W}, P->tabAs, P->stream);
+    chain_factor(P, {H.box}, {H.W}, P->tabAs, P->stream, rows_both(P->g.D, H.box.b, H.box.nch));
     check_launch("local factorisation");
     double* Ainv = dalloc<double>(P, (size_t)H.m * H.m);
     launch_chain_inverse(P, H.box, P->tabAs, H.W, Ainv, P->stream);
@@ -2008,7 +2008,7 @@ ddeig_status ddeig_cell_shift(ddeig_problem* P, double* sigma_out, double* psi_c
   double* v2 = dalloc<double>(P, nc);  // solve
   double* v3 = dalloc<double>(P, nc);  // M solve
   clear_flag(P);
-  chain_factor(P, {cb}, {Wc}, P->tabAs, s);
+  chain_factor(P, {cb}, {Wc}, P->tabAs, s, rows_both(g.D, cb.b, cb.nch));
   check_launch("cell factorisation");
   if (read_flag(P)) {
     dfree(P, Wc); dfree(P, v0); dfree(P, v1); dfree(P, v2); dfree(P, v3);

@@ -469,11 +469,13 @@ void launch_box_stencil(const ddeig_problem* P, const Box& bx, const double* tab
                         double* y, Red* dot, Red* sum, hipStream_t s);
 
 // chain factorisation of boxes: W[i] = S_i^{-1}; flag set on a non-positive pivot
-// (both_ends: eliminated from both ends towards slice nch / 2; wide slices only)
+// (both_ends: eliminated from both ends towards slice nch / 2)
 void chain_factor(ddeig_problem* P, const std::vector<Box>& boxes, const std::vector<double*>& Ws,
                   const double* tab, hipStream_t s, bool both_ends = false);
 long gj_buffer_doubles(int bmax, int njobs);
 size_t factor_entries(int D, const Box& bx, int bmax, int nchmax);
+bool rows_both(int D, int b, int nch);
+bool classes_both(const ddeig_problem* P);
 void launch_gj_invert(ddeig_problem* P, double* A, int b, hipStream_t s);
 // chain solve in place of one right-hand side (tmp: as many values), and the inverse
 void launch_chain_solve(const ddeig_problem* P, const Box& bx, const double* tab, const double* W,

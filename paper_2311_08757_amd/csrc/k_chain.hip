@@ -596,14 +596,11 @@ static bool rows_ok(int b, int nch) {
   return b <= kRowsMaxB && ((size_t)b * nch + 2 * 64 + 2) * sizeof(double) <= kRowsLds;
 }
 
-// Whether the row solves and their factor eliminate from both ends: half the
-// dependent steps, twice the waves, of which a CU holds those of 80 rows.
-// FP32 factors are eliminated from one end: the rounded factors of the two
-// differ in their last bit, and so would the results.
+// Whether the row solves of a box and their FP64 factor eliminate from both
+// ends: half the dependent steps, twice the waves, of which a CU holds those of
+// 80 rows.
 constexpr int kRowsBothB = 80;  // (k_chain_factor2d<5, true> at most)
-static bool rows_both(const ddeig_problem* P, int b, int nch) {
-  return P->g.D == 2 && rows_ok(b, nch) && b <= kRowsBothB && P->opt.local_prec != 1;
-}
+bool rows_both(int D, int b, int nch) { return D == 2 && rows_ok(b, nch) && b <= kRowsBothB; }
 
 // Entries of a 2-D or 3-D box's factor, in either layout; bmax, nchmax: over the
 // problem's classes (one kernel serves them all).
@@ -623,7 +620,6 @@ void chain_factor(ddeig_problem* P, const std::vector<Box>& boxes, const std::ve
   }
   const bool small = P->g.D == 2 && bmax <= kFacMaxB;
   const int rows = P->g.D == 2 && rows_ok(bmax, nch);
-  if (rows_both(P, bmax, nch)) both_ends = true;
   const int nd = both_ends ? 2 : 1;
   const size_t at_once = small ? (size_t)(kFacJobs / nd) : std::max<size_t>(1, std::min(kFacJobs, P->gj_jobs) / nd);
   for (size_t j0 = 0; j0 < boxes.size(); j0 += at_once) {
@@ -1452,7 +1448,7 @@ static void rows_launch(K kern, bool both, int b, int nch, size_t& lds, int& nt)
 bool launch_rows_box(const ddeig_problem* P, const Box& bx, const double* tab, const double* W,
                      double* v, int nrhs, int identity, hipStream_t s) {
   if (P->g.D != 2 || !rows_ok(bx.b, bx.nch)) return false;
-  const bool both = rows_both(P, bx.b, bx.nch);
+  const bool both = rows_both(P->g.D, bx.b, bx.nch);
   auto kern = both ? ROWS_PICK_BOTH(k_rows_box, bx.b) : ROWS_PICK(k_rows_box, bx.b);
   size_t lds;
   int nt;
@@ -1469,6 +1465,15 @@ static void class_extents(const ddeig_problem* P, int& b, int& nch) {
   }
 }
 
+// Row solves of the classes: their FP32 factors are eliminated from one end (the
+// rounded factors of the two orders differ in their last bit, and so would the
+// results).
+bool classes_both(const ddeig_problem* P) {
+  int b, nch;
+  class_extents(P, b, nch);
+  return P->opt.local_prec != 1 && rows_both(P->g.D, b, nch);
+}
+
 bool local_solves_fast_ok(const ddeig_problem* P) {
   int b, nch;
   class_extents(P, b, nch);
@@ -1480,7 +1485,7 @@ static void launch_rows_local(const ddeig_problem* P, const PcgState* st, hipStr
   int b, nch, nt;
   size_t lds;
   class_extents(P, b, nch);
-  const bool both = rows_both(P, b, nch);
+  const bool both = classes_both(P);
   auto kern = ROWS_PICK(k_rows_local, b, WT ROWS_COMMA);
   if constexpr (sizeof(WT) == 8)
     if (both) kern = ROWS_PICK_BOTH(k_rows_local, b, WT ROWS_COMMA);
