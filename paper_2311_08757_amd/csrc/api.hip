@@ -422,14 +422,16 @@ void precond_apply(ddeig_problem* P, double* r, double* z, Red* dot, PcgState* s
     launch_extend(P, r, z, 1, dot, st, c, s, (flags & kPrecRas) ? 1 : 0, 1);
     return;
   }
-  const bool side = coarse;
+  // (rows: R_0 r rides in the row solves, and one stream does)
+  const bool rows = coarse && rows_coarse(P), side = coarse && !rows;
   if (side) {
     check_hip(hipEventRecord(P->ev_fork, s), "record fork");
     check_hip(hipStreamWaitEvent(P->aux, P->ev_fork, 0), "wait fork");
   }
-  launch_local_solves(P, st, s);
+  launch_local_solves(P, st, s, rows ? r : nullptr);
   if (P->opt.local_prec >= 2) launch_embed_fix(P, st, s);
-  if (coarse) {
+  if (rows) launch_coarse_solve(P, st, s);
+  if (side) {
     launch_coarse_rhs(P, r, st, P->aux);
     launch_coarse_solve(P, st, P->aux);
     if (P->opt.local_prec >= 2) launch_coarse_field(P, st, P->aux);
@@ -1785,21 +1787,23 @@ ddeig_status ddeig_profile_iteration(ddeig_problem* P, const double* b, int reps
       check_hip(hipEventRecord(e[4], s), "record");
       launch_extend(P, P->r, P->z, 1, &rz, P->st, chk, s, 0, 1);
     } else {
-      if (coarse) {
+      const bool rows = coarse && rows_coarse(P), side = coarse && !rows;
+      if (side) {
         check_hip(hipEventRecord(P->ev_fork, s), "record fork");
         check_hip(hipStreamWaitEvent(P->aux, P->ev_fork, 0), "wait fork");
       }
-      launch_local_solves(P, P->st, s);
+      launch_local_solves(P, P->st, s, rows ? P->r : nullptr);
       check_hip(hipEventRecord(e[3], s), "record");
       if (P->opt.local_prec >= 2) launch_embed_fix(P, P->st, s);
-      if (coarse) {
+      if (rows) launch_coarse_solve(P, P->st, s);
+      if (side) {
         launch_coarse_rhs(P, P->r, P->st, P->aux);
         launch_coarse_solve(P, P->st, P->aux);
         if (P->opt.local_prec >= 2) launch_coarse_field(P, P->st, P->aux);
         check_hip(hipEventRecord(P->ev_join, P->aux), "record join");
       }
       check_hip(hipEventRecord(e[4], s), "record");
-      if (coarse) check_hip(hipStreamWaitEvent(s, P->ev_join, 0), "wait join");
+      if (side) check_hip(hipStreamWaitEvent(s, P->ev_join, 0), "wait join");
       launch_extend(P, P->r, P->z, coarse, &rz, P->st, chk, s, 0);
     }
     check_hip(hipEventRecord(e[5], s), "record");

@@ -506,6 +506,7 @@ void launch_restrict(const ddeig_problem* P, double* r, PcgState* st, const XrAr
 void launch_local_solves(const ddeig_problem* P, const PcgState* st, hipStream_t s,
                          const double* coarse_r = nullptr);
 bool fused_coarse(const ddeig_problem* P);
+bool rows_coarse(const ddeig_problem* P);
 int chain_group_members();
 size_t chain_part_bytes(int bmax, int mtot, int fp32);
 // FP32 batched chain solves on MFMA (k_chain_mfma.hip)

@@ -1119,7 +1119,8 @@ void launch_chain_batched(const ddeig_problem* P, const PcgState* st, hipStream_
 }
 
 bool local_solves_fast_ok(const ddeig_problem* P);
-void launch_local_solves_fast(const ddeig_problem* P, const PcgState* st, hipStream_t s);
+void launch_local_solves_fast(const ddeig_problem* P, const PcgState* st, hipStream_t s,
+                              bool coarse);
 
 void launch_local_solves(const ddeig_problem* P, const PcgState* st, hipStream_t s,
                          const double* coarse_r) {
@@ -1132,7 +1133,7 @@ void launch_local_solves(const ddeig_problem* P, const PcgState* st, hipStream_t
     return;
   }
   if (local_solves_fast_ok(P)) {
-    launch_local_solves_fast(P, st, s);
+    launch_local_solves_fast(P, st, s, coarse_r != nullptr);
     return;
   }
   if (P->nchainjobs > 0) {
@@ -1209,7 +1210,8 @@ __device__ __forceinline__ double part_sum2(double a, double b) {
 
 // o0, o1: origin of the box; per: periodic in x.  col >= 0: the right-hand side
 // is column col of the identity (v is not read, and the sweep starts at its
-// slice's step).  tbuf: rows_lds(b, nch) bytes of LDS.
+// slice's step).  tbuf: rows_lds(b, nch) bytes of LDS.  csum (nullable): receives
+// phi . v, of the right-hand side (col < 0).
 // Step st = 0 .. 2 h works on slice min(st, 2 h - st); BOTH: h = nch / 2 and the
 // mirrored slice 2 h minus that one is worked on at the same time by waves of
 // its own (an even nch has no slice 2 h; its W reads as zero).  Otherwise h = nch - 1.
@@ -1217,7 +1219,9 @@ template <typename WT, int KM, bool BOTH>
 __device__ __forceinline__ void chain_rows(const Geo& g, const double* __restrict__ T,
                                            const WT* __restrict__ W, double* __restrict__ v, int b,
                                            int nch, int o0, int o1, bool per, int col,
-                                           double* __restrict__ tbuf) {
+                                           double* __restrict__ tbuf,
+                                           const double* __restrict__ phi = nullptr,
+                                           double* __restrict__ csum = nullptr) {
   typedef typename Pair<WT>::type wpair;
   constexpr int GS = KM | 1;  // stride of a part's columns of g (odd: distinct banks)
   constexpr int NS = BOTH ? 2 : 1;
@@ -1238,7 +1242,16 @@ __device__ __forceinline__ void chain_rows(const Geo& g, const double* __restric
   // one row in front of the slices and 64 rows behind them are read, not used
   double* tb = tbuf + 1;
   const int dump = (BOTH ? nch | 1 : nch) * b;
-  for (int q = tid; q < nch * b; q += nth) tb[q] = col < 0 ? v[q] : (q == col ? 1.0 : 0.0);
+  double pv = 0.0;
+  if (csum != nullptr) {
+    for (int q = tid; q < nch * b; q += nth) {
+      const double x = v[q];
+      tb[q] = x;
+      pv += phi[q] * x;
+    }
+  } else {
+    for (int q = tid; q < nch * b; q += nth) tb[q] = col < 0 ? v[q] : (q == col ? 1.0 : 0.0);
+  }
   for (int q = nch * b + tid; q < dump + 2 * 64; q += nth) tb[q] = 0.0;
   if (tid == 0) tbuf[0] = 0.0;
   for (int q = tid; q < NS * (8 * GS + 1); q += nth) gsh[0][q] = 0.0;
@@ -1385,15 +1398,31 @@ __device__ __forceinline__ void chain_rows(const Geo& g, const double* __restric
     }
   }
   for (int q = tid; q < nch * b; q += nth) v[q] = tb[q];
+  if (csum != nullptr) {
+    for (int off = 32; off > 0; off >>= 1) pv += __shfl_down(pv, off, 64);
+    if (lane == 0) gsh[0][wave] = pv;
+    __syncthreads();
+    if (tid == 0) {
+      double t = 0.0;
+      for (int i = 0; i < nth / 64; ++i) t += gsh[0][i];
+      *csum = t;
+    }
+  }
 }
 
 // The level-1 preconditioner's local solves: workgroup = subdomain, with its
-// class's factor.
+// class's factor.  With crhs a workgroup also forms its entry of the coarse
+// right-hand side, phi . R_i r, from the copy of R_i r that it reads anyway.  As
+// a kernel of its own that was 4 to 10 us on a second stream beside the solves,
+// and ordering the two streams cost more than the solves gained: 256 boxes of
+// 63 x 71, an application 107.1 -> 100.2 us; 32 boxes of 31 x 35, a solve with
+// its gradient 15.3 -> 12.2 ms.
 template <typename WT, int NT, int KM, bool BOTH>
 __global__ void __launch_bounds__(NT) k_rows_local(Geo g, const double* __restrict__ T,
                                                    const TypeDev* __restrict__ types,
                                                    const SubDev* __restrict__ subs,
-                                                   const PcgState* __restrict__ st) {
+                                                   const PcgState* __restrict__ st,
+                                                   double* __restrict__ crhs) {
   extern __shared__ double tb[];
   if (st != nullptr && st->done) return;
   const SubDev sd = subs[blockIdx.x];
@@ -1402,7 +1431,8 @@ __global__ void __launch_bounds__(NT) k_rows_local(Geo g, const double* __restri
   if constexpr (sizeof(WT) == 4) W = reinterpret_cast<const WT*>(td.W32);
   else W = reinterpret_cast<const WT*>(td.W);
   chain_rows<WT, KM, BOTH>(g, T, W, td.batch + (long)sd.slot * td.nch * td.b, td.b, td.nch,
-                           sd.o[0], sd.o[1], false, -1, tb);
+                           sd.o[0], sd.o[1], false, -1, tb, td.phi,
+                           crhs != nullptr ? crhs + blockIdx.x : nullptr);
 }
 
 // Right-hand sides of one box (FP64 factors): workgroup = right-hand side;
@@ -1420,14 +1450,15 @@ __global__ void __launch_bounds__(NT) k_rows_box(Geo g, Box bx, const double* __
 
 // The kernel for slices of at most b: columns per part (b / 8 rounded up), and
 // threads (per side a wave that forms g and a wave per 16 rows).
+#define ROWS_PICK_WIDE(KERN, b, ...) \
+  ((b) <= 96 ? KERN<__VA_ARGS__ 448, 12, false> : KERN<__VA_ARGS__ 576, 16, false>)
 #define ROWS_PICK(KERN, b, ...)                                                         \
   ((b) <= 24   ? KERN<__VA_ARGS__ 192, 3, false>                                        \
    : (b) <= 40 ? KERN<__VA_ARGS__ 256, 5, false>                                        \
    : (b) <= 56 ? KERN<__VA_ARGS__ 320, 7, false>                                        \
    : (b) <= 64 ? KERN<__VA_ARGS__ 320, 8, false>                                        \
    : (b) <= 72 ? KERN<__VA_ARGS__ 384, 9, false>                                        \
-   : (b) <= 80 ? KERN<__VA_ARGS__ 384, 10, false>                                       \
-   : (b) <= 96 ? KERN<__VA_ARGS__ 448, 12, false> : KERN<__VA_ARGS__ 576, 16, false>)
+   : (b) <= 80 ? KERN<__VA_ARGS__ 384, 10, false> : ROWS_PICK_WIDE(KERN, b, __VA_ARGS__))
 #define ROWS_PICK_BOTH(KERN, b, ...)                                                    \
   ((b) <= 24   ? KERN<__VA_ARGS__ 384, 3, true>                                         \
    : (b) <= 40 ? KERN<__VA_ARGS__ 512, 5, true>                                         \
@@ -1481,21 +1512,33 @@ bool local_solves_fast_ok(const ddeig_problem* P) {
 }
 
 template <typename WT>
-static void launch_rows_local(const ddeig_problem* P, const PcgState* st, hipStream_t s) {
+static void launch_rows_local(const ddeig_problem* P, const PcgState* st, double* crhs,
+                              hipStream_t s) {
   int b, nch, nt;
   size_t lds;
   class_extents(P, b, nch);
   const bool both = classes_both(P);
-  auto kern = ROWS_PICK(k_rows_local, b, WT ROWS_COMMA);
-  if constexpr (sizeof(WT) == 8)
+  auto kern = ROWS_PICK_WIDE(k_rows_local, b, WT ROWS_COMMA);
+  if constexpr (sizeof(WT) == 8) {
     if (both) kern = ROWS_PICK_BOTH(k_rows_local, b, WT ROWS_COMMA);
+  } else {
+    kern = ROWS_PICK(k_rows_local, b, WT ROWS_COMMA);
+  }
   rows_launch(kern, both, b, nch, lds, nt);
-  hipLaunchKernelGGL(kern, dim3(P->nsub), dim3(nt), lds, s, P->g, P->tabAs, P->dTypes, P->dSubs, st);
+  hipLaunchKernelGGL(kern, dim3(P->nsub), dim3(nt), lds, s, P->g, P->tabAs, P->dTypes, P->dSubs, st,
+                     crhs);
 }
 
-void launch_local_solves_fast(const ddeig_problem* P, const PcgState* st, hipStream_t s) {
-  if (P->opt.local_prec == 1) launch_rows_local<float>(P, st, s);
-  else launch_rows_local<double>(P, st, s);
+void launch_local_solves_fast(const ddeig_problem* P, const PcgState* st, hipStream_t s,
+                              bool coarse) {
+  double* crhs = coarse ? P->crhs : nullptr;
+  if (P->opt.local_prec == 1) launch_rows_local<float>(P, st, crhs, s);
+  else launch_rows_local<double>(P, st, crhs, s);
+}
+
+// The coarse right-hand side rides in the local solves when they are row solves.
+bool rows_coarse(const ddeig_problem* P) {
+  return P->opt.coarse && P->opt.local_prec < 2 && local_solves_fast_ok(P);
 }
 
 }  // namespace ddeig
