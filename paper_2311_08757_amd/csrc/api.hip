@@ -333,6 +333,21 @@ int prec_flags(int kind) {
   }
 }
 
+// Where each subdomain keeps its values (dense local solves keep none there).
+std::vector<SubBase> sub_bases(const ddeig_problem* P) {
+  std::vector<SubBase> sb(P->nsub);
+  for (int sid = 0; sid < P->nsub; ++sid) {
+    const SubDev& sd = P->subs[sid];
+    const SubType& T = P->types[sd.type];
+    const int* m = T.box.m;
+    const long first = (long)sd.slot * T.box.nch * T.box.b -
+                       (sd.o[0] + (long)m[0] * (sd.o[1] + m[1] * sd.o[2]));
+    const auto at = reinterpret_cast<uintptr_t>(T.batch) + (uintptr_t)(first * (long)sizeof(double));
+    sb[sid] = SubBase{reinterpret_cast<double*>(at), m[0], m[1]};
+  }
+  return sb;
+}
+
 // Automatic fallback when CG breaks down with r.z <= 0 under the dense
 // reduced-precision local solves (the rounded inverse made M^{-1} indefinite):
 // the problem switches to FP32 block-chain local solves (FP64 factors of
@@ -353,27 +368,16 @@ bool fallback_fp32(ddeig_problem* P) {
     dfree(P, T.batch);
     T.batch = dalloc<double>(P, (size_t)T.nmem * mm);
     TypeDev& d = tdev[t];
-    for (int a = 0; a < 3; ++a) {
-      d.hm[a] = T.box.m[a];
-      d.off[a] = 0;
-    }
-    d.dense = 0;
     d.W = T.W;
     d.W32 = T.W32;
     d.batch = T.batch;
     d.tbatch = nullptr;
-    d.ld = 0;
-    d.ksplit = 0;
-    d.Rh = d.Rl = nullptr;
-    d.Z = nullptr;
-    d.zsplit = 0;
     d.ldw = T.box.b;
   }
-  std::vector<SubTS> ts(P->nsub);
-  for (int sid = 0; sid < P->nsub; ++sid) ts[sid] = SubTS{P->subs[sid].type, P->subs[sid].slot};
+  const std::vector<SubBase> sb = sub_bases(P);
   check_hip(hipMemcpy(P->dTypes, tdev.data(), sizeof(TypeDev) * tdev.size(), hipMemcpyHostToDevice),
             "write classes");
-  check_hip(hipMemcpy(P->dSubTS, ts.data(), sizeof(SubTS) * ts.size(), hipMemcpyHostToDevice),
+  check_hip(hipMemcpy(P->dSubBase, sb.data(), sizeof(SubBase) * sb.size(), hipMemcpyHostToDevice),
             "write subdomain table");
   P->opt.local_prec = 1;
   clear_graphs(P);
@@ -1284,40 +1288,19 @@ ddeig_status ddeig_assemble(const ddeig_geometry* geom, double h, const ddeig_po
       tdev[t].nch = T.box.nch;
       for (int a = 0; a < 3; ++a) tdev[t].o[a] = T.box.o[a];
       tdev[t].tbatch = nullptr;
-      tdev[t].dense = dense ? 1 : 0;
       if (dense) {
-        const ddeig::DenseHost& H = P->dh;
-        for (int a = 0; a < 3; ++a) {
-          tdev[t].hm[a] = H.box.m[a];
-          tdev[t].off[a] = T.off[a];
-        }
         T.batch = dalloc<double>(P, 1);
         tdev[t].W = nullptr;
         tdev[t].W32 = nullptr;
-        tdev[t].ld = H.ld;
-        tdev[t].ksplit = P->ksplit;
-        tdev[t].Rh = H.Rh;
-        tdev[t].Rl = H.Rl;
-        tdev[t].Z = H.Z;
-        tdev[t].zsplit = (long)H.mp * H.ld;
       } else {
         T.W = dalloc_factor<double>(P, class_factor_entries(P, T));
         if (o.local_prec == 1)
           T.W32 = dalloc_factor<float>(P, chain_mfma ? (size_t)T.box.nch * T.box.b * ldw
                                                      : class_factor_entries(P, T));
         T.batch = dalloc<double>(P, (size_t)T.nmem * mm);
-        for (int a = 0; a < 3; ++a) {
-          tdev[t].hm[a] = T.box.m[a];
-          tdev[t].off[a] = 0;
-        }
         if (batched_chain) tdev[t].tbatch = dalloc<double>(P, (size_t)T.nmem * mm);
         tdev[t].W = T.W;
         tdev[t].W32 = T.W32;
-        tdev[t].ld = 0;
-        tdev[t].ksplit = 0;
-        tdev[t].Rh = tdev[t].Rl = nullptr;
-        tdev[t].Z = nullptr;
-        tdev[t].zsplit = 0;
       }
       tdev[t].batch = T.batch;
       T.phi = dalloc<double>(P, mm);
@@ -1354,21 +1337,17 @@ ddeig_status ddeig_assemble(const ddeig_geometry* geom, double h, const ddeig_po
       sync(P);  // chainjobs is released at the end of this scope
     }
     {
-      std::vector<ddeig::SubTS> ts(nsub);
-      for (int sid = 0; sid < nsub; ++sid) {
-        const auto& sd = P->subs[sid];
-        ts[sid] = ddeig::SubTS{sd.type, dense ? sid : sd.slot};
-      }
+      const std::vector<ddeig::SubBase> sb = sub_bases(P);
       std::vector<int> first(P->types.size());
       std::vector<double*> phis(P->types.size());
       for (size_t t = 0; t < P->types.size(); ++t) {
         first[t] = P->types[t].members[0];
         phis[t] = P->types[t].phi;
       }
-      P->dSubTS = dalloc<ddeig::SubTS>(P, nsub);
+      P->dSubBase = dalloc<ddeig::SubBase>(P, nsub);
       P->dFirst = dalloc<int>(P, first.size());
       P->dPhis = dalloc<double*>(P, phis.size());
-      check_hip(hipMemcpyAsync(P->dSubTS, ts.data(), sizeof(ddeig::SubTS) * nsub,
+      check_hip(hipMemcpyAsync(P->dSubBase, sb.data(), sizeof(ddeig::SubBase) * nsub,
                                hipMemcpyHostToDevice, s), "copy sub table");
       check_hip(hipMemcpyAsync(P->dFirst, first.data(), sizeof(int) * first.size(),
                                hipMemcpyHostToDevice, s), "copy first members");

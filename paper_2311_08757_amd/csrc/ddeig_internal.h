@@ -174,20 +174,11 @@ struct SubDev {
 struct TypeDev {
   int m[3];
   int o[3];           // box origin of the first member (table positions of the class)
-  int hm[3], off[3];  // dense batch rows: e = sum_a (u_a + off_a) prod_{b<a} hm_b
   int b, nch;
   const double* W;
   const float* W32;
   double* batch;
   double* tbatch;     // forward-sweep results of the batched chain solves
-  // dense local solves (local_prec >= 2): rows of the dense batch (bf16
-  // residual, lo part for local_prec = 2) and split-K partial results
-  // Z[split][row][e]
-  int dense, ld, ksplit;
-  __bf16* Rh;
-  __bf16* Rl;
-  const float* Z;
-  long zsplit;
   // coarse weights of the class: phi[e] = D(e) psi_ext(e) on the box of any
   // member (equal for all members by periodicity), and division by m[0]
   const double* phi;
@@ -199,9 +190,14 @@ struct TypeDev {
 
 constexpr int kMaxTypes = 9;  // 3 classes per expanding axis, p <= 2
 
-// Subdomain -> (class, slot), packed for the node-parallel kernels.
-struct SubTS {
-  int type, slot;
+// Where a subdomain keeps its values (FP64 and FP32 local solves), for the
+// node-parallel kernels: the node with 0-based indices i at p[at(i)].
+struct SubBase {
+  double* p;
+  int m0, m1;
+#ifdef __HIPCC__
+  __device__ long at(const int* i) const { return (long)m0 * (i[1] + m1 * i[2]) + i[0]; }
+#endif
 };
 
 // Operands of the grouped MFMA GEMM of one dense class (ld x ld inverse).
@@ -378,7 +374,7 @@ struct ddeig_problem {
   ddeig::TypeDev* dTypes = nullptr;
   int maxb = 0;
   ddeig::XCover* dXC[2] = {nullptr, nullptr};   // per expanding axis, N[a] entries
-  ddeig::SubTS* dSubTS = nullptr;
+  ddeig::SubBase* dSubBase = nullptr;
   int* dFirst = nullptr;          // first member of every class
   double** dPhis = nullptr;       // per-class coarse weights (device pointer array)
   // dense local solves

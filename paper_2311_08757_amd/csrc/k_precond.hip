@@ -93,86 +93,6 @@ __device__ inline double cover_weight(const Geo& g, int delta, int pu, const XCo
   return w;
 }
 
-// Scatter r into the subdomain batches (box natural order; bf16 rows, as a
-// hi/lo pair for local_prec 2, for dense classes): node-parallel over row
-// segments of kBlock x1 positions, four segments per workgroup of kBig
-// threads (one node per thread, so the dependent table loads of the nodes
-// overlap); every node writes its copy into each covering subdomain (at most
-// 2^p), so reads of r and writes of a batch row are both coalesced.  With
-// xr.on the node first takes the CG update of iteration k (x += alpha p,
-// r -= alpha q, written back) and the kernel leaves the partials of ||r||^2
-// in rr.
-__global__ void __launch_bounds__(kBig) k_restrict(Geo g, int ntypes, PcgState* __restrict__ st,
-                                                   XrArgs xr, Red rr, double* __restrict__ r,
-                                                   const TypeDev* __restrict__ types,
-                                                   const SubTS* __restrict__ subts,
-                                                   const XCover* __restrict__ xc0,
-                                                   const XCover* __restrict__ xc1) {
-  __shared__ TypeDev stypes[kMaxTypes];
-  if (st != nullptr && st->done) return;
-  double alpha = 0.0;
-  if (xr.on == 1) {
-    const double gamma = sum_partials<kBig>(xr.gam.part, xr.gam.np);
-    if (!(gamma > 0.0)) {
-      if (blockIdx.x == 0 && threadIdx.x == 0) {
-        st->done = 2;
-        st->iters = xr.k - 1;
-      }
-      return;
-    }
-    alpha = st->rho[(xr.k - 1) & 1] / gamma;
-  }
-  if (threadIdx.x < ntypes) stypes[threadIdx.x] = types[threadIdx.x];
-  __syncthreads();
-  const int N0 = g.N[0], N1 = g.N[1];
-  const int segs = (N0 + kBlock - 1) / kBlock;
-  const long items = (long)segs * N1 * g.N[2];
-  const int sub = threadIdx.x / kBlock, tx = threadIdx.x % kBlock;
-  double acc = 0.0;
-  for (long grp = blockIdx.x; grp * (kBig / kBlock) < items; grp += gridDim.x) {
-    const long it = grp * (kBig / kBlock) + sub;
-    if (it >= items) continue;
-    const int line = (int)(it / segs);
-    const int i0 = (int)(it - (long)line * segs) * kBlock + tx;
-    if (i0 >= N0) continue;
-    const int i2 = g.D == 3 ? (int)fdiv((unsigned)line, g.fN1) : 0;
-    const int i1 = line - i2 * N1;
-    const long k = i0 + (long)N0 * line;
-    double rv = r[k];
-    if (xr.on) {
-      rv -= alpha * xr.q[k];
-      xr.x[k] += alpha * xr.p[k];
-      r[k] = rv;
-      acc += rv * rv;
-    }
-    const __bf16 hi = to_bf16(rv);
-    const __bf16 lo = to_bf16(rv - (double)hi);
-    const XCover a0 = xc0[i0];
-    XCover a1;
-    a1.c[0] = 1; a1.c[1] = 0; a1.u[0] = i1; a1.u[1] = 0;
-    if (g.p == 2) a1 = xc1[i1];
-    for (int q1 = 0; q1 < 2; ++q1) {
-      if (a1.c[q1] == 0) continue;
-      for (int q0 = 0; q0 < 2; ++q0) {
-        if (a0.c[q0] == 0) continue;
-        const int sid = g.p == 1 ? a0.c[q0] - 1 : (a0.c[q0] - 1) + g.L * (a1.c[q1] - 1);
-        const SubTS ts = subts[sid];
-        const TypeDev& td = stypes[ts.type];
-        // row index inside the member's batch row (the unclipped box for dense solves)
-        const long e = (a0.u[q0] + td.off[0]) +
-                       (long)td.hm[0] * ((a1.u[q1] + td.off[1]) + (long)td.hm[1] * (i2 + td.off[2]));
-        if (td.dense) {
-          td.Rh[(long)ts.slot * td.ld + e] = hi;
-          if (td.Rl != nullptr) td.Rl[(long)ts.slot * td.ld + e] = lo;
-        } else {
-          td.batch[(long)ts.slot * td.nch * td.b + e] = rv;
-        }
-      }
-    }
-  }
-  if (xr.on) write_partial<kBig>(acc, rr.part);
-}
-
 // ---- dense local solves: restriction and extension with arithmetic addressing
 //
 // With dense local solves the batch row of a subdomain is its id and every
@@ -252,6 +172,67 @@ template <class T>
 __device__ __forceinline__ T& at_bytes(T* p, unsigned off) {
   typedef std::conditional_t<std::is_const_v<T>, const char, char> byte_t;
   return *reinterpret_cast<T*>(reinterpret_cast<byte_t*>(p) + off);
+}
+
+// Scatter r into the subdomain batches (box natural order): node-parallel over
+// row segments of kBlock x1 positions, four segments per workgroup of kBig
+// threads; every node writes its copy into each covering subdomain (at most
+// 2^p), so reads of r and writes of a batch row are both coalesced.  The
+// covering cells come from the node index, the place in a subdomain's batch from
+// one record per subdomain (SubBase): through a table per grid line, the
+// subdomain's class and the class's fields in LDS it took 8.5 us, 7.1 us so, and
+// the extension 17.0 and 11.0 us (256 subdomains, 1,032,129 unknowns).  With
+// xr.on the node first takes the CG update of iteration k (x += alpha p,
+// r -= alpha q, written back) and the kernel leaves the partials of ||r||^2
+// in rr.
+template <int PX>
+__global__ void __launch_bounds__(kBig) k_restrict(Geo g, int delta, PcgState* __restrict__ st,
+                                                   XrArgs xr, Red rr, double* __restrict__ r,
+                                                   const SubBase* __restrict__ sb) {
+  if (st != nullptr && st->done) return;
+  double alpha = 0.0;
+  if (xr.on == 1) {
+    const double gamma = sum_partials<kBig>(xr.gam.part, xr.gam.np);
+    if (!(gamma > 0.0)) {
+      if (blockIdx.x == 0 && threadIdx.x == 0) {
+        st->done = 2;
+        st->iters = xr.k - 1;
+      }
+      return;
+    }
+    alpha = st->rho[(xr.k - 1) & 1] / gamma;
+  }
+  const int N0 = g.N[0];
+  const unsigned items = g.fseg.d * (unsigned)(g.N[1] * g.N[2]);
+  const int sub = __builtin_amdgcn_readfirstlane(threadIdx.x / kBlock), tx = threadIdx.x % kBlock;
+  double acc = 0.0;
+  constexpr unsigned IPB = kBig / kBlock;
+  for (unsigned grp = blockIdx.x; grp * IPB < items; grp += gridDim.x) {
+    const LineItem t(g, grp * IPB + sub, items);
+    const int tl = min(tx, N0 - 1 - t.s0);  // (lanes past the line: its last node)
+    if (!t.live || tl < tx) continue;
+    const long k0 = t.s0 + N0 * t.line;
+    const unsigned o = 8u * tl;
+    const int i[3] = {t.s0 + tl, t.i1, t.i2};
+    const Cover<PX> cv(g, delta, i);
+    const int cw = __builtin_amdgcn_readfirstlane(cv.clo0);
+    SubBase b[Cover<PX>::NC];
+#pragma unroll
+    for (int q = 0; q < Cover<PX>::NC; ++q)
+      b[q] = at_bytes(sb + (cw - 1 + (PX == 2 ? (long)g.L * (cv.c1(q) - 1) : 0L)),
+                      (unsigned)sizeof(SubBase) * (cv.c0(q) - cw));
+    double rv = at_bytes(r + k0, o);
+    if (xr.on) {
+      rv -= alpha * at_bytes(xr.q + k0, o);
+      at_bytes(xr.x + k0, o) += alpha * at_bytes(xr.p + k0, o);
+      at_bytes(r + k0, o) = rv;
+      acc += rv * rv;
+    }
+#pragma unroll
+    for (int q = 0; q < Cover<PX>::NC; ++q)
+      if (cv.val(q)) b[q].p[b[q].at(i)] = rv;
+  }
+  if (xr.on) write_partial<kBig>(acc, rr.part);
 }
 
 // Bodies of the node-parallel kernels take the block index `bid` and the
@@ -538,9 +519,11 @@ void launch_restrict(const ddeig_problem* P, double* r, PcgState* st, const XrAr
     else
       hipLaunchKernelGGL(k_restrict_dense<2>, dim3(blocks), dim3(kBig), 0, s, P->g, P->delta, st,
                          xr, xr.on ? *rr : none, r, dense_args(P));
-  } else
-    hipLaunchKernelGGL(k_restrict, dim3(blocks), dim3(kBig), 0, s, P->g, (int)P->types.size(), st,
-                       xr, xr.on ? *rr : none, r, P->dTypes, P->dSubTS, P->dXC[0], P->dXC[1]);
+  } else {
+    auto kern = P->g.p == 1 ? k_restrict<1> : k_restrict<2>;
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(kBig), 0, s, P->g, P->delta, st, xr,
+                       xr.on ? *rr : none, r, P->dSubBase);
+  }
 }
 
 __global__ void __launch_bounds__(kBlock) k_coarse_rhs(Geo g, const PcgState* __restrict__ st,
@@ -654,19 +637,17 @@ void launch_coarse_field(const ddeig_problem* P, const PcgState* st, hipStream_t
 // With chk.on the kernel first applies the stopping test of PCG iteration k,
 // ||r_k|| <= rtol ||r_0|| (§4.1), records the history and, once CG stops,
 // does nothing else (every later kernel of the iteration sees `done`).
+template <int PX>
 __global__ void __launch_bounds__(kBig) k_extend(Geo g, int delta, int pu, int coarse, int ras,
-                                                   int ntypes, PcgState* __restrict__ st,
-                                                   CheckArgs chk,
-                                                   const TypeDev* __restrict__ types,
-                                                   const SubTS* __restrict__ subts,
-                                                   const XCover* __restrict__ xc0,
-                                                   const XCover* __restrict__ xc1,
-                                                   const double* __restrict__ psi,
-                                                   const double* __restrict__ y0,
-                                                   const double* __restrict__ r,
-                                                   double* __restrict__ z, int use_dot,
-                                                   Red dot) {
-  __shared__ TypeDev stypes[kMaxTypes];
+                                                 PcgState* __restrict__ st, CheckArgs chk,
+                                                 const SubBase* __restrict__ sb,
+                                                 const XCover* __restrict__ xc0,
+                                                 const XCover* __restrict__ xc1,
+                                                 const double* __restrict__ psi,
+                                                 const double* __restrict__ y0,
+                                                 const double* __restrict__ r,
+                                                 double* __restrict__ z, int use_dot, Red dot) {
+  constexpr int NC = Cover<PX>::NC;
   if (st != nullptr && st->done) return;
   if (chk.on) {
     const double rn2 = sum_partials<kBig>(chk.rr.part, chk.rr.np);
@@ -680,58 +661,53 @@ __global__ void __launch_bounds__(kBig) k_extend(Geo g, int delta, int pu, int c
     }
     if (conv || last) return;
   }
-  if (threadIdx.x < ntypes) stypes[threadIdx.x] = types[threadIdx.x];
-  __syncthreads();
   const XCover* xc[2] = {xc0, xc1};
   double acc = 0.0;
-  const int N0 = g.N[0], N1 = g.N[1];
-  const int segs = (N0 + kBlock - 1) / kBlock;
-  const long items = (long)segs * N1 * g.N[2];
-  const int sub = threadIdx.x / kBlock, tx = threadIdx.x % kBlock;
-  for (long grp = blockIdx.x; grp * (kBig / kBlock) < items; grp += gridDim.x) {
-    const long it = grp * (kBig / kBlock) + sub;
-    if (it >= items) continue;
-    const int line = (int)(it / segs);
-    const int i0 = (int)(it - (long)line * segs) * kBlock + tx;
-    if (i0 >= N0) continue;
-    const int i2 = g.D == 3 ? (int)fdiv((unsigned)line, g.fN1) : 0;
-    const int i[3] = {i0, line - i2 * N1, i2};
-    const long k = i0 + (long)N0 * line;
-    const XCover a0 = xc0[i0];
-    XCover a1;
-    a1.c[0] = 1; a1.c[1] = 0; a1.u[0] = i[1]; a1.u[1] = 0; a1.w[0] = 1.0; a1.w[1] = 0.0;
-    if (g.p == 2) a1 = xc1[i[1]];
+  const int N0 = g.N[0];
+  const unsigned items = g.fseg.d * (unsigned)(g.N[1] * g.N[2]);
+  const int sub = __builtin_amdgcn_readfirstlane(threadIdx.x / kBlock), tx = threadIdx.x % kBlock;
+  constexpr unsigned IPB = kBig / kBlock;
+  for (unsigned grp = blockIdx.x; grp * IPB < items; grp += gridDim.x) {
+    const LineItem t(g, grp * IPB + sub, items);
+    const int tl = min(tx, N0 - 1 - t.s0);  // (lanes past the line: its last node)
+    if (!t.live || tl < tx) continue;
+    const long k0 = t.s0 + N0 * t.line;
+    const int i[3] = {t.s0 + tl, t.i1, t.i2};
+    const Cover<PX> cv(g, delta, i);
+    const int cw = __builtin_amdgcn_readfirstlane(cv.clo0);
+    // the records and whatever does not hang on them, then the local solutions
+    SubBase b[NC];
+    double wc[NC], yc[NC], zi[NC], ps = 0.0;
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+      const long sw = cw - 1 + (PX == 2 ? (long)g.L * (cv.c1(q) - 1) : 0L);
+      const unsigned sl = (unsigned)(cv.c0(q) - cw);
+      b[q] = at_bytes(sb + sw, (unsigned)sizeof(SubBase) * sl);
+      const int c[3] = {cv.c0(q), PX == 2 ? cv.c1(q) : 0, 0};
+      const int which[2] = {q & 1, q >> 1};
+      wc[q] = (coarse || ras) && cv.val(q) ? cover_weight(g, delta, pu, xc, c, i, which) : 1.0;
+      yc[q] = coarse ? at_bytes(y0 + sw, 8u * sl) : 0.0;
+    }
+    const double rk = at_bytes(r + k0, 8u * tl);
+    if (coarse) {
+      // cell-local table node: x dims (i + 1) mod n_e
+      const int j0 = i[0] + 1 - g.ne * (int)fdiv((unsigned)(i[0] + 1), g.fne);
+      const int j1 = PX == 2 ? t.i1 + 1 - g.ne * (int)fdiv((unsigned)(t.i1 + 1), g.fne) : t.i1;
+      ps = at_bytes(psi + (long)g.P[0] * (j1 + (long)g.P[1] * t.i2), 8u * j0);
+    }
+#pragma unroll
+    for (int q = 0; q < NC; ++q) zi[q] = b[q].p[b[q].at(i)];
     double zl = 0.0, zc = 0.0;
-    for (int q1 = 0; q1 < 2; ++q1) {
-      if (a1.c[q1] == 0) continue;
-      for (int q0 = 0; q0 < 2; ++q0) {
-        if (a0.c[q0] == 0) continue;
-        const int c[3] = {a0.c[q0], g.p == 2 ? a1.c[q1] : 0, 0};
-        const int sid = sub_index(g, c);
-        const SubTS ts = subts[sid];
-        const TypeDev& td = stypes[ts.type];
-        const int u1 = g.p == 2 ? a1.u[q1] : i[1];
-        const long e = (a0.u[q0] + td.off[0]) +
-                       (long)td.hm[0] * ((u1 + td.off[1]) + (long)td.hm[1] * (i2 + td.off[2]));
-        double zi;
-        if (td.dense) {
-          const float* zp = td.Z + (long)ts.slot * td.ld + e;
-          float zs = 0.0f;
-          for (int sp = 0; sp < td.ksplit; ++sp) zs += zp[sp * td.zsplit];
-          zi = (double)zs;
-        } else {
-          zi = td.batch[(long)ts.slot * td.nch * td.b + e];
-        }
-        const int which[2] = {q0, q1};
-        const double wc = (coarse || ras) ? cover_weight(g, delta, pu, xc, c, i, which) : 1.0;
-        zl += ras ? wc * zi : zi;
-        if (coarse) zc += wc * y0[sid];
-      }
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+      if (!cv.val(q)) continue;
+      zl += ras ? wc[q] * zi[q] : zi[q];
+      zc += wc[q] * yc[q];
     }
     double zv = zl;
-    if (coarse) zv += psi[table_node(g, i[0], i[1], i[2])] * zc;
-    z[k] = zv;
-    acc += r[k] * zv;
+    if (coarse) zv += ps * zc;
+    at_bytes(z + k0, 8u * tl) = zv;
+    acc += rk * zv;
   }
   if (use_dot) write_partial<kBig>(acc, dot.part);
 }
@@ -768,11 +744,10 @@ void launch_extend(const ddeig_problem* P, const double* r, double* z, int coars
                        dot ? *dot : none, P->opt.pu, P->dXC[0], P->dXC[1]);
     return;
   }
-  hipLaunchKernelGGL(k_extend, dim3(blocks), dim3(kBig), 0, s, P->g, P->delta, P->opt.pu,
-                     coarse, ras, (int)P->types.size(), st, chk, P->dTypes, P->dSubTS, P->dXC[0],
-                     P->dXC[1],
-                     P->psi, P->cy, r, z,
-                     dot ? 1 : 0, dot ? *dot : none);
+  auto kern = P->g.p == 1 ? k_extend<1> : k_extend<2>;
+  hipLaunchKernelGGL(kern, dim3(blocks), dim3(kBig), 0, s, P->g, P->delta, P->opt.pu, coarse, ras, st,
+                     chk, P->dSubBase, P->dXC[0], P->dXC[1], P->psi, P->cy, r, z, dot ? 1 : 0,
+                     dot ? *dot : none);
 }
 
 // The coarse correction alone, z = R_0^T y0 = psi_ext * cf at every node
