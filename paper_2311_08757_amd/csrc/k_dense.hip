@@ -482,8 +482,8 @@ void launch_embed_gmat(const ddeig_problem* P, const EmbedDev& E, const double* 
 // in split order).  The corrected solution replaces split 0 of Z and the other
 // splits are cleared, so the extension reads clipped and unclipped members
 // alike.
-// Block (64 unknowns of the unclipped box, job): thread (unknown, phase) adds
-// the terms t = phase mod 4 in batches of kEmbG for every member (a wave reads
+// Block (64 or 128 unknowns of the unclipped box, job): thread (unknown, phase)
+// adds the terms t = phase mod 4 in batches of kEmbG for every member (a wave reads
 // 256 contiguous bytes of a row of G per load); the 4 phase sums of a member
 // are added in phase order by the thread of phase m mod 4.
 // u_T sits in LDS with the members of one t next to each other (two 16-byte
@@ -498,20 +498,26 @@ static_assert(kEmbChunk % kEmbPh == 0, "members are finished round-robin over th
 static_assert(kEmbChunk == 8 && kEmbUT == kEmbMaxT * kEmbChunk,
               "u_T rows are two float4 of members, for every t < kEmbMaxT");
 
-// The terms of one thread for NM members: gv holds the first batch of G on
-// entry (G[g0 + q gs], q < nq, is the thread's column; nT mH < 2^31 is checked
-// at set-up); each register is refilled with its term of the next batch as
-// soon as it has been used.
-template <int NM>
-__device__ __forceinline__ void embed_accumulate(const float* __restrict__ G, unsigned g0,
-                                                 unsigned gs, int nq,
+// The terms of one thread for NM members and its NE unknowns: gv holds the first
+// batch of G on entry (G[g0[k] + q gs], q < nq, is the thread's column k; nT mH <
+// 2^31 is checked at set-up); each register is refilled with its term of the next
+// batch as soon as it has been used.
+template <int NM, int NE>
+__device__ __forceinline__ void embed_accumulate(const float* __restrict__ G,
+                                                 const unsigned (&g0)[NE], unsigned gs, int nq,
                                                  const float* __restrict__ uT, int ph,
-                                                 float (&gv)[kEmbG], float (&acc)[kEmbChunk]) {
-  for (int q0 = 0; q0 < nq; q0 += kEmbG) {
+                                                 float (&gv)[NE][kEmbG / (NE * NE)],
+                                                 float (&acc)[NE][kEmbChunk]) {
+  constexpr int NG = kEmbG / (NE * NE);
+  for (int q0 = 0; q0 < nq; q0 += NG) {
 #pragma unroll
-    for (int q = 0; q < kEmbG; ++q) {
-      const float g = gv[q];
-      if (q0 + kEmbG + q < nq) gv[q] = G[g0 + (unsigned)(q0 + kEmbG + q) * gs];
+    for (int q = 0; q < NG; ++q) {
+      float g[NE];
+#pragma unroll
+      for (int k = 0; k < NE; ++k) {
+        g[k] = gv[k][q];
+        if (q0 + NG + q < nq) gv[k][q] = G[g0[k] + (unsigned)(q0 + NG + q) * gs];
+      }
       if (q0 + q < nq) {
         const float4* u4 =
             reinterpret_cast<const float4*>(uT + (ph + kEmbPh * (q0 + q)) * kEmbChunk);
@@ -522,7 +528,9 @@ __device__ __forceinline__ void embed_accumulate(const float* __restrict__ G, un
           u[4] = b.x; u[5] = b.y; u[6] = b.z; u[7] = b.w;
         }
 #pragma unroll
-        for (int m = 0; m < NM; ++m) acc[m] += g * u[m];
+        for (int k = 0; k < NE; ++k)
+#pragma unroll
+          for (int m = 0; m < NM; ++m) acc[k][m] += g[k] * u[m];
       }
     }
   }
@@ -530,18 +538,27 @@ __device__ __forceinline__ void embed_accumulate(const float* __restrict__ G, un
 
 // Grid (row chunk, job): the chunks of one job are consecutive in dispatch
 // order, so the blocks that run together read neighbouring pieces of the same
-// rows of G.  Chunks blockIdx.x >= ceil(mH / kEmbE) of job 0 apply the coarse
+// rows of G.  Chunks blockIdx.x >= ceil(mH / (NE kEmbE)) of job 0 apply the coarse
 // inverse instead (rows 4 (blockIdx.x - ychunks) .. + 3 of y0 = A_0^{-1} c),
 // independent of the correction workgroups.
-template <int KS>
+// NE unknowns per thread, kEmbE apart: two share the LDS reads of u_T and the
+// loop's instructions, which with several members a job or many jobs are what the
+// kernel waits for (embed_wide): 256 subdomains of p = 2, 102 MB of G, 30.0 ->
+// 26.1 us, the 64 jobs of a batch of 32 (35 x 31 unknowns) 15.3 -> 10.9 us.  Few
+// workgroups wait for their own chain of loads instead and keep one unknown a
+// thread.  (Two need a shorter batch of G: 32 values in registers spilled, 34.7
+// us.)
+template <int KS, int NE>
 // At most 128 VGPRs (4 waves per SIMD, as many as the LDS allows): with more
 // the compiler hoists LDS reads and the kernel runs at 3 waves, markedly slower.
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4)))
 k_embed_correct(const EmbedJob* __restrict__ jobs, const EmbedDev* __restrict__ cls, int ld,
                 int hm0, int hm1, int mH, const PcgState* __restrict__ st, CoarseSolveArgs cs) {
   __shared__ __align__(16) float uT[kEmbUT];  // uT[t kEmbChunk + m] = u_T of member m
-  __shared__ float red[kEmbPh][kEmbE][kEmbChunk];
-  const int ychunks = (mH + kEmbE - 1) / kEmbE;
+  constexpr int EB = kEmbE * NE, NG = kEmbG / (NE * NE);
+  static_assert(kEmbPh * EB * kEmbChunk <= kEmbUT, "the phase sums take the place of u_T");
+  float (*red)[EB][kEmbChunk] = reinterpret_cast<float (*)[EB][kEmbChunk]>(uT);
+  const int ychunks = (mH + EB - 1) / EB;
   if ((int)blockIdx.x >= ychunks) {
     if (blockIdx.y == 0) coarse_solve_body(cs.n, st, cs.A0inv, cs.c, cs.y, blockIdx.x - ychunks);
     return;
@@ -556,26 +573,41 @@ k_embed_correct(const EmbedJob* __restrict__ jobs, const EmbedDev* __restrict__ 
   float* __restrict__ Z = E.Z;
   const long zsplit = E.zsplit;
   const int el = threadIdx.x % kEmbE, ph = threadIdx.x / kEmbE;
-  const int e = blockIdx.x * kEmbE + el;
-  const bool inS = e < mH && embed_in_box(E, e, hm0, hm1);
   const int nq = (E.nT - ph + kEmbPh - 1) / kEmbPh;  // terms t = ph + kEmbPh q, q < nq
   const float* __restrict__ G = E.G;
-  const unsigned g0 = (unsigned)(ph * mH + e), gs = (unsigned)(kEmbPh * mH);  // G[g0 + q gs]
-  float gv[kEmbG];
-  float zown[kEmbOwn][KS];
-  if (inS) {
+  const unsigned gs = (unsigned)(kEmbPh * mH);  // G[g0 + q gs]
+  int e[NE];
+  bool inS[NE], any = false;
+  unsigned g0[NE];
+  float gv[NE][NG];
+  float zown[NE][kEmbOwn][KS];
 #pragma unroll
-    for (int q = 0; q < kEmbG; ++q)
-      if (q < nq) gv[q] = G[g0 + (unsigned)q * gs];
+  for (int k = 0; k < NE; ++k) {
+    e[k] = blockIdx.x * EB + el + kEmbE * k;
+    inS[k] = e[k] < mH && embed_in_box(E, e[k], hm0, hm1);
+    // (columns outside the box: zero or another's, read and not used)
+    g0[k] = (unsigned)(ph * mH + min(e[k], mH - 1));
+    any = any || inS[k];
+  }
+  if (any) {
 #pragma unroll
-    for (int k = 0; k < kEmbOwn; ++k) {
-      const int m = ph + kEmbPh * k;
-      if (m < jb.nm) {
-        const long base = (long)E.rows[jb.mem0 + m] * ld + e;
+    for (int q = 0; q < NG; ++q)
 #pragma unroll
-        for (int sp = 0; sp < KS; ++sp) zown[k][sp] = Z[sp * zsplit + base];
+      for (int k = 0; k < NE; ++k)
+        if (q < nq) gv[k][q] = G[g0[k] + (unsigned)q * gs];
+#pragma unroll
+    for (int k = 0; k < NE; ++k)
+      if (inS[k]) {
+#pragma unroll
+        for (int o = 0; o < kEmbOwn; ++o) {
+          const int m = ph + kEmbPh * o;
+          if (m < jb.nm) {
+            const long base = (long)E.rows[jb.mem0 + m] * ld + e[k];
+#pragma unroll
+            for (int sp = 0; sp < KS; ++sp) zown[k][o][sp] = Z[sp * zsplit + base];
+          }
+        }
       }
-    }
   }
   const int nmiss = hm0 - E.m[0];
   const int tot = jb.nm * E.nT;  // gather index m nT + t
@@ -609,39 +641,62 @@ k_embed_correct(const EmbedJob* __restrict__ jobs, const EmbedDev* __restrict__ 
     }
   }
   __syncthreads();
-  float acc[kEmbChunk];
+  float acc[NE][kEmbChunk];
 #pragma unroll
-  for (int m = 0; m < kEmbChunk; ++m) acc[m] = 0.0f;
-  if (inS) {
+  for (int k = 0; k < NE; ++k)
+#pragma unroll
+    for (int m = 0; m < kEmbChunk; ++m) acc[k][m] = 0.0f;
+  if (any) {
     switch (jb.nm) {  // 1 <= nm <= kEmbChunk by construction of the jobs
-      case 1: embed_accumulate<1>(G, g0, gs, nq, uT, ph, gv, acc); break;
-      case 2: embed_accumulate<2>(G, g0, gs, nq, uT, ph, gv, acc); break;
-      case 3: embed_accumulate<3>(G, g0, gs, nq, uT, ph, gv, acc); break;
-      case 4: embed_accumulate<4>(G, g0, gs, nq, uT, ph, gv, acc); break;
-      case 5: embed_accumulate<5>(G, g0, gs, nq, uT, ph, gv, acc); break;
-      case 6: embed_accumulate<6>(G, g0, gs, nq, uT, ph, gv, acc); break;
-      case 7: embed_accumulate<7>(G, g0, gs, nq, uT, ph, gv, acc); break;
-      default: embed_accumulate<8>(G, g0, gs, nq, uT, ph, gv, acc); break;
+      case 1: embed_accumulate<1, NE>(G, g0, gs, nq, uT, ph, gv, acc); break;
+      case 2: embed_accumulate<2, NE>(G, g0, gs, nq, uT, ph, gv, acc); break;
+      case 3: embed_accumulate<3, NE>(G, g0, gs, nq, uT, ph, gv, acc); break;
+      case 4: embed_accumulate<4, NE>(G, g0, gs, nq, uT, ph, gv, acc); break;
+      case 5: embed_accumulate<5, NE>(G, g0, gs, nq, uT, ph, gv, acc); break;
+      case 6: embed_accumulate<6, NE>(G, g0, gs, nq, uT, ph, gv, acc); break;
+      case 7: embed_accumulate<7, NE>(G, g0, gs, nq, uT, ph, gv, acc); break;
+      default: embed_accumulate<8, NE>(G, g0, gs, nq, uT, ph, gv, acc); break;
     }
   }
-#pragma unroll
-  for (int m = 0; m < kEmbChunk; ++m) red[ph][el][m] = acc[m];
   __syncthreads();
-  if (!inS) return;
 #pragma unroll
-  for (int k = 0; k < kEmbOwn; ++k) {
-    const int m = ph + kEmbPh * k;
-    if (m >= jb.nm) break;
-    float corr = 0.0f;
-    for (int q = 0; q < kEmbPh; ++q) corr += red[q][el][m];
-    float u = 0.0f;
+  for (int k = 0; k < NE; ++k)
 #pragma unroll
-    for (int sp = 0; sp < KS; ++sp) u += zown[k][sp];
-    const long base = (long)E.rows[jb.mem0 + m] * ld + e;
-    Z[base] = u - corr;
+    for (int m = 0; m < kEmbChunk; ++m) red[ph][el + kEmbE * k][m] = acc[k][m];
+  __syncthreads();
 #pragma unroll
-    for (int sp = 1; sp < KS; ++sp) Z[sp * zsplit + base] = 0.0f;
+  for (int k = 0; k < NE; ++k) {
+    if (!inS[k]) continue;
+#pragma unroll
+    for (int o = 0; o < kEmbOwn; ++o) {
+      const int m = ph + kEmbPh * o;
+      if (m >= jb.nm) break;
+      float corr = 0.0f;
+      for (int q = 0; q < kEmbPh; ++q) corr += red[q][el + kEmbE * k][m];
+      float u = 0.0f;
+#pragma unroll
+      for (int sp = 0; sp < KS; ++sp) u += zown[k][o][sp];
+      const long base = (long)E.rows[jb.mem0 + m] * ld + e[k];
+      Z[base] = u - corr;
+#pragma unroll
+      for (int sp = 1; sp < KS; ++sp) Z[sp * zsplit + base] = 0.0f;
+    }
   }
+}
+
+// Two unknowns per thread while that leaves a workgroup for every CU.
+static bool embed_wide(int mH, int njobs) {
+  return (long)((mH + 2 * kEmbE - 1) / (2 * kEmbE)) * njobs >= 256;
+}
+
+using EmbedKernel = void (*)(const EmbedJob*, const EmbedDev*, int, int, int, int, const PcgState*,
+                             CoarseSolveArgs);
+static EmbedKernel embed_kernel(int ksplit, bool wide) {
+  if (wide)
+    return ksplit == 1 ? k_embed_correct<1, 2>
+                       : (ksplit == 2 ? k_embed_correct<2, 2> : k_embed_correct<3, 2>);
+  return ksplit == 1 ? k_embed_correct<1, 1>
+                     : (ksplit == 2 ? k_embed_correct<2, 1> : k_embed_correct<3, 1>);
 }
 
 // With coarse_solve the launch also applies A_0^{-1} to the coarse right-hand
@@ -651,15 +706,16 @@ void launch_embed_fix(const ddeig_problem* P, const PcgState* st, hipStream_t s,
   if (P->nembjobs == 0) return;
   const DenseHost& H = P->dh;
   // the K split is 1..3 by construction (assemble)
-  auto kern = P->ksplit == 1 ? k_embed_correct<1> : (P->ksplit == 2 ? k_embed_correct<2>
-                                                                     : k_embed_correct<3>);
+  const bool wide = embed_wide(H.m, P->nembjobs);
+  auto kern = embed_kernel(P->ksplit, wide);
+  const int eb = wide ? 2 * kEmbE : kEmbE;
   CoarseSolveArgs cs{0, nullptr, nullptr, nullptr};
   int extra = 0;
   if (coarse_solve) {
     cs = CoarseSolveArgs{P->nsub, P->A0inv, P->crhs, P->cy};
     extra = (P->nsub + kBlock / 64 - 1) / (kBlock / 64);
   }
-  hipLaunchKernelGGL(kern, dim3((H.m + kEmbE - 1) / kEmbE + extra, P->nembjobs), dim3(kBlock), 0,
+  hipLaunchKernelGGL(kern, dim3((H.m + eb - 1) / eb + extra, P->nembjobs), dim3(kBlock), 0,
                      s, P->dEmbJobs, P->dEmb, H.ld, H.box.m[0], H.box.m[1], H.m, st, cs);
 }
 
@@ -713,10 +769,11 @@ void launch_gemm_tiles(const GemmTile* tiles, int ntiles, const GemmType* gt, in
 void launch_embed_jobs(const EmbedJob* jobs, int njobs, const EmbedDev* cls, int ksplit, int ld,
                        int hm0, int hm1, int mH, hipStream_t s) {
   if (njobs <= 0) return;
-  auto kern = ksplit == 1 ? k_embed_correct<1> : (ksplit == 2 ? k_embed_correct<2>
-                                                               : k_embed_correct<3>);
+  const bool wide = embed_wide(mH, njobs);
+  auto kern = embed_kernel(ksplit, wide);
+  const int eb = wide ? 2 * kEmbE : kEmbE;
   const CoarseSolveArgs none{0, nullptr, nullptr, nullptr};
-  hipLaunchKernelGGL(kern, dim3((mH + kEmbE - 1) / kEmbE, njobs), dim3(kBlock), 0, s, jobs, cls,
+  hipLaunchKernelGGL(kern, dim3((mH + eb - 1) / eb, njobs), dim3(kBlock), 0, s, jobs, cls,
                      ld, hm0, hm1, mH, nullptr, none);
 }
 
