@@ -360,11 +360,10 @@ __device__ __forceinline__ void extend_dense_body(const Geo& g, int delta, int c
   // NPT nodes per thread and pass (items it + u IPB): every load of them
   // first, then their sums
   constexpr unsigned IPB = kBig / kBlock;
-  constexpr bool XI = INL && PX == 1;  // the inline field's two weights and y0 values
   for (unsigned grp = bid; grp * NPT * IPB < items; grp += nblk) {
     bool okn[NPT], two[NPT];
     unsigned on[NPT];
-    double wan[NPT][2], yan[NPT][2], rkn[NPT], psn[NPT];
+    double wan[NPT][2], wbn[NPT][PX], yan[NPT][INL ? NC : 1], rkn[NPT], psn[NPT];
     float zsn[NPT][NC][KS];
 #pragma unroll
     for (int u = 0; u < NPT; ++u) {
@@ -382,21 +381,29 @@ __device__ __forceinline__ void extend_dense_body(const Geo& g, int delta, int c
         const int j0 = i[0] + 1 - g.ne * (int)fdiv((unsigned)(i[0] + 1), g.fne);
         const int j1 = PX == 2 ? t.i1 + 1 - g.ne * (int)fdiv((unsigned)(t.i1 + 1), g.fne) : t.i1;
         psn[u] = at_bytes(psi + (long)g.P[0] * (j1 + (long)g.P[1] * t.i2), 8u * j0);
-        if constexpr (XI) {
+        if constexpr (INL) {
+          // the inline field's weights per axis and its y0 values
           const double* w = &xc0[t.s0].w[0];
           wan[u][0] = at_bytes(w, (unsigned)sizeof(XCover) * tl);
           wan[u][1] = at_bytes(w + 1, (unsigned)sizeof(XCover) * tl);
-          yan[u][0] = at_bytes(cf + (pos.cw - 1), 8u * (cv.c0(0) - pos.cw));
-          yan[u][1] = at_bytes(cf + (pos.cw - 1), 8u * (cv.c0(1) - pos.cw));
-        } else if constexpr (!INL) {
+#pragma unroll
+          for (int q1 = 0; q1 < PX; ++q1) wbn[u][q1] = PX == 2 ? xc1[t.i1].w[q1] : 1.0;
+#pragma unroll
+          for (int q = 0; q < NC; ++q)
+            yan[u][q] = at_bytes(cf + (pos.cw - 1 + (PX == 2 ? (long)g.L * (cv.c1(q) - 1) : 0L)),
+                                 8u * (cv.c0(q) - pos.cw));
+        } else {
           yan[u][0] = at_bytes(cf + (PX == 1 ? (long)t.s0 : t.s0 + (long)N0 * t.i1), on[u]);
         }
       }
 #pragma unroll
-      for (int q = 0; q < NC; ++q)
+      for (int q = 0; q < NC; ++q) {
+        // (a line of one cell along axis 1: the same for the whole wave)
+        if (PX == 2 && q >= 2 && cv.clo1 == cv.chi1) continue;
 #pragma unroll
         for (int sp = 0; sp < KS; ++sp)
           zsn[u][q][sp] = at_bytes(da.Z + (sp * da.zsplit + pos.base[q >> 1]), 4u * pos.lane[q & 1]);
+      }
       rkn[u] = at_bytes(r + (t.s0 + N0 * t.line), on[u]);
     }
 #pragma unroll
@@ -411,18 +418,18 @@ __device__ __forceinline__ void extend_dense_body(const Geo& g, int delta, int c
     const double rk = rkn[u];
     double ps = psn[u], zc = 0.0;
     if (coarse) {
-      if constexpr (XI) {
+      if constexpr (INL && PX == 1) {
         // the weights of the one expanding axis (cover_weight for p = 1)
         zc = wan[u][0] * yan[u][0];
         if (two[u]) zc = fma(wan[u][1], yan[u][1], zc);
       } else if constexpr (INL) {
-        const XCover* xc[2] = {xc0, xc1};
+        // (cover_weight for p = 2)
 #pragma unroll
         for (int q = 0; q < NC; ++q) {
           if (!cv.val(q)) continue;
-          const int c[3] = {cv.c0(q), PX == 2 ? cv.c1(q) : 0, 0};
-          const int which[2] = {q & 1, q >> 1};
-          zc += cover_weight(g, delta, pu, xc, c, i, which) * cf[(c[0] - 1) + g.L * (cv.c1(q) - 1)];
+          const int c[3] = {cv.c0(q), cv.c1(q), 0};
+          const double w = pu == 1 ? pu_weight(g, delta, pu, c, i) : wan[u][q & 1] * wbn[u][q >> 1];
+          zc += w * yan[u][q];
         }
       } else {
         zc = yan[u][0];
