@@ -2299,13 +2299,12 @@ ddeig_status ddeig_inverse_iteration(ddeig_problem* P, double* x, double tol_x, 
 
 struct ddeig_batch {
   std::vector<ddeig_problem*> P;
-  hipStream_t stream = nullptr, aux = nullptr, cap = nullptr;
-  hipEvent_t ev_fork = nullptr, ev_join = nullptr;
+  hipStream_t stream = nullptr, cap = nullptr;
   int n = 0, local_prec = 0, ksplit = 1, order = 0;
   int ld = 0, hm0 = 0, hm1 = 0, mH = 0;
   std::vector<ddeig::InstDev> inst;
   ddeig::InstDev* dInst = nullptr;
-  ddeig::BlockMap bm_st{}, bm_node{}, bm_crhs{}, bm_csol{}, bm_cf{};
+  ddeig::BlockMap bm_st{}, bm_node{}, bm_crhs{}, bm_csol{};
   ddeig::GemmTile* dTiles = nullptr;
   int ntiles = 0;
   ddeig::GemmType* dGt = nullptr;
@@ -2415,20 +2414,23 @@ void batch_upload_inst(ddeig_batch* B) {
   check_hip(hipStreamSynchronize(B->stream), "hipStreamSynchronize");
 }
 
+// The local solves of every instance; R_0 r rides in the GEMM's launch, A_0^{-1} c
+// in the correction's (32 instances of 16..256 subdomains: 227.4 ms a solve with
+// the two and the coarse field on a second stream, 221.5 so).
+void batch_local(ddeig_batch* B, hipStream_t s) {
+  auto bc = [&](const ddeig::BlockMap& bm) { return ddeig::BatchCoarse{bm.nblocks, B->dInst, bm.map}; };
+  launch_gemm_tiles(B->dTiles, B->ntiles, B->dGt, B->local_prec, s, B->tile_rows, B->fold,
+                    bc(B->bm_crhs));
+  launch_embed_jobs(B->dEmbJobs, B->nembjobs, B->dEmb, B->zsets, B->ld, B->hm0, B->hm1, B->mH,
+                    bc(B->bm_csol), s);
+}
+
 // One grouped PCG iteration k over every instance (see pcg_run for the kernels),
 // issued on stream s (the batch's stream, or its capture stream).
 void batch_iteration(ddeig_batch* B, int k, int maxit, hipStream_t s) {
   launch_b_stencil_dir(B->dInst, B->bm_st, k, s);
   launch_b_restrict(B->dInst, B->bm_node, k, s);
-  check_hip(hipEventRecord(B->ev_fork, s), "record fork");
-  check_hip(hipStreamWaitEvent(B->aux, B->ev_fork, 0), "wait fork");
-  launch_gemm_tiles(B->dTiles, B->ntiles, B->dGt, B->local_prec, s, B->tile_rows, B->fold);
-  launch_embed_jobs(B->dEmbJobs, B->nembjobs, B->dEmb, B->zsets, B->ld, B->hm0, B->hm1, B->mH, s);
-  launch_b_coarse_rhs(B->dInst, B->bm_crhs, B->aux);
-  launch_b_coarse_solve(B->dInst, B->bm_csol, B->aux);
-  launch_b_coarse_field(B->dInst, B->bm_cf, B->aux);
-  check_hip(hipEventRecord(B->ev_join, B->aux), "record join");
-  check_hip(hipStreamWaitEvent(s, B->ev_join, 0), "wait join");
+  batch_local(B, s);
   launch_b_extend(B->dInst, B->bm_node, k, maxit, B->zsets, s);
 }
 
@@ -2446,16 +2448,7 @@ void batch_pcg(ddeig_batch* B, const std::vector<int>& active, const std::vector
   if (act != nullptr) {
     launch_b_restrict_start(B->dInst, B->bm_node, act, s);
     launch_b_pcg_init(B->dInst, B->n, act, rtol, s);
-    check_hip(hipEventRecord(B->ev_fork, s), "record fork");
-    check_hip(hipStreamWaitEvent(B->aux, B->ev_fork, 0), "wait fork");
-    launch_gemm_tiles(B->dTiles, B->ntiles, B->dGt, B->local_prec, s, B->tile_rows, B->fold);
-    launch_embed_jobs(B->dEmbJobs, B->nembjobs, B->dEmb, B->zsets, B->ld, B->hm0, B->hm1, B->mH,
-                      s);
-    launch_b_coarse_rhs(B->dInst, B->bm_crhs, B->aux);
-    launch_b_coarse_solve(B->dInst, B->bm_csol, B->aux);
-    launch_b_coarse_field(B->dInst, B->bm_cf, B->aux);
-    check_hip(hipEventRecord(B->ev_join, B->aux), "record join");
-    check_hip(hipStreamWaitEvent(s, B->ev_join, 0), "wait join");
+    batch_local(B, s);
     launch_b_extend(B->dInst, B->bm_node, 0, maxit, B->zsets, s, 0);
   } else {
     for (int j = 0; j < B->n; ++j) {
@@ -2552,10 +2545,7 @@ void batch_free(ddeig_batch* B) {
   if (B->stream) (void)hipStreamSynchronize(B->stream);
   for (auto& kv : B->graphs) (void)hipGraphExecDestroy(kv.second);
   for (void* p : B->allocs) (void)hipFree(p);
-  if (B->aux) (void)hipStreamDestroy(B->aux);
   if (B->cap) (void)hipStreamDestroy(B->cap);
-  if (B->ev_fork) (void)hipEventDestroy(B->ev_fork);
-  if (B->ev_join) (void)hipEventDestroy(B->ev_join);
   if (B->hAct) (void)hipHostFree(B->hAct);
   if (B->hst) (void)hipHostFree(B->hst);
   for (auto& e : B->ev_st)
@@ -2617,11 +2607,8 @@ ddeig_status ddeig_batch_create(ddeig_problem* const* probs, int n, int flags, d
     B->hm0 = P0->dh.box.m[0];
     B->hm1 = P0->dh.box.m[1];
     B->mH = P0->dh.m;
-    check_hip(hipStreamCreateWithFlags(&B->aux, hipStreamNonBlocking), "create batch stream");
     if (B->use_graphs)
       check_hip(hipStreamCreateWithFlags(&B->cap, hipStreamNonBlocking), "create capture stream");
-    check_hip(hipEventCreateWithFlags(&B->ev_fork, hipEventDisableTiming), "create event");
-    check_hip(hipEventCreateWithFlags(&B->ev_join, hipEventDisableTiming), "create event");
     int ks_max = 3;
     for (auto* P : B->P) ks_max = std::min(ks_max, P->ksplit);
     // grouped-GEMM tiles: a small autotuner times every K split the Z buffers
@@ -2717,7 +2704,7 @@ ddeig_status ddeig_batch_create(ddeig_problem* const* probs, int n, int flags, d
     }
     // instance descriptors and block maps
     B->inst.resize(n);
-    std::vector<int> c_st(n), c_node(n), c_crhs(n), c_csol(n), c_cf(n);
+    std::vector<int> c_st(n), c_node(n), c_crhs(n), c_csol(n);
     for (int j = 0; j < n; ++j) {
       ddeig_problem* P = B->P[j];
       const ddeig::DenseHost& H = P->dh;
@@ -2727,7 +2714,6 @@ ddeig_status ddeig_batch_create(ddeig_problem* const* probs, int n, int flags, d
       d.pu = P->opt.pu;
       d.nsub = P->nsub;
       d.nb_node = ddeig::node_grid_dense(P->g);  // the single problem's grid (2 nodes per thread)
-      d.nb_cf = ddeig::coarse_field_grid(P->g);
       d.hist_cap = P->hist_cap;
       d.tabAs = P->tabAs;
       d.x = P->u;
@@ -2747,7 +2733,6 @@ ddeig_status ddeig_batch_create(ddeig_problem* const* probs, int n, int flags, d
       d.da = ddeig::DenseArgs{H.Rh, H.Rl, H.Z, (long)H.mp * H.ld, H.ld, B->zsets, H.box.m[0],
                               H.box.m[1]};
       d.psi = P->psi;
-      d.cf = P->cfield;
       d.types = P->dTypes;
       d.subs = P->dSubs;
       d.crhs = P->crhs;
@@ -2770,14 +2755,12 @@ ddeig_status ddeig_batch_create(ddeig_problem* const* probs, int n, int flags, d
       c_node[j] = d.nb_node;
       c_crhs[j] = P->nsub;
       c_csol[j] = (P->nsub + kBlock / 64 - 1) / (kBlock / 64);
-      c_cf[j] = d.nb_cf;
     }
     B->dInst = balloc<ddeig::InstDev>(B, n);
     B->bm_st = make_map(B, c_st);
     B->bm_node = make_map(B, c_node);
     B->bm_crhs = make_map(B, c_crhs);
     B->bm_csol = make_map(B, c_csol);
-    B->bm_cf = make_map(B, c_cf);
     B->dStates = balloc<ddeig::PcgState>(B, n);
     B->hStates.resize(n);
     B->dRes = balloc<double>(B, 2 * (size_t)n);

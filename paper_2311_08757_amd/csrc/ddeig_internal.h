@@ -234,6 +234,16 @@ struct CoarseSolveArgs {
   double* y;
 };
 
+// The same for a batch: n entries (instance, index within it) of a map, whose
+// index is a subdomain (right-hand side, a wave each) or a group of four rows of
+// the instance's coarse inverse (a workgroup each).
+struct InstDev;
+struct BatchCoarse {
+  int n;
+  const InstDev* I;
+  const int2* map;
+};
+
 // A group of at most 64 members of one class in the batched chain solves:
 // class, first member within the class, count, and the group's first member
 // in the partial-product buffer (members of all classes numbered in order); dir:
@@ -273,7 +283,6 @@ struct InstDev {
   Geo g;
   int delta, pu, nsub;
   int nb_node;  // blocks of the node-parallel restriction / extension
-  int nb_cf;    // blocks of the coarse field
   int sty;      // rows of the 2-D stencil tiles (stencil2d_ty)
   int hist_cap;
   const double* tabAs;
@@ -284,7 +293,6 @@ struct InstDev {
   Red gam, rr, rz;
   DenseArgs da;
   const double* psi;
-  double* cf;
   const TypeDev* types;
   const SubDev* subs;
   double* crhs;
@@ -538,18 +546,15 @@ void build_coarse_matrix(ddeig_problem* P, double* A0, hipStream_t s);
 // grouped launches over the instances of a batch (one PCG iteration k)
 int node_grid(const Geo& g);
 int node_grid_dense(const Geo& g);
-int coarse_field_grid(const Geo& g);
 void launch_b_stencil_dir(const InstDev* I, const BlockMap& bm, int k, hipStream_t s);
 void launch_b_restrict(const InstDev* I, const BlockMap& bm, int k, hipStream_t s);
 void launch_b_extend(const InstDev* I, const BlockMap& bm, int k, int maxit, int ksplit,
                      hipStream_t s, int check = 1);
-void launch_b_coarse_rhs(const InstDev* I, const BlockMap& bm, hipStream_t s);
-void launch_b_coarse_solve(const InstDev* I, const BlockMap& bm, hipStream_t s);
-void launch_b_coarse_field(const InstDev* I, const BlockMap& bm, hipStream_t s);
 void launch_gemm_tiles(const GemmTile* tiles, int ntiles, const GemmType* gt, int local_prec,
-                       hipStream_t s, int tile_rows = 128, bool fold = false);
+                       hipStream_t s, int tile_rows = 128, bool fold = false,
+                       const BatchCoarse& bc = BatchCoarse{0, nullptr, nullptr});
 void launch_embed_jobs(const EmbedJob* jobs, int njobs, const EmbedDev* cls, int ksplit, int ld,
-                       int hm0, int hm1, int mH, hipStream_t s);
+                       int hm0, int hm1, int mH, const BatchCoarse& bc, hipStream_t s);
 void launch_b_states(const InstDev* I, int n, PcgState* out, int mark_done, hipStream_t s);
 void launch_b_restrict_start(const InstDev* I, const BlockMap& bm, const int* act, hipStream_t s);
 void launch_b_pcg_init(const InstDev* I, int n, const int* act, double rtol, hipStream_t s);

@@ -27,6 +27,8 @@
 // two stages of global loads in flight and LDS double buffering, split-K
 // partial tiles summed in a fixed order by the extension kernel.  Classes with at most kGemvMax members (the
 // boundary cells) use a streaming matrix-vector kernel instead.
+#include <type_traits>
+
 #include "k_common.h"
 #include "k_coarse.h"
 
@@ -113,9 +115,10 @@ typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
 // registers (317 without: one workgroup per CU, 32 instances of 16..256
 // subdomains 258 ms against 244).
 template <bool RLO, bool ALO, int MI = 2, bool BND = false, bool FOLD = false>
-__global__ void __launch_bounds__(kBlock, FOLD ? 2 : 1)
+__global__ void __launch_bounds__(kBlock, BND ? 2 : 1)
     k_dense_gemm(const GemmTile* __restrict__ tiles, const GemmType* __restrict__ gtypes,
-                 const PcgState* __restrict__ st, int ntiles, CoarseRhsArgs ca) {
+                 const PcgState* __restrict__ st, int ntiles,
+                 std::conditional_t<BND, BatchCoarse, CoarseRhsArgs> ca) {
   using C = GemmCfg<RLO, ALO, MI>;
   constexpr int BK = C::BK, LDK = C::LDK, NR = C::NR, NOP = C::NOP, NV = C::NV, NVT = C::NVT;
   constexpr int NVR = C::NVR, NS = C::NS, WPS = C::WPS;
@@ -124,10 +127,18 @@ __global__ void __launch_bounds__(kBlock, FOLD ? 2 : 1)
   __shared__ __align__(16) __bf16 sm[2][NOP][kTM * LDK];
   if (st != nullptr && st->done) return;
   if ((int)blockIdx.x >= ntiles) {
-    // (its few doubles of LDS are the staging buffer's: with LDS of their own
-    // the bf16x3 kernel would need 40 bytes more than half a CU's)
-    coarse_rhs_body(ca.g, nullptr, ca.r, ca.types, ca.subs, ca.crhs, blockIdx.x - ntiles,
-                    reinterpret_cast<double*>(&sm[0][0][0]));
+    if constexpr (BND) {
+      const int b = ((int)blockIdx.x - ntiles) * (kBlock / 64) + (int)(threadIdx.x >> 6);
+      if (b >= ca.n) return;
+      const int2 m = ca.map[b];
+      const InstDev& d = ca.I[m.x];
+      coarse_rhs_wave(d.g, d.st, d.r, d.types, d.subs, d.crhs, m.y);
+    } else {
+      // (its few doubles of LDS are the staging buffer's: with LDS of their own
+      // the bf16x3 kernel would need 40 bytes more than half a CU's)
+      coarse_rhs_body(ca.g, nullptr, ca.r, ca.types, ca.subs, ca.crhs, blockIdx.x - ntiles,
+                      reinterpret_cast<double*>(&sm[0][0][0]));
+    }
     return;
   }
   const GemmTile t = tiles[blockIdx.x];
@@ -553,12 +564,21 @@ template <int KS, int NE>
 // the compiler hoists LDS reads and the kernel runs at 3 waves, markedly slower.
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4)))
 k_embed_correct(const EmbedJob* __restrict__ jobs, const EmbedDev* __restrict__ cls, int ld,
-                int hm0, int hm1, int mH, const PcgState* __restrict__ st, CoarseSolveArgs cs) {
+                int hm0, int hm1, int mH, const PcgState* __restrict__ st, CoarseSolveArgs cs,
+                int njobs, BatchCoarse bc) {
   __shared__ __align__(16) float uT[kEmbUT];  // uT[t kEmbChunk + m] = u_T of member m
   constexpr int EB = kEmbE * NE, NG = kEmbG / (NE * NE);
   static_assert(kEmbPh * EB * kEmbChunk <= kEmbUT, "the phase sums take the place of u_T");
   float (*red)[EB][kEmbChunk] = reinterpret_cast<float (*)[EB][kEmbChunk]>(uT);
   const int ychunks = (mH + EB - 1) / EB;
+  if ((int)blockIdx.y >= njobs) {
+    const int b = ((int)blockIdx.y - njobs) * ychunks + (int)blockIdx.x;
+    if (b >= bc.n) return;
+    const int2 m = bc.map[b];
+    const InstDev& d = bc.I[m.x];
+    coarse_solve_body(d.nsub, d.st, d.A0inv, d.crhs, d.cy, m.y);
+    return;
+  }
   if ((int)blockIdx.x >= ychunks) {
     if (blockIdx.y == 0) coarse_solve_body(cs.n, st, cs.A0inv, cs.c, cs.y, blockIdx.x - ychunks);
     return;
@@ -690,7 +710,7 @@ static bool embed_wide(int mH, int njobs) {
 }
 
 using EmbedKernel = void (*)(const EmbedJob*, const EmbedDev*, int, int, int, int, const PcgState*,
-                             CoarseSolveArgs);
+                             CoarseSolveArgs, int, BatchCoarse);
 static EmbedKernel embed_kernel(int ksplit, bool wide) {
   if (wide)
     return ksplit == 1 ? k_embed_correct<1, 2>
@@ -716,7 +736,8 @@ void launch_embed_fix(const ddeig_problem* P, const PcgState* st, hipStream_t s,
     extra = (P->nsub + kBlock / 64 - 1) / (kBlock / 64);
   }
   hipLaunchKernelGGL(kern, dim3((H.m + eb - 1) / eb + extra, P->nembjobs), dim3(kBlock), 0,
-                     s, P->dEmbJobs, P->dEmb, H.ld, H.box.m[0], H.box.m[1], H.m, st, cs);
+                     s, P->dEmbJobs, P->dEmb, H.ld, H.box.m[0], H.box.m[1], H.m, st, cs,
+                     P->nembjobs, BatchCoarse{0, nullptr, nullptr});
 }
 
 // Batches of more rows: 128 x 128 MFMA tiles.  local_prec 2 (bf16x3):
@@ -757,24 +778,27 @@ static auto batch_gemm_kernel(int local_prec, int tile_rows) {
 }
 
 void launch_gemm_tiles(const GemmTile* tiles, int ntiles, const GemmType* gt, int local_prec,
-                       hipStream_t s, int tile_rows, bool fold) {
+                       hipStream_t s, int tile_rows, bool fold, const BatchCoarse& bc) {
   if (ntiles <= 0) return;
-  CoarseRhsArgs none{};
-  none.n = 0;
+  constexpr int wpb = kBlock / 64;
   auto kern = fold ? batch_gemm_kernel<true>(local_prec, tile_rows)
                    : batch_gemm_kernel<false>(local_prec, tile_rows);
-  hipLaunchKernelGGL(kern, dim3(ntiles), dim3(kBlock), 0, s, tiles, gt, nullptr, ntiles, none);
+  hipLaunchKernelGGL(kern, dim3(ntiles + (bc.n + wpb - 1) / wpb), dim3(kBlock), 0, s, tiles, gt,
+                     nullptr, ntiles, bc);
 }
 
+// With bc the launch also applies the instances' coarse inverses, in rows of the
+// grid after the jobs'.
 void launch_embed_jobs(const EmbedJob* jobs, int njobs, const EmbedDev* cls, int ksplit, int ld,
-                       int hm0, int hm1, int mH, hipStream_t s) {
-  if (njobs <= 0) return;
+                       int hm0, int hm1, int mH, const BatchCoarse& bc, hipStream_t s) {
   const bool wide = embed_wide(mH, njobs);
   auto kern = embed_kernel(ksplit, wide);
-  const int eb = wide ? 2 * kEmbE : kEmbE;
+  const int eb = wide ? 2 * kEmbE : kEmbE, chunks = (mH + eb - 1) / eb;
+  const int rows = njobs + (bc.n + chunks - 1) / chunks;
+  if (rows <= 0) return;
   const CoarseSolveArgs none{0, nullptr, nullptr, nullptr};
-  hipLaunchKernelGGL(kern, dim3((mH + eb - 1) / eb, njobs), dim3(kBlock), 0, s, jobs, cls,
-                     ld, hm0, hm1, mH, nullptr, none);
+  hipLaunchKernelGGL(kern, dim3(chunks, rows), dim3(kBlock), 0, s, jobs, cls, ld, hm0, hm1, mH,
+                     nullptr, none, njobs, bc);
 }
 
 void launch_dense_gemv(const ddeig_problem* P, const PcgState* st, hipStream_t s) {

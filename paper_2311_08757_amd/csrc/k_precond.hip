@@ -867,11 +867,6 @@ void build_coarse_matrix(ddeig_problem* P, double* A0, hipStream_t s) {
   launch_symmetrise(A0, N, s);
 }
 
-int coarse_field_grid(const Geo& g) {
-  const long npts = g.p == 1 ? (long)g.N[0] : (long)g.N[0] * g.N[1];
-  return (int)std::max<long>(1, std::min<long>((npts + kBlock - 1) / kBlock, 4096));
-}
-
 // Grouped kernels of PCG iteration k over the instances of a batch (2-D,
 // one expanding axis, dense local solves): block b runs block map[b].y of
 // instance map[b].x with that instance's operands, CG state and partials.
@@ -948,87 +943,8 @@ k_b_extend(const InstDev* __restrict__ I, const int2* __restrict__ map, int k, i
   const int2 m = map[blockIdx.x];
   const InstDev& d = I[m.x];
   const CheckArgs chk{check, k, maxit, d.hist_cap, d.rr, d.hist};
-  extend_dense_body<1, KS, false, false, 2>(d.g, d.delta, 1, d.st, chk, d.da, d.psi, d.cf, d.r,
-                                            d.z, 1, d.rz, m.y, d.nb_node);
-}
-
-// The coarse right-hand side (R_0 r)_i of one subdomain by one wave, in the
-// order of coarse_rhs_body's workgroup of kBlock threads: lane l keeps the
-// partial sums of that workgroup's threads l + 64 w (w < kBlock / 64), takes
-// each through the same shuffle tree and adds the wave sums to 0 in w order,
-// so the two give identical bits.  A batch has thousands of subdomains; a
-// wave each needs no workgroup barrier and holds fewer of the CUs that the
-// GEMM on the other stream is using (64 instances: 57 -> 75 us for this
-// kernel, 91 -> 78 us for the overlapping GEMM, 456 -> 446 ms per solve).
-__device__ __forceinline__ void coarse_rhs_wave(const Geo& g, const PcgState* __restrict__ st,
-                                                const double* __restrict__ r,
-                                                const TypeDev* __restrict__ types,
-                                                const SubDev* __restrict__ subs,
-                                                double* __restrict__ crhs, int sid) {
-  constexpr int U = 8, NW = kBlock / 64;
-  if (st != nullptr && st->done) return;
-  const int lane = threadIdx.x & 63;
-  const SubDev sd = subs[sid];
-  const TypeDev td = types[sd.type];
-  const int m0 = td.m[0], m1 = td.m[1];
-  const int mtot = m0 * m1 * td.m[2];
-  double acc[NW];
-#pragma unroll
-  for (int w = 0; w < NW; ++w) acc[w] = 0.0;
-  for (int base = 0; base < mtot; base += U * kBlock) {
-    // every load of the pass first (the steps past the subdomain's end add
-    // only zeros and are skipped), then the sums in the workgroup's order
-    double ph[U][NW], rv[U][NW];
-#pragma unroll
-    for (int q = 0; q < U; ++q)
-#pragma unroll
-      for (int w = 0; w < NW; ++w) {
-        const int e = base + q * kBlock + 64 * w + lane;
-        ph[q][w] = rv[q][w] = 0.0;
-        if (base + q * kBlock < mtot && e < mtot) {
-          const int line = (int)fdiv((unsigned)e, td.fm0);
-          const int u0 = e - line * m0;
-          const int u2 = line / m1, u1 = line - u2 * m1;
-          ph[q][w] = td.phi[e];
-          rv[q][w] = r[(sd.o[0] + u0) +
-                       (long)g.N[0] * ((sd.o[1] + u1) + (long)g.N[1] * (sd.o[2] + u2))];
-        }
-      }
-#pragma unroll
-    for (int q = 0; q < U; ++q)
-#pragma unroll
-      for (int w = 0; w < NW; ++w) acc[w] += ph[q][w] * rv[q][w];
-  }
-  double t = 0.0;
-#pragma unroll
-  for (int w = 0; w < NW; ++w) {
-    double v = acc[w];
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-    t += v;
-  }
-  if (lane == 0) crhs[sid] = t;
-}
-
-// One wave per (instance, subdomain) entry of the map.
-__global__ void __launch_bounds__(kBlock) k_b_coarse_rhs(const InstDev* __restrict__ I,
-                                                         const int2* __restrict__ map, int nmap) {
-  const int b = blockIdx.x * (kBlock / 64) + (int)(threadIdx.x >> 6);
-  if (b >= nmap) return;
-  const int2 m = map[b];
-  const InstDev& d = I[m.x];
-  coarse_rhs_wave(d.g, d.st, d.r, d.types, d.subs, d.crhs, m.y);
-}
-
-__global__ void k_b_coarse_solve(const InstDev* __restrict__ I, const int2* __restrict__ map) {
-  const int2 m = map[blockIdx.x];
-  const InstDev& d = I[m.x];
-  coarse_solve_body(d.nsub, d.st, d.A0inv, d.crhs, d.cy, m.y);
-}
-
-__global__ void k_b_coarse_field(const InstDev* __restrict__ I, const int2* __restrict__ map) {
-  const int2 m = map[blockIdx.x];
-  const InstDev& d = I[m.x];
-  coarse_field_body<1>(d.g, d.delta, d.pu, d.st, d.xc0, nullptr, d.cy, d.cf, m.y, d.nb_cf);
+  extend_dense_body<1, KS, false, true, 2>(d.g, d.delta, 1, d.st, chk, d.da, d.psi, d.cy, d.r, d.z,
+                                           1, d.rz, m.y, d.nb_node, d.pu, d.xc0);
 }
 
 // Copies every instance's CG state into out[] (the host reads them with one
@@ -1067,20 +983,6 @@ void launch_b_normalise(const InstDev* I, const BlockMap& bm, const int* act, hi
 
 void launch_b_finish_norm(const InstDev* I, int n, const int* act, double* res, hipStream_t s) {
   hipLaunchKernelGGL(k_b_finish_norm, dim3(n), dim3(kBlock), 0, s, I, act, res);
-}
-
-void launch_b_coarse_rhs(const InstDev* I, const BlockMap& bm, hipStream_t s) {
-  constexpr int wpb = kBlock / 64;
-  hipLaunchKernelGGL(k_b_coarse_rhs, dim3((bm.nblocks + wpb - 1) / wpb), dim3(kBlock), 0, s, I,
-                     bm.map, bm.nblocks);
-}
-
-void launch_b_coarse_solve(const InstDev* I, const BlockMap& bm, hipStream_t s) {
-  hipLaunchKernelGGL(k_b_coarse_solve, dim3(bm.nblocks), dim3(kBlock), 0, s, I, bm.map);
-}
-
-void launch_b_coarse_field(const InstDev* I, const BlockMap& bm, hipStream_t s) {
-  hipLaunchKernelGGL(k_b_coarse_field, dim3(bm.nblocks), dim3(kBlock), 0, s, I, bm.map);
 }
 
 void launch_b_states(const InstDev* I, int n, PcgState* out, int mark_done, hipStream_t s) {
