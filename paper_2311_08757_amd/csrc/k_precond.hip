@@ -382,12 +382,18 @@ __device__ __forceinline__ void extend_dense_body(const Geo& g, int delta, int c
         const int j1 = PX == 2 ? t.i1 + 1 - g.ne * (int)fdiv((unsigned)(t.i1 + 1), g.fne) : t.i1;
         psn[u] = at_bytes(psi + (long)g.P[0] * (j1 + (long)g.P[1] * t.i2), 8u * j0);
         if constexpr (INL) {
-          // the inline field's weights per axis and its y0 values
-          const double* w = &xc0[t.s0].w[0];
-          wan[u][0] = at_bytes(w, (unsigned)sizeof(XCover) * tl);
-          wan[u][1] = at_bytes(w + 1, (unsigned)sizeof(XCover) * tl);
+          // the inline field's weights per axis (equal ones need no table) and
+          // its y0 values
+          wan[u][0] = wan[u][1] = two[u] ? 0.5 : 1.0;
 #pragma unroll
-          for (int q1 = 0; q1 < PX; ++q1) wbn[u][q1] = PX == 2 ? xc1[t.i1].w[q1] : 1.0;
+          for (int q1 = 0; q1 < PX; ++q1) wbn[u][q1] = PX == 2 && cv.clo1 < cv.chi1 ? 0.5 : 1.0;
+          if (pu != 0) {
+            const double* w = &xc0[t.s0].w[0];
+            wan[u][0] = at_bytes(w, (unsigned)sizeof(XCover) * tl);
+            wan[u][1] = at_bytes(w + 1, (unsigned)sizeof(XCover) * tl);
+#pragma unroll
+            for (int q1 = 0; q1 < PX; ++q1) wbn[u][q1] = PX == 2 ? xc1[t.i1].w[q1] : 1.0;
+          }
 #pragma unroll
           for (int q = 0; q < NC; ++q)
             yan[u][q] = at_bytes(cf + (pos.cw - 1 + (PX == 2 ? (long)g.L * (cv.c1(q) - 1) : 0L)),
@@ -692,7 +698,9 @@ __global__ void __launch_bounds__(kBig) k_extend(Geo g, int delta, int pu, int c
       b[q] = at_bytes(sb + sw, (unsigned)sizeof(SubBase) * sl);
       const int c[3] = {cv.c0(q), PX == 2 ? cv.c1(q) : 0, 0};
       const int which[2] = {q & 1, q >> 1};
-      wc[q] = (coarse || ras) && cv.val(q) ? cover_weight(g, delta, pu, xc, c, i, which) : 1.0;
+      // (equal weights need no table)
+      wc[q] = (cv.clo0 < cv.chi0 ? 0.5 : 1.0) * (PX == 2 && cv.clo1 < cv.chi1 ? 0.5 : 1.0);
+      if (pu != 0 && (coarse || ras) && cv.val(q)) wc[q] = cover_weight(g, delta, pu, xc, c, i, which);
       yc[q] = coarse ? at_bytes(y0 + sw, 8u * sl) : 0.0;
     }
     const double rk = at_bytes(r + k0, 8u * tl);
