@@ -333,8 +333,9 @@ ddeig_status ddeig_profile_kernel(ddeig_problem* P, int which, int reps, const d
  * the direction update (p = z + beta p, q = A_sigma p, p.q), 1 the restriction
  * with the update of x and r (||r||^2), 2 the local solves (the MFMA GEMM over
  * all subdomains, carrying R_0 r when the coarse space rides in the dense
- * launches; or the block-chain solves), 3 the clipped-class correction with
- * the coarse solve (dense local solves; 0 otherwise), 4 the extension with the
+ * launches; or the block-chain solves, carrying it when they are 2-D row
+ * solves), 3 the clipped-class correction with the coarse solve (dense local
+ * solves), the coarse solve (2-D row solves) or 0, 4 the extension with the
  * stopping test and r.z (with the wait for the coarse correction when that
  * runs on the second stream).  Uses the problem's internal vectors (any
  * earlier solve state is overwritten); b: n_dof device values.  Needs the

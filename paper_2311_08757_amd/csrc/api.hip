@@ -392,8 +392,9 @@ bool fallback_fp32(ddeig_problem* P) {
   return true;
 }
 
-// restrict -> {local solves (+ clipped-class correction) | coarse solve on the
-// second stream} -> extend.  xr (nullable) fuses the CG update of x and r into the
+// restrict -> local solves (+ clipped-class correction) with the coarse solve ->
+// extend.  The coarse space rides in the dense launches or in 2-D row solves;
+// beside the other local solves it runs on the second stream.  xr (nullable) fuses the CG update of x and r into the
 // restriction (partials of ||r||^2 into *rr); chk (nullable) folds the PCG
 // stopping test into the extension.  flags (kPrec*; -1: the problem's additive
 // Schwarz preconditioner) selects the parts; the coarse correction alone runs
@@ -459,7 +460,7 @@ struct PcgOut {
 // PCG on A_sigma x = b (x holds x0).  One iteration is four kernels on the
 // library stream: the stencil with the direction update, the restriction with
 // the x / r update, the local solves and the extension with the stopping test
-// (plus the coarse solve on the second stream).  `batch` iterations are queued
+// (plus the coarse solve, see precond_apply).  `batch` iterations are queued
 // between host checks of the device state.
 PcgOut pcg_run(ddeig_problem* P, const double* b, double* x, double rtol, int maxit) {
   const hipStream_t s = P->stream;
@@ -1223,9 +1224,9 @@ ddeig_status ddeig_assemble(const ddeig_geometry* geom, double h, const ddeig_po
         // 64-row tiles (the same sums) while they fit one to a CU: they leave
         // fewer CUs idle and each has half the rows to stage and multiply
         // (256 subdomains of 35 x 31 unknowns in bf16x3, 54 tiles of 128 rows:
-        // 14.1 us, 10.4 us as 108 of 64).  More than one to a CU would read the inverse twice
-        // through the caches for nothing (71 x 63 unknowns in bf16, 210 tiles:
-        // 17.7 us, 21.0 us as 420).
+        // 14.1 us, 10.4 us as 108 of 64).  More than one to a CU would read the
+        // inverse twice through the caches for nothing (71 x 63 unknowns in
+        // bf16, 210 tiles: 17.7 us, 21.0 us as 420).
         P->tile_rows = (nsub + 63) / 64 * (H.ld / 128) * P->ksplit <= 256 ? 64 : 128;
         for (int sp = 0; sp < P->ksplit; ++sp) {
           const int kb0 = 2 * (int)((long)npair * sp / P->ksplit);
@@ -2415,8 +2416,8 @@ void batch_upload_inst(ddeig_batch* B) {
 }
 
 // The local solves of every instance; R_0 r rides in the GEMM's launch, A_0^{-1} c
-// in the correction's (32 instances of 16..256 subdomains: 227.4 ms a solve with
-// the two and the coarse field on a second stream, 221.5 so).
+// in the correction's (32 instances of 16..256 subdomains: 221.5 ms a solve; with
+// these two and the coarse field on a second stream 227.4).
 void batch_local(ddeig_batch* B, hipStream_t s) {
   auto bc = [&](const ddeig::BlockMap& bm) { return ddeig::BatchCoarse{bm.nblocks, B->dInst, bm.map}; };
   launch_gemm_tiles(B->dTiles, B->ntiles, B->dGt, B->local_prec, s, B->tile_rows, B->fold,

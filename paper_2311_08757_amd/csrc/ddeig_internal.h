@@ -347,7 +347,8 @@ struct ddeig_problem {
   ddeig_options opt;
   hipStream_t stream;
   int device = 0;  // the device current at ddeig_assemble
-  // second stream (default priority) for work that overlaps the local solves
+  // second stream (default priority) for the coarse space beside 3-D chain solves
+  // (and 2-D ones without row solves)
   hipStream_t aux = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   // CG state copies of the last two blocks of queued iterations (pinned host
