@@ -1223,8 +1223,8 @@ ddeig_status ddeig_assemble(const ddeig_geometry* geom, double h, const ddeig_po
         const int npair = H.ld / bk / 2;
         // 64-row tiles (the same sums) while they fit one to a CU: they leave
         // fewer CUs idle and each has half the rows to stage and multiply
-        // (256 subdomains of 35 x 31 unknowns in bf16x3, 54 tiles of 128 rows:
-        // 14.1 us, 10.4 us as 108 of 64).  More than one to a CU would read the
+        // (101 subdomains of 35 x 29 unknowns in bf16x3, 24 tiles of 128 rows:
+        // 14.1 us, 10.4 us as 48 of 64).  More than one to a CU would read the
         // inverse twice through the caches for nothing (71 x 63 unknowns in
         // bf16, 210 tiles: 17.7 us, 21.0 us as 420).
         P->tile_rows = (nsub + 63) / 64 * (H.ld / 128) * P->ksplit <= 256 ? 64 : 128;

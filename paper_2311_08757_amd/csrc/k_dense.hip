@@ -788,17 +788,22 @@ void launch_gemm_tiles(const GemmTile* tiles, int ntiles, const GemmType* gt, in
 }
 
 // With bc the launch also applies the instances' coarse inverses, in rows of the
-// grid after the jobs'.
+// grid after the jobs' (where the grid has no room for them, in a launch of their
+// own).
 void launch_embed_jobs(const EmbedJob* jobs, int njobs, const EmbedDev* cls, int ksplit, int ld,
                        int hm0, int hm1, int mH, const BatchCoarse& bc, hipStream_t s) {
   const bool wide = embed_wide(mH, njobs);
   auto kern = embed_kernel(ksplit, wide);
   const int eb = wide ? 2 * kEmbE : kEmbE, chunks = (mH + eb - 1) / eb;
-  const int rows = njobs + (bc.n + chunks - 1) / chunks;
-  if (rows <= 0) return;
+  const int extra = (bc.n + chunks - 1) / chunks;
+  const bool apart = njobs <= 0 || njobs + extra > kEmbMaxJobs;
   const CoarseSolveArgs none{0, nullptr, nullptr, nullptr};
-  hipLaunchKernelGGL(kern, dim3(chunks, rows), dim3(kBlock), 0, s, jobs, cls, ld, hm0, hm1, mH,
-                     nullptr, none, njobs, bc);
+  if (njobs > 0)
+    hipLaunchKernelGGL(kern, dim3(chunks, njobs + (apart ? 0 : extra)), dim3(kBlock), 0, s, jobs, cls,
+                       ld, hm0, hm1, mH, nullptr, none, njobs, bc);
+  if (apart && bc.n > 0)
+    hipLaunchKernelGGL(kern, dim3(bc.n), dim3(kBlock), 0, s, jobs, cls, ld, hm0, hm1, mH, nullptr,
+                       none, 0, bc);
 }
 
 void launch_dense_gemv(const ddeig_problem* P, const PcgState* st, hipStream_t s) {
