@@ -795,52 +795,53 @@ void launch_coarse_extend(const ddeig_problem* P, const double* r, double* z, Re
                      P->cfield, r, z, dot ? 1 : 0, dot ? *dot : none);
 }
 
-// phi_c(k) = D_c(k) psi_ext(k) on box c, 0 elsewhere (column c of R_0^T).
-__device__ inline double coarse_phi(const Geo& g, int delta, int pu, const SubDev& sd,
-                                    const TypeDev& td, const double* psi, const int* i) {
-  for (int a = 0; a < g.D; ++a)
-    if (i[a] < sd.o[a] || i[a] >= sd.o[a] + td.m[a]) return 0.0;
-  return pu_weight(g, delta, pu, sd.c, i) * psi[table_node(g, i[0], i[1], i[2])];
-}
-
-// A0[c][d] = phi_d^T A_sigma phi_c for neighbouring cells (one workgroup per pair).
-__global__ void __launch_bounds__(kBlock) k_coarse_matrix(Geo g, int delta, int pu,
-                                                          const double* __restrict__ T,
+// A0[c][d] = phi_d^T A_sigma phi_c for neighbouring cells (one workgroup per
+// pair), phi_c = D_c psi_ext on the box of c (the classes' phi, column c of
+// R_0^T) and 0 elsewhere.  A node of box d takes the 3^D taps that reach box c.
+// With the weight and psi_ext formed again at every tap: 288 us at 256 cells of
+// 71 x 63 nodes and 1490 us at 256 of 18 x 18 x 15; 36 and 142 us so.
+template <int D>
+__global__ void __launch_bounds__(kBlock) k_coarse_matrix(Geo g, const double* __restrict__ T,
                                                           const TypeDev* __restrict__ types,
                                                           const SubDev* __restrict__ subs,
-                                                          const double* __restrict__ psi,
                                                           double* __restrict__ A0) {
+  constexpr int NT = D == 2 ? 9 : 27;
   const int N = gridDim.x;
   const int cid = blockIdx.x;
   const int nb = blockIdx.y;  // neighbour offset in {-1,0,1}^p
   const SubDev sc = subs[cid];
-  int dc[2] = {nb % 3 - 1, nb / 3 - 1};
-  int cd[3] = {sc.c[0] + dc[0], g.p == 2 ? sc.c[1] + dc[1] : 0, 0};
+  const int dc[2] = {nb % 3 - 1, nb / 3 - 1};
+  const int cd[3] = {sc.c[0] + dc[0], g.p == 2 ? sc.c[1] + dc[1] : 0, 0};
   if (g.p == 1 && dc[1] != -1) return;  // only nb in {0,1,2} for p = 1
   for (int a = 0; a < g.p; ++a)
     if (cd[a] < 1 || cd[a] > g.L) return;
   const int did = sub_index(g, cd);
   const SubDev sdd = subs[did];
-  const TypeDev tc = types[sc.type];
-  const TypeDev tdd = types[sdd.type];
-  const long mtot = (long)tdd.m[0] * tdd.m[1] * tdd.m[2];
+  const TypeDev& tc = types[sc.type];
+  const TypeDev& tdd = types[sdd.type];
+  const int m0 = tdd.m[0], m1 = tdd.m[1], mtot = m0 * m1 * tdd.m[2];
+  const int c0 = tc.m[0], c1 = tc.m[1], c2 = tc.m[2];
+  const double* __restrict__ phic = tc.phi;
   double acc = 0.0;
-  for (long e = threadIdx.x; e < mtot; e += blockDim.x) {
-    const int i[3] = {sdd.o[0] + (int)(e % tdd.m[0]), sdd.o[1] + (int)((e / tdd.m[0]) % tdd.m[1]),
-                      sdd.o[2] + (int)(e / ((long)tdd.m[0] * tdd.m[1]))};
-    const double phid = coarse_phi(g, delta, pu, sdd, tdd, psi, i);
+  for (int e = threadIdx.x; e < mtot; e += kBlock) {
+    const int line = (int)fdiv((unsigned)e, tdd.fm0), u2 = D == 3 ? line / m1 : 0;
+    const int i[3] = {sdd.o[0] + e - line * m0, sdd.o[1] + line - u2 * m1, sdd.o[2] + u2};
+    // the node's place in box c, along each axis
+    const int v0 = i[0] - sc.o[0], v1 = i[1] - sc.o[1], v2 = i[2] - sc.o[2];
+    if (v0 < -1 || v0 > c0 || v1 < -1 || v1 > c1 || (D == 3 && (v2 < -1 || v2 > c2))) continue;
     const long tn = table_node(g, i[0], i[1], i[2]);
-    double aphi = 0.0;
-    for (int t = 0; t < g.ntaps; ++t) {
-      int d[3];
-      tap_offsets(t, g.ntaps, d[0], d[1], d[2]);
-      const int j[3] = {i[0] + d[0], i[1] + d[1], g.D == 3 ? i[2] + d[2] : 0};
-      bool in = true;
-      for (int a = 0; a < g.D; ++a) in = in && j[a] >= 0 && j[a] < g.N[a];
-      if (!in) continue;
-      aphi += T[t * g.tsize + tn] * coarse_phi(g, delta, pu, sc, tc, psi, j);
+    double co[NT], ph[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int w0 = v0 + t % 3 - 1, w1 = v1 + t / 3 % 3 - 1, w2 = D == 3 ? v2 + t / 9 - 1 : 0;
+      const bool in = w0 >= 0 && w0 < c0 && w1 >= 0 && w1 < c1 && (D == 2 || (w2 >= 0 && w2 < c2));
+      co[t] = T[t * g.tsize + tn];
+      ph[t] = in ? phic[w0 + c0 * (w1 + (D == 3 ? c1 * w2 : 0))] : 0.0;
     }
-    acc += phid * aphi;
+    double aphi = 0.0;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) aphi += co[t] * ph[t];
+    acc += tdd.phi[e] * aphi;
   }
   const double s = block_sum(acc);
   if (threadIdx.x == 0) A0[(long)cid * N + did] = s;
@@ -870,8 +871,8 @@ void build_coarse_matrix(ddeig_problem* P, double* A0, hipStream_t s) {
   check_hip(hipMemsetAsync(A0, 0, sizeof(double) * (size_t)N * N, s), "memset A0");
   const int nnb = P->g.p == 1 ? 3 : 9;
   // for p = 1 the neighbour offsets are encoded as nb = 0,1,2 with dc[1] = -1
-  hipLaunchKernelGGL(k_coarse_matrix, dim3(N, nnb), dim3(kBlock), 0, s, P->g, P->delta,
-                     P->opt.pu, P->tabAs, P->dTypes, P->dSubs, P->psi, A0);
+  auto kern = P->g.D == 2 ? k_coarse_matrix<2> : k_coarse_matrix<3>;
+  hipLaunchKernelGGL(kern, dim3(N, nnb), dim3(kBlock), 0, s, P->g, P->tabAs, P->dTypes, P->dSubs, A0);
   launch_symmetrise(A0, N, s);
 }
 
