@@ -789,7 +789,10 @@ __global__ void __launch_bounds__(kBlock, 2) k_stencil3d_march(Geo g, const doub
   const unsigned pl8 = (unsigned)(N01 * 8);
   const int nbytes = (int)(N01 * N2 * 8);
   const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)x, (short)0, nbytes, 0x00020000);
-  const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc((void*)pold, (short)0, upd ? nbytes : 0, 0x00020000);
+  // (the range check subtracts the scalar offset from the size: a resource of fewer
+  // bytes than its scalar offsets would wrap and let every lane read, so without a
+  // previous direction the loads go to x, at its size, and are not used)
+  const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc((void*)(upd ? pold : x), (short)0, nbytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t rn = __builtin_amdgcn_make_buffer_rsrc((void*)pnew, (short)0, nbytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc((void*)y, (short)0, nbytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t rt = __builtin_amdgcn_make_buffer_rsrc((void*)T, (short)0,
