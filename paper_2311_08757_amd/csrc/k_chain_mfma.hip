@@ -121,6 +121,14 @@ __device__ __forceinline__ int cm_slice(int mode, int k, int n, int dir) {
   return i >= 0 && i < n ? i : -1;
 }
 
+// The slot (a subdomain's chain) of a workgroup: numbered along y, and on along z
+// past the 65535 that y has room for (32768 subdomains and more).
+constexpr int kCmMaxY = 65535;
+__device__ __forceinline__ int cm_slot() { return blockIdx.y + kCmMaxY * blockIdx.z; }
+static dim3 cm_grid(int blocks, int mtot) {
+  return dim3(blocks, std::min(mtot, kCmMaxY), (mtot + kCmMaxY - 1) / kCmMaxY);
+}
+
 // Right-hand sides of a step.  Grid: (row blocks, slots).  The values of the
 // neighbouring slice j are t_j inwards (into tbatch), and x_j = t_j - partials
 // outwards (into batch; x_h, the middle's product, is the neighbour of both
@@ -128,14 +136,15 @@ __device__ __forceinline__ int cm_slice(int mode, int k, int n, int dir) {
 template <int MODE, int MAXK>
 __global__ void __launch_bounds__(kBlock) k_cm_rhs(Geo g, const double* __restrict__ T,
                                                    const CmMember* __restrict__ mem, int k, int kc,
-                                                   int pstr, int gstr,
+                                                   int mtot, int pstr, int gstr,
                                                    const float* __restrict__ part,
                                                    float* __restrict__ G,
                                                    const PcgState* __restrict__ st) {
   constexpr int NP = kCmRb + 2 * kCmHalo;
   constexpr int NS = MODE == kCmMid ? 2 : 1;  // neighbours
   __shared__ double prev[NS][NP];
-  const int mtot = gridDim.y, slot = blockIdx.y, half = mtot / 2;  // (lower chains: + half)
+  const int slot = cm_slot(), half = mtot / 2;  // (lower chains: + half)
+  if (slot >= mtot) return;
   const CmMember md = mem[slot];
   if (st != nullptr && st->done) return;
   const int b = md.b, nch = md.nch;
@@ -338,9 +347,11 @@ __global__ void __launch_bounds__(kBlock) k_cm_mm16(const CmJob* __restrict__ jo
 // for a chain of one slice.  Grid: (row blocks, slots).
 template <int MAXK>
 __global__ void __launch_bounds__(kBlock) k_cm_fin(const CmMember* __restrict__ mem, int kc,
-                                                   int pstr, const float* __restrict__ part,
+                                                   int mtot, int pstr,
+                                                   const float* __restrict__ part,
                                                    const PcgState* __restrict__ st) {
-  const int mtot = gridDim.y, slot = blockIdx.y;
+  const int slot = cm_slot();
+  if (slot >= mtot) return;
   const CmMember md = mem[slot];
   if (st != nullptr && st->done) return;
   const int b = md.b, h = md.nch / 2;
@@ -422,20 +433,22 @@ static void cm_solve(const ddeig_problem* P, const PcgState* st, hipStream_t s) 
   const CmJob* jobs = reinterpret_cast<const CmJob*>(base + joff);
   float* part = reinterpret_cast<float*>(base + poff);
   float* G = part + (long)nkc * mtot * pstr;
-  const dim3 grow((bmax + kCmRb - 1) / kCmRb, mtot);
-  const dim3 gmm((bmax + kCmRows - 1) / kCmRows, nkc, njobs);
+  const dim3 grow = cm_grid((bmax + kCmRb - 1) / kCmRb, mtot);
+  constexpr int kMaxZ = 65535;  // jobs of a product launch (grid z)
   auto mm = k_cm_mm<NK>;
   if constexpr (NK % 2 == 0)
     if (P->chain_nm <= 16) mm = k_cm_mm16<NK>;
   auto step = [&](int mode, int k, auto rhs) {
-    hipLaunchKernelGGL(rhs, grow, dim3(kBlock), 0, s, P->g, P->tabAs, mem, k, kc, pstr, gstr, part,
-                       G, st);
-    hipLaunchKernelGGL(mm, gmm, dim3(kBlock), 0, s, jobs, mode, k, mtot, pstr, gstr, G, part, st);
+    hipLaunchKernelGGL(rhs, grow, dim3(kBlock), 0, s, P->g, P->tabAs, mem, k, kc, mtot, pstr, gstr,
+                       part, G, st);
+    for (int j0 = 0; j0 < njobs; j0 += kMaxZ)
+      hipLaunchKernelGGL(mm, dim3((bmax + kCmRows - 1) / kCmRows, nkc, std::min(njobs - j0, kMaxZ)),
+                         dim3(kBlock), 0, s, jobs + j0, mode, k, mtot, pstr, gstr, G, part, st);
   };
   for (int k = 0; k < h; ++k) step(kCmIn, k, k_cm_rhs<kCmIn, MAXK>);
   step(kCmMid, 0, k_cm_rhs<kCmMid, MAXK>);
   for (int k = 0; k < h; ++k) step(kCmOut, k, k_cm_rhs<kCmOut, MAXK>);
-  hipLaunchKernelGGL(k_cm_fin<MAXK>, grow, dim3(kBlock), 0, s, mem, kc, pstr, part, st);
+  hipLaunchKernelGGL(k_cm_fin<MAXK>, grow, dim3(kBlock), 0, s, mem, kc, mtot, pstr, part, st);
 }
 
 // The solves of every class (all classes share nch).
