@@ -121,6 +121,34 @@ struct Cover {
   __device__ int c1(int q) const { return min(clo1 + (q >> 1), chi1); }
 };
 
+// pu_weight of the covering cells of a node with two expanding axes (of slots that
+// exist), every cell's distance formed once.  The extension takes each weight for
+// the coarse term and, RAS, for the local solution; formed for each of the two and
+// each cell anew, every time with all the distances for their sum, they made it
+// keep one workgroup to a CU (71 registers) and cost 23 us: 225 subdomains of 18 x
+// 18 x 15 in bf16, an application of two-level RAS 89.3 us, 65.1 so (63.5 with equal
+// weights); additive 79.5 -> 66.1.
+__device__ __forceinline__ void cover_weights(const Geo& g, int delta, int pu, const Cover<2>& cv,
+                                              const int* i, double (&w)[4]) {
+  if (pu == 0) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      w[q] = (cv.clo0 < cv.chi0 ? 0.5 : 1.0) * (cv.clo1 < cv.chi1 ? 0.5 : 1.0);
+    return;
+  }
+  int d[4];
+  double tot = 0.0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    d[q] = min(face_dist(i[0] + 1, cv.c0(q), g.ne, g.L, delta),
+               face_dist(i[1] + 1, cv.c1(q), g.ne, g.L, delta));
+    if (cv.val(q)) tot += (double)d[q];
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q)  // (a single subdomain has no interior faces)
+    w[q] = d[q] == 0x7fffffff ? 1.0 : (double)d[q] / tot;
+}
+
 // One item of the node-parallel dense kernels: 256 consecutive nodes of one grid
 // line, a thread each.  The item is the same for the four waves that share it,
 // so its part of every address is scalar and a lane adds a 32-bit byte offset.
@@ -337,8 +365,7 @@ __device__ __forceinline__ void extend_dense_body(const Geo& g, int delta, int c
                                                   const double* __restrict__ r,
                                                   double* __restrict__ z, int use_dot,
                                                   const Red& dot, int bid, int nblk, int pu = 0,
-                                                  const XCover* __restrict__ xc0 = nullptr,
-                                                  const XCover* __restrict__ xc1 = nullptr) {
+                                                  const XCover* __restrict__ xc0 = nullptr) {
   constexpr int NC = Cover<PX>::NC;
   if (st != nullptr && st->done) return;
   if (chk.on) {
@@ -363,7 +390,7 @@ __device__ __forceinline__ void extend_dense_body(const Geo& g, int delta, int c
   for (unsigned grp = bid; grp * NPT * IPB < items; grp += nblk) {
     bool okn[NPT], two[NPT];
     unsigned on[NPT];
-    double wan[NPT][2], wbn[NPT][PX], yan[NPT][INL ? NC : 1], rkn[NPT], psn[NPT];
+    double wan[NPT][2], yan[NPT][INL ? NC : 1], rkn[NPT], psn[NPT];
     float zsn[NPT][NC][KS];
 #pragma unroll
     for (int u = 0; u < NPT; ++u) {
@@ -376,24 +403,21 @@ __device__ __forceinline__ void extend_dense_body(const Geo& g, int delta, int c
       const DensePos<PX> pos(g, delta, da, t, tl, cv);
       two[u] = cv.val(1);
       psn[u] = 0.0;
+      // the weights of one expanding axis (equal ones need no table)
+      if (PX == 1 && (RAS || (INL && coarse))) {
+        wan[u][0] = wan[u][1] = two[u] ? 0.5 : 1.0;
+        if (pu != 0) {
+          const double* w = &xc0[t.s0].w[0];
+          wan[u][0] = at_bytes(w, (unsigned)sizeof(XCover) * tl);
+          wan[u][1] = at_bytes(w + 1, (unsigned)sizeof(XCover) * tl);
+        }
+      }
       if (coarse) {
         // cell-local table node: x dims (i + 1) mod n_e
         const int j0 = i[0] + 1 - g.ne * (int)fdiv((unsigned)(i[0] + 1), g.fne);
         const int j1 = PX == 2 ? t.i1 + 1 - g.ne * (int)fdiv((unsigned)(t.i1 + 1), g.fne) : t.i1;
         psn[u] = at_bytes(psi + (long)g.P[0] * (j1 + (long)g.P[1] * t.i2), 8u * j0);
         if constexpr (INL) {
-          // the inline field's weights per axis (equal ones need no table) and
-          // its y0 values
-          wan[u][0] = wan[u][1] = two[u] ? 0.5 : 1.0;
-#pragma unroll
-          for (int q1 = 0; q1 < PX; ++q1) wbn[u][q1] = PX == 2 && cv.clo1 < cv.chi1 ? 0.5 : 1.0;
-          if (pu != 0) {
-            const double* w = &xc0[t.s0].w[0];
-            wan[u][0] = at_bytes(w, (unsigned)sizeof(XCover) * tl);
-            wan[u][1] = at_bytes(w + 1, (unsigned)sizeof(XCover) * tl);
-#pragma unroll
-            for (int q1 = 0; q1 < PX; ++q1) wbn[u][q1] = PX == 2 ? xc1[t.i1].w[q1] : 1.0;
-          }
 #pragma unroll
           for (int q = 0; q < NC; ++q)
             yan[u][q] = at_bytes(cf + (pos.cw - 1 + (PX == 2 ? (long)g.L * (cv.c1(q) - 1) : 0L)),
@@ -422,21 +446,17 @@ __device__ __forceinline__ void extend_dense_body(const Geo& g, int delta, int c
     auto val = [&](int q) { return PX == 1 ? q == 0 || two[u] : cv.val(q); };
     float (&zs)[NC][KS] = zsn[u];
     const double rk = rkn[u];
-    double ps = psn[u], zc = 0.0;
+    double ps = psn[u], zc = 0.0, w[NC];
+    if constexpr (PX == 2 && (RAS || INL)) cover_weights(g, delta, pu, cv, i, w);
+    else if constexpr (RAS || INL) { w[0] = wan[u][0]; w[1] = wan[u][1]; }
     if (coarse) {
       if constexpr (INL && PX == 1) {
-        // the weights of the one expanding axis (cover_weight for p = 1)
-        zc = wan[u][0] * yan[u][0];
-        if (two[u]) zc = fma(wan[u][1], yan[u][1], zc);
+        zc = w[0] * yan[u][0];
+        if (two[u]) zc = fma(w[1], yan[u][1], zc);
       } else if constexpr (INL) {
-        // (cover_weight for p = 2)
 #pragma unroll
-        for (int q = 0; q < NC; ++q) {
-          if (!cv.val(q)) continue;
-          const int c[3] = {cv.c0(q), cv.c1(q), 0};
-          const double w = pu == 1 ? pu_weight(g, delta, pu, c, i) : wan[u][q & 1] * wbn[u][q >> 1];
-          zc += w * yan[u][q];
-        }
+        for (int q = 0; q < NC; ++q)
+          if (cv.val(q)) zc += w[q] * yan[u][q];
       } else {
         zc = yan[u][0];
       }
@@ -449,14 +469,8 @@ __device__ __forceinline__ void extend_dense_body(const Geo& g, int delta, int c
       float zq = 0.0f;
 #pragma unroll
       for (int sp = 0; sp < KS; ++sp) zq += zs[q][sp];
-      if constexpr (RAS) {
-        const XCover* xc[2] = {xc0, xc1};
-        const int c[3] = {cv.c0(q), cv.c1(q), 0};
-        const int which[2] = {q & 1, q >> 1};
-        zl += cover_weight(g, delta, pu, xc, c, i, which) * (double)zq;
-      } else {
-        zl += (double)zq;
-      }
+      if constexpr (RAS) zl += w[q] * (double)zq;
+      else zl += (double)zq;
     }
     // one rounding for the coarse term, whatever the compiler knows of `coarse`
     const double zv = coarse ? fma(ps, zc, zl) : zl;
@@ -474,10 +488,9 @@ __global__ void __launch_bounds__(kBig) k_extend_dense(Geo g, int delta, int coa
                                                        const double* __restrict__ cf,
                                                        const double* __restrict__ r,
                                                        double* __restrict__ z, int use_dot, Red dot,
-                                                       int pu, const XCover* __restrict__ xc0,
-                                                       const XCover* __restrict__ xc1) {
+                                                       int pu, const XCover* __restrict__ xc0) {
   extend_dense_body<PX, KS, RAS, INL>(g, delta, coarse, st, chk, da, psi, cf, r, z, use_dot, dot,
-                                      blockIdx.x, gridDim.x, pu, xc0, xc1);
+                                      blockIdx.x, gridDim.x, pu, xc0);
 }
 
 // One expanding axis: two nodes per thread on node_grid_dense's grid, at most
@@ -490,10 +503,9 @@ k_extend_dense_p1(Geo g, int delta, int coarse,
                                                        const double* __restrict__ cf,
                                                        const double* __restrict__ r,
                                                        double* __restrict__ z, int use_dot, Red dot,
-                                                       int pu, const XCover* __restrict__ xc0,
-                                                       const XCover* __restrict__ xc1) {
+                                                       int pu, const XCover* __restrict__ xc0) {
   extend_dense_body<1, KS, RAS, INL, 2>(g, delta, coarse, st, chk, da, psi, cf, r, z, use_dot, dot,
-                                      blockIdx.x, gridDim.x, pu, xc0, xc1);
+                                      blockIdx.x, gridDim.x, pu, xc0);
 }
 
 DenseArgs dense_args(const ddeig_problem* P) {
@@ -655,7 +667,6 @@ __global__ void __launch_bounds__(kBig) k_extend(Geo g, int delta, int pu, int c
                                                  PcgState* __restrict__ st, CheckArgs chk,
                                                  const SubBase* __restrict__ sb,
                                                  const XCover* __restrict__ xc0,
-                                                 const XCover* __restrict__ xc1,
                                                  const double* __restrict__ psi,
                                                  const double* __restrict__ y0,
                                                  const double* __restrict__ r,
@@ -674,7 +685,6 @@ __global__ void __launch_bounds__(kBig) k_extend(Geo g, int delta, int pu, int c
     }
     if (conv || last) return;
   }
-  const XCover* xc[2] = {xc0, xc1};
   double acc = 0.0;
   const int N0 = g.N[0];
   const unsigned items = g.fseg.d * (unsigned)(g.N[1] * g.N[2]);
@@ -691,16 +701,23 @@ __global__ void __launch_bounds__(kBig) k_extend(Geo g, int delta, int pu, int c
     // the records and whatever does not hang on them, then the local solutions
     SubBase b[NC];
     double wc[NC], yc[NC], zi[NC], ps = 0.0;
+    const bool weigh = coarse || ras;
+    if constexpr (PX == 2) {
+      cover_weights(g, delta, weigh ? pu : 0, cv, i, wc);
+    } else {
+      // (equal weights need no table)
+      wc[0] = wc[1] = cv.clo0 < cv.chi0 ? 0.5 : 1.0;
+      if (pu != 0 && weigh) {
+        const double* w = &xc0[t.s0].w[0];
+        wc[0] = at_bytes(w, (unsigned)sizeof(XCover) * tl);
+        wc[1] = at_bytes(w + 1, (unsigned)sizeof(XCover) * tl);
+      }
+    }
 #pragma unroll
     for (int q = 0; q < NC; ++q) {
       const long sw = cw - 1 + (PX == 2 ? (long)g.L * (cv.c1(q) - 1) : 0L);
       const unsigned sl = (unsigned)(cv.c0(q) - cw);
       b[q] = at_bytes(sb + sw, (unsigned)sizeof(SubBase) * sl);
-      const int c[3] = {cv.c0(q), PX == 2 ? cv.c1(q) : 0, 0};
-      const int which[2] = {q & 1, q >> 1};
-      // (equal weights need no table)
-      wc[q] = (cv.clo0 < cv.chi0 ? 0.5 : 1.0) * (PX == 2 && cv.clo1 < cv.chi1 ? 0.5 : 1.0);
-      if (pu != 0 && (coarse || ras) && cv.val(q)) wc[q] = cover_weight(g, delta, pu, xc, c, i, which);
       yc[q] = coarse ? at_bytes(y0 + sw, 8u * sl) : 0.0;
     }
     const double rk = at_bytes(r + k0, 8u * tl);
@@ -756,12 +773,12 @@ void launch_extend(const ddeig_problem* P, const double* r, double* z, int coars
                            : dense_extend_kernel<false, false>(P->g.p, P->ksplit));
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(kBig), 0, s, P->g, P->delta, coarse, st, chk,
                        dense_args(P), P->psi, inl ? P->cy : P->cfield, r, z, dot ? 1 : 0,
-                       dot ? *dot : none, P->opt.pu, P->dXC[0], P->dXC[1]);
+                       dot ? *dot : none, P->opt.pu, P->dXC[0]);
     return;
   }
   auto kern = P->g.p == 1 ? k_extend<1> : k_extend<2>;
   hipLaunchKernelGGL(kern, dim3(blocks), dim3(kBig), 0, s, P->g, P->delta, P->opt.pu, coarse, ras, st,
-                     chk, P->dSubBase, P->dXC[0], P->dXC[1], P->psi, P->cy, r, z, dot ? 1 : 0,
+                     chk, P->dSubBase, P->dXC[0], P->psi, P->cy, r, z, dot ? 1 : 0,
                      dot ? *dot : none);
 }
 
