@@ -16,7 +16,25 @@
 // r running over the threads, which coalesces.
 #include "k_common.h"
 
+#include <mutex>
+#include <set>
+#include <utility>
+
 namespace ddeig {
+
+// Allows a kernel `bytes` of dynamic LDS, the most that it is ever launched with.
+// The limit belongs to the kernel on a device, not to a problem: set to each
+// launch's own size, two problems on two threads could lower it under each other
+// between the call and the launch.  So it is set once, before the first launch.
+static void allow_lds(int device, const void* kern, size_t bytes) {
+  static std::mutex mu;
+  static std::set<std::pair<int, const void*>> done;
+  std::lock_guard<std::mutex> lk(mu);
+  if (done.count({device, kern})) return;
+  check_hip(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes),
+            "dynamic LDS");
+  done.insert({device, kern});
+}
 
 // In-slice neighbour of box-local u (slice coordinates a < D-1) along tap d.
 __device__ inline bool slice_nbr(const Box& bx, int D, const int* u, const int* d, int& rn) {
@@ -589,6 +607,7 @@ void launch_gj_invert(ddeig_problem* P, double* A, int b, hipStream_t s) {
 // Row solves (chain_rows) of slices of b, nch of them: the LDS copy of the
 // right-hand side has to fit, and one wave holds a slice.
 constexpr size_t kRowsLds = 128 * 1024;
+constexpr size_t kRowsLdsMax = kRowsLds + kRowsMaxB * sizeof(double);  // (a line more for an even count)
 static size_t rows_lds(int b, int nch) {
   return ((size_t)b * (nch | 1) + 2 * 64 + 2) * sizeof(double);
 }
@@ -632,16 +651,16 @@ void chain_factor(ddeig_problem* P, const std::vector<Box>& boxes, const std::ve
       jobs.dir[j] = j / nb;
     }
     if (small) {
+      const int na = bmax <= 32 ? 2 : bmax <= 48 ? 3 : bmax <= 64 ? 4 : bmax <= 80 ? 5 : 8;
 #define FACTOR_PICK(MID)                                                            \
-  (bmax <= 32   ? k_chain_factor2d<2, MID>                                          \
-   : bmax <= 48 ? k_chain_factor2d<3, MID>                                          \
-   : bmax <= 64 ? k_chain_factor2d<4, MID> : k_chain_factor2d<5, MID>)
+  (na == 2   ? k_chain_factor2d<2, MID>                                             \
+   : na == 3 ? k_chain_factor2d<3, MID>                                             \
+   : na == 4 ? k_chain_factor2d<4, MID> : k_chain_factor2d<5, MID>)
       for (int m = 0; m < nd; ++m) {  // the chains, then the slices between two halves
-        auto kern = m ? FACTOR_PICK(true) : bmax <= 80 ? FACTOR_PICK(false) : k_chain_factor2d<8, false>;
+        auto kern = m ? FACTOR_PICK(true) : na <= 5 ? FACTOR_PICK(false) : k_chain_factor2d<8, false>;
         const size_t lds = (size_t)(m + 1) * bmax * bmax * sizeof(double);
-        check_hip(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds),
-                  "factorisation LDS");
+        allow_lds(P->device, reinterpret_cast<const void*>(kern),
+                  (size_t)(m + 1) * (kFacG * na) * (kFacG * na) * sizeof(double));
         hipLaunchKernelGGL(kern, dim3(m ? nb : nj), dim3(kBlock), lds, s, P->g, tab, jobs, rows,
                            P->flag);
       }
@@ -1468,12 +1487,11 @@ __global__ void __launch_bounds__(NT) k_rows_box(Geo g, Box bx, const double* __
 #define ROWS_COMMA ,
 
 template <typename K>
-static void rows_launch(K kern, bool both, int b, int nch, size_t& lds, int& nt) {
+static void rows_launch(const ddeig_problem* P, K kern, bool both, int b, int nch, size_t& lds,
+                        int& nt) {
   lds = rows_lds(b, nch);
   nt = 64 * (RowsLayout(b).nw + 1) * (both ? 2 : 1);
-  check_hip(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds),
-            "chain solve LDS");
+  allow_lds(P->device, reinterpret_cast<const void*>(kern), kRowsLdsMax);
 }
 
 bool launch_rows_box(const ddeig_problem* P, const Box& bx, const double* tab, const double* W,
@@ -1483,7 +1501,7 @@ bool launch_rows_box(const ddeig_problem* P, const Box& bx, const double* tab, c
   auto kern = both ? ROWS_PICK_BOTH(k_rows_box, bx.b) : ROWS_PICK(k_rows_box, bx.b);
   size_t lds;
   int nt;
-  rows_launch(kern, both, bx.b, bx.nch, lds, nt);
+  rows_launch(P, kern, both, bx.b, bx.nch, lds, nt);
   hipLaunchKernelGGL(kern, dim3(nrhs), dim3(nt), lds, s, P->g, bx, tab, W, v, identity);
   return true;
 }
@@ -1524,7 +1542,7 @@ static void launch_rows_local(const ddeig_problem* P, const PcgState* st, double
   } else {
     kern = ROWS_PICK(k_rows_local, b, WT ROWS_COMMA);
   }
-  rows_launch(kern, both, b, nch, lds, nt);
+  rows_launch(P, kern, both, b, nch, lds, nt);
   hipLaunchKernelGGL(kern, dim3(P->nsub), dim3(nt), lds, s, P->g, P->tabAs, P->dTypes, P->dSubs, st,
                      crhs);
 }

@@ -1,4 +1,4 @@
-"""Sizes of the kernels' buffer resources, read from the sources.
+"""Sizes of the kernels' buffer resources and their attributes, read from the sources.
 
 The hardware accepts a raw buffer access when its per-lane offset is below the
 resource's size minus the scalar offset, both unsigned.  A size below the scalar
@@ -41,3 +41,13 @@ def _resources():
 def test_resources_have_their_buffers_size(where, args):
     assert len(args) == 4, where
     assert "?" not in args[2] and not re.fullmatch(r"0[uUlL]*", args[2]), (where, args[2])
+
+
+def test_kernel_attributes_are_set_in_one_place():
+    """The dynamic-LDS limit is the kernel's, shared by all problems and threads: it
+    is set once to the most any launch takes, never by a launch to its own size."""
+    srcs = {p: open(p).read() for p in glob.glob(os.path.join(CSRC, "*.hip"))}
+    calls = [(p, m.start()) for p, s in srcs.items() for m in re.finditer(r"hipFuncSetAttribute\(", s)]
+    assert len(calls) == 1, calls
+    path, at = calls[0]
+    assert "if (done.count(" in srcs[path][srcs[path].rindex("\nstatic ", 0, at):at]
