@@ -27,12 +27,12 @@
 //     k of W_i (W_i is symmetric, so its rows are the columns of the operand)
 //     and they feed four 32-row tiles, whose rows interleave; each wave takes a
 //     quarter of the chunk, with all of its loads in flight at once, and the
-//     four sums are added through LDS.  NK (9, 18 or 34) is the largest that
+//     four sums are added through LDS, in FP64.  NK (9, 18 or 34) is the largest that
 //     leaves about a workgroup per CU: the launch is a stream of W_i (26 MB a
 //     step for three classes of b = 1085, two chains).
 // One more launch finishes the outermost slices.  The right-hand sides are
-// formed and the partials summed in FP64; W_i, g and the products are FP32
-// (FP32 accumulation on the matrix cores).  W_i staged through LDS in chunks of
+// formed and the partials (sums of at most 72 products) added and kept in FP64;
+// W_i, g and the products are FP32 (FP32 accumulation on the matrix cores).  W_i staged through LDS in chunks of
 // 72 rows took 14.8 us a step (1.8 TB/s); this takes 10.2 us, and 8.2 (3.2 TB/s)
 // on 16-wide tiles, which 14 members fill; the right-hand sides 6.9 -> 4.2 us
 // with a quarter of the partials and one descriptor load.
@@ -42,6 +42,7 @@ namespace ddeig {
 
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+typedef __attribute__((__vector_size__(2 * sizeof(double)))) double f64x2;
 
 constexpr int kCmRows = 128;    // output rows per product workgroup
 constexpr int kCmMembers = 64;  // members per job: two 32-wide MFMA tiles per wave
@@ -93,16 +94,16 @@ bool chain_mfma_ok(int b, int m0) {
 // masked values), so their latencies overlap; MAXK (the batch's largest chunk
 // count rounded up) bounds the loads.
 template <int MAXK>
-__device__ inline double cm_prev(const float* __restrict__ part, int nkc, int mtot, int bmax,
+__device__ inline double cm_prev(const double* __restrict__ part, int nkc, int mtot, int bmax,
                                  int slot, int r, const double* sub) {
-  float v[MAXK];
+  double v[MAXK];
 #pragma unroll
   for (int kc = 0; kc < MAXK; ++kc)
     v[kc] = part[((long)min(kc, nkc - 1) * mtot + slot) * bmax + r];
   double acc = 0.0;
 #pragma unroll
   for (int kc = 0; kc < MAXK; ++kc)
-    if (kc < nkc) acc += (double)v[kc];
+    if (kc < nkc) acc += v[kc];
   return sub != nullptr ? *sub - acc : acc;
 }
 
@@ -137,7 +138,7 @@ template <int MODE, int MAXK>
 __global__ void __launch_bounds__(kBlock) k_cm_rhs(Geo g, const double* __restrict__ T,
                                                    const CmMember* __restrict__ mem, int k, int kc,
                                                    int mtot, int pstr, int gstr,
-                                                   const float* __restrict__ part,
+                                                   const double* __restrict__ part,
                                                    float* __restrict__ G,
                                                    const PcgState* __restrict__ st) {
   constexpr int NP = kCmRb + 2 * kCmHalo;
@@ -204,6 +205,21 @@ __global__ void __launch_bounds__(kBlock) k_cm_rhs(Geo g, const double* __restri
   G[(long)slot * gstr + r] = (float)acc;
 }
 
+// Four rows' sums of the four waves (rows at .. at + 3; the waves' sums lie stride
+// apart), FP32 sums of at most 72 products each, added in FP64 and kept so: a chunk's
+// partial in FP32 would hold up to 272 products.
+__device__ __forceinline__ void cm_add4(const float* red, int stride, int at, double* out) {
+  double v[4] = {};
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    const f32x4 w = *reinterpret_cast<const f32x4*>(&red[p * stride + at]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] += (double)w[e];
+  }
+  reinterpret_cast<f64x2*>(out)[0] = f64x2{v[0], v[1]};
+  reinterpret_cast<f64x2*>(out)[1] = f64x2{v[2], v[3]};
+}
+
 // Partial product of a step: rows [R0, R0 + 128) x the job's members x K chunk
 // [K0, K0 + 8 NK) of W_i g, into part[chunk][slot][row].  The half-wave kh of
 // wave w takes k = K0 + (2 w + kh) NK + q, q < NK.
@@ -211,7 +227,7 @@ template <int NK>
 __global__ void __launch_bounds__(kBlock) k_cm_mm(const CmJob* __restrict__ jobs, int mode, int k,
                                                   int mtot, int pstr, int gstr,
                                                   const float* __restrict__ G,
-                                                  float* __restrict__ part,
+                                                  double* __restrict__ part,
                                                   const PcgState* __restrict__ st) {
   __shared__ __attribute__((aligned(16))) float red[4][32 * kCmLdr];
   const CmJob jb = jobs[blockIdx.z];
@@ -264,11 +280,8 @@ __global__ void __launch_bounds__(kBlock) k_cm_mm(const CmJob* __restrict__ jobs
     for (int q = 0; q < 32 * kCmRows / 4 / kBlock; ++q) {
       const int idx = tid + q * kBlock, j = idx / (kCmRows / 4), c4 = 4 * (idx % (kCmRows / 4));
       if (mt + j >= jb.nm || R0 + c4 >= pstr) continue;
-      f32x4 v = *reinterpret_cast<const f32x4*>(&red[0][j * kCmLdr + c4]);
-#pragma unroll
-      for (int p = 1; p < 4; ++p) v += *reinterpret_cast<const f32x4*>(&red[p][j * kCmLdr + c4]);
-      *reinterpret_cast<f32x4*>(
-          &part[((long)blockIdx.y * mtot + jb.slot0 + mt + j) * pstr + R0 + c4]) = v;
+      cm_add4(red[0], 32 * kCmLdr, j * kCmLdr + c4,
+              &part[((long)blockIdx.y * mtot + jb.slot0 + mt + j) * pstr + R0 + c4]);
     }
   }
 }
@@ -282,7 +295,7 @@ template <int NK>
 __global__ void __launch_bounds__(kBlock) k_cm_mm16(const CmJob* __restrict__ jobs, int mode, int k,
                                                     int mtot, int pstr, int gstr,
                                                     const float* __restrict__ G,
-                                                    float* __restrict__ part,
+                                                    double* __restrict__ part,
                                                     const PcgState* __restrict__ st) {
   static_assert(NK % 2 == 0, "whole quarter-wave shares");
   constexpr int NQ = NK / 2;
@@ -336,10 +349,8 @@ __global__ void __launch_bounds__(kBlock) k_cm_mm16(const CmJob* __restrict__ jo
   for (int q = 0; q < 16 * kCmRows / 4 / kBlock; ++q) {
     const int idx = tid + q * kBlock, j = idx / (kCmRows / 4), c4 = 4 * (idx % (kCmRows / 4));
     if (j >= jb.nm || R0 + c4 >= pstr) continue;
-    f32x4 v = *reinterpret_cast<const f32x4*>(&red[0][j * kCmLdr + c4]);
-#pragma unroll
-    for (int p = 1; p < 4; ++p) v += *reinterpret_cast<const f32x4*>(&red[p][j * kCmLdr + c4]);
-    *reinterpret_cast<f32x4*>(&part[((long)blockIdx.y * mtot + jb.slot0 + j) * pstr + R0 + c4]) = v;
+    cm_add4(red[0], 16 * kCmLdr, j * kCmLdr + c4,
+            &part[((long)blockIdx.y * mtot + jb.slot0 + j) * pstr + R0 + c4]);
   }
 }
 
@@ -348,7 +359,7 @@ __global__ void __launch_bounds__(kBlock) k_cm_mm16(const CmJob* __restrict__ jo
 template <int MAXK>
 __global__ void __launch_bounds__(kBlock) k_cm_fin(const CmMember* __restrict__ mem, int kc,
                                                    int mtot, int pstr,
-                                                   const float* __restrict__ part,
+                                                   const double* __restrict__ part,
                                                    const PcgState* __restrict__ st) {
   const int slot = cm_slot();
   if (slot >= mtot) return;
@@ -368,7 +379,7 @@ __global__ void __launch_bounds__(kBlock) k_cm_fin(const CmMember* __restrict__ 
   }
 }
 
-// Strides and sizes: partial rows of whole float4s, G rows of b values and the
+// Strides and sizes: partial rows of whole groups of four, G rows of b values and the
 // zeros that a last K chunk reads.
 static int cm_pstr(int bmax) { return (bmax + 3) / 4 * 4; }
 static int cm_gstr(int bmax) { return bmax + kCmPad; }
@@ -391,7 +402,8 @@ size_t chain_mfma_bytes(int bmax, int mtot, int njobs, size_t* job_off, size_t* 
   off = (off + 255) / 256 * 256;
   *part_off = off;
   const int nk = cm_nk(bmax, njobs), nkc = (bmax + 8 * nk - 1) / (8 * nk);
-  return off + ((size_t)nkc * mtot * cm_pstr(bmax) + (size_t)mtot * cm_gstr(bmax)) * sizeof(float);
+  return off + (size_t)nkc * mtot * cm_pstr(bmax) * sizeof(double) +
+         (size_t)mtot * cm_gstr(bmax) * sizeof(float);
 }
 
 // Fills the descriptors at the head of the (cleared) chain buffer.
@@ -431,8 +443,8 @@ static void cm_solve(const ddeig_problem* P, const PcgState* st, hipStream_t s) 
   unsigned char* base = static_cast<unsigned char*>(P->chain_part);
   const CmMember* mem = reinterpret_cast<const CmMember*>(base);
   const CmJob* jobs = reinterpret_cast<const CmJob*>(base + joff);
-  float* part = reinterpret_cast<float*>(base + poff);
-  float* G = part + (long)nkc * mtot * pstr;
+  double* part = reinterpret_cast<double*>(base + poff);
+  float* G = reinterpret_cast<float*>(part + (long)nkc * mtot * pstr);
   const dim3 grow = cm_grid((bmax + kCmRb - 1) / kCmRb, mtot);
   constexpr int kMaxZ = 65535;  // jobs of a product launch (grid z)
   auto mm = k_cm_mm<NK>;
