@@ -49,7 +49,7 @@ constexpr int kCmMembers = 64;  // members per job: two 32-wide MFMA tiles per w
 constexpr int kCmRb = 256;      // rows per right-hand-side workgroup
 constexpr int kCmHalo = 256;    // largest halo (one slice line + 1) of the rhs kernel
 constexpr int kCmMaxB = 2304;   // largest slice
-constexpr int kCmMaxKc = 32;    // largest number of K chunks (2304 / 72)
+constexpr int kCmMaxKc = 18;    // most K chunks (of 72, up to slices of 1280: cm_nk)
 constexpr int kCmPad = 272;     // the longest K chunk: G rows end in as many zeros
 constexpr int kCmLdr = kCmRows + 4;  // LDS row of a member's partial sums
 
@@ -385,7 +385,10 @@ static int cm_pstr(int bmax) { return (bmax + 3) / 4 * 4; }
 static int cm_gstr(int bmax) { return bmax + kCmPad; }
 
 // Rows of W_i per half-wave: the largest K chunk (8 NK rows) that leaves about
-// three quarters of the CUs a workgroup, so that the partials are few.
+// three quarters of the CUs a workgroup, so that the partials are few.  An
+// application, one level, with NK 34 / 18 / 9 everywhere: two subdomains with slices
+// of 1023 unknowns 374 / 348 / 390 us, 20 of 768 358 / 298 / 343, 24 of 621 333 / 277 /
+// 284, 16 of 437 220 / 198 / 187 (the rule: 18, 18, 9 and 9).
 static int cm_nk(int bmax, int njobs) {
   const int tiles = (bmax + kCmRows - 1) / kCmRows * njobs;
   for (int nk : {34, 18})
