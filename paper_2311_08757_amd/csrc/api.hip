@@ -45,14 +45,6 @@ T* dalloc(ddeig_problem* P, size_t count) {
   return static_cast<T*>(p);
 }
 
-// Storage of a chain factor (zero: the row solves' layout has unused entries).
-template <typename T>
-T* dalloc_factor(ddeig_problem* P, size_t count) {
-  T* p = dalloc<T>(P, count);
-  check_hip(hipMemsetAsync(p, 0, sizeof(T) * count, P->stream), "clear factor");
-  return p;
-}
-
 void dfree(ddeig_problem* P, void* p) {
   if (!p) return;
   auto it = std::find(P->allocs.begin(), P->allocs.end(), p);
@@ -299,7 +291,15 @@ hipGraphExec_t capture_graph(ddeig_problem* P, F&& body) {
 }
 
 // sigma-dependent set-up: shifted table, local factors, coarse matrix.
+// Pivot buffers of the factorisations: kept from the first shift on (a problem that
+// only applies operators needs none).
+void need_pivot_buffers(ddeig_problem* P) {
+  if (!P->gjbuf)
+    P->gjbuf = dalloc<double>(P, (size_t)ddeig::gj_buffer_doubles(P->gj_stride, P->gj_jobs));
+}
+
 ddeig_status finish_shift(ddeig_problem* P) {
+  need_pivot_buffers(P);
   clear_graphs(P);
   launch_shift_table(P, P->stream);
   clear_flag(P);
@@ -363,8 +363,8 @@ bool fallback_fp32(ddeig_problem* P) {
   for (size_t t = 0; t < P->types.size(); ++t) {
     auto& T = P->types[t];
     const long mm = (long)T.box.nch * T.box.b;
-    T.W = dalloc_factor<double>(P, class_factor_entries(P, T));
-    T.W32 = dalloc_factor<float>(P, class_factor_entries(P, T));
+    T.W = dalloc<double>(P, class_factor_entries(P, T));
+    T.W32 = dalloc<float>(P, class_factor_entries(P, T));
     dfree(P, T.batch);
     T.batch = dalloc<double>(P, (size_t)T.nmem * mm);
     TypeDev& d = tdev[t];
@@ -1124,7 +1124,7 @@ ddeig_status ddeig_assemble(const ddeig_geometry* geom, double h, const ddeig_po
       H.m = hb.b * hb.nch;
       H.ld = (H.m + 127) / 128 * 128;
       H.mp = nsub > ddeig::kGemvMax ? (nsub + 127) / 128 * 128 : ddeig::kGemvMax;
-      H.W = dalloc_factor<double>(P, ddeig::factor_entries(g.D, hb, hb.b, hb.nch));
+      H.W = dalloc<double>(P, ddeig::factor_entries(g.D, hb, hb.b, hb.nch));
       const size_t aa = (size_t)H.ld * H.ld, rr = (size_t)H.mp * H.ld;
       // K columns per GEMM stage (the kernel's pipeline depth): 64 with a
       // single bf16 inverse, 32 with the hi/lo pair; K split so that the GEMM
@@ -1294,9 +1294,9 @@ ddeig_status ddeig_assemble(const ddeig_geometry* geom, double h, const ddeig_po
         tdev[t].W = nullptr;
         tdev[t].W32 = nullptr;
       } else {
-        T.W = dalloc_factor<double>(P, class_factor_entries(P, T));
+        T.W = dalloc<double>(P, class_factor_entries(P, T));
         if (o.local_prec == 1)
-          T.W32 = dalloc_factor<float>(P, chain_mfma ? (size_t)T.box.nch * T.box.b * ldw
+          T.W32 = dalloc<float>(P, chain_mfma ? (size_t)T.box.nch * T.box.b * ldw
                                                      : class_factor_entries(P, T));
         T.batch = dalloc<double>(P, (size_t)T.nmem * mm);
         if (batched_chain) tdev[t].tbatch = dalloc<double>(P, (size_t)T.nmem * mm);
@@ -1328,7 +1328,6 @@ ddeig_status ddeig_assemble(const ddeig_geometry* geom, double h, const ddeig_po
           chain_mfma ? ddeig::chain_mfma_bytes(maxb_types, mtot, (int)chainjobs.size(), &joff, &poff)
                      : ddeig::chain_part_bytes(maxb_types, mtot, o.local_prec == 1);
       P->chain_part = dalloc<unsigned char>(P, bytes);
-      check_hip(hipMemsetAsync(P->chain_part, 0, bytes, s), "clear chain buffer");
       if (chain_mfma) ddeig::chain_mfma_setup(P, tdev, chainjobs, s);
       P->nchainjobs = (int)chainjobs.size();
       P->dChainJobs = dalloc<ddeig::ChainJob>(P, chainjobs.size());
@@ -1424,7 +1423,6 @@ ddeig_status ddeig_assemble(const ddeig_geometry* geom, double h, const ddeig_po
               "pinned state");
     P->gj_jobs = (dense ? 1 : (int)P->types.size()) * (chain_mfma ? 2 : 1);
     P->gj_stride = gjmax;
-    P->gjbuf = dalloc<double>(P, (size_t)ddeig::gj_buffer_doubles(gjmax, P->gj_jobs));
     P->psi = dalloc<double>(P, g.tsize);
     P->crhs = dalloc<double>(P, nsub);
     // per-axis covering tables of the expanding directions
@@ -1986,7 +1984,8 @@ ddeig_status ddeig_cell_shift(ddeig_problem* P, double* sigma_out, double* psi_c
     if (!g.isx[a]) s0 += mu_min(g.nel[a], g.h);
   P->sigma = s0;
   launch_shift_table(P, s);
-  double* Wc = dalloc_factor<double>(P, ddeig::factor_entries(g.D, cb, cb.b, cb.nch));
+  need_pivot_buffers(P);
+  double* Wc = dalloc<double>(P, ddeig::factor_entries(g.D, cb, cb.b, cb.nch));
   double* v0 = dalloc<double>(P, nc);  // psi_k
   double* v1 = dalloc<double>(P, nc);  // M psi_k
   double* v2 = dalloc<double>(P, nc);  // solve

@@ -641,6 +641,10 @@ void chain_factor(ddeig_problem* P, const std::vector<Box>& boxes, const std::ve
   const int rows = P->g.D == 2 && rows_ok(bmax, nch);
   const int nd = both_ends ? 2 : 1;
   const size_t at_once = small ? (size_t)(kFacJobs / nd) : std::max<size_t>(1, std::min(kFacJobs, P->gj_jobs) / nd);
+  if (rows)  // (its entries of no row or column stay zero)
+    for (size_t j = 0; j < boxes.size(); ++j)
+      check_hip(hipMemsetAsync(Ws[j], 0, factor_entries(2, boxes[j], bmax, nch) * sizeof(double), s),
+                "clear factor");
   for (size_t j0 = 0; j0 < boxes.size(); j0 += at_once) {
     const int nb = (int)std::min(at_once, boxes.size() - j0), nj = nb * nd;
     FactorJobs jobs{};

@@ -409,7 +409,8 @@ size_t chain_mfma_bytes(int bmax, int mtot, int njobs, size_t* job_off, size_t* 
          (size_t)mtot * cm_gstr(bmax) * sizeof(float);
 }
 
-// Fills the descriptors at the head of the (cleared) chain buffer.
+// Fills the descriptors at the head of the chain buffer and clears G behind the
+// partials.
 void chain_mfma_setup(ddeig_problem* P, const std::vector<TypeDev>& types,
                       const std::vector<ChainJob>& jobs, hipStream_t s) {
   std::vector<CmJob> cj;
@@ -426,12 +427,15 @@ void chain_mfma_setup(ddeig_problem* P, const std::vector<TypeDev>& types,
     }
   }
   size_t joff, poff;
-  chain_mfma_bytes(P->chain_bmax, P->chain_mtot, (int)jobs.size(), &joff, &poff);
+  const size_t bytes =
+      chain_mfma_bytes(P->chain_bmax, P->chain_mtot, (int)jobs.size(), &joff, &poff);
   unsigned char* base = static_cast<unsigned char*>(P->chain_part);
   check_hip(hipMemcpyAsync(base, cm.data(), sizeof(CmMember) * cm.size(), hipMemcpyHostToDevice, s),
             "copy chain members");
   check_hip(hipMemcpyAsync(base + joff, cj.data(), sizeof(CmJob) * cj.size(), hipMemcpyHostToDevice,
                            s), "copy chain jobs");
+  const size_t gbytes = (size_t)P->chain_mtot * cm_gstr(P->chain_bmax) * sizeof(float);
+  check_hip(hipMemsetAsync(base + bytes - gbytes, 0, gbytes, s), "clear right-hand sides");
   check_hip(hipStreamSynchronize(s), "chain descriptors");
 }
 
