@@ -43,7 +43,7 @@ COUNTED_TRAFFIC = {
     "begin": "constexpr int kTM = 128", "end": "// Batches of at most kGemvMax rows",
     # the coarse right-hand-side workgroups the GEMM launch carries
     "extra_sources": ["paper_2311_08757_amd/csrc/k_coarse.h"],
-    "sha256": "14685582014d29dff53b00a9a6e72e1bbabb2ab3b359bc74ea028ab38579fced",
+    "sha256": "5952067b843d995763567d008232a44a2f49c9e8a9554b3386b1d0ce4da5013d",
     "workload": "2d-L256-ne64", "local_prec": "bf16",
     "fetch_kib": 34439.1, "fetch_factor": 2.0, "write_kib": 13448.1, "write_factor": 1.0,
 }

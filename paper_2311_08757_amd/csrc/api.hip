@@ -2640,14 +2640,25 @@ ddeig_status ddeig_batch_create(ddeig_problem* const* probs, int n, int flags, d
       B->tile_rows = choice[2];
       best_tiles = batch_tiles(B, B->ksplit, B->order, B->tile_rows);
       if ((flags & DDEIG_BATCH_REPRODUCIBLE) && B->ksplit > 1) {
-        // The splits folded into one tile (same bits) once there is a tile for
-        // each of the 256 CUs without them: 32 instances of 16..256 subdomains
-        // (n_e = 32, 450 folded tiles) solve in 243.8 ms against 266.7 ms split
-        // in three (64-row tiles: 252.6 against 274.7).  Below that the split
-        // is what fills the chip.
+        // The splits folded into one tile (same bits): their Z sets' writes and reads
+        // against CUs that hold fewer workgroups.
+        //  * single bf16: once there is a tile for each of the 256 CUs (n_e = 32, 450
+        //    tiles: a solve of 32 instances 223.5 ms, 251.1 split in three; 261 tiles
+        //    41.8, 41.9), and with long sums nearly two (n_e = 64, 280 and 350 tiles:
+        //    296 and 328, split 273 and 306; 490 and 700: 434 and 600, 450 and 627).
+        //  * the hi/lo pair, three products to a stage, keeps the matrix cores busy
+        //    and wants the CUs full: split is faster everywhere measured (n_e = 16, 270
+        //    tiles: 93 ms, 109 folded; n_e = 64, 490: 628, 668).  Folded only where the
+        //    tiles are nearly all padding, which costs little: 29 instances of 5..9
+        //    subdomains 51.7 ms, 42.1 split (54.6 with the coarse space on a second
+        //    stream).
         std::vector<ddeig::GemmTile> folded =
             batch_tiles(B, B->ksplit, B->order, B->tile_rows, true);
-        if (folded.size() >= 256) {
+        const size_t enough = B->ld < 2048 ? 256 : 448;
+        long rows = 0;
+        for (auto* P : B->P) rows += P->nsub;
+        const bool padding = rows * (B->ld / 128) <= 16 * (long)folded.size();
+        if (folded.size() >= enough && (B->local_prec == 3 || padding)) {
           B->fold = true;
           best_tiles.swap(folded);
         }

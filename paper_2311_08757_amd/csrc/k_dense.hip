@@ -110,10 +110,11 @@ typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
 // host's) and adds each one's sum to the others' in split order, so that Z
 // holds one set of values with the bits that the extension's sum of the splits'
 // sets would have: for batches with enough tiles to fill the chip without the
-// splits, whose separate sets cost their writes, their reads and a launch's
-// fixed time per tile.  Its bound of two workgroups per CU keeps it at 236
-// registers (317 without: one workgroup per CU, 32 instances of 16..256
-// subdomains 258 ms against 244).
+// splits (the rule: ddeig_batch_create), whose separate sets cost their writes,
+// their reads and a launch's fixed time per tile.  Its bound of two workgroups
+// per CU keeps it at 236 registers (317 without: one workgroup per CU, 32
+// instances of 16..256 subdomains 258 ms against 244); the 128-row form of the
+// hi/lo pair keeps the sum in Z (ZSUM), with it in registers 30 spilled.
 template <bool RLO, bool ALO, int MI = 2, bool BND = false, bool FOLD = false>
 __global__ void __launch_bounds__(kBlock, BND ? 2 : 1)
     k_dense_gemm(const GemmTile* __restrict__ tiles, const GemmType* __restrict__ gtypes,
@@ -280,9 +281,18 @@ __global__ void __launch_bounds__(kBlock, BND ? 2 : 1)
     }
     __syncthreads();
   };
-  floatx16 tot[FOLD ? MI : 1][2];
+  // FOLD: the sum of the splits so far, in registers or (ZSUM) in the tile's own place
+  // in Z, each thread its own entries
+  constexpr bool ZSUM = FOLD && RLO && MI == 2;
+  float* const Z0 = gt.Z + (FOLD ? 0L : (long)t.split * gt.zsplit) + (long)t.m0 * ld + t.n0;
+  // accumulator layout of the 32 x 32 MFMA tile: lane l, element e holds
+  // row 8 (e / 4) + 4 (l / 32) + e % 4, column l % 32
+  auto zrow = [&](int l, int i, int e) { return (wm * MI + i) * 32 + 8 * (e >> 2) + 4 * (l >> 5) + (e & 3); };
+  auto zat = [&](int l, int i, int j, int e) { return (long)zrow(l, i, e) * ld + (wn * 2 + j) * 32 + (l & 31); };
+  auto zin = [&](int l, int i, int e) { return !BND || t.m0 + zrow(l, i, e) < gt.rows; };
+  floatx16 tot[FOLD && !ZSUM ? MI : 1][2];
   int sp = 1;  // FOLD: the next split's first stage is 2 (nk / 2 sp / splits)
-  if constexpr (FOLD) {
+  if constexpr (FOLD && !ZSUM) {
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -295,32 +305,40 @@ __global__ void __launch_bounds__(kBlock, BND ? 2 : 1)
     half(rb, ra, 1, kb + 1);
     if constexpr (FOLD) {
       if (kb + 2 == 2 * (nk / 2 * sp / t.split)) {
-        ++sp;
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
-          for (int j = 0; j < 2; ++j)
+          for (int j = 0; j < 2; ++j) {
+            if constexpr (ZSUM) {
+              // (an opaque copy: the entries' addresses hoisted out of the loop would spill)
+              int l = lane;
+              asm volatile("" : "+v"(l));
+              float old[16];
+#pragma unroll
+              for (int e = 0; e < 16; ++e) old[e] = sp > 1 && zin(l, i, e) ? Z0[zat(l, i, j, e)] : 0.0f;
+#pragma unroll
+              for (int e = 0; e < 16; ++e)
+                if (zin(l, i, e)) Z0[zat(l, i, j, e)] = old[e] + acc[i][j][e];
+            }
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-              tot[i][j][e] += acc[i][j][e];
+              if constexpr (!ZSUM) tot[i][j][e] += acc[i][j][e];
               acc[i][j][e] = 0.0f;
             }
+          }
+        ++sp;
       }
     }
   }
-  // accumulator layout of the 32 x 32 MFMA tile: lane l, element e holds
-  // row 8 (e / 4) + 4 (l / 32) + e % 4, column l % 32
-  float* Zp = gt.Z + (FOLD ? 0L : (long)t.split * gt.zsplit) + (long)t.m0 * ld + t.n0;
+  if constexpr (ZSUM) return;
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
-        const int r = (wm * MI + i) * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-        const int c = (wn * 2 + j) * 32 + (lane & 31);
         const float v = FOLD ? tot[i][j][e] : acc[i][j][e];
-        if (!BND || t.m0 + r < gt.rows) Zp[(long)r * ld + c] = v;
+        if (zin(lane, i, e)) Z0[zat(lane, i, j, e)] = v;
       }
 }
 
