@@ -2301,7 +2301,7 @@ struct ddeig_batch {
   std::vector<ddeig_problem*> P;
   hipStream_t stream = nullptr, cap = nullptr;
   int n = 0, local_prec = 0, ksplit = 1, order = 0;
-  int ld = 0, hm0 = 0, hm1 = 0, mH = 0;
+  int ld = 0, hm0 = 0, hm1 = 0, mH = 0, maxT = 0;
   std::vector<ddeig::InstDev> inst;
   ddeig::InstDev* dInst = nullptr;
   ddeig::BlockMap bm_st{}, bm_node{}, bm_crhs{}, bm_csol{};
@@ -2421,7 +2421,7 @@ void batch_local(ddeig_batch* B, hipStream_t s) {
   auto bc = [&](const ddeig::BlockMap& bm) { return ddeig::BatchCoarse{bm.nblocks, B->dInst, bm.map}; };
   launch_gemm_tiles(B->dTiles, B->ntiles, B->dGt, B->local_prec, s, B->tile_rows, B->fold,
                     bc(B->bm_crhs));
-  launch_embed_jobs(B->dEmbJobs, B->nembjobs, B->dEmb, B->zsets, B->ld, B->hm0, B->hm1, B->mH,
+  launch_embed_jobs(B->dEmbJobs, B->nembjobs, B->dEmb, B->zsets, B->ld, B->hm0, B->hm1, B->mH, B->maxT,
                     bc(B->bm_csol), s);
 }
 
@@ -2607,6 +2607,7 @@ ddeig_status ddeig_batch_create(ddeig_problem* const* probs, int n, int flags, d
     B->hm0 = P0->dh.box.m[0];
     B->hm1 = P0->dh.box.m[1];
     B->mH = P0->dh.m;
+    for (auto* P : B->P) B->maxT = std::max(B->maxT, P->maxT);
     if (B->use_graphs)
       check_hip(hipStreamCreateWithFlags(&B->cap, hipStreamNonBlocking), "create capture stream");
     int ks_max = 3;

@@ -555,7 +555,7 @@ void launch_gemm_tiles(const GemmTile* tiles, int ntiles, const GemmType* gt, in
                        hipStream_t s, int tile_rows = 128, bool fold = false,
                        const BatchCoarse& bc = BatchCoarse{0, nullptr, nullptr});
 void launch_embed_jobs(const EmbedJob* jobs, int njobs, const EmbedDev* cls, int ksplit, int ld,
-                       int hm0, int hm1, int mH, const BatchCoarse& bc, hipStream_t s);
+                       int hm0, int hm1, int mH, int maxT, const BatchCoarse& bc, hipStream_t s);
 void launch_b_states(const InstDev* I, int n, PcgState* out, int mark_done, hipStream_t s);
 void launch_b_restrict_start(const InstDev* I, const BlockMap& bm, const int* act, hipStream_t s);
 void launch_b_pcg_init(const InstDev* I, int n, const int* act, double rtol, hipStream_t s);

@@ -722,9 +722,13 @@ k_embed_correct(const EmbedJob* __restrict__ jobs, const EmbedDev* __restrict__ 
   }
 }
 
-// Two unknowns per thread while that leaves a workgroup for every CU.
-static bool embed_wide(int mH, int njobs) {
-  return (long)((mH + 2 * kEmbE - 1) / (2 * kEmbE)) * njobs >= 256;
+// Two unknowns per thread while that leaves a workgroup for every CU; one and a half
+// where a class misses many nodes, whose long columns of G need more loads in flight
+// than two unknowns' shorter batches have (an application, two axes of n_e = 16: 8 x 8
+// subdomains, 304 workgroups, 47.8 us, with one unknown 45.7; 16 x 16, 456, 63.9 and
+// 69.3; 16 boxes of 71 x 255 with 1020 nodes missing, 284 workgroups, 294 and 286).
+static bool embed_wide(int mH, int njobs, int maxT) {
+  return (long)((mH + 2 * kEmbE - 1) / (2 * kEmbE)) * njobs >= (maxT <= 256 ? 256 : 384);
 }
 
 using EmbedKernel = void (*)(const EmbedJob*, const EmbedDev*, int, int, int, int, const PcgState*,
@@ -744,7 +748,7 @@ void launch_embed_fix(const ddeig_problem* P, const PcgState* st, hipStream_t s,
   if (P->nembjobs == 0) return;
   const DenseHost& H = P->dh;
   // the K split is 1..3 by construction (assemble)
-  const bool wide = embed_wide(H.m, P->nembjobs);
+  const bool wide = embed_wide(H.m, P->nembjobs, P->maxT);
   auto kern = embed_kernel(P->ksplit, wide);
   const int eb = wide ? 2 * kEmbE : kEmbE;
   CoarseSolveArgs cs{0, nullptr, nullptr, nullptr};
@@ -809,8 +813,9 @@ void launch_gemm_tiles(const GemmTile* tiles, int ntiles, const GemmType* gt, in
 // grid after the jobs' (where the grid has no room for them, in a launch of their
 // own).
 void launch_embed_jobs(const EmbedJob* jobs, int njobs, const EmbedDev* cls, int ksplit, int ld,
-                       int hm0, int hm1, int mH, const BatchCoarse& bc, hipStream_t s) {
-  const bool wide = embed_wide(mH, njobs);
+                       int hm0, int hm1, int mH, int maxT, const BatchCoarse& bc,
+                       hipStream_t s) {
+  const bool wide = embed_wide(mH, njobs, maxT);
   auto kern = embed_kernel(ksplit, wide);
   const int eb = wide ? 2 * kEmbE : kEmbE, chunks = (mH + eb - 1) / eb;
   const int extra = (bc.n + chunks - 1) / chunks;
