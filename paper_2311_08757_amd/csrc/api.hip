@@ -394,9 +394,9 @@ bool fallback_fp32(ddeig_problem* P) {
 
 // restrict -> local solves (+ clipped-class correction) with the coarse solve ->
 // extend.  The coarse space rides in the dense launches or in 2-D row solves;
-// beside the other local solves it runs on the second stream.  xr (nullable) fuses the CG update of x and r into the
-// restriction (partials of ||r||^2 into *rr); chk (nullable) folds the PCG
-// stopping test into the extension.  flags (kPrec*; -1: the problem's additive
+// beside the other local solves it runs on the second stream.  xr (nullable) fuses
+// the CG update of x and r into the restriction (partials of ||r||^2 into *rr); chk
+// (nullable) folds the PCG stopping test into the extension.  flags (kPrec*; -1: the problem's additive
 // Schwarz preconditioner) selects the parts; the coarse correction alone runs
 // on the library stream.
 void precond_apply(ddeig_problem* P, double* r, double* z, Red* dot, PcgState* st,

@@ -100,7 +100,7 @@ struct SubType {
   Box box;                  // box of the first member (o of that member)
   int nmem;
   std::vector<int> members; // subdomain ids (x1-fastest cell numbering)
-  double* W = nullptr;      // nch * b * b FP64 Schur-complement inverses
+  double* W = nullptr;      // FP64 Schur-complement inverses (factor_entries)
   float* W32 = nullptr;     // FP32 copy (local_prec = 1)
   double* batch = nullptr;  // nmem * nch * b local vectors
   double* phi = nullptr;    // coarse weights of the class (box order)
@@ -214,7 +214,6 @@ struct GemmType {
 };
 static_assert(sizeof(GemmType) == 64, "rows sits in the padding after ld");
 
-// Batched chain solves: one workgroup per (class, member tile, 64 rows of a slice).
 // Extra workgroups of the dense GEMM launch that form the coarse right-hand
 // side R_0 r (one per subdomain), and of the clipped-class correction launch
 // that apply the coarse inverse y0 = A_0^{-1} c (four rows per workgroup).
@@ -347,8 +346,8 @@ struct ddeig_problem {
   ddeig_options opt;
   hipStream_t stream;
   int device = 0;  // the device current at ddeig_assemble
-  // second stream (default priority) for the coarse space beside 3-D chain solves
-  // (and 2-D ones without row solves)
+  // second stream (default priority) for the coarse space beside 3-D chain solves,
+  // 2-D ones without row solves, and the dense solves of a handful of subdomains
   hipStream_t aux = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   // CG state copies of the last two blocks of queued iterations (pinned host
@@ -445,7 +444,6 @@ struct ddeig_problem {
   int* flag = nullptr;      // factorisation error flag
   double* gjbuf = nullptr;  // blocked Gauss-Jordan panels of gj_jobs matrices of <= gj_stride rows
   int gj_stride = 0, gj_jobs = 1;
-  double* cellS = nullptr;  // scratch for Schur builds (maxb^2)
   std::vector<void*> allocs;
 };
 

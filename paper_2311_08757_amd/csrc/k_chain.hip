@@ -11,9 +11,13 @@
 // and a solve is
 //   forward   t_i = W_i (b_i - E_i t_{i-1}),
 //   backward  x_{n-1} = t_{n-1},  x_i = t_i - W_i E_{i+1}^T x_{i+1}.
+// From both ends (FactorJobs) the slices after the middle one, h = n / 2, are
+// eliminated upwards in the same way and slice h takes both neighbours; a solve runs
+// inwards on either side, through h, and outwards again.
 // E_i and D_i are never stored: they are read from the period-cell table.
-// W_i is stored dense (b x b); since it is symmetric, W_i[s][r] is read with
-// r running over the threads, which coalesces.
+// W_i is stored dense (b x b), where row solves read it in their order (RowsLayout);
+// it is symmetric, so W_i[s][r] is read with r running over the threads, which
+// coalesces.
 #include "k_common.h"
 
 #include <mutex>
@@ -125,12 +129,15 @@ struct RowsLayout {
   }
 };
 
-// 1 / x for a positive, normal x, to about an ulp: the hardware estimate and
-// three Newton steps (a full division is a third longer in the pivot chain).
+// 1 / x for a positive, normal x: the hardware estimate (2^-24) and three Newton
+// steps with fused multiply-adds.  Two bring it within an ulp, and from there the
+// third rounds correctly (P. Markstein, IBM J. Res. Dev. 34, 1990; an x of all ones
+// alone can end an ulp off), as the division does that is a third longer in the
+// pivot chain.
 __device__ __forceinline__ double fast_rcp(double x) {
   double y = __builtin_amdgcn_rcp(x);
 #pragma unroll
-  for (int q = 0; q < 3; ++q) y = y + y * (1.0 - x * y);
+  for (int q = 0; q < 3; ++q) y = __builtin_fma(y, __builtin_fma(-x, y, 1.0), y);
   return y;
 }
 
@@ -1474,7 +1481,9 @@ __global__ void __launch_bounds__(NT) k_rows_box(Geo g, Box bx, const double* __
 }
 
 // The kernel for slices of at most b: columns per part (b / 8 rounded up), and
-// threads (per side a wave that forms g and a wave per 16 rows).
+// threads (per side a wave that forms g and a wave per 16 rows).  In FP64 the widest,
+// 97 to 128 unknowns, spills 46 of its registers: 16 subdomains of 119 lines of 127,
+// 762 us an application (95 wide, 89 lines: 164), k_local_solves 7.3 ms.
 #define ROWS_PICK_WIDE(KERN, b, ...) \
   ((b) <= 96 ? KERN<__VA_ARGS__ 448, 12, false> : KERN<__VA_ARGS__ 576, 16, false>)
 #define ROWS_PICK(KERN, b, ...)                                                         \
@@ -1504,7 +1513,8 @@ bool launch_rows_box(const ddeig_problem* P, const Box& bx, const double* tab, c
                      double* v, int nrhs, int identity, hipStream_t s) {
   if (P->g.D != 2 || !rows_ok(bx.b, bx.nch)) return false;
   const bool both = rows_both(P->g.D, bx.b, bx.nch);
-  auto kern = both ? ROWS_PICK_BOTH(k_rows_box, bx.b) : ROWS_PICK(k_rows_box, bx.b);
+  // (every box of at most kRowsBothB is solved from both ends)
+  auto kern = both ? ROWS_PICK_BOTH(k_rows_box, bx.b) : ROWS_PICK_WIDE(k_rows_box, bx.b);
   size_t lds;
   int nt;
   rows_launch(P, kern, both, bx.b, bx.nch, lds, nt);
@@ -1684,9 +1694,8 @@ bool launch_local_solves_staged(const ddeig_problem* P, const PcgState* st, hipS
   return true;
 }
 
-// Row solves of the classes: their FP32 factors are eliminated from one end (the
-// rounded factors of the two orders differ in their last bit, and so would the
-// results).
+// Row solves of the classes: FP64 factors from both ends, FP32 factors from one (their
+// solves from both ends have not been built or measured).
 bool classes_both(const ddeig_problem* P) {
   int b, nch;
   class_extents(P, b, nch);

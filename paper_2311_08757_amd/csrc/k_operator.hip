@@ -415,7 +415,8 @@ __global__ void __launch_bounds__(kBlock) k_stencil3d(Geo g, const double* __res
 // tile-local index arithmetic (fewer registers, more resident waves).  Same
 // arithmetic and tap order as k_stencil<2, MODE>, which reloads the
 // coefficients for every node and stages entry by entry (h = 1/30, 890,851
-// unknowns: 11.2 us an apply, here 5.2).
+// unknowns: 11.2 us an apply, here 5.2; n_e = 34, the worst, with 30 lanes of 64
+// idle: 5.0 million unknowns 35.0 and 25.6, 20 million 148 and 87).
 // The body takes the block's tile index `bid` (blockIdx.x of a single
 // problem, or the block's index within its instance in a grouped launch).
 // YFAST numbers the tiles y fastest: with bid = xcd_slab(blockIdx.x) an XCD

@@ -656,9 +656,10 @@ void launch_coarse_field(const ddeig_problem* P, const PcgState* st, hipStream_t
 }
 
 // z = sum_c R_c^T y_c (+ R_0^T y0), partials of r.z.  Work items are row
-// segments of kBlock x1 positions, four per workgroup of kBig threads (as in
-// the restriction); the covering cells of a node come from the per-axis
-// tables and are summed in a fixed order.
+// segments of kBlock x1 positions, four per workgroup of kBig threads; the
+// covering cells of a node and their values come as in the restriction (covering,
+// SubBase), distance-based weights of one axis from its table, and the cells are
+// summed in a fixed order.
 // With chk.on the kernel first applies the stopping test of PCG iteration k,
 // ||r_k|| <= rtol ||r_0|| (§4.1), records the history and, once CG stops,
 // does nothing else (every later kernel of the iteration sees `done`).
