@@ -32,10 +32,11 @@
 //     step for three classes of b = 1085, two chains).
 // One more launch finishes the outermost slices.  The right-hand sides are
 // formed and the partials (sums of at most 72 products) added and kept in FP64;
-// W_i, g and the products are FP32 (FP32 accumulation on the matrix cores).  W_i staged through LDS in chunks of
-// 72 rows took 14.8 us a step (1.8 TB/s); this takes 10.2 us, and 8.2 (3.2 TB/s)
-// on 16-wide tiles, which 14 members fill; the right-hand sides 6.9 -> 4.2 us
-// with a quarter of the partials and one descriptor load.
+// W_i, g and the products are FP32 (FP32 accumulation on the matrix cores).  W_i
+// staged through LDS in chunks of 72 rows took 14.8 us a step (1.8 TB/s) and the
+// right-hand sides 6.9; streamed, on 16-wide tiles, which 14 members fill, 8.4 us (3.1
+// TB/s; on 32-wide ones 10.2), and with a quarter of the partials and one descriptor
+// load 4.3 us.
 #include "k_common.h"
 
 namespace ddeig {
